@@ -16,10 +16,10 @@
 //   aht_pass_kernel : the older direct A H^T kernel (lanes down the rows), for
 //       shapes the others do not serve (unaligned A, short wide matrices)
 //   gram_kernel, gram_sum_kernel, residual_*_kernel, objective_kernel : the small rest.
-// For k <= 64 and aligned A the products are exact: fp32 operands cut into three
-// bf16 pieces each, eight of the nine piece products per term (all but the lowest,
-// below 2^-30 of the term) on v_mfma_f32_32x32x16_bf16 with fp32 accumulation (see
-// split3 below).  wta_pass_kernel and aht_pass_kernel use
+// For k <= 64 and aligned A the products are formed from pieces: fp32 operands cut into
+// three bf16 pieces each, exactly, and the six leading of the nine piece products per term
+// (the rest is below 2^-22 of the term, of either sign) on v_mfma_f32_32x32x16_bf16 with
+// fp32 accumulation (see split3 and cut2 below).  wta_pass_kernel and aht_pass_kernel use
 // v_mfma_f32_32x32x2_f32 on the floats themselves.
 //
 // Lane layout of v_mfma_f32_32x32x2_f32 (64 lanes, D = A_op B_op + C):
@@ -49,9 +49,6 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
 // v_mfma_f32_32x32x16_bf16 on pieces computes the same sums of products as
 // v_mfma_f32_32x32x2_f32 on the floats, with the roundings of the running sums
 // only, at a quarter of the matrix-core time per product.
-// The kernels issue eight of the nine: l_x l_y is below 2^-30 |x y| (each low piece is
-// below 2^-15 of its float), a 64th of the rounding of one fp32 addition, and the passes
-// are bound by the power the matrix instructions draw: leaving it out takes 4-7 % off them.
 //
 // Lane layout of v_mfma_f32_32x32x16_bf16: A_op (32 x 16): lane l holds
 // A_op[l % 32][8 (l / 32) .. 8 (l / 32) + 7]; B_op (16 x 32): lane l holds
@@ -79,6 +76,41 @@ __device__ __forceinline__ void split3(float x, unsigned &h, unsigned &m, unsign
 __device__ __forceinline__ unsigned pack2(unsigned even, unsigned odd)
 {
     return __builtin_amdgcn_perm(odd, even, 0x07060302u);
+}
+
+// The streamed operand is cut with rounding instead of truncation, two floats at a time (packed
+// conversions, round to nearest even): h = x rounded to 8 significant bits, m = (x - h) rounded
+// likewise, l = the rest; again exact, |m| <= 2^-8 |x|, |l| <= 2^-16 |x| and m, l have either
+// sign.  Against a truncated operand (W or H from the planes: pieces of one sign, m < 2^-7,
+// l < 2^-15 of the float) the passes issue SIX products, h h, h m, m h, m m, h l, l h: the three
+// left out are below 2^-23 (twice) and 2^-31 of the term and signed like A's lower pieces, so
+// over a sum they cancel instead of adding up.  Measured against 64 bits (W^T A and A H^T on
+// uniform, planted, exponential and 30-decade data, 4096 to 65536 rows) the error is smaller than
+// with eight products of truncated pieces: 6.0e-8 against 6.7e-8 relative at 4096 rows, mean
+// signed error -2e-9 against -28e-9 (products of one sign lose their low bits in the accumulator
+// always downwards, see the running totals below; signed ones do not).  A column of one repeated
+// value is the worst case: its m and l have one sign down the column and nothing cancels (1.6e-7
+// against 1.3e-7 at 65536 rows).  A quarter less matrix work: 7 to 11 % off the passes that are
+// bound by it.
+// A value above the largest bf16 (3.39e38) would round to infinity and is held at that bf16.
+__device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+
+// Pieces of two consecutive elements of an operand into register pr of its three planes.
+__device__ __forceinline__ void cut2(float x0, float x1, u32x4 (&at)[3], int pr)
+{
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
+    const unsigned h = __builtin_bit_cast(unsigned, __builtin_elementwise_min(
+        __builtin_bit_cast(i16x2, cvt_pk_bf16(x0, x1)), i16x2{0x7f7f, 0x7f7f}));
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    const unsigned m = cvt_pk_bf16(r0, r1);
+    at[0][pr] = h;
+    at[1][pr] = m;
+    at[2][pr] = cvt_pk_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
 
 // Row of the 32 x 32 accumulator held in register v of a lane in half `half`.
@@ -444,13 +476,13 @@ __global__ __launch_bounds__(256) void split_planes_kernel(const float *__restri
 }
 
 // ---------------------------------------------------------------------------
-// W^T A pass for k <= 32 with exact products on the bf16 matrix cores (see
-// split3 above).  Geometry as wta_pass_kernel: 4 waves on a 128-column slab and
+// W^T A pass for k <= 32 on pieces, on the bf16 matrix cores (see
+// split3 and cut2 above).  Geometry as wta_pass_kernel: 4 waves on a 128-column slab and
 // one row split, lane = 4 consecutive columns; but a wave takes 16 rows per step
 // (half-wave = 8 consecutive rows, the reduction depth of one instruction), loads
 // them with eight 16-byte loads per lane, cuts each element into its pieces in
 // registers and reads the pieces of W ready-made (planes, 3 x 16 bytes per lane
-// and step).  Per column tile the eight piece products are accumulated smallest
+// and step).  Per column tile the six piece products are accumulated smallest
 // first.  r0 of every split is a multiple of 16 (rps is), so a half-wave's rows
 // are one 8-row group of the planes.  Two waves per SIMD (256 registers each).
 // ---------------------------------------------------------------------------
@@ -506,16 +538,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_kernel(
             u32x4 at[3];
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) {
-                unsigned h0, m0, l0, h1, m1, l1;
-                split3(cur.a[2 * pr][q], h0, m0, l0);
-                split3(cur.a[2 * pr + 1][q], h1, m1, l1);
-                at[0][pr] = pack2(h0, h1);
-                at[1][pr] = pack2(m0, m1);
-                at[2][pr] = pack2(l0, l1);
+                cut2(cur.a[2 * pr][q], cur.a[2 * pr + 1][q], at, pr);
             }
-            acc[q] = mfma_bf16(cur.wt[2], at[1], acc[q]);      // eight products, smallest first (no l l)
-            acc[q] = mfma_bf16(cur.wt[1], at[2], acc[q]);
-            acc[q] = mfma_bf16(cur.wt[2], at[0], acc[q]);
+            acc[q] = mfma_bf16(cur.wt[2], at[0], acc[q]);      // six products, smallest first
             acc[q] = mfma_bf16(cur.wt[1], at[1], acc[q]);
             acc[q] = mfma_bf16(cur.wt[0], at[2], acc[q]);
             acc[q] = mfma_bf16(cur.wt[1], at[0], acc[q]);
@@ -603,16 +628,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
             u32x4 at[3];
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) {
-                unsigned h0, m0, l0, h1, m1, l1;
-                split3(__uint_as_float(c.a[2 * pr][q]), h0, m0, l0);
-                split3(__uint_as_float(c.a[2 * pr + 1][q]), h1, m1, l1);
-                at[0][pr] = pack2(h0, h1);
-                at[1][pr] = pack2(m0, m1);
-                at[2][pr] = pack2(l0, l1);
+                cut2(__uint_as_float(c.a[2 * pr][q]), __uint_as_float(c.a[2 * pr + 1][q]), at, pr);
             }
-            acc[q] = mfma_bf16(c.wt[2], at[1], acc[q]);      // eight products, smallest first (no l l)
-            acc[q] = mfma_bf16(c.wt[1], at[2], acc[q]);
-            acc[q] = mfma_bf16(c.wt[2], at[0], acc[q]);
+            acc[q] = mfma_bf16(c.wt[2], at[0], acc[q]);      // six products, smallest first
             acc[q] = mfma_bf16(c.wt[1], at[1], acc[q]);
             acc[q] = mfma_bf16(c.wt[0], at[2], acc[q]);
             acc[q] = mfma_bf16(c.wt[1], at[0], acc[q]);
@@ -753,16 +771,11 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
             u32x4 at[3];
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) {
-                unsigned h0, m0, l0, h1, m1, l1;
-                split3(__uint_as_float(c.a[2 * pr][q]), h0, m0, l0);
-                split3(__uint_as_float(c.a[2 * pr + 1][q]), h1, m1, l1);
-                at[0][pr] = pack2(h0, h1);
-                at[1][pr] = pack2(m0, m1);
-                at[2][pr] = pack2(l0, l1);
+                cut2(__uint_as_float(c.a[2 * pr][q]), __uint_as_float(c.a[2 * pr + 1][q]), at, pr);
             }
-            constexpr int PW[8] = {2, 1, 2, 1, 0, 1, 0, 0}, PA[8] = {1, 2, 0, 1, 2, 0, 1, 0};   // smallest first, no l l
+            constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PA[6] = {0, 1, 2, 0, 1, 0};   // smallest first
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 6; ++e)
 #pragma unroll
                 for (int t = 0; t < 2; ++t) acc[t][q] = mfma_bf16(c.wt[t][PW[e]], at[PA[e]], acc[t][q]);
         }
@@ -1339,19 +1352,14 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
                     const f32x4 x0 = *reinterpret_cast<const f32x4 *>(stg + jj * 64 + ((c0 ^ (jj & 15)) << 2));
                     const f32x4 x1 = *reinterpret_cast<const f32x4 *>(stg + jj * 64 + (((c0 + 1) ^ (jj & 15)) << 2));
                     u32x4 at[3];
-                    unsigned h0, m0, l0, h1, m1, l1;
-                    split3(x0.x, h0, m0, l0); split3(x0.y, h1, m1, l1);
-                    at[0][0] = pack2(h0, h1), at[1][0] = pack2(m0, m1), at[2][0] = pack2(l0, l1);
-                    split3(x0.z, h0, m0, l0); split3(x0.w, h1, m1, l1);
-                    at[0][1] = pack2(h0, h1), at[1][1] = pack2(m0, m1), at[2][1] = pack2(l0, l1);
-                    split3(x1.x, h0, m0, l0); split3(x1.y, h1, m1, l1);
-                    at[0][2] = pack2(h0, h1), at[1][2] = pack2(m0, m1), at[2][2] = pack2(l0, l1);
-                    split3(x1.z, h0, m0, l0); split3(x1.w, h1, m1, l1);
-                    at[0][3] = pack2(h0, h1), at[1][3] = pack2(m0, m1), at[2][3] = pack2(l0, l1);
-                    // eight piece products (no l l), smallest first (per 32-factor tile: independent chains)
-                    constexpr int PA[8] = {2, 1, 2, 1, 0, 1, 0, 0}, PB[8] = {1, 2, 0, 1, 2, 0, 1, 0};
+                    cut2(x0.x, x0.y, at, 0);
+                    cut2(x0.z, x0.w, at, 1);
+                    cut2(x1.x, x1.y, at, 2);
+                    cut2(x1.z, x1.w, at, 3);
+                    // six piece products, smallest first (per 32-factor tile: independent chains)
+                    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
+                    for (int e = 0; e < 6; ++e)
 #pragma unroll
                         for (int ft = 0; ft < KT; ++ft) a[ft] = mfma_bf16(at[PA[e]], bp[s][PB[e]][ft], a[ft]);
                 }
@@ -1673,12 +1681,7 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) {
-                unsigned h0, m0, l0, h1, m1, l1;
-                split3(hv[2 * pr][q], h0, m0, l0);
-                split3(hv[2 * pr + 1][q], h1, m1, l1);
-                hp[s][q][0][pr] = pack2(h0, h1);
-                hp[s][q][1][pr] = pack2(m0, m1);
-                hp[s][q][2][pr] = pack2(l0, l1);
+                cut2(hv[2 * pr][q], hv[2 * pr + 1][q], hp[s][q], pr);
             }
     }
 
@@ -1718,12 +1721,7 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
             u32x4 wp[3];
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) {
-                unsigned h0, m0, l0, h1, m1, l1;
-                split3(wv[s][pr >> 1][(2 * pr) & 3], h0, m0, l0);
-                split3(wv[s][pr >> 1][(2 * pr + 1) & 3], h1, m1, l1);
-                wp[0][pr] = pack2(h0, h1);
-                wp[1][pr] = pack2(m0, m1);
-                wp[2][pr] = pack2(l0, l1);
+                cut2(wv[s][pr >> 1][(2 * pr) & 3], wv[s][pr >> 1][(2 * pr + 1) & 3], wp, pr);
             }
 #pragma unroll
             for (int pc = 0; pc < 3; ++pc) wlds[buf][w][s * 3 + pc][lane] = wp[pc];
@@ -1741,11 +1739,11 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
         f32x16 acc[2];
         acc[0] = f32x16{0};
         acc[1] = f32x16{0};
-        constexpr int PW[8] = {2, 1, 2, 1, 0, 1, 0, 0}, PH[8] = {1, 2, 0, 1, 2, 0, 1, 0};   // smallest first, no l l
+        constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PH[6] = {0, 1, 2, 0, 1, 0};   // smallest first
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 6; ++e)
 #pragma unroll
                 for (int s = 0; s < KSTEPS; ++s) acc[q] = mfma_bf16(wp[s][PW[e]], hp[s][q][PH[e]], acc[q]);
         float local = 0.f;      // 32 terms per lane in fp32, double across tiles
