@@ -673,19 +673,23 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// The pass for 32 < k <= 64 on exact pieces (aligned A, n % 4 == 0, 64 n < 2^31; planes with
+// The pass for 32 < k <= 64 on pieces (aligned A, n % 4 == 0, 64 n < 2^31; planes with
 // 64 factor slots per row group).  The arithmetic of wta_pass_split_buf_kernel with two
 // 32-factor accumulator tiles per column tile, and another geometry: workgroup = 256
 // columns, wave w = columns 64 w .. 64 w + 63 of them (lane = 2 consecutive columns, 8-byte
-// loads), and all four waves walk the same 16-row steps of the split.  The piece planes of
-// a step (1.5 times the bytes of the step's A) are then fetched from L2 once per workgroup
-// and hit the vector cache for the other three waves, no sum across waves is needed, and
-// each wave stores its own 64 x 64 result: register v of tile (t, q) is factor
+// loads), and all four waves walk the same 16-row steps of the split.  The piece planes of a
+// step are 1.5 times the bytes of a wave's share of A, and read by every wave through the
+// vector cache they were the kernel's largest cost (32768 x 16384, k = 64: 474 us, 370 without
+// them, 445 without cutting A, 383 with two products instead of six).  So the workgroup stages
+// them in LDS once for its four waves: six steps (36 KiB) at a time, double buffered, three
+// 16-byte units per thread requested every second step and written two steps later, one
+// barrier per six steps; 72 KiB per workgroup, two workgroups per compute unit.  The running
+// totals live in registers (the planes of the next steps no longer do).  No sum across waves
+// is needed, and each wave stores its own 64 x 64 result: register v of tile (t, q) is factor
 // 32 t + row(v), column 2 jj + q, so (q = 0, q = 1) pair up to 8-byte stores, 256
-// contiguous bytes per row.  Loads run two steps ahead of the arithmetic (three register
-// stages), held there by scheduling barriers.  Measured on 32768 x 16384, k = 64: 490 us
-// against 531 us for waves interleaved down the rows of one 64-column slab; the matrix
-// pipe is busy 70 % of the cycles at the 1.7 GHz the chip sustains under this load.
+// contiguous bytes per row.  Loads of A run two steps ahead of the arithmetic (three register
+// stages), held there by scheduling barriers.  Measured in the iteration on 32768 x 16384:
+// 480 -> 400 us (5.4 TB/s; its bare 8-byte loads take 338), on 16384 x 8192 131 -> 107 us.
 // ---------------------------------------------------------------------------
 // Several 64-factor slices of a wider factor in one launch (SLICES; ranks above 64): a
 // one-dimensional grid whose workgroup L stands for (tile, slice) with the slices of one
@@ -706,7 +710,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
     constexpr int KP = 64;
     constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
     constexpr int kPolicy = SLICES ? 0 : kStreamLoad;
-    __shared__ float tot[kWtaWaves * kTotFloats];
+    constexpr int kSteps = 6;                          // 16-row steps per group of staged planes
+    constexpr int kUnits = kSteps * 2 * 3 * KP;        // 16-byte units of planes in a group
+    __shared__ u32x4 pst[2][kUnits];
     int bx = blockIdx.x, by = blockIdx.y;
     if (SLICES) {
         const int L = blockIdx.x, within = L >> 3;
@@ -723,104 +729,116 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    float *mytot = tot + w * kTotFloats;   // register (t, q, v) of this lane at ((2 t + q) * 16 + v) * 64 + lane
-    tot_clear(mytot, lane);
     const int jj = lane & 31, half = lane >> 5;
     const int64_t jw = (int64_t)bx * 256 + 64 * w;
-    if (jw >= n) return;     // no barrier below: a wave wholly past the edge has nothing to do
+    const bool live = jw < n;   // a wave wholly past the edge only helps to stage the planes
     const int64_t colr = jw + 2 * jj;
     const int64_t col = colr < n ? colr : 0;   // lanes past the edge read valid data that is never stored
     const int64_t r0 = (int64_t)by * rps;
     const int64_t r1 = (r0 + rps < rows) ? r0 + rps : rows;
     const unsigned rowb = (unsigned)(n * 4);
     const unsigned loff = (unsigned)(half * 8) * rowb + (unsigned)col * 4;
-    const unsigned poff = (unsigned)(half * 3 * KP + jj) * 16;
     const int64_t ngroups = (rows + 7) >> 3;
 
-    f32x16 acc[2][2];
+    f32x16 acc[2][2], tot[2][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int q = 0; q < 2; ++q) acc[t][q] = f32x16{0};
+        for (int q = 0; q < 2; ++q) acc[t][q] = f32x16{0}, tot[t][q] = f32x16{0};
 
-    struct Stage {
-        u32x2 a[8];
-        u32x4 wt[2][3];
-    };
+    struct Stage { u32x2 a[8]; };
     auto load_stage = [&](Stage &s, int64_t ib) {
-        int64_t av = r1 - ib;                       // rows of this step inside the split
+        int64_t av = live ? r1 - ib : 0;            // rows of this step inside the split
         av = av < 0 ? 0 : (av > 16 ? 16 : av);
-        const int64_t g = ib >> 3;
-        int64_t ng = av ? ngroups - g : 0;          // 8-row groups of planes that exist
-        ng = ng < 0 ? 0 : (ng > 2 ? 2 : ng);
         const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(A + (av ? ib : 0) * n), 0, (int)(av * rowb), kRsrcFlags);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b64(ra, loff + r * rowb, 0, kPolicy);
+    };
+    // a third of the planes of the group of rows from ib on: 3 units per thread
+    struct Third { u32x4 u[3]; };
+    auto load_third = [&](Third &p, int64_t ib, int part) {
+        const int64_t g = ib >> 3;
+        int64_t ng = ib < r1 ? ngroups - g : 0;     // 8-row groups of planes that exist
+        ng = ng < 0 ? 0 : (ng > 2 * kSteps ? 2 * kSteps : ng);
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<u32x4 *>(planes + (ng ? g : 0) * 3 * KP), 0, (int)(ng * 3 * KP * 16), kRsrcFlags);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b64(ra, loff + r * rowb, 0, kPolicy);
+        for (int e = 0; e < 3; ++e)
+            p.u[e] = __builtin_amdgcn_raw_buffer_load_b128(rp, (unsigned)((3 * part + e) * 256 + tid) * 16, 0, 0);
+    };
+    auto store_third = [&](const Third &p, int buf, int part) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) pst[buf][(3 * part + e) * 256 + tid] = p.u[e];
+    };
+    auto compute = [&](const Stage &c, int buf, int st) {
+        u32x4 wt[2][3];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
-                s.wt[t][pl] = __builtin_amdgcn_raw_buffer_load_b128(rp, poff + (pl * KP + 32 * t) * 16, 0, 0);
-    };
-    auto compute = [&](const Stage &c) {
+            for (int pl = 0; pl < 3; ++pl) wt[t][pl] = pst[buf][((2 * st + half) * 3 + pl) * KP + 32 * t + jj];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             u32x4 at[3];
 #pragma unroll
-            for (int pr = 0; pr < 4; ++pr) {
+            for (int pr = 0; pr < 4; ++pr)
                 cut2(__uint_as_float(c.a[2 * pr][q]), __uint_as_float(c.a[2 * pr + 1][q]), at, pr);
-            }
             constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PA[6] = {0, 1, 2, 0, 1, 0};   // smallest first
 #pragma unroll
             for (int e = 0; e < 6; ++e)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t][q] = mfma_bf16(c.wt[t][PW[e]], at[PA[e]], acc[t][q]);
+                for (int t = 0; t < 2; ++t) acc[t][q] = mfma_bf16(wt[t][PW[e]], at[PA[e]], acc[t][q]);
         }
     };
-    // three steps per trip, loads two steps ahead; a step past the split loads nothing (zero
-    // extent) and is skipped
     auto flush = [&]() {
-        // a tile at a time: 16 reads in flight, then the adds, then the writes
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                float old[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) old[v] = mytot[((2 * t + q) * 16 + v) * 64 + lane];
+            for (int q = 0; q < 2; ++q)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    mytot[((2 * t + q) * 16 + v) * 64 + lane] = old[v] + acc[t][q][v];
+                    tot[t][q][v] += acc[t][q][v];
                     acc[t][q][v] = 0.f;
                 }
-            }
     };
     Stage s0, s1, s2;
-    int trips = 2 * w;   // the waves of a workgroup flush at different times
+    Third th;
     load_stage(s0, r0);
     __builtin_amdgcn_sched_barrier(0);   // issue order = age order, also here: the waits in the loop count loads in flight
     load_stage(s1, r0 + 16);
-    for (int64_t i = r0; i < r1; i += 48) {
-        if (++trips > kFlushSteps / 3) {
-            flush();
-            trips = 1;
-        }
-        load_stage(s2, i + 32);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(s0);
-        __builtin_amdgcn_sched_barrier(0);
-        load_stage(s0, i + 48);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + 16 < r1) compute(s1);
-        __builtin_amdgcn_sched_barrier(0);
-        load_stage(s1, i + 64);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + 32 < r1) compute(s2);
-        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+        load_third(th, r0, part);
+        store_third(th, 0, part);
     }
+    __syncthreads();
+    int buf = 0, groups = 0;
+    for (int64_t i = r0; i < r1; i += 16 * kSteps) {
+        if (++groups > kFlushSteps / kSteps) {
+            flush();
+            groups = 1;
+        }
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+            const int64_t ib = i + 32 * part;
+            Stage &x = part == 0 ? s0 : (part == 1 ? s2 : s1);
+            Stage &y = part == 0 ? s1 : (part == 1 ? s0 : s2);
+            Stage &z = part == 0 ? s2 : (part == 1 ? s1 : s0);
+            load_third(th, i + 16 * kSteps, part);
+            load_stage(z, ib + 32);
+            __builtin_amdgcn_sched_barrier(0);
+            if (live && ib < r1) compute(x, buf, 2 * part);
+            __builtin_amdgcn_sched_barrier(0);
+            load_stage(x, ib + 48);
+            __builtin_amdgcn_sched_barrier(0);
+            if (live && ib + 16 < r1) compute(y, buf, 2 * part + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            store_third(th, buf ^ 1, part);
+        }
+        __syncthreads();    // the next group's planes are written, this group's are read
+        buf ^= 1;
+    }
+    flush();
 
     if (colr < n) {
         float *dst = ppart + (int64_t)by * k * n + colr;
@@ -831,8 +849,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
                 const int c = 32 * t + acc_row(v, half);
                 if (c < k) {
                     f32x2 *p = reinterpret_cast<f32x2 *>(dst + (int64_t)c * n);
-                    f32x2 val = {mytot[((2 * t) * 16 + v) * 64 + lane] + acc[t][0][v],
-                                 mytot[((2 * t + 1) * 16 + v) * 64 + lane] + acc[t][1][v]};
+                    f32x2 val = {tot[t][0][v], tot[t][1][v]};
                     if (accumulate) {
                         const f32x2 old = *p;
                         val.x += old.x;
@@ -1909,8 +1926,11 @@ int wta_splits(int64_t rows, int64_t n, int k)
     // 256 above.
     const int64_t width = k > 32 ? 256 : kWtaCols;
     const int64_t slabs = (n + width - 1) / width;
+    // Rounded down: 512 workgroups are resident at once, and one more split than fits leaves its
+    // last workgroups to a second round (20011 x 10000 at k = 50: 40 slabs x 13 splits = 520
+    // workgroups took 252 us; 40 x 12, and the planes staged in LDS, 162).
     const int64_t target = 512;
-    int64_t s = (target + slabs - 1) / slabs;
+    int64_t s = target / slabs;
     int64_t max_by_rows = (rows + 255) / 256;         // at least 256 rows per split ...
     if (slabs * max_by_rows < 128) {
         // ... unless that leaves most of the chip idle: small matrices are split down to one
