@@ -1807,20 +1807,151 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
     if (tid == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
 }
 
+// ---------------------------------------------------------------------------
+// The objective as a streaming pass for any k <= 2 KS <= 64, 16-byte aligned A and H and
+// n % 4 == 0, with the fp32 matrix instruction (at a few factors the roundings of the pieces'
+// running sums would show near a good fit; here the sums are those of residual_kernel).  The
+// geometry of residual_stream_kernel: a wave owns 64 columns and walks down the rows of a split, a
+// lane 2 consecutive columns; its slab of H stays in registers, the rows of W go through LDS four
+// 32-row tiles at a time, and the next tile of A is requested before the current one's arithmetic.
+// Half h of the wave takes factors KS h .. KS h + KS - 1, one per instruction, so that a lane's
+// share of a row of W is one contiguous run.  Rows from m on read as zero, of A (outside the
+// tile's buffer extent) and of W, and add nothing; a request past the split fetches tile 0 instead
+// and is never used.  Against residual_kernel, whose waves wait for H, the products and A of every
+// slab in turn: see launch_residual.
+// ---------------------------------------------------------------------------
+template <int KS>
+__global__ __launch_bounds__(256, 2) void residual_stream_f32_kernel(const float *__restrict__ A,
+                                                                     const float *__restrict__ W,
+                                                                     const float *__restrict__ H, int64_t m,
+                                                                     int64_t n, int k, int64_t rps,
+                                                                     double *__restrict__ partial)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    __shared__ double wsum[4];
+    __shared__ f32x4 wlds[2][4][KS / 4][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int jj = lane & 31, half = lane >> 5;
+    const int64_t jw = (int64_t)blockIdx.x * 256 + 64 * w;   // this wave's 64 columns
+    const int64_t col = jw + 2 * jj;
+    const bool colok = col < n;                       // n is even: both columns or none
+    const int64_t j0 = jw < n ? jw : 0;               // a wave wholly past column n fetches the first slab
+    const int64_t r0 = (int64_t)blockIdx.y * rps;     // rps % 32 == 0
+    const int64_t r1 = (r0 + rps < m) ? r0 + rps : m;
+    const unsigned rowb = (unsigned)(n * 4);
+    const unsigned lane_off = colok ? (unsigned)(4 * half) * rowb + 8u * jj : 0u;
+
+    f32x2 hv[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int c = KS * half + s;
+        const bool in = colok && c < k;
+        const f32x2 t = *reinterpret_cast<const f32x2 *>(H + (in ? (int64_t)c * n + col : 0));
+        hv[s].x = in ? t.x : 0.f;
+        hv[s].y = in ? t.y : 0.f;
+    }
+
+    f32x4 wv[KS / 4];
+    bool wok = false;
+    auto load_w = [&](int64_t i0) {
+        const int64_t row = (i0 < r1 ? i0 : 0) + jj;
+        wok = row < m;
+        const float *src = W + (wok ? row : 0) * k;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) wv[s >> 2][s & 3] = src[KS * half + s < k ? KS * half + s : 0];
+    };
+    auto store_w = [&](int buf) {
+#pragma unroll
+        for (int s = 0; s < KS; s += 4) {
+            f32x4 t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] = wok && KS * half + s + e < k ? wv[s >> 2][e] : 0.f;
+            wlds[buf][w][s >> 2][lane] = t;
+        }
+    };
+    typedef f32x2 ATile[16];
+    auto load_a = [&](ATile &a, int64_t i0) {
+        const int64_t base = i0 < r1 ? i0 : 0;
+        const int64_t av = m - base < 32 ? m - base : 32;
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(A + base * n + j0), 0, (int)(av * rowb - j0 * 4), kRsrcFlags);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(ra, lane_off + (unsigned)acc_row(v, 0) * rowb, 0, kStreamLoad);
+            a[v] = __builtin_bit_cast(f32x2, t);
+        }
+    };
+    double total = 0.0;
+    auto tile = [&](const ATile &a, int buf, int t, bool valid) {
+        f32x16 acc[2];
+        acc[0] = f32x16{0};
+        acc[1] = f32x16{0};
+#pragma unroll
+        for (int s = 0; s < KS; s += 4) {
+            const f32x4 x = wlds[buf][t][s >> 2][lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) acc[q] = mfma32(x[e], hv[s + e][q], acc[q]);
+        }
+        float local = 0.f;      // 32 terms per lane in fp32, double across tiles
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float d0 = a[v].x - acc[0][v], d1 = a[v].y - acc[1][v];
+            local += d0 * d0;
+            local += d1 * d1;
+        }
+        total += valid ? (double)local : 0.0;
+    };
+    // four tiles per trip, as in residual_stream_kernel
+    ATile a0, a1;
+    int64_t i = r0;
+    load_w(i + 32 * w);
+    store_w(0);
+    load_w(i + 128 + 32 * w);
+    load_a(a0, i);
+    __syncthreads();
+    int buf = 0;
+    for (; i < r1; i += 128) {
+        store_w(buf ^ 1);
+        load_w(i + 256 + 32 * w);
+        load_a(a1, i + 32);
+        __builtin_amdgcn_sched_barrier(0);
+        tile(a0, buf, 0, true);
+        load_a(a0, i + 64);
+        __builtin_amdgcn_sched_barrier(0);
+        tile(a1, buf, 1, i + 32 < r1);
+        load_a(a1, i + 96);
+        __builtin_amdgcn_sched_barrier(0);
+        tile(a0, buf, 2, i + 64 < r1);
+        load_a(a0, i + 128);
+        __builtin_amdgcn_sched_barrier(0);
+        tile(a1, buf, 3, i + 96 < r1);
+        __syncthreads();    // the group's buffer is free, the next group's is written
+        buf ^= 1;
+    }
+    if (!colok) total = 0.0;   // such lanes subtracted a zero product from columns of other lanes
+    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
+    if (lane == 0) wsum[w] = total;
+    __syncthreads();
+    if (tid == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+
 // Sum of `count` doubles by one block of 256 threads in a fixed order: thread t adds entries
-// t, t + 256, ..., then thread 0 adds the 256 sums in thread order (one thread alone needs a
-// dependent load per entry: 33 us for 512 entries, 0.3 ms for 4096).
+// t, t + 256, ..., then the lanes of a wave by butterfly and the four waves in order (one thread
+// alone needs a dependent load per entry: 33 us for 512 entries, 0.3 ms for 4096).
 __device__ __forceinline__ double block_sum_f64(const double *__restrict__ partial, int64_t count)
 {
-    __shared__ double part[256];
+    __shared__ double part[4];
     double s = 0.0;
     for (int64_t i = threadIdx.x; i < count; i += 256) s += partial[i];
-    part[threadIdx.x] = s;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    double total = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < 256; ++i) total += part[i];
-    return total;     // valid in thread 0
+    return (part[0] + part[1]) + (part[2] + part[3]);
 }
 
 // out[0] = sqrt(sum of `count` partials).  One block of 256 threads.
@@ -2216,9 +2347,15 @@ static int residual_splits(int64_t m, int64_t n)
     return (int)s;
 }
 
+static int64_t residual_rows_per_split(int64_t m, int64_t n)
+{
+    const int splits = residual_splits(m, n);
+    return ((m + splits - 1) / splits + 31) & ~(int64_t)31;
+}
+
 int64_t residual_partials(int64_t m, int64_t n)
 {
-    const int64_t a = (m + 31) / 32, b = ((n + 255) / 256) * residual_splits(m & ~(int64_t)31, n) + 1;
+    const int64_t a = (m + 31) / 32, b = ((n + 255) / 256) * residual_splits(m, n) + 1;
     return a > b ? a : b;
 }
 
@@ -2244,6 +2381,30 @@ hipError_t launch_residual(const float *A, int64_t m, int64_t n, int k, const fl
                                m - m32, n, k, partial + count);
             ++count;
         }
+        hipLaunchKernelGGL(residual_finish_kernel, dim3(1), dim3(256), 0, st, (const double *)partial, count, out);
+        return hipGetLastError();
+    }
+    // The fp32 streaming kernel (32 rows of A with 32-bit byte offsets: 128 n < 2^31) from four row
+    // tiles per workgroup on, about 2^24 elements; below that its pipeline does not fill.  Whole call,
+    // residual_kernel against it: 16384 x 8192, k = 10 / 29 / 64: 145 / 226 / 379 -> 111 / 139 / 245 us;
+    // 2000 x 8192, k = 10: 85 -> 40; 8192 x 2048, k = 20: 61 -> 45; but 4099 x 1000, k = 20: 37 -> 41.
+    // Above 48 factors its registers spill, and on few columns (residual_kernel's serial loop over
+    // slabs is short there) it loses: 16384 x 1000, k = 64: 74 -> 80; 8192 x 2048: 99 -> 80.
+    if (n < ((int64_t)1 << 24) && vec_ok(A, n) && vec_ok(H, n) && residual_rows_per_split(m, n) >= 128 &&
+        (k <= 48 || n >= 2048)) {
+        const int splits = residual_splits(m, n);
+        const int64_t rps = residual_rows_per_split(m, n);
+        const dim3 grid((unsigned)((n + 255) / 256), (unsigned)splits);
+        const int64_t count = (int64_t)grid.x * grid.y;
+#define NMFMU_RESIDUAL_F32(KS) \
+    hipLaunchKernelGGL(residual_stream_f32_kernel<KS>, grid, dim3(256), 0, st, A, W, H, m, n, k, rps, partial)
+        if (k <= 8) NMFMU_RESIDUAL_F32(4);
+        else if (k <= 16) NMFMU_RESIDUAL_F32(8);
+        else if (k <= 24) NMFMU_RESIDUAL_F32(12);
+        else if (k <= 32) NMFMU_RESIDUAL_F32(16);
+        else if (k <= 48) NMFMU_RESIDUAL_F32(24);
+        else NMFMU_RESIDUAL_F32(32);
+#undef NMFMU_RESIDUAL_F32
         hipLaunchKernelGGL(residual_finish_kernel, dim3(1), dim3(256), 0, st, (const double *)partial, count, out);
         return hipGetLastError();
     }
