@@ -72,7 +72,7 @@ struct Common {
     unsigned *counters;
     float *gw, *gh, *gpart;
     float *gwp, *ghp;   // partial Gram tiles handed from one finisher to the next
-    float *gws, *ghs;   // the same, added up in groups by the pass that runs in between
+    float *gws, *ghs;   // the same, added up by the pass that runs in between
 };
 
 Common carve_common(Carve &c, int k)
@@ -85,8 +85,8 @@ Common carve_common(Carve &c, int k)
     r.gpart = c.take<float>((size_t)kGramMaxBlocks * kt * kt * 1024);
     r.gwp = c.take<float>((size_t)kFinMaxBlocks * kt * kt * 1024);
     r.ghp = c.take<float>((size_t)kFinMaxBlocks * kt * kt * 1024);
-    r.gws = c.take<float>((size_t)(kFinMaxBlocks / kGramGroup) * kt * kt * 1024);
-    r.ghs = c.take<float>((size_t)(kFinMaxBlocks / kGramGroup) * kt * kt * 1024);
+    r.gws = c.take<float>((size_t)kt * kt * 1024);
+    r.ghs = c.take<float>((size_t)kt * kt * 1024);
     return r;
 }
 
@@ -241,19 +241,21 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
     const int64_t rps1 = wta_rows_per_split(m, s1), rps2 = wta_rows_per_split(n, s2);
     if (rows_plan_runs(A, m, n, k, p.mirrored)) {
         // Row plan: both products stream the row-major A.  The W^T A pass reads the piece
-        // planes of W and, on the side, adds the tile sets of W^T W up in groups; the H update writes
+        // planes of W and, on the side, adds the tile sets of W^T W up; the H update writes
         // the planes of H^T and the tile sets of H H^T, which a small launch adds up; the A H^T pass
         // with the fused W update writes the planes of the new W and the tile sets of its W^T W.
         const int nbw = aht_rows_blocks(m, k), nbh = factor_update_blocks(n);
-        const int ngw = gram_groups(nbw);
+        // up to 16 sets are one trip to L2 for the finisher itself: the side job would cost a small pass
+        // more than that (256 x 192, k = 4: 5.9 instead of 4.8 us)
+        const bool few = nbw <= 16;
         // planes and W^T W of the W handed in, with the summation order of an updating launch
         NMF_HIP(launch_aht_rows(nullptr, m, n, k, nullptr, nullptr, W, p.planes, c.gwp, eps, st, true));
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
         for (int it = 0; it < iters; ++it) {
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            NMF_HIP(launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, c.gwp, nbw, c.gws));
+            NMF_HIP(launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, few ? nullptr : c.gwp, nbw, c.gws));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            NMF_HIP(launch_factor_update(H, nullptr, p.ppart, s1, nullptr, c.gws, ngw, c.ghp, k, n, eps, st, map, p.planes2));
+            NMF_HIP(launch_factor_update(H, nullptr, p.ppart, s1, nullptr, few ? c.gwp : c.gws, few ? nbw : 1, c.ghp, k, n, eps, st, map, p.planes2));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             NMF_HIP(launch_gram_sum(c.ghp, nbh, k, c.gh, st));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
@@ -284,26 +286,24 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         const int nbw = factor_update_blocks(m), nbh = factor_update_blocks(n);
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
         // The tiles of a finisher are needed, summed, by the next finisher; the pass that runs
-        // in between adds them up in groups of kGramGroup on the side (its first workgroups),
-        // the finisher sums the few group sets while it stages G: no launch of its own.
-        const int ngw = gram_groups(nbw), ngh = gram_groups(nbh);
+        // in between adds them up on the side (its first workgroups): no launch of its own.
         for (int it = 0; it < iters; ++it) {
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             NMF_HIP(launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, c.gwp, nbw, c.gws));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            NMF_HIP(launch_factor_update(H, p.Ht, p.ppart, s1, nullptr, c.gws, ngw, c.ghp, k, n, eps, st, map, p.planes));
+            NMF_HIP(launch_factor_update(H, p.Ht, p.ppart, s1, nullptr, c.gws, 1, c.ghp, k, n, eps, st, map, p.planes));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             NMF_HIP(launch_wta_pass(p.At, n, m, k, p.Ht, p.planes, true, p.ppart, s2, rps2, false, st, c.ghp, nbh, c.ghs));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             const bool report = mon && (!mon->last_only || it == iters - 1);
-            NMF_HIP(launch_factor_update(p.Wt, W, p.ppart, s2, nullptr, c.ghs, ngh, c.gwp, k, m, eps, st, map, p.planes,
+            NMF_HIP(launch_factor_update(p.Wt, W, p.ppart, s2, nullptr, c.ghs, 1, c.gwp, k, m, eps, st, map, p.planes,
                                          report ? mon->dpart : nullptr));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (report) {
                 // ||A - W H||_F from what this W update leaves behind: <A H^T, W>, H H^T, W^T W
                 NMF_HIP(launch_gram_sum(c.gwp, nbw, k, c.gw, st));
-                NMF_HIP(launch_gram_sum(c.ghs, ngh, k, c.gh, st));
+                NMF_HIP(launch_gram_sum(c.ghs, 1, k, c.gh, st));
                 NMF_HIP(launch_objective(mon->dpart, nbw, c.gw, c.gh, k, mon->normA2,
                                          mon->out + (mon->last_only ? 0 : it), st));
             }

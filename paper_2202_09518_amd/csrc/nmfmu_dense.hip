@@ -310,29 +310,30 @@ __global__ __launch_bounds__(512) void gram_kernel(const float *__restrict__ X, 
 
 // Side job of the pass kernels: the Gram tiles a finisher left behind (nsets sets of
 // kt x kt tiles of 1024 floats) are needed, summed, by the finisher AFTER this pass.  The
-// first workgroups of the pass add them up in groups of kGramGroup sets (in set order) so
-// that the finisher has at most kFinMaxBlocks / kGramGroup sets to sum and no separate
-// launch is needed.  Job j = a quarter of the entries of group j / 4, dealt to the workgroups in order.
-__device__ __forceinline__ void sum_tile_groups(const float *__restrict__ gtiles, int nsets, int k,
-                                                float *__restrict__ gsum)
+// first workgroups of the pass add them up so that no separate launch is needed: job j = entries
+// 64 j .. 64 j + 63, dealt to the workgroups in order; four lanes share an entry, lane q adds sets
+// q, q + 4, ... in order, and the four sums meet in a fixed tree.  (Sums of 16 sets each, left to the
+// finisher's workgroups to finish, cost every one of them 256 KiB of reads at 33 to 64 factors.)
+__device__ __forceinline__ void sum_tile_sets(const float *__restrict__ gtiles, int nsets, int k,
+                                              float *__restrict__ gsum)
 {
-    const int ngroups = (nsets + kGramGroup - 1) / kGramGroup;
+    constexpr int B = 16;
     const int kt = (k + 31) >> 5;
     const int stride = kt * kt * 1024;
-    const int nwg = gridDim.x * gridDim.y;
-    for (int job = blockIdx.y * gridDim.x + blockIdx.x; job < 4 * ngroups; job += nwg) {
-        const int group = job >> 2, quarter = job & 3;
-        const int first = group * kGramGroup;
-        const int count = (nsets - first < kGramGroup) ? nsets - first : kGramGroup;
-        for (int e = quarter * (stride / 4) + threadIdx.x; e < (quarter + 1) * (stride / 4); e += blockDim.x) {
-            float t[kGramGroup];
+    const int nwg = gridDim.x * gridDim.y, q = threadIdx.x & 3;
+    for (int job = blockIdx.y * gridDim.x + blockIdx.x; job < stride / 64; job += nwg) {
+        const float *src = gtiles + job * 64 + (threadIdx.x >> 2);
+        float sum = 0.f;
+        for (int s = q; s < nsets; s += 4 * B) {
+            float t[B];
 #pragma unroll
-            for (int b = 0; b < kGramGroup; ++b) t[b] = gtiles[(int64_t)(first + (b < count ? b : 0)) * stride + e];
-            float sum = 0.f;
+            for (int b = 0; b < B; ++b) t[b] = src[(int64_t)(s + 4 * b < nsets ? s + 4 * b : 0) * stride];
 #pragma unroll
-            for (int b = 0; b < kGramGroup; ++b) sum += (b < count) ? t[b] : 0.f;
-            gsum[(int64_t)group * stride + e] = sum;
+            for (int b = 0; b < B; ++b) sum += s + 4 * b < nsets ? t[b] : 0.f;
         }
+        sum += __shfl_xor(sum, 1);
+        sum += __shfl_xor(sum, 2);
+        if (q == 0) gsum[job * 64 + (threadIdx.x >> 2)] = sum;
     }
 }
 
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void wta_pass_kernel(const flo
     constexpr int NW = kWtaWaves;
     constexpr int LD = 132;
     __shared__ float red[KT * 32 * LD];
-    if (gtiles) sum_tile_groups(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int jj = lane & 31, half = lane >> 5;
     const int64_t j0 = (int64_t)blockIdx.x * kWtaCols;
@@ -494,7 +495,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_kernel(
 {
     constexpr int NW = kWtaWaves;
     __shared__ float tot[NW * kTotFloats];
-    if (gtiles) sum_tile_groups(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     float *mytot = tot + w * kTotFloats;
     tot_clear(mytot, lane);
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
     constexpr int NW = kWtaWaves;
     constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
     __shared__ float tot[NW * kTotFloats];
-    if (gtiles) sum_tile_groups(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *mytot = tot + w * kTotFloats;
@@ -725,7 +726,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
         ppart += (int64_t)z * slice_ppart;
         k = (k - 64 * z < 64) ? k - 64 * z : 64;
     } else if (gtiles) {
-        sum_tile_groups(gtiles, nsets, k, gsum);
+        sum_tile_sets(gtiles, nsets, k, gsum);
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -867,21 +868,31 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
 //     X[c][j] <- X[c][j] * (sum_s part[s][c][j]) / (sum_d G[c][d] X[d][j] + eps).
 // With X = H, part = W^T A, G = W^T W this is the H-update line of Algorithm 3;
 // with X = W^T, part = (A H^T)^T, G = H H^T it is the W-update line.
-// A block covers 64 columns at a time; thread (column j, group g of 8) holds
-// the old column in registers and produces factor indices c = g, g+8, ...
+// A block covers CW columns at a time; thread (column j, group g of 512 / CW) holds the
+// old column in registers and produces factor indices c = g, g + FG, ...; groups beyond the
+// KP factors take a share of the row splits each, added up through LDS in order.
 // Every element is written by the thread that computed it, after a block
 // barrier that follows all reads of the old column.
 // G comes either complete (Gfull, ld k) or as `nbin` partial 32 x 32 tiles in
 // accumulator layout (gin), which every block sums in block order while
 // staging G into LDS.  Optional outputs: Xt (len x k), staged through LDS so a
-// block stores one contiguous run of 64 k floats, and gout: this block's
+// block stores one contiguous run of CW k floats, and gout: this block's
 // partial Gram tiles of the NEW X (X X^T), computed from the LDS copy (one tile: the
 // same register as both MFMA operands; four tiles at 33 to 64 factors: each wave one
 // tile over half of a chunk's columns); the next finisher consumes them, so no
 // separate Gram kernel and no cross-block reduction are needed.  With
 // part == nullptr (and splits == 0) nothing is updated and only gout is produced.
+//
+// The kernel is a chain of trips to L2 (G, the old column, the splits in batches) with little to
+// compute, so what counts is how many trips are in flight: the first chunk's old values and first
+// batch of splits are requested together with G, a batch holds up to 32 loads per thread, a
+// thread loads only its own factors' old values (the column meets in LDS), and short factors are
+// cut into narrower chunks so that more workgroups share the splits (see factor_update_width).
+// With every thread loading the whole column, batches of 2 to 4 splits and G as 16 partial sums:
+// 25 us at k = 50 on 9998 columns and 12 splits, now 17; 10.5 at k = 20 on 4096, now 6.7; 27 at
+// k = 16 on 512 columns and 128 splits, now 10; 13 at k = 32 on 16384, now 9.6.
 // ---------------------------------------------------------------------------
-template <int KP>
+template <int KP, int CW, bool BIG>
 __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                                                             const float *__restrict__ part,
                                                             int splits,
@@ -892,61 +903,118 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                                                             double *__restrict__ dpart, int k,
                                                             int64_t len, float eps, BlockMap bm)
 {
-    constexpr int NW = 8, KT = KP / 32 > 0 ? KP / 32 : 1, NC = (KP + 7) / 8, LD = KP + 1;
+    constexpr int NW = 8, KT = KP / 32 > 0 ? KP / 32 : 1, LD = KP + 4;
+    constexpr int NG = 512 / CW, FG = NG < KP ? NG : KP, SPL = NG / FG, NC = KP / FG;
+    constexpr int SB = 32 / NC < 16 ? 32 / NC : 16;   // splits per batch
     constexpr int LDT = 32 * KT + 1;   // the Gram tiles read 32 factor indices per tile
     // one LDS array: G and the chunk's new values during the updates, then (after a barrier)
     // the eight waves' copies of a Gram tile for the sum over waves
-    constexpr int GS = KP * LD, TS = 64 * LDT;
-    constexpr int SM = (GS + TS > NW * 1024) ? GS + TS : NW * 1024;
-    __shared__ float Sm[SM];
-    float *Gs = Sm, *Ts = Sm + GS;
+    constexpr int GS = KP * LD, XS = KP * CW, TS = CW * LDT, PS = (SPL - 1) * KP * CW;
+    constexpr int SM = (GS + XS + TS + PS > NW * 1024) ? GS + XS + TS + PS : NW * 1024;
+    __shared__ __align__(16) float Sm[SM];
+    float *Gs = Sm, *Xs = Sm + GS, *Ts = Xs + XS, *Ps = Ts + TS;   // Xs: the chunk's old values [KP][CW]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int kt = (k + 31) >> 5;
+    const int jl = tid % CW, grp = tid / CW, fc = grp % FG;
+    const int sp = __builtin_amdgcn_readfirstlane(grp / FG);   // CW x FG threads share it: whole waves
+    const int64_t nchunks = (len + CW - 1) / CW;
+    const int s_lo = SPL > 1 ? (int)((int64_t)splits * sp / SPL) : 0;
+    const int s_hi = SPL > 1 ? (int)((int64_t)splits * (sp + 1) / SPL) : splits;
+
+    // The loads below are buffer loads with 32-bit lane offsets, so that the many in flight hold no
+    // addresses.  A descriptor covers the array from the chunk's first column on: what lies past its
+    // end (a factor or a set that does not exist) reads as zero, and lanes past the last column or
+    // factor read a neighbour's value that is never used.  BIG: k x len floats exceed 2^31 bytes, so
+    // every row (one per wave at CW = 64) gets a descriptor of its own.
+    static_assert(!BIG || CW == 64, "long factors have 64-column chunks");
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    auto rsrc = [](const float *base, int64_t floats) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, (int)(floats * 4), kRsrcFlags);
+    };
+    auto ld = [](__amdgpu_buffer_rsrc_t r, unsigned off) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    };
+    const int fu = BIG ? __builtin_amdgcn_readfirstlane(fc) : 0;
+    const unsigned rowb = BIG ? 0u : (unsigned)len * 4u;
+    float pb[SB][NC], xo[NC];
+    // splits s .. s + SB - 1 of chunk ch
+    auto request_splits = [&](int64_t ch, int s) {
+        const int64_t left = len - ch * CW;
+#pragma unroll
+        for (int u = 0; u < SB; ++u) {
+            const bool ok = s + u < s_hi;
+            const float *base = part + (ok ? (int64_t)(s + u) * k * len + ch * CW : 0);
+            if (BIG) {
+#pragma unroll
+                for (int ci = 0; ci < NC; ++ci) {
+                    const int c = fu + FG * ci;
+                    pb[u][ci] = ld(rsrc(base + (c < k ? c * len : 0), ok && c < k ? (left < CW ? left : CW) : 0), jl * 4u);
+                }
+            } else {
+                const __amdgpu_buffer_rsrc_t r = rsrc(base, ok ? k * len - ch * CW : 0);
+#pragma unroll
+                for (int ci = 0; ci < NC; ++ci) pb[u][ci] = ld(r, (unsigned)(fc + FG * ci) * rowb + jl * 4u);
+            }
+        }
+    };
+    // the old column and the first batch of splits of chunk ch: requested, not waited for
+    auto request = [&](int64_t ch) {
+        const int64_t left = len - ch * CW;
+        const __amdgpu_buffer_rsrc_t r = rsrc(X + ch * CW, BIG ? 0 : k * len - ch * CW);
+#pragma unroll
+        for (int ci = 0; ci < NC; ++ci) {
+            const int c = (BIG ? fu : fc) + FG * ci;
+            xo[ci] = BIG ? ld(rsrc(X + (c < k ? c * len + ch * CW : 0), c < k ? (left < CW ? left : CW) : 0), jl * 4u)
+                         : ld(r, c * rowb + jl * 4u);
+        }
+        if (part) request_splits(ch, s_lo);
+    };
+    request(blockIdx.x);
 
     // A thread's entries of G (8 at KP = 64) are independent: the loads of up to four entries are
-    // requested together, kGramGroup sets per entry at a time (each trip to L2 costs a microsecond
+    // requested together, kGramBatch sets per entry at a time (each trip to L2 costs a microsecond
     // here), and each entry's sets are added in set order.
+    constexpr int kGramBatch = 16;
     constexpr int EPT = (KP * KP + 64 * NW - 1) / (64 * NW), EG = EPT < 4 ? EPT : 4;
     for (int i0 = 0; i0 < EPT; i0 += EG) {
         float gv[EG];
-        const float *src[EG];
-        bool use[EG];
+        unsigned off[EG];
         const int64_t stride = (int64_t)kt * kt * 1024;
 #pragma unroll
         for (int i = 0; i < EG; ++i) {
             const int e = tid + 64 * NW * (i0 + i);
             const int c = e / KP, d = e % KP;
             // Stacked independent runs: factor indices of different runs do not interact.
-            use[i] = e < KP * KP && c < k && d < k && (!bm.on || bm.id[c] == bm.id[d]);
+            const bool use = e < KP * KP && c < k && d < k && (!bm.on || bm.id[c] == bm.id[d]);
             const int r1 = c & 31, r2 = d & 31;
             const int pos = ((r1 & 3) + 4 * (r1 >> 3)) * 64 + r2 + 32 * ((r1 >> 2) & 1);
-            src[i] = Gfull ? Gfull + (use[i] ? c * k + d : 0)
-                           : gin + (use[i] ? (int64_t)((c >> 5) * kt + (d >> 5)) * 1024 + pos : 0);
+            off[i] = !use ? 0x7fffffffu : 4u * (unsigned)(Gfull ? c * k + d : ((c >> 5) * kt + (d >> 5)) * 1024 + pos);
             gv[i] = 0.f;
         }
-        if (Gfull) {
+        if (Gfull || nbin == 1) {
+            const __amdgpu_buffer_rsrc_t r = rsrc(Gfull ? Gfull : gin, Gfull ? k * k : stride);
 #pragma unroll
-            for (int i = 0; i < EG; ++i) gv[i] = *src[i];
+            for (int i = 0; i < EG; ++i) gv[i] = ld(r, off[i]);
         } else {
-            for (int b = 0; b < nbin; b += kGramGroup) {
-                float t[EG][kGramGroup];
+            const __amdgpu_buffer_rsrc_t r = rsrc(gin, nbin * stride);
+            for (int b = 0; b < nbin; b += kGramBatch) {
+                float t[EG][kGramBatch];
 #pragma unroll
                 for (int i = 0; i < EG; ++i)
 #pragma unroll
-                    for (int u = 0; u < kGramGroup; ++u) t[i][u] = src[i][(b + u < nbin ? b + u : 0) * stride];
+                    for (int u = 0; u < kGramBatch; ++u) t[i][u] = ld(r, off[i] + (unsigned)(b + u) * (unsigned)stride * 4u);
 #pragma unroll
                 for (int i = 0; i < EG; ++i)
 #pragma unroll
-                    for (int u = 0; u < kGramGroup; ++u) gv[i] += b + u < nbin ? t[i][u] : 0.f;
+                    for (int u = 0; u < kGramBatch; ++u) gv[i] += t[i][u];
             }
         }
 #pragma unroll
         for (int i = 0; i < EG; ++i) {
             const int e = tid + 64 * NW * (i0 + i);
-            if (e < KP * KP) Gs[(e / KP) * LD + e % KP] = use[i] ? gv[i] : 0.f;
+            if (e < KP * KP) Gs[(e / KP) * LD + e % KP] = gv[i];
         }
     }
-    __syncthreads();
 
     // Gram tiles of the new X.  One tile (KT = 1): every wave adds up its share of the columns.
     // Four tiles (KT = 2): wave w adds up tile w % 4 over half w / 4 of a chunk's columns, which
@@ -954,92 +1022,88 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
     constexpr bool G2 = KT == 2;
     f32x16 acc = {0};
 
-    const int jl = lane, grp = w;
     double dacc = 0.0;   // sum over this thread's entries of numerator x new value (objective monitor)
-    const int64_t nchunks = (len + 63) >> 6;
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const int64_t j = ch * 64 + jl;
+        const int64_t j = ch * CW + jl;
         const bool okj = j < len;
-        float h[KP];
-#pragma unroll
-        for (int d = 0; d < KP; ++d) {
-            const bool in = okj && d < k;
-            const float v = X[in ? (int64_t)d * len + j : 0];
-            h[d] = in ? v : 0.f;
-        }
         float p[NC];
 #pragma unroll
         for (int ci = 0; ci < NC; ++ci) p[ci] = 0.f;
-        // Partial sums in split order; a few splits' loads are issued together.
-        constexpr int SB = (KP > 32) ? 2 : 4;
-        int s = 0;
-        for (; s + SB <= splits; s += SB) {
-            float t[SB][NC];
+        // Partial sums in split order, a batch of splits at a time.
+        for (int s = s_lo; s < s_hi; s += SB) {
+            if (s > s_lo) request_splits(ch, s);
 #pragma unroll
             for (int u = 0; u < SB; ++u)
+#pragma unroll
+                for (int ci = 0; ci < NC; ++ci) p[ci] += pb[u][ci];
+        }
+        if (sp == 0) {
+#pragma unroll
+            for (int ci = 0; ci < NC; ++ci) Xs[(fc + FG * ci) * CW + jl] = okj ? xo[ci] : 0.f;
+        }
+        if (SPL > 1 && sp > 0) {
+#pragma unroll
+            for (int ci = 0; ci < NC; ++ci) Ps[((sp - 1) * KP + fc + FG * ci) * CW + jl] = p[ci];
+        }
+        __syncthreads();   // Gs and the chunk's old values are complete, Ts is free
+        if (sp == 0) {
+            // denominators: 16 old values of the column at a time against all of the thread's rows of G
+            float den[NC][4];
+#pragma unroll
+            for (int ci = 0; ci < NC; ++ci)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) den[ci][u] = 0.f;
+            constexpr int DB = KP < 16 ? KP : 16;
+#pragma unroll 1   // unrolled, every LDS read is scheduled first and the registers spill
+            for (int d0 = 0; d0 < KP; d0 += DB) {
+                float h[DB];
+#pragma unroll
+                for (int d = 0; d < DB; ++d) h[d] = Xs[(d0 + d) * CW + jl];
 #pragma unroll
                 for (int ci = 0; ci < NC; ++ci) {
-                    const int c = grp + 8 * ci;
-                    const bool in = okj && c < k;
-                    const float v = part[in ? ((int64_t)(s + u) * k + c) * len + j : 0];
-                    t[u][ci] = in ? v : 0.f;
+                    const float *g = Gs + (fc + FG * ci) * LD + d0;
+#pragma unroll
+                    for (int d = 0; d < DB; d += 4) {
+                        const f32x4 gq = *reinterpret_cast<const f32x4 *>(g + d);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) den[ci][u] += gq[u] * h[d + u];
+                    }
                 }
-#pragma unroll
-            for (int u = 0; u < SB; ++u)
-#pragma unroll
-                for (int ci = 0; ci < NC; ++ci) p[ci] += t[u][ci];
-        }
-        for (; s < splits; ++s) {
+            }
 #pragma unroll
             for (int ci = 0; ci < NC; ++ci) {
-                const int c = grp + 8 * ci;
-                const bool in = okj && c < k;
-                const float v = part[in ? ((int64_t)s * k + c) * len + j : 0];
-                p[ci] += in ? v : 0.f;
+                const int c = fc + FG * ci;
+#pragma unroll
+                for (int q = 1; q < SPL; ++q) p[ci] += Ps[((q - 1) * KP + c) * CW + jl];
+                if (c < k && part == nullptr) {
+                    // Gram-only mode: no update, the tiles of the current X are produced
+                    // with exactly the summation order an updating launch would use.
+                    Ts[jl * LDT + c] = okj ? xo[ci] : 0.f;
+                } else if (c < k) {
+                    float nv = 0.f;
+                    if (okj) {
+                        const int64_t at = (int64_t)c * len + j;
+                        nv = xo[ci] * p[ci] / (((den[ci][0] + den[ci][1]) + (den[ci][2] + den[ci][3])) + eps);
+                        X[at] = nv;
+                        dacc += (double)p[ci] * (double)nv;
+                    }
+                    Ts[jl * LDT + c] = nv;   // columns past the end contribute zeros
+                }
             }
         }
-        __syncthreads();   // every old value of this chunk is in registers; Ts is free
-#pragma unroll
-        for (int ci = 0; ci < NC; ++ci) {
-            const int c = grp + 8 * ci;
-            if (c < k && part == nullptr) {
-                // Gram-only mode: no update, the tiles of the current X are produced
-                // with exactly the summation order an updating launch would use.
-                const float v = X[okj ? (int64_t)c * len + j : 0];
-                Ts[jl * LDT + c] = okj ? v : 0.f;
-            } else if (c < k) {
-                float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
-                const float *g = Gs + c * LD;
-#pragma unroll
-                for (int d = 0; d < KP; d += 4) {
-                    d0 += g[d + 0] * h[d + 0];
-                    d1 += g[d + 1] * h[d + 1];
-                    d2 += g[d + 2] * h[d + 2];
-                    d3 += g[d + 3] * h[d + 3];
-                }
-                const float den = ((d0 + d1) + (d2 + d3)) + eps;
-                float nv = 0.f;
-                if (okj) {
-                    const int64_t at = (int64_t)c * len + j;
-                    nv = X[at] * p[ci] / den;
-                    X[at] = nv;
-                    dacc += (double)p[ci] * (double)nv;
-                }
-                Ts[jl * LDT + c] = nv;   // columns past the end contribute zeros
-            }
-        }
+        if (ch + gridDim.x < nchunks) request(ch + gridDim.x);   // other columns: nobody writes them
         __syncthreads();
         if (Xt) {
-            for (int e = tid; e < 64 * k; e += 64 * NW) {
+            for (int e = tid; e < CW * k; e += 64 * NW) {
                 const int jj = e / k, c = e % k;
-                if (ch * 64 + jj < len) Xt[(ch * 64 + jj) * k + c] = Ts[jj * LDT + c];
+                if (ch * CW + jj < len) Xt[(ch * CW + jj) * k + c] = Ts[jj * LDT + c];
             }
         }
         constexpr int PKP = KP <= 32 ? 32 : 64;   // factor slots per row group of the planes
-        if (planes && tid < 8 * PKP) {
+        if (planes && tid < (CW / 8) * PKP) {
             // bf16 piece planes of the new X^T rows of this chunk (layout of split_planes_kernel)
             const int gl = tid / PKP, c = tid % PKP;
-            const int64_t grow = ch * 8 + gl;
+            const int64_t grow = ch * (CW / 8) + gl;
             if (grow * 8 < len) {
                 u32x4 o[3];
 #pragma unroll
@@ -1062,14 +1126,14 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
             const int jj = lane & 31, half = lane >> 5;
             const int ta = (w & 3) >> 1, tb = w & 1, hb = w >> 2;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int row = 32 * hb + 2 * q + half;    // column pair of this chunk
+            for (int q = 0; q < CW / 4; ++q) {
+                const int row = (CW / 2) * hb + 2 * q + half;    // column pair of this chunk
                 acc = mfma32(Ts[row * LDT + 32 * ta + jj], Ts[row * LDT + 32 * tb + jj], acc);
             }
         } else if (gout) {
             const int jj = lane & 31, half = lane >> 5;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < CW / 16; ++q) {
                 const int row = 2 * (w + NW * q) + half;   // column pair of this chunk
                 const float va = Ts[row * LDT + jj];
                 acc = mfma32(va, va, acc);
@@ -1269,7 +1333,7 @@ __global__ __launch_bounds__(512) void aht_pass_kernel(const float *__restrict__
 // the block's rows with GH = H H^T (k x k, complete); then from the new rows in LDS: their
 // bf16 piece planes (operand of the next W^T A pass), this workgroup's share of W^T W (fp32
 // matrix instruction, one tile set per workgroup in gout, which the next W^T A pass adds up
-// in groups) and, with dpart, its share of <A H^T, W_new> in double.
+// up) and, with dpart, its share of <A H^T, W_new> in double.
 // KT = 2 (33 <= k <= 64): planes of 64 factor slots (96 registers per chunk), every cut of A
 // feeds two accumulator chains, R = 2 (four accumulator tiles), 65-float rows in the epilogue,
 // and the block's four tiles of W^T W are added to running tiles in LDS (wave w: tile w % 4
@@ -2280,11 +2344,34 @@ hipError_t launch_gram_sum(const float *gpart, int nb, int k, float *G, hipStrea
     return hipGetLastError();
 }
 
+// Columns per workgroup and chunk of the finisher: 64 fill whole cache lines and leave a row to a
+// wave; shorter factors take narrower chunks, which put up to 256 workgroups on the splits
+// (k = 16 on 512 columns and 128 splits: 27 us with 8 workgroups of 64 columns, 11 with 32 of 16;
+// k = 20 on 4096: 10.5 with 64 workgroups, 7.8 with 128 of 32).
+static int factor_update_width(int64_t len) { return len <= 2048 ? 16 : (len <= 8192 ? 32 : 64); }
+
 int factor_update_blocks(int64_t len)
 {
-    int64_t b = (len + 63) / 64;
+    const int cw = factor_update_width(len);
+    int64_t b = (len + cw - 1) / cw;
     if (b > kFinMaxBlocks) b = kFinMaxBlocks;
     return (int)b;
+}
+
+template <int CW, bool BIG>
+static void factor_update_dispatch(dim3 grid, hipStream_t st, float *X, float *Xt, const float *part, int splits,
+                                   const float *Gfull, const float *gin, int nbin, float *gout, u32x4 *pl,
+                                   double *dpart, int k, int64_t len, float eps, const BlockMap &bm)
+{
+    const dim3 block(512);
+    if (k <= 8)
+        hipLaunchKernelGGL((factor_update_kernel<8, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    else if (k <= 16)
+        hipLaunchKernelGGL((factor_update_kernel<16, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    else if (k <= 32)
+        hipLaunchKernelGGL((factor_update_kernel<32, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    else
+        hipLaunchKernelGGL((factor_update_kernel<64, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
 }
 
 hipError_t launch_factor_update(float *X, float *Xt, const float *part, int splits,
@@ -2297,15 +2384,14 @@ hipError_t launch_factor_update(float *X, float *Xt, const float *part, int spli
     if (map) bm = *map;
     else bm.on = 0;
     // Without Gram output there is no reason to cap the grid: one block per chunk.
-    int64_t blocks = gout ? factor_update_blocks(len) : (len + 63) / 64;
+    const int cw = factor_update_width(len);
+    int64_t blocks = gout ? factor_update_blocks(len) : (len + cw - 1) / cw;
     if (blocks > 65535) blocks = 65535;
-    const dim3 grid((unsigned)blocks), block(512);
-    if (k <= 8)
-        hipLaunchKernelGGL((factor_update_kernel<8>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else if (k <= 32)
-        hipLaunchKernelGGL((factor_update_kernel<32>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else
-        hipLaunchKernelGGL((factor_update_kernel<64>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    const dim3 grid((unsigned)blocks);
+    if (cw == 16) factor_update_dispatch<16, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    else if (cw == 32) factor_update_dispatch<32, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    else if (k * len < ((int64_t)1 << 29)) factor_update_dispatch<64, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    else factor_update_dispatch<64, true>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
     return hipGetLastError();
 }
 

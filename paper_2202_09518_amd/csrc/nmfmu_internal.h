@@ -16,7 +16,6 @@ constexpr int kAhtWaves = 8;        // waves per workgroup in the A H^T pass
 constexpr int kAhtRowTiles = 2;     // 32-row tiles per workgroup in that pass
 constexpr int kGramMaxBlocks = 64;  // partial Gram matrices before the final sum
 constexpr int kFinMaxBlocks = 256;  // finisher blocks when they also emit Gram partials
-constexpr int kGramGroup = 16;      // sets of Gram tiles added up per group by the following pass
 constexpr int kMaxKTiles = 2;       // 32-wide rank tiles: k <= 64
 
 inline int k_tiles(int k) { return (k + 31) / 32; }
@@ -65,8 +64,7 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
                            int64_t rows_per_split, bool accumulate, hipStream_t st,
                            const float *gtiles = nullptr, int nsets = 0, float *gsum = nullptr);
 // gtiles (optional): nsets sets of partial Gram tiles for rank k that the first workgroups of
-// the pass add up in groups of kGramGroup into gsum (gram_groups(nsets) sets).
-inline int gram_groups(int nsets) { return (nsets + kGramGroup - 1) / kGramGroup; }
+// the pass add up into gsum (one set).
 // Ranks above 64, all ceil(k / 64) slices of 64 factors in one launch each: planes of every slice of X
 // (rows x k; slice z at planes + z * planes_bytes(rows)), the pass over A for every slice (aligned A,
 // n % 4 == 0; partials of slice z at ppart + z * splits * 64 * n, packed for that slice's width), and
