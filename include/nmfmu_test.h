@@ -24,7 +24,9 @@ extern "C" {
  *       update fused)   [5] W update (0 for the direct kernel)
  * and kernel_ms[6] names the plan that ran: 2 the row plan (k <= 32, aligned A:
  * both passes stream the row-major A, [0], [3] and [5] are 0 because the Gram
- * matrices and the W update are by-products of the other three kernels), 1 the
+ * matrices and the W update are by-products of the other three kernels; with
+ * n <= 512 columns both products of an iteration are one launch, which is then
+ * [1] except for the run's last W update, whose launch is [4]), 1 the
  * mirrored plan (see nmf_mu_workspace_bytes), 0 the small plan.  kernel_ms[7] and
  * [8]: milliseconds per launch of the W^T A pass and (plans 1 and 2, else 0) of
  * the A H^T pass, from 20 launches back to back between two events after the

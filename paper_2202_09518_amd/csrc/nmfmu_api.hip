@@ -139,6 +139,7 @@ int check_common(const void *a, const void *w, const void *h, int64_t m, int64_t
 // one extra copy of A in the workspace; without it the direct A H^T kernel runs.
 struct DensePlan {
     bool mirrored;
+    bool one_pass = false;     // both products in one reading of A: ppart and planes2 only
     Common c;
     float *ppart;              // row-split partials of either pass
     void *planes;              // bf16 piece planes of the factor a pass contracts with
@@ -182,6 +183,27 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
     return p;
 }
 
+size_t one_pass_bytes(int64_t m, int64_t n, int k)
+{
+    return common_bytes(k) + align_up((size_t)one_pass_blocks(m, n) * k * n * sizeof(float)) + align_up(planes_bytes(n));
+}
+
+DensePlan carve_one_pass(void *ws, int64_t m, int64_t n, int k)
+{
+    Carve cv(ws);
+    DensePlan p;
+    p.mirrored = false;
+    p.one_pass = true;
+    p.c = carve_common(cv, k);
+    p.ppart = cv.take<float>((size_t)one_pass_blocks(m, n) * k * n);
+    p.planes2 = cv.take<char>(planes_bytes(n));
+    p.planes = nullptr;
+    p.At = p.Wt = p.Ht = nullptr;
+    p.s1 = p.s2 = 0;
+    p.rps1 = p.rps2 = 0;
+    return p;
+}
+
 // Which plan runs.  Up to 32 factors the row plan comes first wherever its kernel applies.  From 33
 // to 64 factors its A H^T pass is slower than the W^T A kernel on a transposed copy (622 against
 // 525 us on 32768 x 16384, 167 against 132 us on 16384 x 8192), so there the mirrored plan comes
@@ -215,6 +237,37 @@ int dense_workspace(const float *A, int64_t m, int64_t n, int k, void **ws, bool
     return ensure_workspace(small, ws);
 }
 
+bool have_workspace(size_t need)
+{
+    void *ws = nullptr;
+    if ((g.ws && g.ws_bytes >= need) || (g.ws_owned && ensure_workspace(need, &ws) == NMF_OK)) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// The plan of a dense run with `extra` bytes behind it (*tail): the one-pass plan where it applies,
+// else the row or the mirrored plan, else the small one; whatever the workspace can hold.
+int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, DensePlan *p, char **tail)
+{
+    void *ws = nullptr;
+    size_t bytes = one_pass_bytes(m, n, k);
+    if (one_pass_ok(A, n, k) && have_workspace(bytes + extra)) {
+        *p = carve_one_pass(g.ws, m, n, k);
+    } else {
+        bool mirrored = false;
+        bytes = dense_bytes(m, n, k, true);
+        if (!rows_plan_first(A, m, n, k) && have_workspace(bytes + extra)) {
+            mirrored = true;
+        } else {
+            bytes = dense_bytes(m, n, k, false);
+            if (int rc = ensure_workspace(bytes + extra, &ws)) return rc;
+        }
+        *p = carve_dense(g.ws, m, n, k, mirrored);
+    }
+    if (tail) *tail = static_cast<char *>(g.ws) + bytes;
+    return NMF_OK;
+}
+
 constexpr int kDenseKernels = 6;
 
 // Per-iteration objective of a dense run (device memory): out[it] after iteration it.
@@ -235,6 +288,43 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
                hipEvent_t *ev = nullptr, const BlockMap *map = nullptr, const Monitor *mon = nullptr)
 {
     const Common &c = p.c;
+    if (p.one_pass) {
+        // Per iteration: the pass that finishes the previous one (A H^T, the W update) and leaves W^T A
+        // and W^T W of the new W as one share per workgroup, then the H update; the last W update has a
+        // pass of its own without W^T A.  Up to kFewSets tile sets are added by the consumer's
+        // workgroups themselves, more by a launch of their own.
+        constexpr int kFewSets = 32;
+        const int nbw = one_pass_blocks(m, n), nbh = factor_update_blocks(n);
+        auto pass = [&](int done, bool product) -> int {       // `done` H updates so far
+            const bool report = done && mon && (!mon->last_only || done == iters);
+            const bool whole = nbh > kFewSets;      // whether or not the objective is wanted: same bits
+            if (done && (whole || report)) NMF_HIP(launch_gram_sum(c.ghp, nbh, k, c.gh, st));
+            NMF_HIP(launch_one_pass(A, m, n, k, p.planes2, whole ? c.gh : nullptr, c.ghp, nbh, W, W, p.ppart, c.gwp, eps, st,
+                                    done > 0, product, report ? mon->dpart : nullptr));
+            if (report) {
+                NMF_HIP(launch_gram_sum(c.gwp, nbw, k, c.gw, st));
+                NMF_HIP(launch_objective(mon->dpart, nbw, c.gw, c.gh, k, mon->normA2,
+                                         mon->out + (mon->last_only ? 0 : done - 1), st));
+            }
+            return NMF_OK;
+        };
+        if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+        for (int it = 0; it < iters; ++it) {
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (int rc = pass(it, true)) return rc;
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (nbw > kFewSets) NMF_HIP(launch_gram_sum(c.gwp, nbw, k, c.gw, st));
+            NMF_HIP(launch_factor_update(H, nullptr, p.ppart, nbw, nbw > kFewSets ? c.gw : nullptr, c.gwp, nbw, c.ghp, k, n,
+                                         eps, st, map, p.planes2));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (it == iters - 1)
+                if (int rc = pass(iters, false)) return rc;
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+        }
+        return NMF_OK;
+    }
     // The plan may have been carved for a larger rank (stacks of an ensemble): split
     // counts follow the rank actually run; the partial buffer holds the largest case.
     const int s1 = wta_splits(m, n, k), s2 = wta_splits(n, m, k);
@@ -772,13 +862,23 @@ int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k, float *W, floa
     // can hold the copy, and only with a normal positive eps: with eps = 0 a zero column gives 0 / 0.
     const int64_t n4 = (n + 3) & ~(int64_t)3;
     const bool misaligned = (reinterpret_cast<uintptr_t>(A) & 15u) != 0 || n != n4;
-    if (misaligned && eps >= 1.17549435e-38f && aht_rows_ok(nullptr, m, n4, k)) {
-        const size_t base = dense_bytes(m, n4, k, false);
-        const size_t need = base + align_up((size_t)m * n4 * sizeof(float)) + align_up((size_t)k * n4 * sizeof(float));
-        if ((g.ws && g.ws_bytes >= need) || (g.ws_owned && ensure_workspace(need, &ws) == NMF_OK)) {
-            ws = g.ws;
-            const DensePlan p = carve_dense(ws, m, n4, k, false);
-            Carve cv(static_cast<char *>(ws) + base);
+    if (misaligned && eps >= 1.17549435e-38f) {
+        const size_t copies = align_up((size_t)m * n4 * sizeof(float)) + align_up((size_t)k * n4 * sizeof(float));
+        size_t base = one_pass_bytes(m, n4, k);
+        DensePlan p;
+        bool padded = false;
+        if (one_pass_ok(nullptr, n4, k) && have_workspace(base + copies)) {
+            p = carve_one_pass(g.ws, m, n4, k);
+            padded = true;
+        } else if (aht_rows_ok(nullptr, m, n4, k)) {
+            base = dense_bytes(m, n4, k, false);
+            if (have_workspace(base + copies)) {
+                p = carve_dense(g.ws, m, n4, k, false);
+                padded = true;
+            }
+        }
+        if (padded) {
+            Carve cv(static_cast<char *>(g.ws) + base);
             float *Ap = cv.take<float>((size_t)m * n4);
             float *Hp = cv.take<float>((size_t)k * n4);
             NMF_HIP(launch_pad_copy(A, n, Ap, n4, m, n, st));
@@ -787,11 +887,9 @@ int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k, float *W, floa
             NMF_HIP(launch_pad_copy(Hp, n4, H, n, k, n, st));
             return NMF_OK;
         }
-        (void)hipGetLastError();
     }
-    bool mirrored = false;
-    if (int rc = dense_workspace(A, m, n, k, &ws, &mirrored)) return rc;
-    const DensePlan p = carve_dense(ws, m, n, k, mirrored);
+    DensePlan p;
+    if (int rc = dense_plan(A, m, n, k, 0, &p, nullptr)) return rc;
     return dense_body(A, m, n, k, W, H, iters, eps, p, st);
 }
 
@@ -803,10 +901,9 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
     if (iters < 1 || iters > 4096) return fail(NMF_EINVAL, "profiled run needs 1 <= iters <= 4096%s");
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
-    void *ws = nullptr;
-    bool mirrored = false;
-    if (int rc = dense_workspace(A, m, n, k, &ws, &mirrored)) return rc;
-    const DensePlan p = carve_dense(ws, m, n, k, mirrored);
+    DensePlan p;
+    if (int rc = dense_plan(A, m, n, k, 0, &p, nullptr)) return rc;
+    const bool mirrored = p.mirrored, one_pass = p.one_pass;
     constexpr int NK = kDenseKernels;
     std::vector<hipEvent_t> ev((size_t)iters * NK + 1, nullptr);
     int rc = NMF_OK;
@@ -826,7 +923,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
                 sum[j] += ms;
             }
         for (int j = 0; j < NK; ++j) kernel_ms[j] = (float)(sum[j] / iters);
-        kernel_ms[NK] = rows_plan_runs(A, m, n, k, mirrored) ? 2.f : (mirrored ? 1.f : 0.f);
+        kernel_ms[NK] = one_pass || rows_plan_runs(A, m, n, k, mirrored) ? 2.f : (mirrored ? 1.f : 0.f);
         kernel_ms[NK + 1] = kernel_ms[NK + 2] = 0.f;
     }
     // The pass kernels once more, `reps` launches back to back between two events: the
@@ -836,14 +933,17 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
         const int reps = 20;
         const int s1 = wta_splits(m, n, k), s2 = wta_splits(n, m, k);
         const int64_t rps1 = wta_rows_per_split(m, s1), rps2 = wta_rows_per_split(n, s2);
-        const bool rows_plan = rows_plan_runs(A, m, n, k, mirrored);
+        const bool rows_plan = !one_pass && rows_plan_runs(A, m, n, k, mirrored);
         const Common &c = p.c;
-        for (int which = 0; which < ((mirrored || rows_plan) ? 2 : 1) && rc == NMF_OK; ++which) {
-            if (which == 0) (void)launch_split_planes(W, m, k, p.planes, st);
+        for (int which = 0; which < ((mirrored || rows_plan || one_pass) ? 2 : 1) && rc == NMF_OK; ++which) {
+            if (one_pass) (void)0;
+            else if (which == 0) (void)launch_split_planes(W, m, k, p.planes, st);
             else if (!rows_plan) (void)launch_split_planes(p.Ht, n, k, p.planes, st);
             hipError_t e = hipEventRecord(ev[0], st);
             for (int r = 0; r < reps && e == hipSuccess; ++r)
-                e = which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st)
+                e = one_pass ? launch_one_pass(A, m, n, k, p.planes2, nullptr, c.ghp, factor_update_blocks(n), W, nullptr, p.ppart,
+                                               c.gwp, eps, st, which == 1, which == 0)
+                    : which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st)
                     : rows_plan  // the fused pass without its stores to W
                         ? launch_aht_rows(A, m, n, k, p.planes2, c.gh, W, p.planes, c.gwp, eps, st, false, nullptr,
                                           nullptr, true)
@@ -1450,24 +1550,16 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     if (!(tol >= 0.0) || check_every < 1) return fail(NMF_EINVAL, "tol must be >= 0 and check_every >= 1%s");
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
-    void *ws = nullptr;
-    bool mirrored = false;
     // the residual scratch and the monitor's few doubles ride behind whichever dense plan fits
     const size_t extra = residual_scratch_bytes(m, n) + align_up((size_t)kFinMaxBlocks * sizeof(double)) +
                          align_up(4097 * sizeof(double)) + kAlign;
-    const size_t big = dense_bytes(m, n, k, true) + extra, small = dense_bytes(m, n, k, false) + extra;
-    if (!rows_plan_first(A, m, n, k) &&
-        ((g.ws && g.ws_bytes >= big) || (g.ws_owned && ensure_workspace(big, &ws) == NMF_OK))) {
-        mirrored = true;
-    } else {
-        (void)hipGetLastError();
-        if (int rc = ensure_workspace(small, &ws)) return rc;
-    }
-    ws = g.ws;
-    const bool rows_plan = rows_plan_runs(A, m, n, k, mirrored);
-    const bool fast = mirrored || rows_plan;   // plans whose W update leaves the objective's terms behind
-    const DensePlan p = carve_dense(ws, m, n, k, mirrored);
-    Carve cv(static_cast<char *>(ws) + dense_bytes(m, n, k, mirrored));
+    DensePlan p;
+    char *tail = nullptr;
+    if (int rc = dense_plan(A, m, n, k, extra, &p, &tail)) return rc;
+    const bool mirrored = p.mirrored;
+    // plans whose W update leaves the objective's terms behind
+    const bool fast = mirrored || p.one_pass || rows_plan_runs(A, m, n, k, mirrored);
+    Carve cv(tail);
     double *scratch = cv.take<double>((size_t)residual_partials(m, n) + 1);
     Monitor mon;
     mon.dpart = cv.take<double>(kFinMaxBlocks);
@@ -1527,27 +1619,17 @@ int nmf_mu_dense_monitor(const float *A, int64_t m, int64_t n, int32_t k, float 
     std::lock_guard<std::mutex> lock(g.mu);
     const size_t extra = align_up((size_t)kFinMaxBlocks * sizeof(double)) + align_up(4097 * sizeof(double)) +
                          align_up((size_t)iters * sizeof(double)) + residual_scratch_bytes(m, n);
-    const size_t big = dense_bytes(m, n, k, true) + extra, small = dense_bytes(m, n, k, false) + extra;
-    void *ws = nullptr;
-    bool mirrored = false;
-    if (!rows_plan_first(A, m, n, k) &&
-        ((g.ws && g.ws_bytes >= big) || (g.ws_owned && ensure_workspace(big, &ws) == NMF_OK))) {
-        mirrored = true;
-    } else {
-        (void)hipGetLastError();
-        if (int rc = ensure_workspace(small, &ws)) return rc;
-    }
-    ws = g.ws;
-    const bool rows_plan = rows_plan_runs(A, m, n, k, mirrored);
-    const DensePlan p = carve_dense(ws, m, n, k, mirrored);
-    Carve cv(static_cast<char *>(ws) + dense_bytes(m, n, k, mirrored));
+    DensePlan p;
+    char *tail = nullptr;
+    if (int rc = dense_plan(A, m, n, k, extra, &p, &tail)) return rc;
+    Carve cv(tail);
     Monitor mon;
     mon.dpart = cv.take<double>(kFinMaxBlocks);
     mon.normA2 = cv.take<double>(4097);
     mon.out = cv.take<double>((size_t)iters);
     mon.res = cv.take<double>((size_t)residual_partials(m, n) + 1);
     mon.last_only = false;
-    if (mirrored || rows_plan) NMF_HIP(launch_sumsq(A, m * n, mon.normA2 + 1, mon.normA2, st));
+    if (p.mirrored || p.one_pass || rows_plan_runs(A, m, n, k, p.mirrored)) NMF_HIP(launch_sumsq(A, m * n, mon.normA2 + 1, mon.normA2, st));
     if (int rc = dense_body(A, m, n, k, W, H, iters, eps, p, st, false, nullptr, nullptr, &mon)) return rc;
     NMF_HIP(hipMemcpyAsync(objective_host, mon.out, (size_t)iters * sizeof(double), hipMemcpyDeviceToHost, st));
     NMF_HIP(hipStreamSynchronize(st));
@@ -1571,7 +1653,8 @@ int nmf_mu_dense_noalloc(const float *A, int64_t m, int64_t n, int32_t k, float 
     // the kernels restore that, but an earlier call may have been cut short.  A fill kernel, not
     // a memset: the call may be under graph capture.
     NMF_HIP(launch_fill_f32(static_cast<float *>(ws), 64, 0.f, st));
-    const DensePlan p = carve_dense(ws, m, n, k, false);
+    const bool one = one_pass_ok(A, n, k) && one_pass_bytes(m, n, k) <= kScratchBytes;
+    const DensePlan p = one ? carve_one_pass(ws, m, n, k) : carve_dense(ws, m, n, k, false);
     return dense_body(A, m, n, k, W, H, iters, eps, p, st);
 }
 

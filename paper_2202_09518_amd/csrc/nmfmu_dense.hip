@@ -1609,6 +1609,329 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// Both products in one reading of A, for few columns (k <= 32, 16-byte aligned A, n % 4 == 0,
+// n <= 512 / NRW; the "one-pass plan").  A block of 32 NRW rows is all that the W update of these rows
+// needs, and W^T A of the NEXT iteration needs only their new values: so a workgroup takes a
+// block, forms A H^T, updates W and at once adds the new rows' share of W^T A and W^T W.
+//   update:  W <- W * (A H^T) / (W H H^T + eps) for the block's rows (else W is taken as it is)
+//   product: this workgroup's sum of W^T A over its row blocks goes to ppart[blockIdx.x] (k x n)
+// and its W^T W, always, to gout (one tile set); with dpart its share of <A H^T, W> in double.
+//
+// 8 waves = NRW row tiles x NCW column groups; wave (rw, cw) owns 32 rows and 64 columns of the
+// block.  The arithmetic is that of the other passes: A cut with rounding against truncated
+// pieces of H and W, six piece products, fp32 accumulation.
+//   1. A arrives coalesced (4 rows x 256 bytes per instruction, requested a block ahead) and goes
+//      to the wave's 8 KiB of LDS, swizzled by row as in aht_rows_kernel; read back row by lane it
+//      is the operand of A H^T (B_op: the planes of the wave's 64 columns of H^T, which stay in
+//      registers over all blocks).
+//   2. The waves' 32 x 32 shares of A H^T meet in LDS; each lane owns 2 NRW entries of the
+//      block's rows (factor = lane % 32), for which it has formed W H H^T meanwhile; it
+//      updates them, and leaves the pieces of the new rows in LDS.
+//   3. Every wave reads its tile again, columns by lane, for W^T A.
+// Two barriers per block.  An accumulator of W^T A takes in at most kOnePassFlush blocks (512 rows)
+// before it is added, in rounded fp32, to ppart.
+// The pieces of W never leave the chip, and A comes from memory once per iteration instead of
+// twice.  One workgroup (8 waves, 116 KiB of LDS) fills a compute unit; its chain of LDS round
+// trips, not the memory, bounds it: 314 us on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
+// against 215 us for the W^T A pass and 340 us for aht_rows_kernel there.  Two chunks of columns
+// per wave (n up to 1024), with the second reading from the caches, gained 0.95 to 1.15x only,
+// three lost to the row plan (0.73 to 1.01x): hence the limit.
+// ---------------------------------------------------------------------------
+constexpr int kOnePassFlush = 16;
+template <int NRW, int POLICY, bool update, bool product>
+__global__ __launch_bounds__(512, 2) void one_pass_kernel(
+    const float *__restrict__ A, const u32x4 *__restrict__ planesH, const float *__restrict__ GH,
+    const float *__restrict__ ghsets, int nbh, const float *W, float *Wnew, float *__restrict__ ppart,
+    float *__restrict__ gout, double *__restrict__ dpart, int64_t rows, int64_t n, int k, float eps)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr int NCW = 8 / NRW, RB = 32 * NRW, NO = 2 * NRW, LDW = 36;
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    constexpr unsigned kOut = 0x7fffffffu;   // an offset outside every extent: reads as zero
+    float *lds = aht_rows_lds;               // staging tiles: 8 x 2048 floats
+    float *Qp = lds + 8 * 2048;              // the waves' shares of A H^T: 8 x 1024
+    u32x4 *Wp = reinterpret_cast<u32x4 *>(Qp + 8 * 1024);              // pieces of the new rows [3][RB / 8][32]
+    float *Ws = reinterpret_cast<float *>(Wp + 3 * (RB / 8) * 32);     // old rows [RB][LDW]
+    float *Gs = Ws + RB * LDW;               // H H^T [32][LDW], symmetric: row c is column c
+    __shared__ double dsum[8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = w / NCW, cw = w % NCW;
+    const int jj = lane & 31, half = lane >> 5;
+    float *stg = lds + w * 2048;
+    const unsigned rowb = (unsigned)(n * 4);
+    const int nchunks = (int)((n + 63) >> 6);
+    const int64_t ngroups = (n + 7) >> 3;
+    const int64_t nblocks = (rows + RB - 1) / RB;
+    const int lrow = lane >> 4, lch = lane & 15;
+
+    struct Rows { u32x4 a[8]; };       // coalesced: instruction u = rows 4 u .. 4 u + 3, lane = (row, 16-byte chunk)
+    auto load_rows = [&](Rows &s, int64_t blk) {
+        const int64_t rbase = blk * RB + 32 * rw;
+        int64_t av = rows - rbase;                  // rows of this wave's tile that exist
+        av = av < 0 || blk >= nblocks || cw >= nchunks ? 0 : (av > 32 ? 32 : av);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(A + (av ? rbase * n + cw * 64 : 0)), 0,
+            (int)(av ? av * (int64_t)rowb - cw * 256 : 0), kRsrcFlags);
+        unsigned lo = (cw * 64 + lch * 4 < n) ? (unsigned)lrow * rowb + (unsigned)lch * 16 : kOut;
+        asm volatile("" : "+v"(lo));   // the rows' offsets are added here, not kept in registers across the block
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s.a[u] = __builtin_amdgcn_raw_buffer_load_b128(r, lo + (unsigned)(4 * u) * rowb, 0, POLICY);
+    };
+    float wnext[NO];                   // this lane's entries of W of the next block
+    const int ob = w * 4 * NRW + half * NO;
+    auto load_w = [&](int64_t blk) {
+        int64_t av = rows - blk * RB;
+        av = av < 0 || blk >= nblocks ? 0 : (av > RB ? RB : av);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(W + (av ? blk * RB * k : 0)), 0, (int)(av * k * 4), kRsrcFlags);
+#pragma unroll
+        for (int i = 0; i < NO; ++i)
+            wnext[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, jj < k ? (unsigned)((ob + i) * k + jj) * 4u : kOut, 0, 0));
+    };
+    u32x4 bp[4][3];                    // planes of H^T, this wave's 64 columns
+    if (update) {
+        const int64_t g = (int64_t)cw * 8;
+        int64_t ng = ngroups - g;                   // 8-column groups of planes that exist
+        ng = ng < 0 ? 0 : (ng > 8 ? 8 : ng);
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u32x4 *>(planesH + (ng ? g : 0) * 3 * 32), 0, (int)(ng * 3 * 32 * 16), kRsrcFlags);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                bp[s][pl] = __builtin_amdgcn_raw_buffer_load_b128(rp, (unsigned)(((2 * s + half) * 3 + pl) * 32 + jj) * 16, 0, 0);
+    }
+    auto to_lds = [&](const Rows &s) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int row = 4 * u + lrow;
+            *reinterpret_cast<f32x4 *>(stg + row * 64 + ((lch ^ (row & 15)) << 2)) = __builtin_bit_cast(f32x4, s.a[u]);
+        }
+    };
+
+    Rows ra;
+    int64_t blk = blockIdx.x;
+    load_rows(ra, blk);
+    load_w(blk);
+    if (update) {
+        // H H^T: complete, or the H update's tile sets added up in set order
+        constexpr int B = 16;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = tid + 512 * i, d = e >> 5, c = e & 31;
+            const bool in = c < k && d < k;
+            const int pos = ((d & 3) + 4 * (d >> 3)) * 64 + c + 32 * ((d >> 2) & 1);
+            float g = 0.f;
+            if (GH) {
+                g = GH[in ? d * k + c : 0];
+            } else {
+                for (int b = 0; b < nbh; b += B) {
+                    float t[B];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) t[u] = ghsets[(b + u < nbh ? b + u : 0) * 1024 + (in ? pos : 0)];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) g += b + u < nbh ? t[u] : 0.f;
+                }
+            }
+            Gs[d * LDW + c] = in ? g : 0.f;
+        }
+        __syncthreads();
+    }
+
+    f32x16 acc[2], gacc = {0};
+    acc[0] = f32x16{0};
+    acc[1] = f32x16{0};
+    double dacc = 0.0;
+    bool first = true;      // nothing in ppart yet
+    // adds the accumulators to this workgroup's partial; the row tiles of a column group in order
+    auto flush = [&]() {
+        if (NRW > 1) {
+            __syncthreads();          // the staging tiles are free
+            if (rw > 0) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) stg[(q * 16 + v) * 64 + lane] = acc[q][v];
+            }
+            __syncthreads();
+        }
+        if (rw == 0) {
+            // nothing to add to yet: an extent of zero reads as zeros; factors and columns that do not
+            // exist lie outside the extent and are dropped
+            float *part = ppart + (int64_t)blockIdx.x * k * n;
+            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(part, 0, first ? 0 : k * (int)rowb, kRsrcFlags);
+            const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(part, 0, k * (int)rowb, kRsrcFlags);
+            const int col = cw * 64 + 2 * jj;
+            unsigned at = col < n ? (unsigned)(4 * half) * rowb + (unsigned)col * 4 : kOut;
+            asm volatile("" : "+v"(at));
+            u32x2 old[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) old[v] = __builtin_amdgcn_raw_buffer_load_b64(ro, at + (unsigned)acc_row(v, 0) * rowb, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                f32x2 val = {acc[0][v], acc[1][v]};
+#pragma unroll
+                for (int r = 1; r < NRW; ++r) {
+                    const float *o = lds + (r * NCW + cw) * 2048;
+                    val.x += o[v * 64 + lane];
+                    val.y += o[(16 + v) * 64 + lane];
+                }
+                val.x += __uint_as_float(old[v].x);
+                val.y += __uint_as_float(old[v].y);
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, val), rn, at + (unsigned)acc_row(v, 0) * rowb, 0, 0);
+            }
+        }
+        if (NRW > 1) __syncthreads();
+        acc[0] = f32x16{0};
+        acc[1] = f32x16{0};
+        first = false;
+    };
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};   // smallest first
+    int done = 0;
+    for (; blk < nblocks; blk += gridDim.x) {
+        const int64_t i0 = blk * RB, next = blk + gridDim.x;
+        float wold[NO];
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            wold[i] = wnext[i];
+            Ws[(ob + i) * LDW + jj] = wold[i];
+        }
+        to_lds(ra);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(ra, next);
+        load_w(next);
+        __builtin_amdgcn_sched_barrier(0);
+        float wn[NO];
+        if (update) {
+            f32x16 q[2];
+            q[0] = f32x16{0};
+            q[1] = f32x16{0};
+#pragma unroll
+            for (int s = 0; s < 4; s += 2) {      // two steps, two chains of products
+                u32x4 at[2][3];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int c0 = 4 * (s + t) + 2 * half;
+                    const f32x4 x0 = *reinterpret_cast<const f32x4 *>(stg + jj * 64 + ((c0 ^ (jj & 15)) << 2));
+                    const f32x4 x1 = *reinterpret_cast<const f32x4 *>(stg + jj * 64 + (((c0 + 1) ^ (jj & 15)) << 2));
+                    cut2(x0.x, x0.y, at[t], 0);
+                    cut2(x0.z, x0.w, at[t], 1);
+                    cut2(x1.x, x1.y, at[t], 2);
+                    cut2(x1.z, x1.w, at[t], 3);
+                }
+#pragma unroll
+                for (int e = 0; e < 6; ++e)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) q[t] = mfma_bf16(at[t][PA[e]], bp[s + t][PB[e]], q[t]);
+                __builtin_amdgcn_sched_barrier(0);   // hoisted LDS reads would spill
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) Qp[w * 1024 + v * 64 + lane] = q[0][v] + q[1][v];
+            // W H H^T of this lane's entries (its wave wrote their rows above)
+            float den[NO][2];
+#pragma unroll
+            for (int i = 0; i < NO; ++i) den[i][0] = den[i][1] = 0.f;
+#pragma unroll 2
+            for (int d = 0; d < 32; d += 4) {
+                const f32x4 g = *reinterpret_cast<const f32x4 *>(Gs + jj * LDW + d);
+#pragma unroll
+                for (int i = 0; i < NO; ++i) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(Ws + (ob + i) * LDW + d);
+                    den[i][0] += x.x * g.x;
+                    den[i][1] += x.y * g.y;
+                    den[i][0] += x.z * g.z;
+                    den[i][1] += x.w * g.w;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NO; ++i) {
+                const int row = ob + i, rt = row >> 5, r = row & 31;
+                const float *src = Qp + rt * NCW * 1024 + ((r & 3) | ((r >> 3) << 2)) * 64 + 32 * ((r >> 2) & 1) + jj;
+                float qs = src[0];
+#pragma unroll
+                for (int c = 1; c < NCW; ++c) qs += src[c * 1024];
+                wn[i] = 0.f;
+                if (i0 + row < rows && jj < k) {
+                    wn[i] = wold[i] * qs / ((den[i][0] + den[i][1]) + eps);
+                    if (Wnew) Wnew[(i0 + row) * k + jj] = wn[i];
+                    dacc += (double)qs * (double)wn[i];
+                }
+            }
+        } else {
+            __syncthreads();           // the last block's readers of Wp are done
+#pragma unroll
+            for (int i = 0; i < NO; ++i) wn[i] = wold[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NO; ++i) gacc = mfma32(wn[i], wn[i], gacc);   // rows of the two halves
+        if (product) {
+#pragma unroll
+            for (int i = 0; i < NO; i += 2) {
+                unsigned h[2], m[2], l[2];
+                split3(wn[i], h[0], m[0], l[0]);
+                split3(wn[i + 1], h[1], m[1], l[1]);
+                const int row = ob + i;
+                unsigned *dst = reinterpret_cast<unsigned *>(Wp + (row >> 3) * 32 + jj) + ((row & 7) >> 1);
+                dst[0] = pack2(h[0], h[1]);
+                dst[(RB / 8) * 32 * 4] = pack2(m[0], m[1]);
+                dst[2 * (RB / 8) * 32 * 4] = pack2(l[0], l[1]);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int st = 0; st < 2; ++st) {
+                u32x2 x[8];            // columns 2 jj, 2 jj + 1 of rows 16 st + 8 half + e
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int row = 16 * st + 8 * half + e;
+                    x[e] = *reinterpret_cast<const u32x2 *>(stg + row * 64 + (((jj >> 1) ^ (row & 15)) << 2) + ((jj & 1) << 1));
+                }
+                u32x4 wt[3], at[2][3];
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) wt[pl] = Wp[(pl * (RB / 8) + 4 * rw + 2 * st + half) * 32 + jj];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int pr = 0; pr < 4; ++pr) cut2(__uint_as_float(x[2 * pr][q]), __uint_as_float(x[2 * pr + 1][q]), at[q], pr);
+#pragma unroll
+                for (int e = 0; e < 6; ++e)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) acc[q] = mfma_bf16(wt[PB[e]], at[q][PA[e]], acc[q]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (++done == kOnePassFlush) {
+                flush();
+                done = 0;
+            }
+        } else {
+            __syncthreads();           // the shares of A H^T are read; the next block writes its own
+        }
+    }
+    if (product && done) flush();
+    if (dpart) {
+        for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
+        if (lane == 0) dsum[w] = dacc;
+    }
+    // this workgroup's W^T W: the eight waves' tiles added in wave order
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) Qp[w * 1024 + v * 64 + lane] = gacc[v];
+    __syncthreads();
+    for (int e = tid; e < 1024; e += 512) {
+        float t = Qp[e];
+#pragma unroll
+        for (int ww = 1; ww < 8; ++ww) t += Qp[ww * 1024 + e];
+        gout[(int64_t)blockIdx.x * 1024 + e] = t;
+    }
+    if (dpart && tid == 0) {
+        double t = 0.0;
+        for (int i = 0; i < 8; ++i) t += dsum[i];
+        dpart[blockIdx.x] = t;
+    }
+}
+
 // G (k x k, ld k) = sum over nb sets of partial 32 x 32 tiles (accumulator layout).
 // Eight lanes share one entry: lane q adds sets q, q+8, ... in order, then the
 // eight sums are combined in a fixed tree, so the result does not depend on timing.
@@ -2594,6 +2917,62 @@ hipError_t launch_aht_rows(const float *A, int64_t rows, int64_t n, int k, const
     if (k > 32) return aht_rows_launch<2, 2>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
     if (aht_rows_tiles(rows, k) == 4) return aht_rows_launch<4, 1>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
     return aht_rows_launch<2, 1>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
+}
+
+bool one_pass_ok(const float *A, int64_t n, int k)
+{
+    // Whatever the number of rows: per iteration against the row plan (us), n = 160, k = 16, m = 256 /
+    // 16000 / 262144: 26.6 / 41.9 / 192 -> 17.0 / 33.8 / 103; n = 512: 27.2 / 48.4 / 326 -> 17.5 / 39.7 /
+    // 175.  1.07 to 2.06x over n = 160 to 512, m = 256 to 262144, k = 4 to 32.
+    return k <= 32 && vec_ok(A, n) && n <= 512;
+}
+
+int one_pass_blocks(int64_t rows, int64_t n)
+{
+    const int rb = n <= 256 ? 64 : 32;
+    const int64_t b = (rows + rb - 1) / rb;
+    return (int)(b < kFinMaxBlocks ? b : kFinMaxBlocks);
+}
+
+template <int NRW, int POLICY, bool update, bool product>
+static hipError_t one_pass_launch(dim3 grid, hipStream_t st, const float *A, const u32x4 *planesH, const float *GH,
+                                  const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, double *dpart,
+                                  int64_t rows, int64_t n, int k, float eps)
+{
+    constexpr int kLdsBytes = (8 * 2048 + 8 * 1024 + 3 * 4 * NRW * 32 * 4 + 32 * NRW * 36 + 32 * 36) * (int)sizeof(float);
+    static bool raised = false;      // more dynamic LDS than the default limit: asked for once per process
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&one_pass_kernel<NRW, POLICY, update, product>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    hipLaunchKernelGGL((one_pass_kernel<NRW, POLICY, update, product>), grid, dim3(512), kLdsBytes, st, A, planesH, GH, ghsets, nbh, W, Wnew,
+                       ppart, gout, dpart, rows, n, k, eps);
+    return hipGetLastError();
+}
+
+hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const void *planesH, const float *GH,
+                           const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, float eps,
+                           hipStream_t st, bool update, bool product, double *dpart)
+{
+    if (!one_pass_ok(A, n, k) || !gout || (!update && !product) || (product && !ppart) || (update && (!planesH || (!GH && !ghsets))))
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)one_pass_blocks(rows, n));
+    const u32x4 *ph = static_cast<const u32x4 *>(planesH);
+#define NMFMU_ONE_PASS(NRW, POL) \
+    return !update ? one_pass_launch<NRW, POL, false, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
+         : product ? one_pass_launch<NRW, POL, true, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
+                   : one_pass_launch<NRW, POL, true, false>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps)
+    // A that stays in the last-level cache from one iteration to the next is loaded to stay there
+    const bool stream = rows * n * 4 > ((int64_t)192 << 20);
+    if (n <= 256) {
+        if (stream) NMFMU_ONE_PASS(2, kStreamLoad);
+        NMFMU_ONE_PASS(2, 0);
+    }
+    if (stream) NMFMU_ONE_PASS(1, kStreamLoad);
+    NMFMU_ONE_PASS(1, 0);
+#undef NMFMU_ONE_PASS
 }
 
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st)

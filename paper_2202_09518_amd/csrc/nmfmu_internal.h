@@ -122,6 +122,17 @@ hipError_t launch_aht_rows(const float *A, int64_t rows, int64_t n, int k, const
                            const float *GH, float *W, void *planesW, float *gout, float eps, hipStream_t st,
                            bool gram_only = false, const BlockMap *map = nullptr, double *dpart = nullptr,
                            bool dry = false);
+// Both products in one reading of A (few columns; see one_pass_kernel).  ppart: one k x n partial
+// of W^T A per workgroup (one_pass_blocks of them), gout: one tile set of W^T W each, dpart
+// (optional): one double each.  H H^T either complete (GH) or as nbh tile sets (ghsets).
+// update: W is updated first, into Wnew (W itself, or null: not stored; planesH: piece planes of H^T);
+// product: W^T A is wanted.
+bool one_pass_ok(const float *A, int64_t n, int k);
+int one_pass_blocks(int64_t rows, int64_t n);
+hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const void *planesH, const float *GH,
+                           const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, float eps,
+                           hipStream_t st, bool update, bool product, double *dpart = nullptr);
+
 // out[0] = sum of in[0 .. count), added in a fixed order (strided per thread, then the threads in order).
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st);
 
