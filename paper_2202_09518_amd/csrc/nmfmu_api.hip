@@ -140,6 +140,7 @@ int check_common(const void *a, const void *w, const void *h, int64_t m, int64_t
 struct DensePlan {
     bool mirrored;
     bool one_pass = false;     // both products in one reading of A: ppart and planes2 only
+    int64_t a_rows = 0;        // mirrored: rows of A itself when those of W are padded (0: the same)
     Common c;
     float *ppart;              // row-split partials of either pass
     void *planes;              // bf16 piece planes of the factor a pass contracts with
@@ -268,6 +269,105 @@ int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, DenseP
     return NMF_OK;
 }
 
+// What a dense run works on: A, W and H as handed in, or copies the streaming kernels can take.
+struct DenseRun {
+    DensePlan p;
+    const float *A;
+    float *W, *H;
+    int64_t m, n;
+    char *tail;      // `extra` bytes
+    bool have_at;    // the mirrored plan's A^T is made
+};
+
+// A that the streaming kernels cannot take as it is (base not 16-byte aligned, or n % 4 != 0) is
+// copied once per call into an aligned array of n4 = n rounded up to 4 columns, the new columns
+// zero, and H likewise: a zero column of A keeps its column of H at zero and adds nothing to any
+// product, so the run on the copies is the run on A and H.  The one-pass and the row plan run on
+// those.  The mirrored plan also reads A^T, whose columns are the rows of A: m is rounded up to 4
+// in A^T and in a copy of W, whose new rows are zero and stay zero for the same reason.
+// Only with a normal positive eps (with eps = 0 a zero column gives 0 / 0), and where the workspace
+// can hold the copies.  Microseconds per iteration, 20 or 30 per call, copies included, against the
+// plan that ran before (the kernels for any alignment, or the row plan at 33 factors and up):
+// 32768 x 16382, k = 32: 1020 -> 800 (row plan); mirrored plan: 20011 x 9998, k = 50 634 -> 424;
+// 20011 x 10000, k = 40 788 -> 409; 2001 x 6001, k = 50 169 -> 68; 5001 x 3000, k = 12 62 -> 50;
+// one iteration: 5001 x 3001, k = 12 117 -> 119, k = 40 192 -> 124.
+int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters, float eps, size_t extra,
+             hipStream_t st, DenseRun *r)
+{
+    const int64_t n4 = (n + 3) & ~(int64_t)3, m4 = (m + 3) & ~(int64_t)3;
+    const bool copy_a = (reinterpret_cast<uintptr_t>(A) & 15u) != 0 || n != n4;
+    const size_t copies = (copy_a ? align_up((size_t)m * n4 * sizeof(float)) : 0) +
+                          (n != n4 ? align_up((size_t)k * n4 * sizeof(float)) : 0);
+    *r = DenseRun{};
+    r->A = A;
+    r->W = W;
+    r->H = H;
+    r->m = m;
+    r->n = n;
+    bool padded = false, pad_w = false;
+    size_t base = 0;
+    if (eps >= 1.17549435e-38f && (copy_a || m != m4) && iters > 0) {
+        const bool one = one_pass_ok(nullptr, n4, k), rows = rows_plan_first(nullptr, m, n4, k);
+        if (one || rows) {
+            if (copy_a) {
+                base = one_pass_bytes(m, n4, k);
+                if (one && have_workspace(base + copies + extra)) {
+                    r->p = carve_one_pass(g.ws, m, n4, k);
+                    padded = true;
+                } else if (rows) {
+                    base = dense_bytes(m, n4, k, false);
+                    if ((padded = have_workspace(base + copies + extra))) r->p = carve_dense(g.ws, m, n4, k, false);
+                }
+            }
+        } else {
+            // large matrices of more than 32 factors: one iteration alone does not earn the transposed copy
+            const bool can_rows = aht_rows_ok(nullptr, m, n4, k);
+            pad_w = m != m4;
+            base = dense_bytes(m4, n4, k, true);
+            const size_t wcopy = pad_w ? align_up((size_t)m4 * k * sizeof(float)) : 0;
+            if ((iters > 1 || !copy_a || !can_rows) && (padded = have_workspace(base + copies + wcopy + extra))) {
+                r->p = carve_dense(g.ws, m4, n4, k, true);
+                r->p.a_rows = m;
+                r->m = m4;
+            } else {
+                pad_w = false;
+                base = dense_bytes(m, n4, k, false);
+                if (copy_a && can_rows && (padded = have_workspace(base + copies + extra)))
+                    r->p = carve_dense(g.ws, m, n4, k, false);
+            }
+        }
+    }
+    if (!padded) return dense_plan(A, m, n, k, extra, &r->p, &r->tail);
+    Carve cv(static_cast<char *>(g.ws) + base);
+    if (copy_a) {
+        float *Ap = cv.take<float>((size_t)m * n4);
+        if (r->p.mirrored) NMF_HIP(launch_transpose(A, m, n, r->p.At, st, r->m, Ap, n4));
+        else NMF_HIP(launch_pad_copy(A, n, Ap, n4, m, n, st));
+        r->have_at = r->p.mirrored;
+        r->A = Ap;
+        r->n = n4;
+    }
+    if (n != n4) {
+        r->H = cv.take<float>((size_t)k * n4);
+        NMF_HIP(launch_pad_copy(H, n, r->H, n4, k, n, st));
+    }
+    if (pad_w) {
+        r->W = cv.take<float>((size_t)m4 * k);
+        NMF_HIP(launch_pad_copy(W, k, r->W, k, m, k, st));
+        NMF_HIP(launch_fill_f32(r->W + m * k, (m4 - m) * k, 0.f, st));
+    }
+    r->tail = cv.base + cv.off;
+    return NMF_OK;
+}
+
+// The factors of a run on copies go back to the caller's.
+int close_run(const DenseRun &r, int k, float *W, float *H, int64_t m, int64_t n, hipStream_t st)
+{
+    if (r.H != H) NMF_HIP(launch_pad_copy(r.H, r.n, H, n, k, n, st));
+    if (r.W != W) NMF_HIP(launch_pad_copy(r.W, k, W, k, m, k, st));
+    return NMF_OK;
+}
+
 constexpr int kDenseKernels = 6;
 
 // Per-iteration objective of a dense run (device memory): out[it] after iteration it.
@@ -329,7 +429,7 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
     // counts follow the rank actually run; the partial buffer holds the largest case.
     const int s1 = wta_splits(m, n, k), s2 = wta_splits(n, m, k);
     const int64_t rps1 = wta_rows_per_split(m, s1), rps2 = wta_rows_per_split(n, s2);
-    if (rows_plan_runs(A, m, n, k, p.mirrored)) {
+    if (!p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored)) {
         // Row plan: both products stream the row-major A.  The W^T A pass reads the piece
         // planes of W and, on the side, adds the tile sets of W^T W up; the H update writes
         // the planes of H^T and the tile sets of H H^T, which a small launch adds up; the A H^T pass
@@ -362,8 +462,9 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         }
         return NMF_OK;
     }
+    const int64_t ma = p.a_rows ? p.a_rows : m;
     if (p.mirrored) {
-        if (!a_is_mirrored) NMF_HIP(launch_transpose(A, m, n, p.At, st));
+        if (!a_is_mirrored) NMF_HIP(launch_transpose(A, ma, n, p.At, st, m));
         NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
         NMF_HIP(launch_transpose(H, k, n, p.Ht, st));
     }
@@ -379,7 +480,7 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         // in between adds them up on the side (its first workgroups): no launch of its own.
         for (int it = 0; it < iters; ++it) {
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            NMF_HIP(launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, c.gwp, nbw, c.gws));
+            NMF_HIP(launch_wta_pass(A, ma, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, c.gwp, nbw, c.gws));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             NMF_HIP(launch_factor_update(H, p.Ht, p.ppart, s1, nullptr, c.gws, 1, c.ghp, k, n, eps, st, map, p.planes));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
@@ -853,44 +954,10 @@ int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k, float *W, floa
         return sliced_dense_body(A, m, n, k, W, H, iters, eps, p, static_cast<hipStream_t>(stream));
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // A that the streaming kernels cannot take as it is (base not 16-byte aligned, or n % 4 != 0) is
-    // copied once per call into an aligned array of n4 = n rounded up to 4 columns, the new columns
-    // zero, and H likewise: a zero column of A keeps its column of H at zero and adds nothing to any
-    // product, so the run on the copies is the run on A and H.  The copy costs less than the
-    // transposes of the mirrored plan and the iterations run the row plan (1.02 -> 0.80 ms per
-    // iteration on 32768 x 16382 at k = 32 with 20 iterations per call); taken when the workspace
-    // can hold the copy, and only with a normal positive eps: with eps = 0 a zero column gives 0 / 0.
-    const int64_t n4 = (n + 3) & ~(int64_t)3;
-    const bool misaligned = (reinterpret_cast<uintptr_t>(A) & 15u) != 0 || n != n4;
-    if (misaligned && eps >= 1.17549435e-38f) {
-        const size_t copies = align_up((size_t)m * n4 * sizeof(float)) + align_up((size_t)k * n4 * sizeof(float));
-        size_t base = one_pass_bytes(m, n4, k);
-        DensePlan p;
-        bool padded = false;
-        if (one_pass_ok(nullptr, n4, k) && have_workspace(base + copies)) {
-            p = carve_one_pass(g.ws, m, n4, k);
-            padded = true;
-        } else if (aht_rows_ok(nullptr, m, n4, k)) {
-            base = dense_bytes(m, n4, k, false);
-            if (have_workspace(base + copies)) {
-                p = carve_dense(g.ws, m, n4, k, false);
-                padded = true;
-            }
-        }
-        if (padded) {
-            Carve cv(static_cast<char *>(g.ws) + base);
-            float *Ap = cv.take<float>((size_t)m * n4);
-            float *Hp = cv.take<float>((size_t)k * n4);
-            NMF_HIP(launch_pad_copy(A, n, Ap, n4, m, n, st));
-            NMF_HIP(launch_pad_copy(H, n, Hp, n4, k, n, st));
-            if (int rc = dense_body(Ap, m, n4, k, W, Hp, iters, eps, p, st)) return rc;
-            NMF_HIP(launch_pad_copy(Hp, n4, H, n, k, n, st));
-            return NMF_OK;
-        }
-    }
-    DensePlan p;
-    if (int rc = dense_plan(A, m, n, k, 0, &p, nullptr)) return rc;
-    return dense_body(A, m, n, k, W, H, iters, eps, p, st);
+    DenseRun r;
+    if (int rc = open_run(A, m, n, k, W, H, iters, eps, 0, st, &r)) return rc;
+    if (int rc = dense_body(r.A, r.m, r.n, k, r.W, r.H, iters, eps, r.p, st, r.have_at)) return rc;
+    return close_run(r, k, W, H, m, n, st);
 }
 
 int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H,
@@ -1524,6 +1591,12 @@ int residual_to_host(const float *A, int64_t m, int64_t n, int k, const float *W
     (void)blocks;
     return NMF_OK;
 }
+// the same for a run that may work on a copy of A with padded columns
+size_t run_scratch_bytes(int64_t m, int64_t n)
+{
+    const int64_t a = residual_partials(m, n), b = residual_partials(m, (n + 3) & ~(int64_t)3);
+    return align_up(((size_t)(a > b ? a : b) + 1) * sizeof(double));
+}
 size_t residual_scratch_bytes(int64_t m, int64_t n) { return align_up(((size_t)residual_partials(m, n) + 1) * sizeof(double)); }
 }  // namespace
 
@@ -1551,16 +1624,15 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
     // the residual scratch and the monitor's few doubles ride behind whichever dense plan fits
-    const size_t extra = residual_scratch_bytes(m, n) + align_up((size_t)kFinMaxBlocks * sizeof(double)) +
+    const size_t extra = run_scratch_bytes(m, n) + align_up((size_t)kFinMaxBlocks * sizeof(double)) +
                          align_up(4097 * sizeof(double)) + kAlign;
-    DensePlan p;
-    char *tail = nullptr;
-    if (int rc = dense_plan(A, m, n, k, extra, &p, &tail)) return rc;
-    const bool mirrored = p.mirrored;
+    DenseRun r;
+    if (int rc = open_run(A, m, n, k, W, H, max_iters, eps, extra, st, &r)) return rc;
+    const bool mirrored = r.p.mirrored;
     // plans whose W update leaves the objective's terms behind
-    const bool fast = mirrored || p.one_pass || rows_plan_runs(A, m, n, k, mirrored);
-    Carve cv(tail);
-    double *scratch = cv.take<double>((size_t)residual_partials(m, n) + 1);
+    const bool fast = mirrored || r.p.one_pass || rows_plan_runs(r.A, m, r.n, k, mirrored);
+    Carve cv(r.tail);
+    double *scratch = cv.take<double>(run_scratch_bytes(m, n) / sizeof(double));
     Monitor mon;
     mon.dpart = cv.take<double>(kFinMaxBlocks);
     mon.normA2 = cv.take<double>(4097);
@@ -1570,17 +1642,17 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     int done = 0;
     double res = 0.0;
     bool exact = true;       // `res` comes from the tiled evaluation (not from the expansion)
-    if (int rc = residual_to_host(A, m, n, k, W, H, scratch, &res, st)) return rc;
+    if (int rc = residual_to_host(r.A, m, r.n, k, r.W, r.H, scratch, &res, st)) return rc;
     double normA2 = 0.0;
     if (fast && max_iters > 0 && res > tol) {
-        NMF_HIP(launch_sumsq(A, m * n, mon.normA2 + 1, mon.normA2, st));
+        NMF_HIP(launch_sumsq(r.A, m * r.n, mon.normA2 + 1, mon.normA2, st));
         NMF_HIP(hipMemcpyAsync(&normA2, mon.normA2, sizeof(double), hipMemcpyDeviceToHost, st));
         NMF_HIP(hipStreamSynchronize(st));
     }
-    bool have_at = false;
+    bool have_at = r.have_at;
     while (done < max_iters && res > tol) {
         const int chunk = (max_iters - done < check_every) ? max_iters - done : check_every;
-        if (int rc = dense_body(A, m, n, k, W, H, chunk, eps, p, st, have_at, nullptr, nullptr, fast ? &mon : nullptr))
+        if (int rc = dense_body(r.A, r.m, r.n, k, r.W, r.H, chunk, eps, r.p, st, have_at, nullptr, nullptr, fast ? &mon : nullptr))
             return rc;
         have_at = mirrored;
         done += chunk;
@@ -1598,11 +1670,12 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
                 continue;
             }
         }
-        if (int rc = residual_to_host(A, m, n, k, W, H, scratch, &res, st)) return rc;
+        if (int rc = residual_to_host(r.A, m, r.n, k, r.W, r.H, scratch, &res, st)) return rc;
         exact = true;
     }
     if (!exact)
-        if (int rc = residual_to_host(A, m, n, k, W, H, scratch, &res, st)) return rc;
+        if (int rc = residual_to_host(r.A, m, r.n, k, r.W, r.H, scratch, &res, st)) return rc;
+    if (int rc = close_run(r, k, W, H, m, n, st)) return rc;
     *iters_done_host = done;
     *residual_host = res;
     return NMF_OK;
@@ -1618,19 +1691,20 @@ int nmf_mu_dense_monitor(const float *A, int64_t m, int64_t n, int32_t k, float 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
     const size_t extra = align_up((size_t)kFinMaxBlocks * sizeof(double)) + align_up(4097 * sizeof(double)) +
-                         align_up((size_t)iters * sizeof(double)) + residual_scratch_bytes(m, n);
-    DensePlan p;
-    char *tail = nullptr;
-    if (int rc = dense_plan(A, m, n, k, extra, &p, &tail)) return rc;
-    Carve cv(tail);
+                         align_up((size_t)iters * sizeof(double)) + run_scratch_bytes(m, n);
+    DenseRun r;
+    if (int rc = open_run(A, m, n, k, W, H, iters, eps, extra, st, &r)) return rc;
+    Carve cv(r.tail);
     Monitor mon;
     mon.dpart = cv.take<double>(kFinMaxBlocks);
     mon.normA2 = cv.take<double>(4097);
     mon.out = cv.take<double>((size_t)iters);
-    mon.res = cv.take<double>((size_t)residual_partials(m, n) + 1);
+    mon.res = cv.take<double>(run_scratch_bytes(m, n) / sizeof(double));
     mon.last_only = false;
-    if (p.mirrored || p.one_pass || rows_plan_runs(A, m, n, k, p.mirrored)) NMF_HIP(launch_sumsq(A, m * n, mon.normA2 + 1, mon.normA2, st));
-    if (int rc = dense_body(A, m, n, k, W, H, iters, eps, p, st, false, nullptr, nullptr, &mon)) return rc;
+    if (r.p.mirrored || r.p.one_pass || rows_plan_runs(r.A, m, r.n, k, r.p.mirrored))
+        NMF_HIP(launch_sumsq(r.A, m * r.n, mon.normA2 + 1, mon.normA2, st));
+    if (int rc = dense_body(r.A, r.m, r.n, k, r.W, r.H, iters, eps, r.p, st, r.have_at, nullptr, nullptr, &mon)) return rc;
+    if (int rc = close_run(r, k, W, H, m, n, st)) return rc;
     NMF_HIP(hipMemcpyAsync(objective_host, mon.out, (size_t)iters * sizeof(double), hipMemcpyDeviceToHost, st));
     NMF_HIP(hipStreamSynchronize(st));
     return NMF_OK;

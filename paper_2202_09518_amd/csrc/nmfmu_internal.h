@@ -190,7 +190,9 @@ int csc_finish_blocks(int64_t nnz);
 // `cols` on are set to zero.  Any alignment.
 hipError_t launch_pad_copy(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t rows, int64_t cols,
                            hipStream_t st);
-// out (cols x rows) = in^T.
-hipError_t launch_transpose(const float *in, int64_t rows, int64_t cols, float *out, hipStream_t st);
+// out = in^T (in: rows x cols).  ld > rows: rows of out are ld long, ldc > cols: out has ldc rows, what lies
+// beyond in is zero; copy (optional): in with its rows extended to ldc, read once for both.
+hipError_t launch_transpose(const float *in, int64_t rows, int64_t cols, float *out, hipStream_t st, int64_t ld = 0,
+                            float *copy = nullptr, int64_t ldc = 0);
 
 }  // namespace nmfmu

@@ -1,0 +1,75 @@
+"""Dense runs on copies with padded rows or columns (m % 4, n % 4 or the base of A not what the streaming
+kernels take), against the oracle: all three plans, the monitored and the stopped run, and
+a workspace that cannot hold the copies."""
+import numpy as np
+import pytest
+
+from oracle import nmf_oracle as orc
+
+EPS = 1e-16
+
+
+def data(m, n, k):
+    r = np.random.default_rng(m + 3 * n + 7 * k)
+    return r.random((m, n), dtype=np.float32), r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+
+
+def on_device(A, offset):
+    import torch
+    flat = torch.empty(A.size + 4, device="cuda")
+    view = flat[offset:offset + A.size].view(A.shape)
+    view.copy_(torch.from_numpy(A))
+    return view
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,offset", [(2501, 1701, 0), (2502, 1702, 0), (2503, 1704, 0), (2504, 1703, 0), (2504, 1704, 1),
+                                        (33, 2049, 0), (3, 600, 0), (1, 515, 0), (12285, 701, 0), (12289, 513, 2)])
+@pytest.mark.parametrize("k,iters", [(12, 3), (33, 1), (33, 2), (64, 3)])
+def test_padded_runs(m, n, offset, k, iters):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A, W, H = data(m, n, k)
+    Ad = on_device(A, offset)
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    nmf.nmf_mu_dense(Ad, m, n, k, Wd, Hd, iters, EPS)
+    Wm, Hm = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    got = nmf.nmf_mu_dense_monitor(Ad, m, n, k, Wm, Hm, iters, EPS)
+    Wt, Ht = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    done, last = nmf.nmf_mu_dense_tol(Ad, m, n, k, Wt, Ht, iters, EPS, 0.0, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(Ad, torch.from_numpy(A).cuda())
+    Wr, Hr = orc.mu_dense(A, W, H, iters, float(np.float32(EPS)))
+    want = orc.residual_dense(A, Wr, Hr)
+    # up to three updates of each factor, sums of one sign: a few roundings of 2^-24 per sum
+    for w, h in ((Wd, Hd), (Wm, Hm), (Wt, Ht)):
+        assert orc.rel_fro(w.cpu().numpy(), Wr) < 3e-6
+        assert orc.rel_fro(h.cpu().numpy(), Hr) < 3e-6
+    assert torch.equal(Wd, Wm) and torch.equal(Hd, Hm)
+    assert done == iters
+    # the objective from its by-products: errors of 2^-22 of ||A||^2 against the square of the residual;
+    # the exact one: roundings of the reconstruction, below 2^-22 of an entry, which is all there is where one
+    # row is fitted exactly
+    normA2 = float((A.astype(np.float64) ** 2).sum())
+    assert abs(got[-1] - want) <= max(1e-5 * want, 3e-7 * normA2 / want)
+    assert abs(last - want) <= max(1e-5 * want, 2.0 ** -22 * normA2 ** 0.5)
+
+
+@pytest.mark.gpu
+def test_workspace_without_room_for_the_copies():
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    m, n, k = 1501, 2001, 40
+    A, W, H = data(m, n, k)
+    ws = torch.empty(nmf.nmf_mu_workspace_bytes(4, m, n, 0, k, 0), dtype=torch.uint8, device="cuda")
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    nmf.nmf_mu_set_workspace(ws)
+    try:
+        nmf.nmf_mu_dense(torch.from_numpy(A).cuda(), m, n, k, Wd, Hd, 2, EPS)
+        torch.cuda.synchronize()
+    finally:
+        nmf.nmf_mu_set_workspace(None)
+    Wr, Hr = orc.mu_dense(A, W, H, 2, float(np.float32(EPS)))
+    assert orc.rel_fro(Wd.cpu().numpy(), Wr) < 2e-6 and orc.rel_fro(Hd.cpu().numpy(), Hr) < 2e-6
