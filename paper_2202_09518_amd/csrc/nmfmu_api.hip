@@ -1361,9 +1361,9 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     // computes the same matrix again for its H update).
     auto iteration = [&](double *out) -> int {
         NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
-        NMF_HIP(launch_aht_csr(colptr, rowidx, cvals, part_c, long_c, long_n + 1, k, W, c.gw, Ht, eps, nnz, m, st));   // H update on H^T
+        NMF_HIP(launch_aht_csr(colptr, rowidx, cvals, part_c, long_c, long_n + 1, k, W, c.gw, Ht, eps, nnz, n, m, st));   // H update on H^T
         NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st));
-        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, W, eps, nnz, n, st, false,
+        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, W, eps, nnz, m, n, st, false,
                                out ? dpart : nullptr));                                                       // W update
         if (out) {
             NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
@@ -1376,7 +1376,7 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
         double res = 0.0;
         NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
         NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st));
-        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, W, eps, nnz, n, st, false, dpart, true));
+        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, W, eps, nnz, m, n, st, false, dpart, true));
         NMF_HIP(launch_objective(dpart, kCsrDparts, c.gw, c.gh, k, normA2, obj, st));
         NMF_HIP(hipMemcpyAsync(&res, obj, sizeof(double), hipMemcpyDeviceToHost, st));
         NMF_HIP(hipStreamSynchronize(st));
@@ -1555,7 +1555,7 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
             if (s > 0) {
                 NMF_HIP(launch_csr_partition(rowptr_loc, rows, kCsrParts, part_r, st));
                 NMF_HIP(launch_csr_long_rows(rowptr_loc, rows, long_r, long_n, (unsigned)(max_nnz / kLongRow + 1), st));
-                NMF_HIP(launch_aht_csr(rowptr_loc, ci, va, part_r, long_r, long_n, k, Ht, c.gh, Wb, eps, cnt, n, st));
+                NMF_HIP(launch_aht_csr(rowptr_loc, ci, va, part_r, long_r, long_n, k, Ht, c.gh, Wb, eps, cnt, rows, n, st));
             }
             if (s < iters) {
                 NMF_HIP(launch_csc_build(rowptr_loc, ci, va, rows, n, cnt, sorted_cols, payload, sorted_payload,
@@ -1563,7 +1563,7 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
                 NMF_HIP(launch_csr_partition(colptr, n, kCsrParts, part_c, st));
                 NMF_HIP(launch_csr_long_rows(colptr, n, long_c, long_n + 1, (unsigned)(max_nnz / kLongRow + 1), st));
                 NMF_HIP(launch_aht_csr(colptr, rowidx, cvals, part_c, long_c, long_n + 1, k, Wb, nullptr, Num, eps,
-                                       cnt, rows, st, true));
+                                       cnt, n, rows, st, true));
             }
             NMF_HIP(hipEventRecord(g.sl_freed[slot], st));
         }

@@ -46,6 +46,7 @@ __device__ __forceinline__ float row_times_gram(float x, const float *Gs, int ld
 {
     float d0 = 0.f, d1 = 0.f;
     const int cc = (c < k) ? c : 0;
+#pragma unroll 4
     for (int d = 0; d + 1 < k; d += 2) {
         d0 += group_bcast<LPR>(x, d) * Gs[d * ldg + cc];
         d1 += group_bcast<LPR>(x, d + 1) * Gs[(d + 1) * ldg + cc];
@@ -103,34 +104,38 @@ __global__ __launch_bounds__(256) void csr_long_rows_kernel(const int64_t *__res
 
 __global__ void zero_u32_kernel(unsigned *p) { if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0u; }
 
-// One gather step of a lane group: entries [e, e + LPR) of a row (fewer at its
-// end), UNR at a time so that several table rows are in flight; lanes past the
-// end hold (column 0, value 0): they gather row 0 of the table and add nothing.
-// T has `trows` rows of k floats.
-template <int LPR>
-__device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx,
-                                              const float *__restrict__ vals,
-                                              const float *__restrict__ T, int trows, int k, int c,
-                                              int64_t e, int64_t e1, float acc)
+// The entry a lane holds for its group: its table row (clamped: an index outside the table, from
+// malformed input, is pulled to its edge, no stray access) as an offset into the table, and its value;
+// past the row's end: row 0 of the table, value 0, which adds nothing.  NARROW: the table has at most 2^30
+// floats, and the lane that loads an entry multiplies it by k once for the whole group.
+template <bool NARROW>
+__device__ __forceinline__ void load_entry(const int32_t *__restrict__ colidx, const float *__restrict__ vals,
+                                           int trows, int k, int64_t e, bool ok, int &off, float &val)
 {
-    const int64_t left = e1 - e;
-    const int cnt = left < LPR ? (left > 0 ? (int)left : 0) : LPR;
-    int colv = 0;
-    float valv = 0.f;
-    if (c < cnt) {
-        colv = colidx[e + c];
-        valv = vals[e + c];
+    off = 0;
+    val = 0.f;
+    if (ok) {
+        const int col = min(max(colidx[e], 0), trows - 1);
+        off = NARROW ? col * k : col;
+        val = vals[e];
     }
+}
+
+// acc + the products of the `cnt` entries the group's lanes hold (`any`: the largest cnt of the wave's
+// groups), UNR at a time so that several table rows are in flight.
+template <int LPR, bool NARROW>
+__device__ __forceinline__ float gather_entries(const float *__restrict__ T, int k, int cc, int off, float val,
+                                                int cnt, float acc)
+{
     constexpr int UNR = (LPR < 8) ? LPR : 8;
-    const int cc = (c < k) ? c : 0;
     for (int t0 = 0; __any(t0 < cnt); t0 += UNR) {
         float a[UNR], h[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            // an index outside the table (malformed input) is pulled to its edge: no stray access
-            const int col = min(max(group_bcast<LPR>(colv, t0 + u), 0), trows - 1);
-            a[u] = group_bcast<LPR>(valv, t0 + u);
-            h[u] = T[(int64_t)col * k + cc];
+            const int o = group_bcast<LPR>(off, t0 + u);
+            a[u] = group_bcast<LPR>(val, t0 + u);
+            if (NARROW) h[u] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(T) + (unsigned)(o + cc) * 4u);
+            else h[u] = T[(int64_t)o * k + cc];
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) acc += a[u] * h[u];
@@ -138,11 +143,19 @@ __device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx
     return acc;
 }
 
-// The test that sends a row to the long-row kernel, on the row pointers as given (the list of
-// long rows is built with the same test).
-__device__ __forceinline__ bool rowptr_long(const int64_t *__restrict__ rowptr, int64_t row, bool valid)
+// One gather step of a lane group: entries [e, e + LPR) of a row (fewer at its end).
+template <int LPR, bool NARROW>
+__device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx,
+                                              const float *__restrict__ vals,
+                                              const float *__restrict__ T, int trows, int k, int c,
+                                              int64_t e, int64_t e1, float acc)
 {
-    return valid && rowptr[row + 1] - rowptr[row] > kLongRow;
+    const int64_t left = e1 - e;
+    const int cnt = left < LPR ? (left > 0 ? (int)left : 0) : LPR;
+    int off;
+    float val;
+    load_entry<NARROW>(colidx, vals, trows, k, e + c, c < cnt, off, val);
+    return gather_entries<LPR, NARROW>(T, k, (c < k) ? c : 0, off, val, cnt, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -150,7 +163,19 @@ __device__ __forceinline__ bool rowptr_long(const int64_t *__restrict__ rowptr, 
 // With the CSR of A, T = Ht, G = H H^T, X = W: AHT, WHHT and the W update of
 // Algorithm 3 in one kernel (the row of A H^T lives in one register per lane);
 // with the column-ordered copy, T = W, G = W^T W, X = Ht: WTA and the H update.
-// Wavefront gw works on rows [part[gw], part[gw + 1]), 64 / LPR rows at a time.
+// The first kCsrLongBlocks workgroups take the rows in `list` (more than kLongRow entries), one
+// workgroup per row: its lane groups take the row's chunks round robin and their sums are added in
+// group order; with none they end at once.  In the others wavefront gw works on rows
+// [part[gw], part[gw + 1]):
+//   SPLIT = false: 64 / LPR rows at a time, a lane group each, LPR entries of each per step;
+//   SPLIT = true:  one row at a time, 64 entries per step dealt to all lane groups, the groups'
+//                  sums added by butterfly (see launch_aht_csr for which).
+// What bounds it depends on the size.  With a table beyond the caches: the bytes of the gathered rows.
+// With small tables: the chain range -> row pointers -> entries -> table rows -> update, a trip to
+// L2 or memory each; so G (one entry or a few per thread) and the row of X are requested before
+// the entries and waited for after them, and the next step's entries are requested before the
+// current ones are gathered.  65536 x 16384, 1.07 million entries, k = 12: 23 and 35 us for the two updates
+// with a launch of 4.5 for the long rows each, now 21 and 18.6 with the long rows in the same launch.
 // accumulate != 0: no update; the gathered sums are added to W instead (the
 // numerator of an update collected over several row batches of the matrix; GH unused).
 // accumulate == 2: nothing is written to W (needs dpart; GH unused).
@@ -159,126 +184,117 @@ __device__ __forceinline__ bool rowptr_long(const int64_t *__restrict__ rowptr, 
 // share of <A H^T, W> for the objective ||A||^2 - 2 <A H^T, W> + <H H^T, W^T W>; lanes by
 // butterfly, then the 4 waves in order.
 // ---------------------------------------------------------------------------
-template <int LPR>
+template <int LPR, bool SPLIT, bool NARROW>
 __global__ __launch_bounds__(256) void aht_csr_kernel(const int64_t *__restrict__ rowptr,
                                                       const int32_t *__restrict__ colidx,
                                                       const float *__restrict__ vals,
-                                                      const int64_t *__restrict__ part, int k,
+                                                      const int64_t *__restrict__ part,
+                                                      const int32_t *__restrict__ list,
+                                                      const unsigned *__restrict__ count, unsigned list_cap, int k,
                                                       const float *__restrict__ Ht,
                                                       const float *__restrict__ GH, float *W,
                                                       float eps, int accumulate,
                                                       double *__restrict__ dpart, int64_t nnz, int trows)
 {
-    constexpr int LDG = 65, RPW = 64 / LPR;
-    __shared__ float Gs[64 * LDG];
+    constexpr int LDG = LPR + 1, RPW = 64 / LPR, NG = 256 / LPR, EPG = (LPR * LPR + 255) / 256;
+    __shared__ float Gs[LPR * LDG];
+    __shared__ float part_acc[NG][LPR];
     __shared__ double dsum[4];
-    if (!accumulate) stage_gram(Gs, GH, k, LDG);
-    double dacc = 0.0;
     const int lane = threadIdx.x & 63;
-    const int c = lane % LPR;
-    const int gw = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t r_lo = part[gw], r_hi = part[gw + 1];          // same for the whole wavefront
-    for (int64_t base = r_lo; base < r_hi; base += RPW) {
-        const int64_t row = base + lane / LPR;
-        bool valid = row < r_hi;
-        // row pointers outside [0, nnz] (malformed input) are pulled into the arrays
-        int64_t e = valid ? min(max(rowptr[row], (int64_t)0), nnz) : 0;
-        int64_t e1 = valid ? min(max(rowptr[row + 1], (int64_t)0), nnz) : 0;
-        if (rowptr_long(rowptr, row, valid)) {       // left to the long-row kernel
-            valid = false;
-            e1 = e;
+    const int c = lane % LPR, cc = (c < k) ? c : 0;
+    double dacc = 0.0;
+    // G: requested first, put into LDS (one barrier) when the first row's sums are there
+    float gq[EPG];
+#pragma unroll
+    for (int i = 0; i < EPG; ++i) gq[i] = !accumulate && (int)threadIdx.x + 256 * i < k * k ? GH[threadIdx.x + 256 * i] : 0.f;
+    bool staged = accumulate != 0;      // uniform over a wave; every wave passes the barrier once
+    auto stage = [&]() {
+        if (staged) return;
+        staged = true;
+#pragma unroll
+        for (int i = 0; i < EPG; ++i) {
+            const int e = threadIdx.x + 256 * i;
+            if (e < k * k) Gs[(e / k) * LDG + e % k] = gq[i];
         }
-        float acc = 0.f;
-        while (__any(e < e1)) {
-            acc = gather_chunk<LPR>(colidx, vals, Ht, trows, k, c, e, e1, acc);
-            e += LPR;
-        }
-        const float w = (valid && c < k) ? W[row * k + c] : 0.f;
+        __syncthreads();
+    };
+    // the row's update from its sum; `mine`: this lane writes factor c of it
+    auto finish = [&](int64_t row, bool valid, bool mine, float w, float acc) {
+        mine = mine && valid && c < k;
         if (accumulate == 2) {
-            if (valid && c < k) dacc += (double)acc * (double)w;
-            continue;
+            if (mine) dacc += (double)acc * (double)w;
+        } else if (accumulate) {
+            if (mine) W[row * k + c] = w + acc;
+        } else {
+            stage();
+            const float den = row_times_gram<LPR>(w, Gs, LDG, k, c) + eps;
+            if (mine) {
+                const float wn = w * acc / den;
+                W[row * k + c] = wn;
+                dacc += (double)acc * (double)wn;
+            }
         }
-        if (accumulate) {
-            if (valid && c < k) W[row * k + c] = w + acc;
-            continue;
+    };
+    if (blockIdx.x < kCsrLongBlocks) {
+        const unsigned n_long = *count < list_cap ? *count : list_cap;
+        const int grp = threadIdx.x / LPR;
+        for (unsigned li = blockIdx.x; li < n_long; li += kCsrLongBlocks) {
+            const int64_t row = list[li];
+            const int64_t e0 = min(max(rowptr[row], (int64_t)0), nnz), e1 = min(max(rowptr[row + 1], (int64_t)0), nnz);
+            float acc = 0.f;
+            for (int64_t e = e0 + (int64_t)grp * LPR; __any(e < e1); e += (int64_t)NG * LPR)
+                acc = gather_chunk<LPR, NARROW>(colidx, vals, Ht, trows, k, c, e, e1, acc);
+            part_acc[grp][threadIdx.x % LPR] = acc;
+            __syncthreads();
+            float total = 0.f;           // every lane adds up its factor, the first group's lanes write it
+            for (int gI = 0; gI < NG; ++gI) total += part_acc[gI][c];
+            const float w = (c < k) ? W[row * k + c] : 0.f;
+            finish(row, true, threadIdx.x < LPR, w, total);
+            __syncthreads();
         }
-        const float den = row_times_gram<LPR>(w, Gs, LDG, k, c) + eps;
-        if (valid && c < k) {
-            const float wn = w * acc / den;
-            W[row * k + c] = wn;
-            dacc += (double)acc * (double)wn;
+    } else {
+        const int gw = __builtin_amdgcn_readfirstlane((blockIdx.x - kCsrLongBlocks) * 4 + (threadIdx.x >> 6));
+        const int64_t r_lo = part[gw], r_hi = part[gw + 1];          // same for the whole wavefront
+        constexpr int STEP = SPLIT ? 1 : RPW;
+        for (int64_t base = r_lo; base < r_hi; base += STEP) {
+            const int64_t row = SPLIT ? base : base + lane / LPR;
+            bool valid = row < r_hi;
+            // row pointers outside [0, nnz] (malformed input) are pulled into the arrays
+            const int64_t p0 = valid ? rowptr[row] : 0, p1 = valid ? rowptr[row + 1] : 0;
+            int64_t e = min(max(p0, (int64_t)0), nnz), e1 = min(max(p1, (int64_t)0), nnz);
+            if (valid && p1 - p0 > kLongRow) {       // left to the long-row workgroups
+                valid = false;
+                e1 = e;
+            }
+            const float w = (valid && c < k) ? W[row * k + c] : 0.f;
+            float acc = 0.f;
+            constexpr int CHUNK = SPLIT ? 64 : LPR;      // entries of a row per step
+            if (SPLIT) e += lane - c;                    // this group's share of the first step
+            int64_t left = e1 - e;
+            int off;
+            float val;
+            load_entry<NARROW>(colidx, vals, trows, k, e + c, c < left, off, val);
+            while (__any(left > 0)) {
+                const int o = off, cnt = left < LPR ? (left > 0 ? (int)left : 0) : LPR;
+                const float v = val;
+                e += CHUNK;
+                left -= CHUNK;
+                load_entry<NARROW>(colidx, vals, trows, k, e + c, c < left, off, val);
+                acc = gather_entries<LPR, NARROW>(Ht, k, cc, o, v, cnt, acc);
+            }
+            if (SPLIT) {
+#pragma unroll
+                for (int x = LPR; x < 64; x <<= 1) acc += __shfl_xor(acc, x);
+            }
+            finish(row, valid, !SPLIT || lane < LPR, w, acc);
         }
     }
+    if (!(blockIdx.x < kCsrLongBlocks)) stage();      // a wave without rows still owes the others its barrier
     if (dpart) {     // uniform over the grid
         for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
         if (lane == 0) dsum[threadIdx.x >> 6] = dacc;
         __syncthreads();
         if (threadIdx.x == 0) dpart[blockIdx.x] = ((dsum[0] + dsum[1]) + dsum[2]) + dsum[3];
-    }
-}
-
-// The same update for the rows in `list` (more than kLongRow entries): one
-// workgroup per row, its lane groups take the row's chunks round robin and
-// their sums are added in group order.
-template <int LPR>
-__global__ __launch_bounds__(256) void aht_csr_long_kernel(const int64_t *__restrict__ rowptr,
-                                                           const int32_t *__restrict__ colidx,
-                                                           const float *__restrict__ vals,
-                                                           const int32_t *__restrict__ list,
-                                                           const unsigned *__restrict__ count, int k,
-                                                           const float *__restrict__ Ht,
-                                                           const float *__restrict__ GH, float *W,
-                                                           float eps, int accumulate,
-                                                           double *__restrict__ dpart, int64_t nnz, int trows,
-                                                           unsigned list_cap)
-{
-    constexpr int LDG = 65, NG = 256 / LPR;
-    __shared__ float Gs[64 * LDG];
-    __shared__ float part_acc[NG][LPR];
-    const unsigned n_long = *count < list_cap ? *count : list_cap;
-    if (n_long == 0) {
-        if (dpart && threadIdx.x == 0) dpart[blockIdx.x] = 0.0;
-        return;
-    }
-    double dacc = 0.0;      // first wavefront only: it finishes the rows
-    if (!accumulate) stage_gram(Gs, GH, k, LDG);
-    const int c = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-    for (unsigned li = blockIdx.x; li < n_long; li += gridDim.x) {
-        const int64_t row = list[li];
-        const int64_t e0 = min(max(rowptr[row], (int64_t)0), nnz), e1 = min(max(rowptr[row + 1], (int64_t)0), nnz);
-        float acc = 0.f;
-        for (int64_t e = e0 + (int64_t)grp * LPR; __any(e < e1); e += (int64_t)NG * LPR)
-            acc = gather_chunk<LPR>(colidx, vals, Ht, trows, k, c, e, e1, acc);
-        part_acc[grp][c] = acc;
-        __syncthreads();
-        if (grp == 0) {        // LPR is a multiple of 64 only for LPR = 64; smaller groups share a wave
-            float total = 0.f;
-            for (int gI = 0; gI < NG; ++gI) total += part_acc[gI][c];
-            part_acc[0][c] = total;
-        }
-        __syncthreads();
-        if (threadIdx.x < 64) {     // first wavefront: its first group finishes the row
-            const float tot = part_acc[0][c];
-            const bool mine = threadIdx.x < LPR;
-            const float w = (mine && c < k) ? W[row * k + c] : 0.f;
-            if (accumulate == 2) {
-                if (mine && c < k) dacc += (double)tot * (double)w;
-            } else if (accumulate) {
-                if (mine && c < k) W[row * k + c] = w + tot;
-            } else {
-                const float den = row_times_gram<LPR>(w, Gs, LDG, k, c) + eps;
-                if (mine && c < k) {
-                    const float wn = w * tot / den;
-                    W[row * k + c] = wn;
-                    dacc += (double)tot * (double)wn;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    if (dpart && threadIdx.x < 64) {
-        for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
-        if (threadIdx.x == 0) dpart[blockIdx.x] = dacc;
     }
 }
 
@@ -487,22 +503,44 @@ hipError_t launch_csr_long_rows(const int64_t *rowptr, int64_t m, int32_t *list,
     return hipGetLastError();
 }
 
+template <int LPR, bool SPLIT>
+static void aht_csr_dispatch(bool narrow, hipStream_t st, const int64_t *rowptr, const int32_t *colidx, const float *vals,
+                             const int64_t *part, const int32_t *list, const unsigned *count, unsigned cap, int k,
+                             const float *Ht, const float *GH, float *W, float eps, int acc, double *dpart, int64_t nnz,
+                             int trows)
+{
+    const dim3 grid(kCsrLongBlocks + kCsrParts / 4), block(256);
+    if (narrow)
+        hipLaunchKernelGGL((aht_csr_kernel<LPR, SPLIT, true>), grid, block, 0, st, rowptr, colidx, vals, part, list, count, cap,
+                           k, Ht, GH, W, eps, acc, dpart, nnz, trows);
+    else
+        hipLaunchKernelGGL((aht_csr_kernel<LPR, SPLIT, false>), grid, block, 0, st, rowptr, colidx, vals, part, list, count, cap,
+                           k, Ht, GH, W, eps, acc, dpart, nnz, trows);
+}
+
 hipError_t launch_aht_csr(const int64_t *rowptr, const int32_t *colidx, const float *vals,
                           const int64_t *part, const int32_t *long_list, const unsigned *long_count,
-                          int k, const float *Ht, const float *GH, float *W, float eps, int64_t nnz, int64_t trows,
-                          hipStream_t st, bool accumulate, double *dpart, bool dry)
+                          int k, const float *Ht, const float *GH, float *W, float eps, int64_t nnz, int64_t rows,
+                          int64_t trows, hipStream_t st, bool accumulate, double *dpart, bool dry)
 {
-    if (trows < 1 || trows > 0x7fffffff || nnz < 0) return hipErrorInvalidValue;
+    if (trows < 1 || trows > 0x7fffffff || nnz < 0 || rows < 1) return hipErrorInvalidValue;
     if ((dpart && accumulate) || (dry && (!dpart || accumulate))) return hipErrorInvalidValue;
     const int lpr = lanes_per_row(k);
-    const dim3 grid(kCsrParts / 4), block(256);
     const int acc = dry ? 2 : (accumulate ? 1 : 0);
-    double *dlong = dpart ? dpart + kCsrParts / 4 : nullptr;
-    NMFMU_LPR_SWITCH(lpr, hipLaunchKernelGGL((aht_csr_kernel<L>), grid, block, 0, st, rowptr, colidx,
-                                             vals, part, k, Ht, GH, W, eps, acc, dpart, nnz, (int)trows));
-    NMFMU_LPR_SWITCH(lpr, hipLaunchKernelGGL((aht_csr_long_kernel<L>), dim3(kCsrLongBlocks), block, 0, st, rowptr,
-                                             colidx, vals, long_list, long_count, k, Ht, GH, W, eps, acc, dlong, nnz,
-                                             (int)trows, (unsigned)(nnz / kLongRow + 1)));
+    const bool narrow = trows * k <= ((int64_t)1 << 30);
+    const unsigned cap = (unsigned)(nnz / kLongRow + 1);
+    // From 64 entries per row on average a row fills the wave's lanes by itself, and fewer, longer rows
+    // than lane groups leave no group idle: 16384 rows of 65 entries at k = 12 took 35 us a row per
+    // group, 18.6 a row per wave; 524288 rows of 210 at k = 32, where the gathered bytes decide,
+    // 2276 and 2254.  Shorter rows waste lanes at the end of their one step (65536 rows of 16 at k = 12: 21).
+    const bool split = lpr < 64 && nnz >= 64 * rows;
+    if (split) {
+        NMFMU_LPR_SWITCH(lpr, (aht_csr_dispatch<L, (L < 64)>(narrow, st, rowptr, colidx, vals, part, long_list, long_count, cap, k, Ht,
+                                                         GH, W, eps, acc, dpart, nnz, (int)trows)));
+    } else {
+        NMFMU_LPR_SWITCH(lpr, (aht_csr_dispatch<L, false>(narrow, st, rowptr, colidx, vals, part, long_list, long_count, cap, k, Ht,
+                                                          GH, W, eps, acc, dpart, nnz, (int)trows)));
+    }
     return hipGetLastError();
 }
 

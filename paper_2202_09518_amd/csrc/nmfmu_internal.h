@@ -148,7 +148,7 @@ hipError_t launch_residual(const float *A, int64_t m, int64_t n, int k, const fl
 constexpr int kCsrParts = 16384;      // row ranges (= wavefronts) of a sparse update launch
 constexpr int64_t kRowCost = 8;       // work of a row besides its entries, in entries
 constexpr int64_t kLongRow = 16384;   // rows with more entries go to a whole workgroup
-constexpr int kCsrLongBlocks = 256;   // workgroups of the long-row kernel
+constexpr int kCsrLongBlocks = 256;   // workgroups of it that take long rows, the first of the launch
 constexpr int kCsrDparts = kCsrParts / 4 + kCsrLongBlocks;
 // part[0 .. nparts]: row ranges of equal work; part[w] = first row r with
 // rowptr[r] + kRowCost * r >= w * ceil((rowptr[m] + kRowCost * m) / nparts), part[nparts] = m.
@@ -159,12 +159,12 @@ hipError_t launch_csr_long_rows(const int64_t *rowptr, int64_t m, int32_t *list,
                                 unsigned cap, hipStream_t st);
 hipError_t launch_aht_csr(const int64_t *rowptr, const int32_t *colidx, const float *vals,
                           const int64_t *part, const int32_t *long_list, const unsigned *long_count,
-                          int k, const float *Ht, const float *GH, float *W, float eps, int64_t nnz, int64_t trows,
-                          hipStream_t st, bool accumulate = false, double *dpart = nullptr, bool dry = false);
-// nnz, trows: lengths of the entry arrays and of the table Ht (rows); row pointers and column
+                          int k, const float *Ht, const float *GH, float *W, float eps, int64_t nnz, int64_t rows,
+                          int64_t trows, hipStream_t st, bool accumulate = false, double *dpart = nullptr, bool dry = false);
+// nnz, rows, trows: lengths of the entry arrays, of W and of the table Ht (rows); row pointers and column
 // indices beyond them are pulled to the edge, so that malformed input cannot cause a stray access.
 // accumulate: X[i][:] += (gathered sum) instead of the update (GH unused).
-// dpart (updating launch only; kCsrDparts doubles): per workgroup of the two kernels, the sum of
+// dpart (updating launch only; kCsrDparts doubles): per workgroup, the sum of
 // gathered sum x new value over its rows, i.e. <A H^T, W_new> in pieces (objective monitor).
 // dry (needs dpart): W is left alone and dpart gets <A H^T, W> of the factors as they are.
 // X[i][:] <- X[i][:] * Num[i][:] / (X[i][:] G + eps), i < rows (X, Num rows x k).
