@@ -1311,8 +1311,20 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
         return fail(NMF_EUNSUPPORTED, "CSR path needs nnz < 2^31 and m < 2^31%s");
     void *ws = nullptr;
     const bool watch = objective_host || tolp;
-    if (int rc = ensure_workspace(csr_bytes(n, nnz, k) + (watch ? csr_monitor_bytes(tolp ? 1 : iters) : 0), &ws))
-        return rc;
+    const size_t need = csr_bytes(n, nnz, k) + (watch ? csr_monitor_bytes(tolp ? 1 : iters) : 0);
+    // Both factors are gathered from row by row; where their rows straddle cache lines (k not a
+    // length of csr_row_length) the run works on copies with longer rows, if the workspace holds them:
+    // 1000000 x 300000 with 40 entries per row, per iteration, k = 12 1660 -> 1482 us, k = 24 2128 -> 1592,
+    // k = 50 3726 -> 3310.  Tables that the L2 caches hold gain nothing (65536 x 16384, k = 12: 58.9 and
+    // 60.4; 100000 x 100000, k = 24, 9.6 MB each: 647 and 544).
+    const int ldk = csr_row_length(k);
+    const size_t wide = align_up((size_t)m * ldk * sizeof(float)) + align_up((size_t)n * ldk * sizeof(float));
+    const bool copies = ldk != k && (iters > 1 || tolp) && (int64_t)(m > n ? m : n) * k * 4 > ((int64_t)8 << 20) &&
+                        have_workspace(need + wide);
+    if (!copies)
+        if (int rc = ensure_workspace(need, &ws)) return rc;
+    ws = g.ws;
+    const int ld = copies ? ldk : k;
     Carve cv(ws);
     const Common c = carve_common(cv, k);
     float *Ht = cv.take<float>((size_t)n * k);
@@ -1355,18 +1367,31 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     NMF_HIP(launch_csr_long_rows(rowptr, m, long_r, long_n, (unsigned)(nnz / kLongRow + 1), st));
     NMF_HIP(launch_csr_long_rows(colptr, n, long_c, long_n + 1, (unsigned)(nnz / kLongRow + 1), st));
 
-    NMF_HIP(launch_transpose(H, k, n, Ht, st));
+    float *Wx = W;
+    if (copies) {
+        Carve tail(static_cast<char *>(ws) + need);
+        Wx = tail.take<float>((size_t)m * ldk);
+        Ht = tail.take<float>((size_t)n * ldk);
+        NMF_HIP(launch_restride(W, k, Wx, ldk, m, k, st));
+    }
+    // The factors go back to the caller's.
+    auto hand_back = [&]() -> int {
+        NMF_HIP(launch_transpose(Ht, n, k, H, st, 0, nullptr, 0, ld));
+        if (copies) NMF_HIP(launch_restride(Wx, ldk, W, k, m, k, st));
+        return NMF_OK;
+    };
+    NMF_HIP(launch_transpose(H, k, n, Ht, st, ld));
     // One iteration; with `out`, ||A - W H||_F of its result goes there, from what the W update
     // leaves behind: <A H^T, W>, H H^T, and W^T W of the new W (computed here; the next iteration
     // computes the same matrix again for its H update).
     auto iteration = [&](double *out) -> int {
-        NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
-        NMF_HIP(launch_aht_csr(colptr, rowidx, cvals, part_c, long_c, long_n + 1, k, W, c.gw, Ht, eps, nnz, n, m, st));   // H update on H^T
-        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st));
-        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, W, eps, nnz, m, n, st, false,
-                               out ? dpart : nullptr));                                                       // W update
+        NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, st, ld));
+        NMF_HIP(launch_aht_csr(colptr, rowidx, cvals, part_c, long_c, long_n + 1, k, Wx, c.gw, Ht, eps, nnz, n, m, st, false, nullptr, false, ld, ld));   // H update on H^T
+        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st, ld));
+        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, Wx, eps, nnz, m, n, st, false,
+                               out ? dpart : nullptr, false, ld, ld));                                                       // W update
         if (out) {
-            NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
+            NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, st, ld));
             NMF_HIP(launch_objective(dpart, kCsrDparts, c.gw, c.gh, k, normA2, out, st));
         }
         return NMF_OK;
@@ -1374,9 +1399,9 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     if (tolp) {
         // objective of the factors as given: the W pass without its update
         double res = 0.0;
-        NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
-        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st));
-        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, W, eps, nnz, m, n, st, false, dpart, true));
+        NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, st, ld));
+        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st, ld));
+        NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, Wx, eps, nnz, m, n, st, false, dpart, true, ld, ld));
         NMF_HIP(launch_objective(dpart, kCsrDparts, c.gw, c.gh, k, normA2, obj, st));
         NMF_HIP(hipMemcpyAsync(&res, obj, sizeof(double), hipMemcpyDeviceToHost, st));
         NMF_HIP(hipStreamSynchronize(st));
@@ -1389,7 +1414,7 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
             NMF_HIP(hipStreamSynchronize(st));
             done += chunk;
         }
-        NMF_HIP(launch_transpose(Ht, n, k, H, st));
+        if (int rc = hand_back()) return rc;
         NMF_HIP(hipStreamSynchronize(st));
         *tolp->iters_done = done;
         *tolp->residual = res;
@@ -1397,7 +1422,7 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     }
     for (int it = 0; it < iters; ++it)
         if (int rc = iteration(objective_host ? obj + it : nullptr)) return rc;
-    NMF_HIP(launch_transpose(Ht, n, k, H, st));
+    if (int rc = hand_back()) return rc;
     if (objective_host) {
         NMF_HIP(hipMemcpyAsync(objective_host, obj, (size_t)iters * sizeof(double), hipMemcpyDeviceToHost, st));
         NMF_HIP(hipStreamSynchronize(st));

@@ -46,7 +46,8 @@ __device__ __forceinline__ float row_times_gram(float x, const float *Gs, int ld
 {
     float d0 = 0.f, d1 = 0.f;
     const int cc = (c < k) ? c : 0;
-#pragma unroll 4
+    constexpr int U = LPR <= 8 ? 1 : 4;
+#pragma unroll U
     for (int d = 0; d + 1 < k; d += 2) {
         d0 += group_bcast<LPR>(x, d) * Gs[d * ldg + cc];
         d1 += group_bcast<LPR>(x, d + 1) * Gs[(d + 1) * ldg + cc];
@@ -107,16 +108,16 @@ __global__ void zero_u32_kernel(unsigned *p) { if (threadIdx.x == 0 && blockIdx.
 // The entry a lane holds for its group: its table row (clamped: an index outside the table, from
 // malformed input, is pulled to its edge, no stray access) as an offset into the table, and its value;
 // past the row's end: row 0 of the table, value 0, which adds nothing.  NARROW: the table has at most 2^30
-// floats, and the lane that loads an entry multiplies it by k once for the whole group.
+// floats, and the lane that loads an entry multiplies it by the table's row length once for the whole group.
 template <bool NARROW>
 __device__ __forceinline__ void load_entry(const int32_t *__restrict__ colidx, const float *__restrict__ vals,
-                                           int trows, int k, int64_t e, bool ok, int &off, float &val)
+                                           int trows, int ldt, int64_t e, bool ok, int &off, float &val)
 {
     off = 0;
     val = 0.f;
     if (ok) {
         const int col = min(max(colidx[e], 0), trows - 1);
-        off = NARROW ? col * k : col;
+        off = NARROW ? col * ldt : col;
         val = vals[e];
     }
 }
@@ -124,7 +125,7 @@ __device__ __forceinline__ void load_entry(const int32_t *__restrict__ colidx, c
 // acc + the products of the `cnt` entries the group's lanes hold (`any`: the largest cnt of the wave's
 // groups), UNR at a time so that several table rows are in flight.
 template <int LPR, bool NARROW>
-__device__ __forceinline__ float gather_entries(const float *__restrict__ T, int k, int cc, int off, float val,
+__device__ __forceinline__ float gather_entries(const float *__restrict__ T, int ldt, int cc, int off, float val,
                                                 int cnt, float acc)
 {
     constexpr int UNR = (LPR < 8) ? LPR : 8;
@@ -135,7 +136,7 @@ __device__ __forceinline__ float gather_entries(const float *__restrict__ T, int
             const int o = group_bcast<LPR>(off, t0 + u);
             a[u] = group_bcast<LPR>(val, t0 + u);
             if (NARROW) h[u] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(T) + (unsigned)(o + cc) * 4u);
-            else h[u] = T[(int64_t)o * k + cc];
+            else h[u] = T[(int64_t)o * ldt + cc];
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) acc += a[u] * h[u];
@@ -147,15 +148,15 @@ __device__ __forceinline__ float gather_entries(const float *__restrict__ T, int
 template <int LPR, bool NARROW>
 __device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx,
                                               const float *__restrict__ vals,
-                                              const float *__restrict__ T, int trows, int k, int c,
+                                              const float *__restrict__ T, int trows, int ldt, int k, int c,
                                               int64_t e, int64_t e1, float acc)
 {
     const int64_t left = e1 - e;
     const int cnt = left < LPR ? (left > 0 ? (int)left : 0) : LPR;
     int off;
     float val;
-    load_entry<NARROW>(colidx, vals, trows, k, e + c, c < cnt, off, val);
-    return gather_entries<LPR, NARROW>(T, k, (c < k) ? c : 0, off, val, cnt, acc);
+    load_entry<NARROW>(colidx, vals, trows, ldt, e + c, c < cnt, off, val);
+    return gather_entries<LPR, NARROW>(T, ldt, (c < k) ? c : 0, off, val, cnt, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -176,6 +177,7 @@ __device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx
 // the entries and waited for after them, and the next step's entries are requested before the
 // current ones are gathered.  65536 x 16384, 1.07 million entries, k = 12: 23 and 35 us for the two updates
 // with a launch of 4.5 for the long rows each, now 21 and 18.6 with the long rows in the same launch.
+// ldx, ldt: row lengths of W and of the table (at least k, see csr_row_length).
 // accumulate != 0: no update; the gathered sums are added to W instead (the
 // numerator of an update collected over several row batches of the matrix; GH unused).
 // accumulate == 2: nothing is written to W (needs dpart; GH unused).
@@ -185,7 +187,7 @@ __device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx
 // butterfly, then the 4 waves in order.
 // ---------------------------------------------------------------------------
 template <int LPR, bool SPLIT, bool NARROW>
-__global__ __launch_bounds__(256) void aht_csr_kernel(const int64_t *__restrict__ rowptr,
+__global__ __launch_bounds__(256, LPR == 64 ? 6 : 8) void aht_csr_kernel(const int64_t *__restrict__ rowptr,
                                                       const int32_t *__restrict__ colidx,
                                                       const float *__restrict__ vals,
                                                       const int64_t *__restrict__ part,
@@ -194,7 +196,8 @@ __global__ __launch_bounds__(256) void aht_csr_kernel(const int64_t *__restrict_
                                                       const float *__restrict__ Ht,
                                                       const float *__restrict__ GH, float *W,
                                                       float eps, int accumulate,
-                                                      double *__restrict__ dpart, int64_t nnz, int trows)
+                                                      double *__restrict__ dpart, int64_t nnz, int trows,
+                                                      int ldx, int ldt)
 {
     constexpr int LDG = LPR + 1, RPW = 64 / LPR, NG = 256 / LPR, EPG = (LPR * LPR + 255) / 256;
     __shared__ float Gs[LPR * LDG];
@@ -224,13 +227,13 @@ __global__ __launch_bounds__(256) void aht_csr_kernel(const int64_t *__restrict_
         if (accumulate == 2) {
             if (mine) dacc += (double)acc * (double)w;
         } else if (accumulate) {
-            if (mine) W[row * k + c] = w + acc;
+            if (mine) W[row * ldx + c] = w + acc;
         } else {
             stage();
             const float den = row_times_gram<LPR>(w, Gs, LDG, k, c) + eps;
             if (mine) {
                 const float wn = w * acc / den;
-                W[row * k + c] = wn;
+                W[row * ldx + c] = wn;
                 dacc += (double)acc * (double)wn;
             }
         }
@@ -243,12 +246,12 @@ __global__ __launch_bounds__(256) void aht_csr_kernel(const int64_t *__restrict_
             const int64_t e0 = min(max(rowptr[row], (int64_t)0), nnz), e1 = min(max(rowptr[row + 1], (int64_t)0), nnz);
             float acc = 0.f;
             for (int64_t e = e0 + (int64_t)grp * LPR; __any(e < e1); e += (int64_t)NG * LPR)
-                acc = gather_chunk<LPR, NARROW>(colidx, vals, Ht, trows, k, c, e, e1, acc);
+                acc = gather_chunk<LPR, NARROW>(colidx, vals, Ht, trows, ldt, k, c, e, e1, acc);
             part_acc[grp][threadIdx.x % LPR] = acc;
             __syncthreads();
             float total = 0.f;           // every lane adds up its factor, the first group's lanes write it
             for (int gI = 0; gI < NG; ++gI) total += part_acc[gI][c];
-            const float w = (c < k) ? W[row * k + c] : 0.f;
+            const float w = (c < k) ? W[row * ldx + c] : 0.f;
             finish(row, true, threadIdx.x < LPR, w, total);
             __syncthreads();
         }
@@ -266,21 +269,21 @@ __global__ __launch_bounds__(256) void aht_csr_kernel(const int64_t *__restrict_
                 valid = false;
                 e1 = e;
             }
-            const float w = (valid && c < k) ? W[row * k + c] : 0.f;
+            const float w = (valid && c < k) ? W[row * ldx + c] : 0.f;
             float acc = 0.f;
             constexpr int CHUNK = SPLIT ? 64 : LPR;      // entries of a row per step
             if (SPLIT) e += lane - c;                    // this group's share of the first step
             int64_t left = e1 - e;
             int off;
             float val;
-            load_entry<NARROW>(colidx, vals, trows, k, e + c, c < left, off, val);
+            load_entry<NARROW>(colidx, vals, trows, ldt, e + c, c < left, off, val);
             while (__any(left > 0)) {
                 const int o = off, cnt = left < LPR ? (left > 0 ? (int)left : 0) : LPR;
                 const float v = val;
                 e += CHUNK;
                 left -= CHUNK;
-                load_entry<NARROW>(colidx, vals, trows, k, e + c, c < left, off, val);
-                acc = gather_entries<LPR, NARROW>(Ht, k, cc, o, v, cnt, acc);
+                load_entry<NARROW>(colidx, vals, trows, ldt, e + c, c < left, off, val);
+                acc = gather_entries<LPR, NARROW>(Ht, ldt, cc, o, v, cnt, acc);
             }
             if (SPLIT) {
 #pragma unroll
@@ -429,7 +432,7 @@ __global__ __launch_bounds__(256) void pad_copy_kernel(const float *__restrict__
     }
 }
 
-// out (ldc x ld) = in^T, in is rows x cols with ldc >= cols and ld >= rows: what lies beyond in is set to
+// out (ldc x ld) = in^T, in is rows x cols (rows ldin apart) with ldc >= cols and ld >= rows: what lies beyond in is set to
 // zero.  COPY: copy (rows x ldc) = in with the same zero columns, from the same reading of it.
 // Tiles of 64 x 64: whole 256-byte runs on both sides at any alignment, 16 loads in flight per
 // thread (20011 x 9998, the first iteration of a run at k = 50 with 32 x 32 tiles, four loads each,
@@ -437,7 +440,7 @@ __global__ __launch_bounds__(256) void pad_copy_kernel(const float *__restrict__
 template <bool COPY>
 __global__ __launch_bounds__(256) void transpose_kernel(const float *__restrict__ in, int64_t rows,
                                                         int64_t cols, float *__restrict__ out, int64_t ld,
-                                                        float *__restrict__ copy, int64_t ldc)
+                                                        float *__restrict__ copy, int64_t ldc, int64_t ldin)
 {
     __shared__ float tile[64][65];
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -449,7 +452,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const float *__restrict_
         for (int i = 0; i < 16; ++i) {
             const int64_t r = r0 + ty + 4 * i;
             const bool ok = r < rows && c0 + tx < cols;
-            v[i] = in[ok ? r * cols + c0 + tx : 0];
+            v[i] = in[ok ? r * ldin + c0 + tx : 0];
             v[i] = ok ? v[i] : 0.f;
         }
 #pragma unroll
@@ -507,27 +510,30 @@ template <int LPR, bool SPLIT>
 static void aht_csr_dispatch(bool narrow, hipStream_t st, const int64_t *rowptr, const int32_t *colidx, const float *vals,
                              const int64_t *part, const int32_t *list, const unsigned *count, unsigned cap, int k,
                              const float *Ht, const float *GH, float *W, float eps, int acc, double *dpart, int64_t nnz,
-                             int trows)
+                             int trows, int ldx, int ldt)
 {
     const dim3 grid(kCsrLongBlocks + kCsrParts / 4), block(256);
     if (narrow)
         hipLaunchKernelGGL((aht_csr_kernel<LPR, SPLIT, true>), grid, block, 0, st, rowptr, colidx, vals, part, list, count, cap,
-                           k, Ht, GH, W, eps, acc, dpart, nnz, trows);
+                           k, Ht, GH, W, eps, acc, dpart, nnz, trows, ldx, ldt);
     else
         hipLaunchKernelGGL((aht_csr_kernel<LPR, SPLIT, false>), grid, block, 0, st, rowptr, colidx, vals, part, list, count, cap,
-                           k, Ht, GH, W, eps, acc, dpart, nnz, trows);
+                           k, Ht, GH, W, eps, acc, dpart, nnz, trows, ldx, ldt);
 }
 
 hipError_t launch_aht_csr(const int64_t *rowptr, const int32_t *colidx, const float *vals,
                           const int64_t *part, const int32_t *long_list, const unsigned *long_count,
                           int k, const float *Ht, const float *GH, float *W, float eps, int64_t nnz, int64_t rows,
-                          int64_t trows, hipStream_t st, bool accumulate, double *dpart, bool dry)
+                          int64_t trows, hipStream_t st, bool accumulate, double *dpart, bool dry, int ldx, int ldt)
 {
+    if (ldx == 0) ldx = k;
+    if (ldt == 0) ldt = k;
+    if (ldx < k || ldt < k) return hipErrorInvalidValue;
     if (trows < 1 || trows > 0x7fffffff || nnz < 0 || rows < 1) return hipErrorInvalidValue;
     if ((dpart && accumulate) || (dry && (!dpart || accumulate))) return hipErrorInvalidValue;
     const int lpr = lanes_per_row(k);
     const int acc = dry ? 2 : (accumulate ? 1 : 0);
-    const bool narrow = trows * k <= ((int64_t)1 << 30);
+    const bool narrow = trows * ldt <= ((int64_t)1 << 30);
     const unsigned cap = (unsigned)(nnz / kLongRow + 1);
     // From 64 entries per row on average a row fills the wave's lanes by itself, and fewer, longer rows
     // than lane groups leave no group idle: 16384 rows of 65 entries at k = 12 took 35 us a row per
@@ -536,10 +542,10 @@ hipError_t launch_aht_csr(const int64_t *rowptr, const int32_t *colidx, const fl
     const bool split = lpr < 64 && nnz >= 64 * rows;
     if (split) {
         NMFMU_LPR_SWITCH(lpr, (aht_csr_dispatch<L, (L < 64)>(narrow, st, rowptr, colidx, vals, part, long_list, long_count, cap, k, Ht,
-                                                         GH, W, eps, acc, dpart, nnz, (int)trows)));
+                                                         GH, W, eps, acc, dpart, nnz, (int)trows, ldx, ldt)));
     } else {
         NMFMU_LPR_SWITCH(lpr, (aht_csr_dispatch<L, false>(narrow, st, rowptr, colidx, vals, part, long_list, long_count, cap, k, Ht,
-                                                          GH, W, eps, acc, dpart, nnz, (int)trows)));
+                                                          GH, W, eps, acc, dpart, nnz, (int)trows, ldx, ldt)));
     }
     return hipGetLastError();
 }
@@ -573,6 +579,25 @@ hipError_t launch_fill_f32(float *p, int64_t count, float v, hipStream_t st)
     return hipGetLastError();
 }
 
+// dst (rows of ldd) = the first k columns of src (rows of lds); a thread per entry of a few rows at a time.
+__global__ __launch_bounds__(256) void restride_kernel(const float *__restrict__ src, int lds, float *__restrict__ dst,
+                                                       int ldd, int64_t rows, int k)
+{
+    const int per = 256 / k, c = threadIdx.x % k, r = threadIdx.x / k;
+    if (r >= per) return;
+    for (int64_t row = (int64_t)blockIdx.x * per + r; row < rows; row += (int64_t)gridDim.x * per)
+        dst[row * ldd + c] = src[row * lds + c];
+}
+
+hipError_t launch_restride(const float *src, int lds, float *dst, int ldd, int64_t rows, int k, hipStream_t st)
+{
+    if (k < 1 || k > 64 || lds < k || ldd < k) return hipErrorInvalidValue;
+    int64_t b = (rows + 256 / k - 1) / (256 / k);
+    if (b > 16384) b = 16384;
+    hipLaunchKernelGGL(restride_kernel, dim3((unsigned)b), dim3(256), 0, st, src, lds, dst, ldd, rows, k);
+    return hipGetLastError();
+}
+
 hipError_t launch_pad_copy(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t rows, int64_t cols,
                            hipStream_t st)
 {
@@ -583,14 +608,15 @@ hipError_t launch_pad_copy(const float *src, int64_t ld_src, float *dst, int64_t
 }
 
 hipError_t launch_transpose(const float *in, int64_t rows, int64_t cols, float *out, hipStream_t st, int64_t ld,
-                            float *copy, int64_t ldc)
+                            float *copy, int64_t ldc, int64_t ldin)
 {
+    if (ldin < cols) ldin = cols;
     if (ld < rows) ld = rows;
     if (ldc < cols) ldc = cols;
     int64_t tiles = ((ld + 63) / 64) * ((ldc + 63) / 64);
     if (tiles > 65536) tiles = 65536;
-    if (copy) hipLaunchKernelGGL(transpose_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, st, in, rows, cols, out, ld, copy, ldc);
-    else hipLaunchKernelGGL(transpose_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, st, in, rows, cols, out, ld, copy, ldc);
+    if (copy) hipLaunchKernelGGL(transpose_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, st, in, rows, cols, out, ld, copy, ldc, ldin);
+    else hipLaunchKernelGGL(transpose_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, st, in, rows, cols, out, ld, copy, ldc, ldin);
     return hipGetLastError();
 }
 

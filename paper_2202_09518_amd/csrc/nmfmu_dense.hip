@@ -204,7 +204,7 @@ __device__ __forceinline__ f32x4 load4(const float *__restrict__ X, int64_t ncol
 }
 
 // ---------------------------------------------------------------------------
-// Gram matrices.  MODE 0: G = X^T X, X is rows x k (the factor W).
+// Gram matrices.  MODE 0: G = X^T X, X is rows x k (the factor W), rows ld apart.
 //                 MODE 1: G = X X^T, X is k x cols (the factor H).
 // blockIdx.y selects one 32 x 32 tile (t1, t2) of G; every block sums a slice
 // of the long dimension, writes its partial tile, and the block that arrives
@@ -213,7 +213,7 @@ __device__ __forceinline__ f32x4 load4(const float *__restrict__ X, int64_t ncol
 template <int MODE, bool VEC>
 __global__ __launch_bounds__(512) void gram_kernel(const float *__restrict__ X, int64_t len, int k,
                                                    float *__restrict__ G, float *gpart,
-                                                   unsigned *counters)
+                                                   unsigned *counters, int ld)
 {
     constexpr int NW = 8;
     __shared__ float red[1024];
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(512) void gram_kernel(const float *__restrict__ X, 
             for (int u = 0; u < UN; ++u) {
                 const int64_t row = 2 * (p + u * tw) + half;
                 const bool in1 = row < len && c1 < k, in2 = row < len && c2 < k;
-                const float va = X[in1 ? row * k + c1 : 0], vb = X[in2 ? row * k + c2 : 0];
+                const float va = X[in1 ? row * ld + c1 : 0], vb = X[in2 ? row * ld + c2 : 0];
                 a[u] = in1 ? va : 0.f;
                 b[u] = in2 ? vb : 0.f;
             }
@@ -2504,18 +2504,18 @@ hipError_t launch_gram_w(const float *X, int64_t rows, int k, float *G, float *g
 {
     const int kt = k_tiles(k);
     dim3 grid(gram_blocks(rows, 512), kt * kt);
-    hipLaunchKernelGGL((gram_kernel<0, false>), grid, dim3(512), 0, st, X, rows, k, G, gpart, counters);
+    hipLaunchKernelGGL((gram_kernel<0, false>), grid, dim3(512), 0, st, X, rows, k, G, gpart, counters, k);
     return hipGetLastError();
 }
 
-hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, hipStream_t st)
+hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, hipStream_t st, int ld)
 {
     const int kt = k_tiles(k);
     int64_t nb = (rows + 511) / 512;
     if (nb > kFinMaxBlocks) nb = kFinMaxBlocks;
     if (nb < 1) nb = 1;
     hipLaunchKernelGGL((gram_kernel<0, false>), dim3((unsigned)nb, kt * kt), dim3(512), 0, st, X, rows, k,
-                       static_cast<float *>(nullptr), tiles, static_cast<unsigned *>(nullptr));
+                       static_cast<float *>(nullptr), tiles, static_cast<unsigned *>(nullptr), ld ? ld : k);
     return launch_gram_sum(tiles, (int)nb, k, G, st);
 }
 
@@ -2525,9 +2525,9 @@ hipError_t launch_gram_h(const float *X, int k, int64_t cols, float *G, float *g
     const int kt = k_tiles(k);
     dim3 grid(gram_blocks(cols, 512), kt * kt);
     if (vec_ok(X, cols))
-        hipLaunchKernelGGL((gram_kernel<1, true>), grid, dim3(512), 0, st, X, cols, k, G, gpart, counters);
+        hipLaunchKernelGGL((gram_kernel<1, true>), grid, dim3(512), 0, st, X, cols, k, G, gpart, counters, k);
     else
-        hipLaunchKernelGGL((gram_kernel<1, false>), grid, dim3(512), 0, st, X, cols, k, G, gpart, counters);
+        hipLaunchKernelGGL((gram_kernel<1, false>), grid, dim3(512), 0, st, X, cols, k, G, gpart, counters, k);
     return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ hipError_t launch_gram_w(const float *X, int64_t rows, int k, float *G, float *g
                          unsigned *counters, hipStream_t st);
 // The same for a long factor (millions of rows): up to kFinMaxBlocks blocks write partial tiles
 // (tiles: kFinMaxBlocks sets), summed by launch_gram_sum.
-hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, hipStream_t st);
+hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, hipStream_t st, int ld = 0);
 // G (k x k, ld k) = X X^T for X k x cols (row-major, ld cols).
 hipError_t launch_gram_h(const float *X, int k, int64_t cols, float *G, float *gpart,
                          unsigned *counters, hipStream_t st);
@@ -160,7 +160,13 @@ hipError_t launch_csr_long_rows(const int64_t *rowptr, int64_t m, int32_t *list,
 hipError_t launch_aht_csr(const int64_t *rowptr, const int32_t *colidx, const float *vals,
                           const int64_t *part, const int32_t *long_list, const unsigned *long_count,
                           int k, const float *Ht, const float *GH, float *W, float eps, int64_t nnz, int64_t rows,
-                          int64_t trows, hipStream_t st, bool accumulate = false, double *dpart = nullptr, bool dry = false);
+                          int64_t trows, hipStream_t st, bool accumulate = false, double *dpart = nullptr, bool dry = false,
+                          int ldx = 0, int ldt = 0);
+// ldx, ldt: row lengths of W and of the table Ht (0: k).
+// Row length at which a factor of k columns is gathered row by row without straddling cache lines (128
+// bytes): whole fractions of a line up to 32, one and a half or two lines above.
+inline int csr_row_length(int k) { return k <= 4 ? 4 : k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : k <= 48 ? 48 : 64; }
+hipError_t launch_restride(const float *src, int lds, float *dst, int ldd, int64_t rows, int k, hipStream_t st);
 // nnz, rows, trows: lengths of the entry arrays, of W and of the table Ht (rows); row pointers and column
 // indices beyond them are pulled to the edge, so that malformed input cannot cause a stray access.
 // accumulate: X[i][:] += (gathered sum) instead of the update (GH unused).
@@ -190,9 +196,9 @@ int csc_finish_blocks(int64_t nnz);
 // `cols` on are set to zero.  Any alignment.
 hipError_t launch_pad_copy(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t rows, int64_t cols,
                            hipStream_t st);
-// out = in^T (in: rows x cols).  ld > rows: rows of out are ld long, ldc > cols: out has ldc rows, what lies
+// out = in^T (in: rows x cols, rows ldin apart).  ld > rows: rows of out are ld long, ldc > cols: out has ldc rows, what lies
 // beyond in is zero; copy (optional): in with its rows extended to ldc, read once for both.
 hipError_t launch_transpose(const float *in, int64_t rows, int64_t cols, float *out, hipStream_t st, int64_t ld = 0,
-                            float *copy = nullptr, int64_t ldc = 0);
+                            float *copy = nullptr, int64_t ldc = 0, int64_t ldin = 0);
 
 }  // namespace nmfmu
