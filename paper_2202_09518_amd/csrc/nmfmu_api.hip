@@ -1194,18 +1194,28 @@ static int ooc_run(const float *A_host, int64_t m, int64_t n, int32_t k, float *
     NMF_HIP(hipEventRecord(g.ev_entry, st));
     NMF_HIP(hipStreamWaitEvent(g.copy_stream, g.ev_entry, 0));
 
-    int64_t issued = 0;   // batches handed to the copy stream so far, over all sweeps
+    // Every other sweep walks the batches backwards, so that it begins with those the last one left in the
+    // slots: they are not copied again.  The link is the bound (16384 x 16384 in 8 batches, 3 slots, 3
+    // iterations: 32 copies of 128 MiB took 76 ms, 23 take 56).  Position i of a sweep overwrites the
+    // slot of position i - slots, whose work on the batch is awaited by an event.
+    std::vector<int> slot_of((size_t)nb, 0);
     for (int s = 0; s <= iters; ++s) {
-        for (int64_t b = 0; b < nb; ++b, ++issued) {
-            const int slot = (int)(issued % slots);
+        auto batch_at = [&](int64_t i) { return (s & 1) ? nb - 1 - i : i; };
+        for (int64_t i = 0; i < nb; ++i) {
+            const int64_t b = batch_at(i);
+            const bool upload = s == 0 || i >= slots;
+            if (upload) slot_of[(size_t)b] = i < slots ? (int)i : slot_of[(size_t)batch_at(i - slots)];
+            const int slot = slot_of[(size_t)b];
             const int64_t i0 = b * batch_rows;
             const int64_t rb = (i0 + batch_rows <= m) ? batch_rows : m - i0;
             float *Ab = reinterpret_cast<float *>(static_cast<char *>(g.stage) + slot * slot_bytes);
-            if (issued >= slots) NMF_HIP(hipStreamWaitEvent(g.copy_stream, g.ev_freed[slot], 0));
-            NMF_HIP(hipMemcpyAsync(Ab, A_host + i0 * n, (size_t)rb * n * sizeof(float),
-                                   hipMemcpyHostToDevice, g.copy_stream));
-            NMF_HIP(hipEventRecord(g.ev_copied[slot], g.copy_stream));
-            NMF_HIP(hipStreamWaitEvent(st, g.ev_copied[slot], 0));
+            if (upload) {
+                if (i >= slots) NMF_HIP(hipStreamWaitEvent(g.copy_stream, g.ev_freed[slot], 0));
+                NMF_HIP(hipMemcpyAsync(Ab, A_host + i0 * n, (size_t)rb * n * sizeof(float),
+                                       hipMemcpyHostToDevice, g.copy_stream));
+                NMF_HIP(hipEventRecord(g.ev_copied[slot], g.copy_stream));
+                NMF_HIP(hipStreamWaitEvent(st, g.ev_copied[slot], 0));
+            }
             if (dpart && s == 0) NMF_HIP(launch_sumsq(Ab, rb * n, normA2 + 1, normb + b, st));
             if (s > 0) {
                 if (use_rows)    // also leaves the piece planes of the batch's new rows for the pass below
@@ -1215,7 +1225,7 @@ static int ooc_run(const float *A_host, int64_t m, int64_t n, int32_t k, float *
                     NMF_HIP(launch_aht_pass(Ab, rb, n, k, H, c.gh, W + i0 * k, eps, st, dpart ? dpart + b * bpb : nullptr));
             }
             if (s < iters)
-                NMF_HIP(launch_wta_pass(Ab, rb, n, k, W + i0 * k, planes, use_rows && s > 0, ppart, splits, rps, b > 0, st));
+                NMF_HIP(launch_wta_pass(Ab, rb, n, k, W + i0 * k, planes, use_rows && s > 0, ppart, splits, rps, i > 0, st));
             NMF_HIP(hipEventRecord(g.ev_freed[slot], st));
         }
         if (dpart && s == 0) NMF_HIP(launch_sum_f64(normb, nb, normA2, st));
