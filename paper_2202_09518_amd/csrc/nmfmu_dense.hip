@@ -576,6 +576,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_kernel(
 // are read the same way (extent = the 8-row groups that exist).  Two steps are
 // written out so that the staging registers alternate without copies.
 // ---------------------------------------------------------------------------
+template <int POLICY>
 __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
     const float *__restrict__ A, const u32x4 *__restrict__ planes, float *__restrict__ ppart,
     int64_t rows, int64_t n, int k, int64_t rps, int accumulate,
@@ -619,7 +620,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<u32x4 *>(planes + (ng ? g : 0) * 3 * 32), 0, (int)(ng * 3 * 32 * 16), kRsrcFlags);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b128(ra, loff + r * rowb, 0, kStreamLoad);
+        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b128(ra, loff + r * rowb, 0, POLICY);
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) s.wt[pl] = __builtin_amdgcn_raw_buffer_load_b128(rp, poff + pl * 32 * 16, 0, 0);
     };
@@ -699,7 +700,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
 // with the default cache policy then; a single slice streams A non-temporally).  Slice z
 // reads planes + z * slice_planes and writes ppart + z * slice_ppart; it holds
 // min(64, ktotal - 64 z) factors.
-template <bool SLICES>
+template <bool SLICES, int POLICY>
 __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kernel(
     const float *__restrict__ A, const u32x4 *__restrict__ planes, float *__restrict__ ppart,
     int64_t rows, int64_t n, int k, int64_t rps, int accumulate,
@@ -710,7 +711,6 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     constexpr int KP = 64;
     constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
-    constexpr int kPolicy = SLICES ? 0 : kStreamLoad;
     constexpr int kSteps = 6;                          // 16-row steps per group of staged planes
     constexpr int kUnits = kSteps * 2 * 3 * KP;        // 16-byte units of planes in a group
     __shared__ u32x4 pst[2][kUnits];
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
         const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(A + (av ? ib : 0) * n), 0, (int)(av * rowb), kRsrcFlags);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b64(ra, loff + r * rowb, 0, kPolicy);
+        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b64(ra, loff + r * rowb, 0, POLICY);
     };
     // a third of the planes of the group of rows from ib on: 3 units per thread
     struct Third { u32x4 u[3]; };
@@ -1343,7 +1343,7 @@ __global__ __launch_bounds__(512) void aht_pass_kernel(const float *__restrict__
 // whole pass with the stores to W and its planes left out (timing).
 // ---------------------------------------------------------------------------
 extern __shared__ float aht_rows_lds[];
-template <int R, int KT>
+template <int R, int KT, int POLICY>
 __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
     const float *__restrict__ A, const u32x4 *__restrict__ planesH, const float *__restrict__ GH,
     float *W, u32x4 *__restrict__ planesW, float *__restrict__ gout,
@@ -1401,7 +1401,7 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
                 const unsigned lo = (ch * 64 + lch * 4 < n) ? loff : 0x7fffffffu;
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    s.a[u] = __builtin_amdgcn_raw_buffer_load_b128(ra, lo + (unsigned)(4 * u) * rowb, 0, kStreamLoad);
+                    s.a[u] = __builtin_amdgcn_raw_buffer_load_b128(ra, lo + (unsigned)(4 * u) * rowb, 0, POLICY);
             };
             u32x4 bp[4][3][KT];
             auto load_b = [&](int64_t chl) {
@@ -2355,9 +2355,14 @@ __global__ __launch_bounds__(256) void sumsq_kernel(const float *__restrict__ X,
 {
     __shared__ double wsum[4];
     double acc = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256) {
-        const float v = X[e];
-        acc += (double)v * (double)v;
+    // eight loads in flight per thread: one at a time, 192 MiB took 65 us
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += 8 * step) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = e + u * step < count ? X[e + u * step] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += (double)v[u] * (double)v[u];
     }
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
@@ -2446,6 +2451,11 @@ static inline bool vec_ok(const void *p, int64_t ld)
 {
     return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld & 3) == 0;
 }
+
+// A that the last-level cache (256 MiB) keeps from one pass to the next is loaded to stay there, not
+// marked for eviction: 12288 x 4096, k = 20 (192 MiB): A H^T pass 39.4 -> 34.2 us, W^T A 38.2 -> 36.0;
+// 2000 x 1204, k = 12: 13.7 -> 11.7 and 8.3 -> 8.0.
+static bool stream_a(int64_t rows, int64_t n) { return rows * n * 4 > ((int64_t)224 << 20); }
 
 int wta_splits(int64_t rows, int64_t n, int k)
 {
@@ -2578,7 +2588,7 @@ hipError_t launch_wta_pass_slices(const float *A, int64_t rows, int64_t n, int k
     const int nslices = (k + 63) / 64;
     const int gx = (int)((n + 255) / 256), gy = splits;
     const int64_t tiles8 = ((int64_t)gx * gy + 7) / 8 * 8;
-    hipLaunchKernelGGL((wta_pass_split64_wide_kernel<true>), dim3((unsigned)(tiles8 * nslices)), dim3(64 * kWtaWaves), 0, st, A,
+    hipLaunchKernelGGL((wta_pass_split64_wide_kernel<true, 0>), dim3((unsigned)(tiles8 * nslices)), dim3(64 * kWtaWaves), 0, st, A,
                        static_cast<const u32x4 *>(planes), ppart, rows, n, k, rps, 0, static_cast<const float *>(nullptr), 0,
                        static_cast<float *>(nullptr), gx, gy, nslices, (int64_t)(planes_bytes(rows) / 16),
                        (int64_t)splits * 64 * n);
@@ -2632,7 +2642,8 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
         const dim3 block(64 * kWtaWaves);
         // buffer loads address 16 rows with 32-bit offsets: 64 n bytes must stay below 2^31
         if (vec && n < ((int64_t)1 << 25))
-            hipLaunchKernelGGL(wta_pass_split_buf_kernel, grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
+            if (stream_a(rows, n)) hipLaunchKernelGGL(wta_pass_split_buf_kernel<kStreamLoad>, grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
+            else hipLaunchKernelGGL(wta_pass_split_buf_kernel<0>, grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
         else
             hipLaunchKernelGGL((wta_pass_split_kernel<false>), grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
         break;
@@ -2644,9 +2655,14 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
                 if (e != hipSuccess) return e;
             }
             const dim3 grid256((unsigned)((n + 255) / 256), (unsigned)splits);
-            hipLaunchKernelGGL((wta_pass_split64_wide_kernel<false>), grid256, dim3(64 * kWtaWaves), 0, st, A,
-                               static_cast<const u32x4 *>(planes), ppart, rows, n, k, rps, acc, gtiles, nsets, gsum,
-                               0, 0, 1, (int64_t)0, (int64_t)0);
+            if (stream_a(rows, n))
+                hipLaunchKernelGGL((wta_pass_split64_wide_kernel<false, kStreamLoad>), grid256, dim3(64 * kWtaWaves), 0, st, A,
+                                   static_cast<const u32x4 *>(planes), ppart, rows, n, k, rps, acc, gtiles, nsets, gsum,
+                                   0, 0, 1, (int64_t)0, (int64_t)0);
+            else
+                hipLaunchKernelGGL((wta_pass_split64_wide_kernel<false, 0>), grid256, dim3(64 * kWtaWaves), 0, st, A,
+                                   static_cast<const u32x4 *>(planes), ppart, rows, n, k, rps, acc, gtiles, nsets, gsum,
+                                   0, 0, 1, (int64_t)0, (int64_t)0);
         } else {
             if (!W) return hipErrorInvalidValue;   // this kernel reads the factor itself, not its planes
             wta_dispatch<2>(vec, grid, st, A, W, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
@@ -2872,9 +2888,14 @@ bool aht_rows_ok(const float *A, int64_t m, int64_t n, int k)
     return aht_rows_can(A, n, k) && ((m >= 12288 && n >= 512) || m * n <= ((int64_t)1 << 22));
 }
 
-// row tiles per workgroup: 128-row blocks when they fill the chip, else 64-row blocks; two
+// row tiles per workgroup: 128-row blocks when they fill the chip, else 64-row or 32-row blocks; two
 // 32-factor tiles leave registers for two row tiles only
-static int aht_rows_tiles(int64_t rows, int k) { return k <= 32 && (rows + 127) / 128 >= 192 ? 4 : 2; }
+static int aht_rows_tiles(int64_t rows, int k)
+{
+    if (k > 32) return 2;
+    // 32-row blocks below 8192 rows: 2000 x 1204, k = 12, 18.0 us on 32 workgroups of 64 rows, 13.7 on 63
+    return (rows + 127) / 128 >= 192 ? 4 : (rows + 63) / 64 >= 128 ? 2 : 1;
+}
 
 int aht_rows_blocks(int64_t rows, int k)
 {
@@ -2884,7 +2905,7 @@ int aht_rows_blocks(int64_t rows, int k)
     return (int)b;
 }
 
-template <int R, int KT>
+template <int R, int KT, int POLICY>
 static hipError_t aht_rows_launch(dim3 grid, hipStream_t st, const float *A, const u32x4 *ph, const float *GH, float *W,
                                   u32x4 *pw, float *gout, double *dpart, int64_t rows, int64_t n, int k, float eps,
                                   int mode, const BlockMap &bm)
@@ -2892,12 +2913,12 @@ static hipError_t aht_rows_launch(dim3 grid, hipStream_t st, const float *A, con
     constexpr int kLdsBytes = (8 * 2048 + 4 * R * KT * 1024 + (KT == 2 ? 4096 : 0)) * (int)sizeof(float);
     static bool raised = false;      // more dynamic LDS than the default limit: asked for once per process
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&aht_rows_kernel<R, KT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&aht_rows_kernel<R, KT, POLICY>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    hipLaunchKernelGGL((aht_rows_kernel<R, KT>), grid, dim3(512), kLdsBytes, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
+    hipLaunchKernelGGL((aht_rows_kernel<R, KT, POLICY>), grid, dim3(512), kLdsBytes, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
     return hipGetLastError();
 }
 
@@ -2914,9 +2935,16 @@ hipError_t launch_aht_rows(const float *A, int64_t rows, int64_t n, int k, const
     const u32x4 *ph = static_cast<const u32x4 *>(planesH);
     u32x4 *pw = static_cast<u32x4 *>(planesW);
     const int mode = gram_only ? 1 : (dry ? 2 : 0);
-    if (k > 32) return aht_rows_launch<2, 2>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
-    if (aht_rows_tiles(rows, k) == 4) return aht_rows_launch<4, 1>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
-    return aht_rows_launch<2, 1>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm);
+    const bool stream = stream_a(rows, n);
+    const int tiles = aht_rows_tiles(rows, k);
+#define NMFMU_AHT_ROWS(R, KT) \
+    return stream ? aht_rows_launch<R, KT, kStreamLoad>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm) \
+                  : aht_rows_launch<R, KT, 0>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm)
+    if (k > 32) NMFMU_AHT_ROWS(2, 2);
+    if (tiles == 4) NMFMU_AHT_ROWS(4, 1);
+    if (tiles == 2) NMFMU_AHT_ROWS(2, 1);
+    NMFMU_AHT_ROWS(1, 1);
+#undef NMFMU_AHT_ROWS
 }
 
 bool one_pass_ok(const float *A, int64_t n, int k)
@@ -2964,8 +2992,7 @@ hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const
     return !update ? one_pass_launch<NRW, POL, false, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
          : product ? one_pass_launch<NRW, POL, true, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
                    : one_pass_launch<NRW, POL, true, false>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps)
-    // A that stays in the last-level cache from one iteration to the next is loaded to stay there
-    const bool stream = rows * n * 4 > ((int64_t)192 << 20);
+    const bool stream = stream_a(rows, n);
     if (n <= 256) {
         if (stream) NMFMU_ONE_PASS(2, kStreamLoad);
         NMFMU_ONE_PASS(2, 0);
