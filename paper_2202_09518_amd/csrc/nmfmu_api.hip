@@ -574,15 +574,36 @@ struct Sliced {
     size_t planes_cap, ppart_elems;
 };
 
+// Row splits of a pass whose slices run side by side: every split of every slice is a partial result
+// written and read again, and the slices already fill the chip (512 workgroups at a time), so the fewest
+// splits whose last round of workgroups is nearly full.  Rank 256 on 16384 x 8192: 16 and 8 splits
+// (134 MB of partials for each product) 930 us per iteration, 4 and 2 894.
+int sliced_splits(int64_t rows, int64_t cols, int width, int nslices)
+{
+    const int most = wta_splits(rows, cols, width);
+    const int64_t per = (cols + 255) / 256 * nslices;
+    int best = most;
+    double full = 0.0;
+    for (int s = 1; s <= most; ++s) {
+        const double rounds = (double)(per * s) / 512.0, use = rounds / std::ceil(rounds);
+        if (use > full + 1e-9) {
+            full = use;
+            best = s;
+        }
+        if (use >= 0.9) break;
+    }
+    return best;
+}
+
 int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float *X, int64_t cols,
                float *out, bool accumulate, hipStream_t st)
 {
     // factor columns per pass: the widest the pass kernels take from planes alone for this X
     // (the slices of F are not contiguous, so the kernel that reads the factor itself is out)
     const int kSlice = wta_planes_only_width(X, cols);
-    const int splits = wta_splits(rows, cols, kSlice);
-    const int64_t rps = wta_rows_per_split(rows, splits);
     const int nslices = (k + 63) / 64;
+    const int splits = sliced_splits(rows, cols, kSlice, kSlice == 64 ? nslices : 1);
+    const int64_t rps = wta_rows_per_split(rows, splits);
     if (kSlice == 64 && k > 64) {
         // all slices in one launch each: the slices of a tile of X run side by side and share its bytes
         if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems || planes_bytes(rows) * nslices > e.planes_cap)
