@@ -20,8 +20,9 @@
 // 4): lane c of the group owns factor index c.  A wave holds 64 / LPR rows, so
 // short rows are packed several to a wave.  The group reads its row's entries
 // LPR at a time with coalesced loads and hands them round with lane shuffles.
+// From 64 entries per row on average a whole wave takes one row at a time.
 // Rows are dealt to wavefronts in contiguous ranges of equal work (stored
-// entries plus a per-row cost), and rows too long for one group are split
+// entries plus a per-row cost), and rows too long for one wave are split
 // over a whole workgroup.
 #include <hipcub/hipcub.hpp>
 

@@ -11,6 +11,8 @@
 //       reduction of the matrix instruction
 //   factor_update_kernel : sums the partials, updates H (or W^T in the mirrored
 //       plan), writes the operand planes and the Gram tiles of the new factor
+//   one_pass_kernel : up to 512 columns, A H^T, the W update and W^T A of the next iteration in one
+//       reading of A
 //   aht_rows_kernel : A H^T on the row-major A (coalesced loads turned through
 //       LDS) with the W update, the planes and the Gram tiles of the new W fused
 //   aht_pass_kernel : the older direct A H^T kernel (lanes down the rows), for
@@ -1037,7 +1039,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
         }
         if (sp == 0) {
 #pragma unroll
-            for (int ci = 0; ci < NC; ++ci) Xs[(fc + FG * ci) * CW + jl] = okj ? xo[ci] : 0.f;
+            for (int ci = 0; ci < NC; ++ci) Xs[(fc + FG * ci) * CW + jl] = okj && fc + FG * ci < k ? xo[ci] : 0.f;
         }
         if (SPL > 1 && sp > 0) {
 #pragma unroll
