@@ -235,7 +235,9 @@ int nmf_mu_csr_tol(const int64_t *rowptr, const int32_t *colidx, const float *va
 /*
  * Out-of-memory dense MU: A stays in host memory and is streamed to the device
  * in batches of `batch_rows` rows (co-linear batching, Algorithm 5; W and H
- * stay resident on the device).  Each sweep uploads A once: a batch first gets
+ * stay resident on the device).  Each sweep goes over A once, every other one
+ * backwards, and uploads what the staging slots do not hold from the last (ranks
+ * above NMF_MU_MAX_K: all of it, always forwards): a batch first gets
  * its W rows updated with the current H, then contributes W_b^T A_b and
  * W_b^T W_b of the updated rows to the next H update.  iters iterations take
  * iters + 1 sweeps and give the same sequence H1, W1, H2, W2, ... as
