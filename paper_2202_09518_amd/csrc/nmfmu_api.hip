@@ -1171,7 +1171,11 @@ static int ooc_run(const float *A_host, int64_t m, int64_t n, int32_t k, float *
     // The W update of a batch: the streaming row kernel where it applies (staging slots are aligned,
     // so that is a matter of n, k and the batch height), else the direct kernel.
     const bool use_rows = aht_rows_can(nullptr, n, k);
-    auto w_blocks = [&](int64_t rows) { return use_rows ? (int64_t)aht_rows_blocks(rows, k) : aht_pass_blocks(rows); };
+    // Row tiles per workgroup are chosen once, for a full batch: with a choice of its own a shorter last batch could
+    // have more workgroups than a full one (8192 rows: 128 of 64 rows, 8000 rows: 250 of 32), and more than the
+    // shares that are laid out here for it.
+    const int tiles = use_rows ? aht_rows_tiles(batch_rows, k) : 0;
+    auto w_blocks = [&](int64_t rows) { return use_rows ? (int64_t)aht_rows_blocks(rows, k, tiles) : aht_pass_blocks(rows); };
     const int64_t bpb = w_blocks(batch_rows);
     const size_t mon_bytes = objective_host
         ? align_up((size_t)(nb * bpb) * sizeof(double)) + align_up((size_t)nb * sizeof(double)) +
@@ -1241,7 +1245,7 @@ static int ooc_run(const float *A_host, int64_t m, int64_t n, int32_t k, float *
             if (s > 0) {
                 if (use_rows)    // also leaves the piece planes of the batch's new rows for the pass below
                     NMF_HIP(launch_aht_rows(Ab, rb, n, k, planes_ht, c.gh, W + i0 * k, planes, c.gwp, eps, st, false, nullptr,
-                                            dpart ? dpart + b * bpb : nullptr));
+                                            dpart ? dpart + b * bpb : nullptr, false, tiles));
                 else
                     NMF_HIP(launch_aht_pass(Ab, rb, n, k, H, c.gh, W + i0 * k, eps, st, dpart ? dpart + b * bpb : nullptr));
             }
@@ -1256,7 +1260,7 @@ static int ooc_run(const float *A_host, int64_t m, int64_t n, int32_t k, float *
             // leaves the tail of its segment untouched, so its workgroups are counted, not bpb),
             // H H^T of the H they used, W^T W of the W they left
             const int64_t last_rows = m - (nb - 1) * batch_rows;
-            if (w_blocks(last_rows) != bpb) {
+            if (w_blocks(last_rows) < bpb) {
                 // close the gap so that the shares are one contiguous run
                 NMF_HIP(hipMemsetAsync(dpart + (nb - 1) * bpb + w_blocks(last_rows), 0,
                                        (size_t)(bpb - w_blocks(last_rows)) * sizeof(double), st));

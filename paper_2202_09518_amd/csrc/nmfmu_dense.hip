@@ -2889,16 +2889,16 @@ bool aht_rows_ok(const float *A, int64_t m, int64_t n, int k)
 
 // row tiles per workgroup: 128-row blocks when they fill the chip, else 64-row or 32-row blocks; two
 // 32-factor tiles leave registers for two row tiles only
-static int aht_rows_tiles(int64_t rows, int k)
+int aht_rows_tiles(int64_t rows, int k)
 {
     if (k > 32) return 2;
     // 32-row blocks below 8192 rows: 2000 x 1204, k = 12, 18.0 us on 32 workgroups of 64 rows, 13.7 on 63
     return (rows + 127) / 128 >= 192 ? 4 : (rows + 63) / 64 >= 128 ? 2 : 1;
 }
 
-int aht_rows_blocks(int64_t rows, int k)
+int aht_rows_blocks(int64_t rows, int k, int tiles)
 {
-    const int64_t rb = 32 * aht_rows_tiles(rows, k);
+    const int64_t rb = 32 * (tiles ? tiles : aht_rows_tiles(rows, k));
     int64_t b = (rows + rb - 1) / rb;
     if (b > kFinMaxBlocks) b = kFinMaxBlocks;
     return (int)b;
@@ -2923,19 +2923,19 @@ static hipError_t aht_rows_launch(dim3 grid, hipStream_t st, const float *A, con
 
 hipError_t launch_aht_rows(const float *A, int64_t rows, int64_t n, int k, const void *planesH,
                            const float *GH, float *W, void *planesW, float *gout, float eps, hipStream_t st,
-                           bool gram_only, const BlockMap *map, double *dpart, bool dry)
+                           bool gram_only, const BlockMap *map, double *dpart, bool dry, int tiles)
 {
-    if (k > 64 || !planesW || !gout) return hipErrorInvalidValue;
+    if (tiles == 0) tiles = aht_rows_tiles(rows, k);
+    if (k > 64 || !planesW || !gout || (k > 32 ? tiles != 2 : tiles != 1 && tiles != 2 && tiles != 4)) return hipErrorInvalidValue;
     if (!gram_only && (!A || !planesH || !GH || !vec_ok(A, n) || n >= ((int64_t)1 << 24))) return hipErrorInvalidValue;
     BlockMap bm;
     if (map) bm = *map;
     else bm.on = 0;
-    const dim3 grid((unsigned)aht_rows_blocks(rows, k));
+    const dim3 grid((unsigned)aht_rows_blocks(rows, k, tiles));
     const u32x4 *ph = static_cast<const u32x4 *>(planesH);
     u32x4 *pw = static_cast<u32x4 *>(planesW);
     const int mode = gram_only ? 1 : (dry ? 2 : 0);
     const bool stream = stream_a(rows, n);
-    const int tiles = aht_rows_tiles(rows, k);
 #define NMFMU_AHT_ROWS(R, KT) \
     return stream ? aht_rows_launch<R, KT, kStreamLoad>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm) \
                   : aht_rows_launch<R, KT, 0>(grid, st, A, ph, GH, W, pw, gout, dpart, rows, n, k, eps, mode, bm)

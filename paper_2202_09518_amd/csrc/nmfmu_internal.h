@@ -117,11 +117,14 @@ int64_t aht_pass_blocks(int64_t rows);
 // operands this kernel takes; aht_rows_ok: and a shape on which it fills the chip.
 bool aht_rows_can(const float *A, int64_t n, int k);
 bool aht_rows_ok(const float *A, int64_t m, int64_t n, int k);
-int aht_rows_blocks(int64_t rows, int k);
+// tiles: 32-row tiles per workgroup, 0: aht_rows_tiles(rows, k).  The count of workgroups grows with the rows only at a
+// fixed number of tiles: a caller that sizes for one height and launches a smaller one names the tiles.
+int aht_rows_tiles(int64_t rows, int k);
+int aht_rows_blocks(int64_t rows, int k, int tiles = 0);
 hipError_t launch_aht_rows(const float *A, int64_t rows, int64_t n, int k, const void *planesH,
                            const float *GH, float *W, void *planesW, float *gout, float eps, hipStream_t st,
                            bool gram_only = false, const BlockMap *map = nullptr, double *dpart = nullptr,
-                           bool dry = false);
+                           bool dry = false, int tiles = 0);
 // Both products in one reading of A (few columns; see one_pass_kernel).  ppart: one k x n partial
 // of W^T A per workgroup (one_pass_blocks of them), gout: one tile set of W^T W each, dpart
 // (optional): one double each.  H H^T either complete (GH) or as nbh tile sets (ghsets).
