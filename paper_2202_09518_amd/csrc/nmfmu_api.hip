@@ -1174,7 +1174,9 @@ static int ooc_run(const float *A_host, int64_t m, int64_t n, int32_t k, float *
     // Row tiles per workgroup are chosen once, for a full batch: with a choice of its own a shorter last batch could
     // have more workgroups than a full one (8192 rows: 128 of 64 rows, 8000 rows: 250 of 32), and more than the
     // shares that are laid out here for it.
-    const int tiles = use_rows ? aht_rows_tiles(batch_rows, k) : 0;
+    // At least two: one share per 64 rows is what nmf_mu_ooc_monitor's workspace is documented to hold, and the link
+    // bounds a batch, not the workgroups of its W update.
+    const int tiles = use_rows ? std::max(2, aht_rows_tiles(batch_rows, k)) : 0;
     auto w_blocks = [&](int64_t rows) { return use_rows ? (int64_t)aht_rows_blocks(rows, k, tiles) : aht_pass_blocks(rows); };
     const int64_t bpb = w_blocks(batch_rows);
     const size_t mon_bytes = objective_host
