@@ -368,6 +368,12 @@ int close_run(const DenseRun &r, int k, float *W, float *H, int64_t m, int64_t n
     return NMF_OK;
 }
 
+// A dense_body on this plan streams A itself for both products and leaves the plan's A^T alone.
+bool takes_row_plan(const DensePlan &p, const float *A, int64_t m, int64_t n, int k)
+{
+    return !p.one_pass && !p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored);
+}
+
 constexpr int kDenseKernels = 6;
 
 // Per-iteration objective of a dense run (device memory): out[it] after iteration it.
@@ -429,7 +435,7 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
     // counts follow the rank actually run; the partial buffer holds the largest case.
     const int s1 = wta_splits(m, n, k), s2 = wta_splits(n, m, k);
     const int64_t rps1 = wta_rows_per_split(m, s1), rps2 = wta_rows_per_split(n, s2);
-    if (!p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored)) {
+    if (takes_row_plan(p, A, m, n, k)) {
         // Row plan: both products stream the row-major A.  The W^T A pass reads the piece
         // planes of W and, on the side, adds the tile sets of W^T W up; the H update writes
         // the planes of H^T and the tile sets of H H^T, which a small launch adds up; the A H^T pass
@@ -1085,6 +1091,12 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
     // Stacking needs the mirrored plan for the largest stack plus room for the packed
     // factors; without that much workspace the runs go one by one with the plan that fits.
     const size_t big = dense_bytes(m, n, Kmax, true) + stack_bytes;
+    // Whose transpose the workspace holds: a run that takes the row plan makes none, also where the next
+    // one on the same A, of a larger rank, needs it.
+    const float *at_of = nullptr;
+    auto note_at = [&](const DensePlan &p, const float *a, int rank) {
+        if (p.mirrored && !takes_row_plan(p, a, m, n, rank)) at_of = a;
+    };
     const bool can_stack = (g.ws && g.ws_bytes >= big) || (g.ws_owned && ensure_workspace(big, &ws) == NMF_OK);
     if (!can_stack) {
         (void)hipGetLastError();
@@ -1092,8 +1104,8 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
         if (int rc = dense_workspace(nullptr, m, n, kmax, &ws, &mirrored)) return rc;
         const DensePlan p1 = carve_dense(ws, m, n, kmax, mirrored);
         for (int r = 0; r < n_runs; ++r) {
-            const bool same_a = r > 0 && A[r] == A[r - 1];
-            if (int rc = dense_body(A[r], m, n, k[r], W[r], H[r], iters, eps, p1, st, same_a)) return rc;
+            if (int rc = dense_body(A[r], m, n, k[r], W[r], H[r], iters, eps, p1, st, at_of == A[r])) return rc;
+            note_at(p1, A[r], k[r]);
         }
         return NMF_OK;
     }
@@ -1106,10 +1118,11 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
     float *Hall = reinterpret_cast<float *>(tail + align_up((size_t)m * Kmax * sizeof(float)));
     for (size_t si = 0; si < stacks.size(); ++si) {
         const Stack &sk = stacks[si];
-        const bool same_a = si > 0 && A[sk.first] == A[stacks[si - 1].first];
+        const bool have_at = at_of == A[sk.first];
         if (sk.count == 1) {
             const int r = sk.first;
-            if (int rc = dense_body(A[r], m, n, k[r], W[r], H[r], iters, eps, p, st, same_a)) return rc;
+            if (int rc = dense_body(A[r], m, n, k[r], W[r], H[r], iters, eps, p, st, have_at)) return rc;
+            note_at(p, A[r], k[r]);
             continue;
         }
         BlockMap map;
@@ -1125,8 +1138,9 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
             off += k[r];
         }
         for (int c = off; c < 64; ++c) map.id[c] = 255;
-        if (int rc = dense_body(A[sk.first], m, n, sk.K, Wall, Hall, iters, eps, p, st, same_a, nullptr, &map))
+        if (int rc = dense_body(A[sk.first], m, n, sk.K, Wall, Hall, iters, eps, p, st, have_at, nullptr, &map))
             return rc;
+        note_at(p, A[sk.first], sk.K);
         off = 0;
         for (int i = 0; i < sk.count; ++i) {
             const int r = sk.first + i;
