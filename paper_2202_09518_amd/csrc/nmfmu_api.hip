@@ -1752,6 +1752,7 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     if (!exact)
         if (int rc = residual_to_host(r.A, m, r.n, k, r.W, r.H, scratch, &res, st)) return rc;
     if (int rc = close_run(r, k, W, H, m, n, st)) return rc;
+    if (r.W != W || r.H != H) NMF_HIP(hipStreamSynchronize(st));    // blocking also where the factors are copied back
     *iters_done_host = done;
     *residual_host = res;
     return NMF_OK;
