@@ -115,6 +115,18 @@ __device__ __forceinline__ void cut2(float x0, float x1, u32x4 (&at)[3], int pr)
     at[2][pr] = cvt_pk_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
 
+// Sum of N requested values, added in a fixed tree: long lists of partial results meet in batches of this
+// kind, so that no value passes through a chain of more roundings than there are batches plus log2 N.
+template <int N>
+__device__ __forceinline__ float tree_sum(float (&t)[N])
+{
+#pragma unroll
+    for (int w = N / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int i = 0; i < w; ++i) t[i] += t[i + w];
+    return t[0];
+}
+
 // Row of the 32 x 32 accumulator held in register v of a lane in half `half`.
 __device__ __forceinline__ int acc_row(int v, int half) { return (v & 3) + 4 * half + 8 * (v >> 2); }
 
@@ -312,7 +324,7 @@ __global__ __launch_bounds__(512) void gram_kernel(const float *__restrict__ X, 
 // kt x kt tiles of 1024 floats) are needed, summed, by the finisher AFTER this pass.  The
 // first workgroups of the pass add them up so that no separate launch is needed: job j = entries
 // 64 j .. 64 j + 63, dealt to the workgroups in order; four lanes share an entry, lane q adds sets
-// q, q + 4, ... in order, and the four sums meet in a fixed tree.  (Sums of 16 sets each, left to the
+// q, q + 4, ... a batch of 16 at a time, and the four sums meet in a fixed tree.  (Sums of 16 sets each, left to the
 // finisher's workgroups to finish, cost every one of them 256 KiB of reads at 33 to 64 factors.)
 __device__ __forceinline__ void sum_tile_sets(const float *__restrict__ gtiles, int nsets, int k,
                                               float *__restrict__ gsum)
@@ -329,7 +341,8 @@ __device__ __forceinline__ void sum_tile_sets(const float *__restrict__ gtiles, 
 #pragma unroll
             for (int b = 0; b < B; ++b) t[b] = src[(int64_t)(s + 4 * b < nsets ? s + 4 * b : 0) * stride];
 #pragma unroll
-            for (int b = 0; b < B; ++b) sum += s + 4 * b < nsets ? t[b] : 0.f;
+            for (int b = 0; b < B; ++b) t[b] = s + 4 * b < nsets ? t[b] : 0.f;
+            sum += tree_sum(t);
         }
         sum += __shfl_xor(sum, 1);
         sum += __shfl_xor(sum, 2);
@@ -973,7 +986,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
 
     // A thread's entries of G (8 at KP = 64) are independent: the loads of up to four entries are
     // requested together, kGramBatch sets per entry at a time (each trip to L2 costs a microsecond
-    // here), and each entry's sets are added in set order.
+    // here), and each batch is added in a tree.
     constexpr int kGramBatch = 16;
     constexpr int EPT = (KP * KP + 64 * NW - 1) / (64 * NW), EG = EPT < 4 ? EPT : 4;
     for (int i0 = 0; i0 < EPT; i0 += EG) {
@@ -1004,9 +1017,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
 #pragma unroll
                     for (int u = 0; u < kGramBatch; ++u) t[i][u] = ld(r, off[i] + (unsigned)(b + u) * (unsigned)stride * 4u);
 #pragma unroll
-                for (int i = 0; i < EG; ++i)
-#pragma unroll
-                    for (int u = 0; u < kGramBatch; ++u) gv[i] += t[i][u];
+                for (int i = 0; i < EG; ++i) gv[i] += tree_sum(t[i]);
             }
         }
 #pragma unroll
@@ -1029,13 +1040,16 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
         float p[NC];
 #pragma unroll
         for (int ci = 0; ci < NC; ++ci) p[ci] = 0.f;
-        // Partial sums in split order, a batch of splits at a time.
+        // Partial sums in split order, a batch of splits at a time: the batch is added up by itself.
         for (int s = s_lo; s < s_hi; s += SB) {
             if (s > s_lo) request_splits(ch, s);
 #pragma unroll
-            for (int u = 0; u < SB; ++u)
+            for (int ci = 0; ci < NC; ++ci) {
+                float b = pb[0][ci];
 #pragma unroll
-                for (int ci = 0; ci < NC; ++ci) p[ci] += pb[u][ci];
+                for (int u = 1; u < SB; ++u) b += pb[u][ci];
+                p[ci] += b;
+            }
         }
         if (sp == 0) {
 #pragma unroll
@@ -1716,7 +1730,7 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
     load_rows(ra, blk);
     load_w(blk);
     if (update) {
-        // H H^T: complete, or the H update's tile sets added up in set order
+        // H H^T: complete, or the H update's tile sets added up, a batch of 16 at a time
         constexpr int B = 16;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -1732,7 +1746,8 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
 #pragma unroll
                     for (int u = 0; u < B; ++u) t[u] = ghsets[(b + u < nbh ? b + u : 0) * 1024 + (in ? pos : 0)];
 #pragma unroll
-                    for (int u = 0; u < B; ++u) g += b + u < nbh ? t[u] : 0.f;
+                    for (int u = 0; u < B; ++u) t[u] = b + u < nbh ? t[u] : 0.f;
+                    g += tree_sum(t);
                 }
             }
             Gs[d * LDW + c] = in ? g : 0.f;
@@ -1830,9 +1845,9 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) Qp[w * 1024 + v * 64 + lane] = q[0][v] + q[1][v];
             // W H H^T of this lane's entries (its wave wrote their rows above)
-            float den[NO][2];
+            float den[NO][4];
 #pragma unroll
-            for (int i = 0; i < NO; ++i) den[i][0] = den[i][1] = 0.f;
+            for (int i = 0; i < NO; ++i) den[i][0] = den[i][1] = den[i][2] = den[i][3] = 0.f;
 #pragma unroll 2
             for (int d = 0; d < 32; d += 4) {
                 const f32x4 g = *reinterpret_cast<const f32x4 *>(Gs + jj * LDW + d);
@@ -1841,8 +1856,8 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
                     const f32x4 x = *reinterpret_cast<const f32x4 *>(Ws + (ob + i) * LDW + d);
                     den[i][0] += x.x * g.x;
                     den[i][1] += x.y * g.y;
-                    den[i][0] += x.z * g.z;
-                    den[i][1] += x.w * g.w;
+                    den[i][2] += x.z * g.z;
+                    den[i][3] += x.w * g.w;
                 }
             }
             __syncthreads();
@@ -1855,7 +1870,7 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
                 for (int c = 1; c < NCW; ++c) qs += src[c * 1024];
                 wn[i] = 0.f;
                 if (i0 + row < rows && jj < k) {
-                    wn[i] = wold[i] * qs / ((den[i][0] + den[i][1]) + eps);
+                    wn[i] = wold[i] * qs / (((den[i][0] + den[i][1]) + (den[i][2] + den[i][3])) + eps);
                     if (Wnew) Wnew[(i0 + row) * k + jj] = wn[i];
                     dacc += (double)qs * (double)wn[i];
                 }
@@ -1933,7 +1948,7 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
 }
 
 // G (k x k, ld k) = sum over nb sets of partial 32 x 32 tiles (accumulator layout).
-// Eight lanes share one entry: lane q adds sets q, q+8, ... in order, then the
+// Eight lanes share one entry: lane q adds sets q, q+8, ..., a batch of 16 at a time, then the
 // eight sums are combined in a fixed tree, so the result does not depend on timing.
 __global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__ gpart, int nb, int k,
                                                        float *__restrict__ G)
@@ -1951,7 +1966,8 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__
 #pragma unroll
         for (int u = 0; u < 16; ++u) t[u] = src[(b + 8 * u < nb ? b + 8 * u : 0) * stride];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) s += b + 8 * u < nb ? t[u] : 0.f;
+        for (int u = 0; u < 16; ++u) t[u] = b + 8 * u < nb ? t[u] : 0.f;
+        s += tree_sum(t);
     }
     s += __shfl_xor(s, 1, 8);
     s += __shfl_xor(s, 2, 8);
