@@ -699,8 +699,11 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
 // them in LDS once for its four waves: six steps (36 KiB) at a time, double buffered, three
 // 16-byte units per thread requested every second step and written two steps later, one
 // barrier per six steps; 72 KiB per workgroup, two workgroups per compute unit.  The running
-// totals live in registers (the planes of the next steps no longer do).  No sum across waves
-// is needed, and each wave stores its own 64 x 64 result: register v of tile (t, q) is factor
+// totals live in registers (the planes of the next steps no longer do) and take the
+// accumulators in after every group, 96 terms: by then a sum of terms of one sign or of equal
+// ones has lost little (a column of one value, 20011 rows at k = 50: 6.9e-8 of the float64
+// result, 3.7e-7 with 480 terms; misaligned A, which ran on the fp32 instruction before, is
+// as close as there), for 1 % of the time.  No sum across waves is needed, and each wave stores its own 64 x 64 result: register v of tile (t, q) is factor
 // 32 t + row(v), column 2 jj + q, so (q = 0, q = 1) pair up to 8-byte stores, 256
 // contiguous bytes per row.  Loads of A run two steps ahead of the arithmetic (three register
 // stages), held there by scheduling barriers.  Measured in the iteration on 32768 x 16384:
@@ -785,7 +788,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
 #pragma unroll
         for (int e = 0; e < 3; ++e) pst[buf][(3 * part + e) * 256 + tid] = p.u[e];
     };
-    auto compute = [&](const Stage &c, int buf, int st) {
+    auto compute = [&](const Stage &c, int buf, int st) {     // step 0 of a group starts the accumulators
         u32x4 wt[2][3];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -801,19 +804,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
 #pragma unroll
             for (int e = 0; e < 6; ++e)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t][q] = mfma_bf16(wt[t][PW[e]], at[PA[e]], acc[t][q]);
+                for (int t = 0; t < 2; ++t)
+                    acc[t][q] = mfma_bf16(wt[t][PW[e]], at[PA[e]], st == 0 && e == 0 ? f32x16{0} : acc[t][q]);
         }
-    };
-    auto flush = [&]() {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    tot[t][q][v] += acc[t][q][v];
-                    acc[t][q][v] = 0.f;
-                }
     };
     Stage s0, s1, s2;
     Third th;
@@ -826,12 +819,8 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
         store_third(th, 0, part);
     }
     __syncthreads();
-    int buf = 0, groups = 0;
+    int buf = 0;
     for (int64_t i = r0; i < r1; i += 16 * kSteps) {
-        if (++groups > kFlushSteps / kSteps) {
-            flush();
-            groups = 1;
-        }
 #pragma unroll
         for (int part = 0; part < 3; ++part) {
             const int64_t ib = i + 32 * part;
@@ -849,10 +838,13 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
             __builtin_amdgcn_sched_barrier(0);
             store_third(th, buf ^ 1, part);
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) tot[t][q] += acc[t][q];
         __syncthreads();    // the next group's planes are written, this group's are read
         buf ^= 1;
     }
-    flush();
 
     if (colr < n) {
         float *dst = ppart + (int64_t)by * k * n + colr;

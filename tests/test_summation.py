@@ -26,3 +26,40 @@ def test_one_iteration_of_long_factors(m, n, k):
     assert orc.rel_fro(Hd.cpu().numpy(), Hr) < 2.0 ** -23
     # W adds the same for its own update, with the error of H in common
     assert orc.rel_fro(Wd.cpu().numpy(), Wr) < 1.5 * 2.0 ** -23
+
+
+# a column of one value: every product has the same low bits, and an accumulator that takes in too many of them loses
+# the same share of each
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(4000, 516, 50), (4000, 4004, 64), (20011, 9996, 50)])
+def test_products_with_columns_of_one_value(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(m + n + k)
+    A = np.broadcast_to(r.random((1, n), dtype=np.float32), (m, n)).copy()
+    W = r.random((m, k), dtype=np.float32)
+    P = torch.empty((k, n), device="cuda")
+    nmf.nmf_wta_dense(torch.from_numpy(A).cuda(), m, n, k, torch.from_numpy(W).cuda(), P)
+    torch.cuda.synchronize()
+    # few row splits (16, 8, 12), whose sum adds little: the float64 result to two roundings of 2^-24, one of the result,
+    # and from the sums of up to 96 terms a loss of
+    # the size of one
+    assert orc.rel_fro(P.cpu().numpy(), W.astype(np.float64).T @ A.astype(np.float64)) < 2.0 ** -23
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(2003, 4001, 64), (4001, 2003, 64), (5001, 3001, 40)])
+def test_misaligned_matrices_at_33_to_64_factors(m, n, k):
+    """One iteration on the padded copies, whose products are summed from pieces."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(m + n + k)
+    A, W, H = r.random((m, n), dtype=np.float32), r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    nmf.nmf_mu_dense(torch.from_numpy(A).cuda(), m, n, k, Wd, Hd, 1, EPS)
+    Wr, Hr = orc.mu_dense(A, W, H, 1, float(np.float32(EPS)))
+    # with the products on the fp32 matrix instruction 7.7e-8 to 9.0e-8: one and a half roundings of 2^-24
+    assert orc.rel_fro(Hd.cpu().numpy(), Hr) < 1.5 * 2.0 ** -24
+    assert orc.rel_fro(Wd.cpu().numpy(), Wr) < 1.5 * 2.0 ** -24
