@@ -2044,12 +2044,16 @@ __global__ __launch_bounds__(256) void residual_kernel(const float *__restrict__
 // owns 64 of the columns and walks down all the rows of the split, a lane 2 consecutive
 // columns.  Once per wave its slab of H is cut into bf16 pieces (B_op: lane l holds factors
 // 8 (l / 32) .. + 7 of 16 for column l % 32), kept in registers for every row tile.  Per
-// 32-row tile a wave forms the two 32 x 32 tiles of W H with 2 x 8 instructions each from
-// pieces of the rows of W (A_op: lane l holds 8 consecutive factors of row l % 32) that the
-// workgroup makes once for its four waves (wave w cuts tile w of every group of
-// four tiles into LDS, double buffered, one barrier per group), and subtracts them from the
+// 32-row tile a wave forms the two 32 x 32 tiles of A - W H with 6 instructions per 16 factors
+// each from pieces of the rows of -W (A_op: lane l holds 8 consecutive factors of row l % 32) that
+// the workgroup makes once for its four waves (wave w cuts tile w of every group of
+// four tiles into LDS, double buffered, one barrier per group), and the
 // tile of A, loaded in the accumulator layout (lane l, register v: row (v % 4) + 4 (l / 32) +
 // 8 (v / 4), its 2 columns: 8-byte loads, 1 KiB contiguous per row over the workgroup).  The
+// accumulators start as A and take the largest products first, so that near a good fit they are
+// small when the small products come and lose little of them: with W H summed up and subtracted
+// afterwards the objective of a fit to 1e-4 was 1.4e-5 (k = 32) to 2.6e-5 (k = 16) too large, now
+// 6e-7, as at other ranks (residual_stream_f32_kernel: 4e-7 to 1.2e-6), in the same time.  The
 // next tile of A is requested before the current tile's arithmetic, the rows of W two groups
 // ahead.  One double per workgroup.  On the 32768 x 16384, k = 32 case the kernel takes
 // 0.37 ms on random operands and 0.31 ms, the time of its loads alone, on all-zero ones:
@@ -2134,12 +2138,12 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
                 cut2(wv[s][pr >> 1][(2 * pr) & 3], wv[s][pr >> 1][(2 * pr + 1) & 3], wp, pr);
             }
 #pragma unroll
-            for (int pc = 0; pc < 3; ++pc) wlds[buf][w][s * 3 + pc][lane] = wp[pc];
+            for (int pc = 0; pc < 3; ++pc) wlds[buf][w][s * 3 + pc][lane] = wp[pc] ^ 0x80008000u;
         }
     };
-    // one tile, its A already requested: pieces of W from LDS, products, differences.  The two
-    // 32-column halves are two chains of 8 KSTEPS instructions one after the other, so the
-    // differences of the first half can issue under the products of the second.
+    // one tile, its A already requested: pieces of -W from LDS, products, squares.  The two
+    // 32-column halves are two chains of 6 KSTEPS instructions one after the other, so the
+    // squares of the first half can issue under the products of the second.
     auto tile = [&](const ATile &a, int buf, int t, bool valid) {
         u32x4 wp[KSTEPS][3];
 #pragma unroll
@@ -2147,9 +2151,9 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
 #pragma unroll
             for (int pc = 0; pc < 3; ++pc) wp[s][pc] = wlds[buf][t][s * 3 + pc][lane];
         f32x16 acc[2];
-        acc[0] = f32x16{0};
-        acc[1] = f32x16{0};
-        constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PH[6] = {0, 1, 2, 0, 1, 0};   // smallest first
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][v] = a[v].x, acc[1][v] = a[v].y;
+        constexpr int PW[6] = {0, 0, 1, 1, 0, 2}, PH[6] = {0, 1, 0, 1, 2, 0};   // largest first
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -2159,9 +2163,8 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
         float local = 0.f;      // 32 terms per lane in fp32, double across tiles
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const float d0 = a[v].x - acc[0][v], d1 = a[v].y - acc[1][v];
-            local += d0 * d0;
-            local += d1 * d1;
+            local += acc[0][v] * acc[0][v];
+            local += acc[1][v] * acc[1][v];
         }
         total += valid ? (double)local : 0.0;
     };
@@ -2202,8 +2205,8 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
 
 // ---------------------------------------------------------------------------
 // The objective as a streaming pass for any k <= 2 KS <= 64, 16-byte aligned A and H and
-// n % 4 == 0, with the fp32 matrix instruction (at a few factors the roundings of the pieces'
-// running sums would show near a good fit; here the sums are those of residual_kernel).  The
+// n % 4 == 0, with the fp32 matrix instruction, which takes two factors per step instead of 16 and
+// the floats as they are: no rank is rounded up to 16, and the sums are those of residual_kernel.  The
 // geometry of residual_stream_kernel: a wave owns 64 columns and walks down the rows of a split, a
 // lane 2 consecutive columns; its slab of H stays in registers, the rows of W go through LDS four
 // 32-row tiles at a time, and the next tile of A is requested before the current one's arithmetic.

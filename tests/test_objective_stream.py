@@ -22,3 +22,23 @@ def test_objective_of_streamed_sizes(m, n, k, noise):
     # A - W H: at most 64 roundings of 2^-24 each per product of one sign, against a difference of noise / 2
     # on average: relative error of the norm below 64 2^-24 / noise
     assert abs(got - want) <= 64 * 2.0 ** -24 / noise * want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n", [(2017, 8200), (1000, 512)])
+@pytest.mark.parametrize("k", [15, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("noise", [1e-3, 1e-4])
+def test_objective_near_a_good_fit(m, n, k, noise):
+    """The same accuracy at every rank, whichever kernel serves it (16 and 32 have one of their own)."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(m + n + k)
+    W, H = r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+    A = (W.astype(np.float64) @ H * (1 + noise * r.random((m, n)))).astype(np.float32)
+    got = nmf.nmf_residual_dense(torch.from_numpy(A).cuda(), m, n, k, torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda())
+    want = orc.residual_dense(A, W, H)
+    # A - W H = W H u, u uniform in [0, noise): where W H is off by a mean share of e, the norm is off by
+    # e E[u] / E[u^2] = 1.5 e / noise.  Roundings to nearest of 2^-24 leave a mean far below one of them; 2^-8 of
+    # one is allowed
+    assert abs(got - want) <= 1.5 * 2.0 ** -32 / noise * want
