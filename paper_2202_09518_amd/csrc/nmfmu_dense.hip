@@ -2479,6 +2479,12 @@ int wta_splits(int64_t rows, int64_t n, int k)
     // workgroups took 252 us; 40 x 12, and the planes staged in LDS, 162).
     const int64_t target = 512;
     int64_t s = target / slabs;
+    // With one split on fewer than 384 slabs (three quarters of the places) the chip is better served by two rounds of
+    // half as long workgroups: pass and finisher, 1 -> 2 splits, k = 32 on 16384 rows: 258 slabs 577 -> 529 us, 300 540
+    // -> 507, 400 634 -> 639, 500 690 -> 711; k = 64 on 8192 rows: 258 672 -> 606, 300 728 -> 644, 400 867 -> 844,
+    // but 252 -> 259 per iteration at k = 40 on 2048 rows (A^T of 102400 x 2048).
+    // (Two splits against three on 172 and 200 slabs: 302 and 317 us against 329 and 356.)
+    if (s == 1 && slabs < 384) s = 2;
     int64_t max_by_rows = (rows + 255) / 256;         // at least 256 rows per split ...
     if (slabs * max_by_rows < 128) {
         // ... unless that leaves most of the chip idle: small matrices are split down to one
