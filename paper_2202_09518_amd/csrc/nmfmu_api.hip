@@ -486,12 +486,12 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         // in between adds them up on the side (its first workgroups): no launch of its own.
         for (int it = 0; it < iters; ++it) {
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            NMF_HIP(launch_wta_pass(A, ma, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, c.gwp, nbw, c.gws));
+            NMF_HIP(launch_wta_pass(A, ma, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, c.gwp, nbw, c.gws, true));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             NMF_HIP(launch_factor_update(H, p.Ht, p.ppart, s1, nullptr, c.gws, 1, c.ghp, k, n, eps, st, map, p.planes));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            NMF_HIP(launch_wta_pass(p.At, n, m, k, p.Ht, p.planes, true, p.ppart, s2, rps2, false, st, c.ghp, nbh, c.ghs));
+            NMF_HIP(launch_wta_pass(p.At, n, m, k, p.Ht, p.planes, true, p.ppart, s2, rps2, false, st, c.ghp, nbh, c.ghs, true));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             const bool report = mon && (!mon->last_only || it == iters - 1);
             NMF_HIP(launch_factor_update(p.Wt, W, p.ppart, s2, nullptr, c.ghs, 1, c.gwp, k, m, eps, st, map, p.planes,
@@ -1037,11 +1037,11 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
             for (int r = 0; r < reps && e == hipSuccess; ++r)
                 e = one_pass ? launch_one_pass(A, m, n, k, p.planes2, nullptr, c.ghp, factor_update_blocks(n), W, nullptr, p.ppart,
                                                c.gwp, eps, st, which == 1, which == 0)
-                    : which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st)
+                    : which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, nullptr, 0, nullptr, mirrored)
                     : rows_plan  // the fused pass without its stores to W
                         ? launch_aht_rows(A, m, n, k, p.planes2, c.gh, W, p.planes, c.gwp, eps, st, false, nullptr,
                                           nullptr, true)
-                        : launch_wta_pass(p.At, n, m, k, p.Ht, p.planes, true, p.ppart, s2, rps2, false, st);
+                        : launch_wta_pass(p.At, n, m, k, p.Ht, p.planes, true, p.ppart, s2, rps2, false, st, nullptr, 0, nullptr, true);
             if (e == hipSuccess) e = hipEventRecord(ev[1], st);
             if (e == hipSuccess) e = hipEventSynchronize(ev[1]);
             float ms = 0.f;

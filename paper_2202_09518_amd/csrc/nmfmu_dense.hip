@@ -2463,8 +2463,13 @@ static inline bool vec_ok(const void *p, int64_t ld)
 
 // A that the last-level cache (256 MiB) keeps from one pass to the next is loaded to stay there, not
 // marked for eviction: 12288 x 4096, k = 20 (192 MiB): A H^T pass 39.4 -> 34.2 us, W^T A 38.2 -> 36.0;
-// 2000 x 1204, k = 12: 13.7 -> 11.7 and 8.3 -> 8.0.
-static bool stream_a(int64_t rows, int64_t n) { return rows * n * 4 > ((int64_t)224 << 20); }
+// 2000 x 1204, k = 12: 13.7 -> 11.7 and 8.3 -> 8.0.  A run that reads A and A^T in turn has two matrices to
+// keep; per iteration there, marked against kept: 2 x 120 MiB, k = 40 102 and 97 us, 2 x 144 110 and 110 (k = 20 83 and
+// 81), 2 x 160, k = 64 124 and 128, 2 x 192, k = 40 132 and 137, 2 x 220, k = 64 147 and 155.
+static bool stream_a(int64_t rows, int64_t n, bool two = false)
+{
+    return rows * n * 4 > ((int64_t)(two ? 152 : 224) << 20);
+}
 
 int wta_splits(int64_t rows, int64_t n, int k)
 {
@@ -2641,7 +2646,7 @@ hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, 
 
 hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const float *W,
                            void *planes, bool planes_ready, float *ppart, int splits, int64_t rps,
-                           bool accumulate, hipStream_t st, const float *gtiles, int nsets, float *gsum)
+                           bool accumulate, hipStream_t st, const float *gtiles, int nsets, float *gsum, bool two)
 {
     dim3 grid((unsigned)((n + kWtaCols - 1) / kWtaCols), (unsigned)splits);
     const bool vec = vec_ok(A, n);
@@ -2658,7 +2663,7 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
         const dim3 block(64 * kWtaWaves);
         // buffer loads address 16 rows with 32-bit offsets: 64 n bytes must stay below 2^31
         if (vec && n < ((int64_t)1 << 25))
-            if (stream_a(rows, n)) hipLaunchKernelGGL(wta_pass_split_buf_kernel<kStreamLoad>, grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
+            if (stream_a(rows, n, two)) hipLaunchKernelGGL(wta_pass_split_buf_kernel<kStreamLoad>, grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
             else hipLaunchKernelGGL(wta_pass_split_buf_kernel<0>, grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
         else
             hipLaunchKernelGGL((wta_pass_split_kernel<false>), grid, block, 0, st, A, pl, ppart, rows, n, k, rps, acc, gtiles, nsets, gsum);
@@ -2671,7 +2676,7 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
                 if (e != hipSuccess) return e;
             }
             const dim3 grid256((unsigned)((n + 255) / 256), (unsigned)splits);
-            if (stream_a(rows, n))
+            if (stream_a(rows, n, two))
                 hipLaunchKernelGGL((wta_pass_split64_wide_kernel<false, kStreamLoad>), grid256, dim3(64 * kWtaWaves), 0, st, A,
                                    static_cast<const u32x4 *>(planes), ppart, rows, n, k, rps, acc, gtiles, nsets, gsum,
                                    0, 0, 1, (int64_t)0, (int64_t)0);

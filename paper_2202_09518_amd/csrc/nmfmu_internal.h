@@ -62,7 +62,8 @@ hipError_t launch_split_planes_slice(const float *X, int64_t rows, int64_t ld, i
 hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const float *W,
                            void *planes, bool planes_ready, float *ppart, int splits,
                            int64_t rows_per_split, bool accumulate, hipStream_t st,
-                           const float *gtiles = nullptr, int nsets = 0, float *gsum = nullptr);
+                           const float *gtiles = nullptr, int nsets = 0, float *gsum = nullptr, bool two = false);
+// two: A is read in turn with its transpose (what the last-level cache would have to keep).
 // gtiles (optional): nsets sets of partial Gram tiles for rank k that the first workgroups of
 // the pass add up into gsum (one set).
 // Ranks above 64, all ceil(k / 64) slices of 64 factors in one launch each: planes of every slice of X
