@@ -238,26 +238,35 @@ int dense_workspace(const float *A, int64_t m, int64_t n, int k, void **ws, bool
     return ensure_workspace(small, ws);
 }
 
-bool have_workspace(size_t need)
+// Workspace for a plan that a smaller one can stand in for: whether it is there or can be had.  Under capture of
+// `st` nothing is grown (that synchronises, which would end the capture), and the block that is held is not given
+// up for one that the device has no room for (the calls that follow would free and allocate it every time).
+bool have_workspace(size_t need, hipStream_t st)
 {
+    if (g.ws && g.ws_bytes >= need) return true;
+    if (!g.ws_owned) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    size_t left = 0, total = 0;
     void *ws = nullptr;
-    if ((g.ws && g.ws_bytes >= need) || (g.ws_owned && ensure_workspace(need, &ws) == NMF_OK)) return true;
-    (void)hipGetLastError();
-    return false;
+    const bool can = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+                     hipMemGetInfo(&left, &total) == hipSuccess && need <= left + g.ws_bytes &&
+                     ensure_workspace(need, &ws) == NMF_OK;
+    if (!can) (void)hipGetLastError();
+    return can;
 }
 
 // The plan of a dense run with `extra` bytes behind it (*tail): the one-pass plan where it applies,
 // else the row or the mirrored plan, else the small one; whatever the workspace can hold.
-int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, DensePlan *p, char **tail)
+int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStream_t st, DensePlan *p, char **tail)
 {
     void *ws = nullptr;
     size_t bytes = one_pass_bytes(m, n, k);
-    if (one_pass_ok(A, n, k) && have_workspace(bytes + extra)) {
+    if (one_pass_ok(A, n, k) && have_workspace(bytes + extra, st)) {
         *p = carve_one_pass(g.ws, m, n, k);
     } else {
         bool mirrored = false;
         bytes = dense_bytes(m, n, k, true);
-        if (!rows_plan_first(A, m, n, k) && have_workspace(bytes + extra)) {
+        if (!rows_plan_first(A, m, n, k) && have_workspace(bytes + extra, st)) {
             mirrored = true;
         } else {
             bytes = dense_bytes(m, n, k, false);
@@ -311,12 +320,12 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
         if (one || rows) {
             if (copy_a) {
                 base = one_pass_bytes(m, n4, k);
-                if (one && have_workspace(base + copies + extra)) {
+                if (one && have_workspace(base + copies + extra, st)) {
                     r->p = carve_one_pass(g.ws, m, n4, k);
                     padded = true;
                 } else if (rows) {
                     base = dense_bytes(m, n4, k, false);
-                    if ((padded = have_workspace(base + copies + extra))) r->p = carve_dense(g.ws, m, n4, k, false);
+                    if ((padded = have_workspace(base + copies + extra, st))) r->p = carve_dense(g.ws, m, n4, k, false);
                 }
             }
         } else {
@@ -325,19 +334,19 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
             pad_w = m != m4;
             base = dense_bytes(m4, n4, k, true);
             const size_t wcopy = pad_w ? align_up((size_t)m4 * k * sizeof(float)) : 0;
-            if ((iters > 1 || !copy_a || !can_rows) && (padded = have_workspace(base + copies + wcopy + extra))) {
+            if ((iters > 1 || !copy_a || !can_rows) && (padded = have_workspace(base + copies + wcopy + extra, st))) {
                 r->p = carve_dense(g.ws, m4, n4, k, true);
                 r->p.a_rows = m;
                 r->m = m4;
             } else {
                 pad_w = false;
                 base = dense_bytes(m, n4, k, false);
-                if (copy_a && can_rows && (padded = have_workspace(base + copies + extra)))
+                if (copy_a && can_rows && (padded = have_workspace(base + copies + extra, st)))
                     r->p = carve_dense(g.ws, m, n4, k, false);
             }
         }
     }
-    if (!padded) return dense_plan(A, m, n, k, extra, &r->p, &r->tail);
+    if (!padded) return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
     Carve cv(static_cast<char *>(g.ws) + base);
     if (copy_a) {
         float *Ap = cv.take<float>((size_t)m * n4);
@@ -996,7 +1005,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
     DensePlan p;
-    if (int rc = dense_plan(A, m, n, k, 0, &p, nullptr)) return rc;
+    if (int rc = dense_plan(A, m, n, k, 0, st, &p, nullptr)) return rc;
     const bool mirrored = p.mirrored, one_pass = p.one_pass;
     constexpr int NK = kDenseKernels;
     std::vector<hipEvent_t> ev((size_t)iters * NK + 1, nullptr);
@@ -1097,9 +1106,7 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
     auto note_at = [&](const DensePlan &p, const float *a, int rank) {
         if (p.mirrored && !takes_row_plan(p, a, m, n, rank)) at_of = a;
     };
-    const bool can_stack = (g.ws && g.ws_bytes >= big) || (g.ws_owned && ensure_workspace(big, &ws) == NMF_OK);
-    if (!can_stack) {
-        (void)hipGetLastError();
+    if (!have_workspace(big, st)) {
         bool mirrored = false;
         if (int rc = dense_workspace(nullptr, m, n, kmax, &ws, &mirrored)) return rc;
         const DensePlan p1 = carve_dense(ws, m, n, kmax, mirrored);
@@ -1371,7 +1378,7 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     const int ldk = csr_row_length(k);
     const size_t wide = align_up((size_t)m * ldk * sizeof(float)) + align_up((size_t)n * ldk * sizeof(float));
     const bool copies = ldk != k && (iters > 1 || tolp) && (int64_t)(m > n ? m : n) * k * 4 > ((int64_t)8 << 20) &&
-                        have_workspace(need + wide);
+                        have_workspace(need + wide, st);
     if (!copies)
         if (int rc = ensure_workspace(need, &ws)) return rc;
     ws = g.ws;
