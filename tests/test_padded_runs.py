@@ -52,7 +52,7 @@ def test_padded_runs(m, n, offset, k, iters):
     # the exact one: roundings of the reconstruction, below 2^-22 of an entry, which is all there is where one
     # row is fitted exactly
     normA2 = float((A.astype(np.float64) ** 2).sum())
-    assert abs(got[-1] - want) <= max(1e-5 * want, 3e-7 * normA2 / want)
+    assert abs(got[-1] ** 2 - want ** 2) <= max(2e-5 * want ** 2, 6e-7 * normA2)
     assert abs(last - want) <= max(1e-5 * want, 2.0 ** -22 * normA2 ** 0.5)
 
 

@@ -1,8 +1,9 @@
 """The cut of the streamed operand: three bf16 pieces by rounding to nearest even, six products per term.
 
-The claims are checked on the CPU with exact rationals (the pieces are produced here with integer
-arithmetic); the GPU test drives the passes at the edges of the cut (values that would round to
-infinity, one repeated value, exact powers of two, zeros)."""
+The CPU tests check the arithmetic that the kernels rely on, with exact rationals on pieces produced here with
+integer arithmetic; they say nothing about the kernels' own cut.  That is what the GPU tests are for: the passes
+at the edges of the cut (values that would round to infinity, one repeated value, exact powers of two, zeros), and
+on single products, where a wrong piece shows."""
 from fractions import Fraction
 
 import numpy as np
@@ -101,3 +102,23 @@ def test_wta_at_the_edges_of_the_cut(k, n, kind):
     got = P.cpu().numpy().astype(np.float64)
     # left-out products 2^-22 of a term at most, sums of 200 terms of one sign in fp32: 200 * 2^-24 at most
     assert np.abs(got - want).max() <= (2.0 ** -22 + 200 * 2.0 ** -24) * np.abs(want).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", [32, 64])
+def test_single_products_hold_to_the_products_left_out(k):
+    """One row: every element of W^T A is one product, whose pieces cannot make up for one another."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    n = 1024
+    r = np.random.default_rng(k)
+    A = (r.random((1, n), dtype=np.float32) * np.float32(2.0) ** r.integers(-30, 30, (1, n))).astype(np.float32)
+    W = (r.random((1, k), dtype=np.float32) * np.float32(2.0) ** r.integers(-30, 30, (1, k))).astype(np.float32)
+    P = torch.empty((k, n), device="cuda")
+    nmf.nmf_wta_dense(torch.from_numpy(A).cuda(), 1, n, k, torch.from_numpy(W).cuda(), P)
+    torch.cuda.synchronize()
+    want = W.astype(np.float64).T * A.astype(np.float64)
+    # 2^-22 of the product left out, and the six that are added in fp32, smallest first: a loss of 2^-23 of the sum at
+    # most for each of the last three, the others are below 2^-7 of it
+    assert (np.abs(P.cpu().numpy() - want) <= (2.0 ** -22 + 4 * 2.0 ** -23) * want).all()

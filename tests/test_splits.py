@@ -22,3 +22,25 @@ def test_splits_of_wide_matrices(k, width):
                 assert s == 2
             if slabs >= 128:
                 assert splits(256, n, k) == 1       # at least 256 rows per split
+
+
+# 258 slabs and two splits at both widths; A and A^T just above and below what the cache is taken to hold of two
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(600, 33024, 32), (600, 66048, 64), (9732, 4096, 33), (9724, 4096, 20)])
+def test_one_iteration_at_the_lines(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    A, W, H = (torch.rand(s, generator=g, device="cuda") for s in ((m, n), (m, k), (k, n)))
+    Wd, Hd = W.clone(), H.clone()
+    nmf.nmf_mu_dense(A, m, n, k, Wd, Hd, 1, 1e-16)
+    A, W, H = A.double(), W.double(), H.double()
+    Wt = W.t().contiguous()
+    H = H * (Wt @ A) / ((Wt @ W) @ H + 1e-16)
+    Ht = H.t().contiguous()
+    W = W * (A @ Ht) / (W @ (H @ Ht) + 1e-16)
+    # numerator, denominator, product and quotient, a rounding of 2^-24 each, for H and again for W
+    assert ((Hd - H).norm() / H.norm()).item() < 2.0 ** -22
+    assert ((Wd - W).norm() / W.norm()).item() < 2.0 ** -22
