@@ -11,20 +11,23 @@
  * eps is added once, to the finished denominator.  Operands and results are
  * IEEE single precision.  For k <= NMF_MU_MAX_K and 16-byte aligned A the two
  * products over A are formed on the bf16 matrix cores from exact pieces: every
- * float is cut into three bf16 values that add up to it bit for bit, the six
- * leading piece products of a term are accumulated in fp32 (each is exact there;
- * the three left out are below 2^-22 of the term together and of either sign, so
- * they cancel over a sum), and
- * no matrix accumulator runs over more than 512 terms before it is added, in
- * rounded fp32, to a running total; long sums stay within 3e-7 relative of the
- * float64 result.  Unaligned A and the Gram matrices use the fp32 matrix
+ * float is cut into three bf16 values that add up to it bit for bit, and the six
+ * leading piece products of a term are accumulated in fp32.  The three left out
+ * are below 2^-22 of the term together, which is what the matrix cores' sums
+ * drop of a term anyway.  No matrix accumulator runs over more than 512 terms
+ * (96 for k > 32) before it is added, in rounded fp32, to a running total.
+ * Against float64, root mean square over the result: 5e-8 to 1.8e-7 of sums over
+ * 2000 to 65536 terms, whether A varies or repeats one value down a column; where
+ * A and a factor hold one value each throughout, all terms lose the same bits
+ * and a sum can be 2e-6 off.  The Gram matrices, the small plan's A H^T, and W^T A
+ * for k > 32 on a misaligned A that is used as it is take the fp32 matrix
  * instruction (fp32 operands, fp32 accumulation).
  *
  * Conventions shared by every entry point
  *   - All matrices are row-major and contiguous: A is m x n (leading dimension
  *     n), W is m x k (ld k), H is k x n (ld n).  Base pointers must be 4-byte
- *     aligned; the fast paths need 16-byte aligned A and H and n % 4 == 0,
- *     anything else takes a slower, equally correct path.
+ *     aligned; the fast kernels need 16-byte aligned A and H and n % 4 == 0,
+ *     anything else is copied once per call or takes slower, equally correct ones.
  *   - "device" pointers are HIP device memory of the current device; "host"
  *     pointers are host memory.  The caller owns every buffer; the library
  *     keeps no reference to them after the call's work has finished.
@@ -84,21 +87,28 @@ const char *nmf_last_error(void);
  *   A      device, m x n, read-only
  *   W, H   device, in/out
  *   iters  >= 0;  eps >= 0 and finite
- * Asynchronous on `stream`.  Three plans, chosen per call; they give the same
- * iteration and differ in low-order bits.  Row plan (16-byte aligned A,
+ * Asynchronous on `stream`.  Four plans, chosen per call; they give the same
+ * iteration and differ in low-order bits.  One-pass plan (k <= 32, 16-byte aligned
+ * A, n % 4 == 0, n <= 512): both products of an iteration in one reading of A;
+ * workspace kind 4 plus 1024 k n bytes at most.  Row plan (16-byte aligned A,
  * n % 4 == 0, n < 2^24, and m >= 12288 with n >= 512, or m n <= 2^22): both products stream
  * the row-major A, the W update is fused into the A H^T pass; workspace kind 4.
- * It comes first for k <= 32.  Mirrored plan (33 <= k <= 64, and shapes the
+ * It comes next for k <= 32.  Mirrored plan (33 <= k <= 64, and shapes the
  * row plan does not serve, if the workspace can hold a second copy of A): A is
  * transposed once per call and A^T is streamed for the A H^T product;
  * workspace kind 0.  Without room for that copy: the row plan for
  * 33 <= k <= 64 where it applies (its A H^T pass is about a fifth slower than
  * the mirrored one), else the small plan, a direct A H^T kernel on A (lanes
- * down the rows: slower); workspace kind 4.  An A whose base is not 16-byte
- * aligned or whose n is not a multiple of 4 is copied once per call, with H,
- * into aligned arrays of n rounded up to 4 columns (zero columns change no
- * result) when the workspace can hold them (about the size of kind 0) and eps
- * is a normal positive float, and the row plan runs on the copies.
+ * down the rows: slower); workspace kind 4.
+ * An A whose base is not 16-byte aligned or whose n is not a multiple of 4 is
+ * copied once per call, with H, into aligned arrays of n4 = n rounded up to 4
+ * columns, and the plan for m x n4 runs on the copies; the mirrored plan, whose A^T
+ * has the rows of A as columns, also takes m4 = m rounded up to 4 rows and a copy
+ * of W (zero rows and columns change no result).  This needs eps to be a normal
+ * positive float and the workspace of that plan for m4 x n4 plus 4 (m n4 + k n4 +
+ * m4 k) + 768 bytes, so the mirrored plan then holds A twice; a workspace that is
+ * too small, or a stream under capture while the library's own is, leaves A
+ * as it is and takes the slower kernels.
  * Ranks NMF_MU_MAX_K < k <= NMF_MU_MAX_K_SLICED run the same iteration with every
  * product written as F^T X (a reduction over the rows of two row-major
  * matrices) and computed 64 factor columns of F at a time by the k <= 64 pass
@@ -113,8 +123,9 @@ int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k,
 /*
  * nmf_mu_dense for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments and result as nmf_mu_dense on its small plan (the direct A H^T
- * kernel; no transposed copy of A), k <= NMF_MU_MAX_K.  The scratch memory
+ * arguments and result as nmf_mu_dense on its plans without copies of A (the
+ * one-pass plan where it applies and fits, else the row plan, else the small
+ * plan), k <= NMF_MU_MAX_K.  The scratch memory
  * (row-split partial sums, operand planes of W, Gram scratch) is a fixed array
  * of NMF_MU_NOALLOC_SCRATCH_BYTES in the library's device image instead of
  * allocated memory; every device the library runs on holds one copy until the
@@ -145,7 +156,7 @@ int nmf_residual_dense(const float *A, int64_t m, int64_t n, int32_t k,
  * Algorithm 1 with its stopping rule read as: iterate until ||A - W H||_F <= tol
  * or max_iters iterations have run.  The objective is evaluated before the first
  * iteration and then after every `check_every` iterations (each evaluation is
- * one more pass over A and a stream synchronisation; with the fast plan the
+ * one more pass over A and a stream synchronisation; with all but the small plan the
  * checks after iterations first use the expansion of nmf_mu_dense_monitor, which
  * costs no pass, and fall back to the exact evaluation only when that value is
  * within its error bound of tol, so the stopping decision is the exact one).  On return
@@ -164,8 +175,8 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
  * Gram matrices); ||A||^2 is computed once per call.  The products are fp32
  * sums, so the value carries an absolute error of about 2e-7 ||A||^2 / f: exact
  * to 1e-4 relative while f >= 0.05 ||A||, a few percent at f = 0.005 ||A||;
- * nmf_residual_dense gives the exact value (one more pass over A).  When the
- * fast plan's workspace cannot be had, every value is the exact tiled one.
+ * nmf_residual_dense gives the exact value (one more pass over A).  On the
+ * small plan every value is the exact tiled one.
  * objective_host: HOST memory, iters doubles.  Blocking.  W, H as nmf_mu_dense
  * (bit-identical result).
  */
@@ -185,7 +196,11 @@ int nmf_mu_dense_monitor(const float *A, int64_t m, int64_t n, int32_t k, float 
  * of a factor per stored entry, without atomics, so results are reproducible
  * from run to run.  Needs nnz < 2^31 and m < 2^31.  The build is a stable sort
  * by column on `stream` whose scratch (about 24 bytes per stored entry) is part
- * of the workspace; the whole call only enqueues work and returns.  The
+ * of the workspace; the whole call only enqueues work and returns.  A run of
+ * several iterations whose larger factor exceeds 8 MiB works on copies of the factors
+ * with rows of L = 4, 8, 16, 32, 48 or 64 floats, the next from k on (a gathered row
+ * then lies in as few cache lines as it can), if k is none of these and the
+ * workspace holds 4 L (m + n) + 512 bytes more than kind 1.  The
  * structure is not validated (that would need the device's answer): entry
  * ranges and column indices are clamped to the arrays' bounds where they are
  * used, so malformed row pointers or indices give a meaningless result but no
@@ -339,10 +354,13 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
  * the partial sums), 4 dense (row plan and small plan: partial sums and operand
  * planes only), 1 csr (includes the scratch of the one-time sort, about 24 bytes
  * per stored entry), 2 ooc (excluding the
- * staging slots), 3 batched (enough for any mix of ranks; k is only checked),
+ * staging slots), 3 batched (enough for any mix of ranks; k is only checked; no
+ * padded copies are made there),
  * 5 dense with k > NMF_MU_MAX_K (rank-sliced), 6 the rank-sliced out-of-memory
  * pipeline (nmf_mu_ooc_hostw, and nmf_mu_ooc above NMF_MU_MAX_K; excluding the
- * staging slots).  0 on invalid arguments.
+ * staging slots).  What the one-pass plan, the copies of a misaligned A and the
+ * sparse copies take beyond these is stated at nmf_mu_dense and nmf_mu_csr; it is
+ * used when it is there.  0 on invalid arguments.
  */
 size_t nmf_mu_workspace_bytes(int kind, int64_t m, int64_t n, int64_t nnz,
                               int32_t k, int64_t batch_rows);

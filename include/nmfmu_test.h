@@ -15,7 +15,8 @@ extern "C" {
 #endif
 
 /*
- * nmf_mu_dense with timing: the same launches on `stream`, with a HIP event
+ * nmf_mu_dense with timing, on A as it is (no copy of a misaligned A is made, so such
+ * an A takes the slower kernels here): the same launches on `stream`, with a HIP event
  * recorded between them; synchronises `stream` before returning.  On return
  * kernel_ms[0..5] (HOST memory, 9 floats) hold the average milliseconds per
  * launch of the kernels of one iteration, in launch order:
