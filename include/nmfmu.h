@@ -14,12 +14,12 @@
  * float is cut into three bf16 values that add up to it bit for bit, and the six
  * leading piece products of a term are accumulated in fp32.  The three left out
  * are below 2^-22 of the term together, which is what the matrix cores' sums
- * drop of a term anyway.  No matrix accumulator runs over more than 512 terms
- * (96 for k > 32) before it is added, in rounded fp32, to a running total.
- * Against float64, root mean square over the result: 5e-8 to 1.8e-7 of sums over
- * 2000 to 65536 terms, whether A varies or repeats one value down a column; where
- * A and a factor hold one value each throughout, all terms lose the same bits
- * and a sum can be 2e-6 off.  The Gram matrices, the small plan's A H^T, and W^T A
+ * drop of a term anyway.  No matrix accumulator runs over more than 256 terms
+ * before it is added, in rounded fp32, to a running total.  Against float64, root
+ * mean square over the result: 5e-8 to 1.6e-7 of sums over 1000 to 500000
+ * terms, 2e-7 where A repeats one value down a column or along a row; where A and
+ * a factor hold one value each throughout, all terms lose the same bits and a sum
+ * can be 2e-6 off.  The Gram matrices, the small plan's A H^T, and W^T A
  * for k > 32 on a misaligned A that is used as it is take the fp32 matrix
  * instruction (fp32 operands, fp32 accumulation).
  *

@@ -85,15 +85,15 @@ __device__ __forceinline__ unsigned pack2(unsigned even, unsigned odd)
 // likewise, l = the rest; again exact, |m| <= 2^-8 |x|, |l| <= 2^-16 |x| and m, l have either
 // sign.  Against a truncated operand (W or H from the planes: pieces of one sign, m < 2^-7,
 // l < 2^-15 of the float) the passes issue SIX products, h h, h m, m h, m m, h l, l h: the three
-// left out are below 2^-23 (twice) and 2^-31 of the term and signed like A's lower pieces, so
-// over a sum they cancel instead of adding up.  Measured against 64 bits (W^T A and A H^T on
-// uniform, planted, exponential and 30-decade data, 4096 to 65536 rows) the error is smaller than
-// with eight products of truncated pieces: 6.0e-8 against 6.7e-8 relative at 4096 rows, mean
-// signed error -2e-9 against -28e-9 (products of one sign lose their low bits in the accumulator
-// always downwards, see the running totals below; signed ones do not).  A column of one repeated
-// value is the worst case: its m and l have one sign down the column and nothing cancels (1.6e-7
-// against 1.3e-7 at 65536 rows).  A quarter less matrix work: 7 to 11 % off the passes that are
-// bound by it.
+// left out are below 2^-23 (twice) and 2^-31 of the term and signed like A's lower pieces.
+// With the first two of them added back the errors against 64 bits were the same to the second
+// digit on planted, uniform and repeated-value data (2003 x 4004 to 65536 x 1024, k = 20 to 64), and
+// where A and W hold one value each the results agreed to every digit printed: the matrix adder
+// drops bits of that size of every term that joins a grown accumulator (see the running totals
+// below).  They would cost 4 (32768 x 16384, k = 32) to 15 % (rank 256, one pass) of an iteration.
+// Against eight products of truncated pieces, which lose their low bits always downwards, the error
+// is smaller at the same lengths of accumulation: 6.0e-8 against 6.7e-8 at 4096 rows, mean signed
+// error -2e-9 against -28e-9.
 // A value above the largest bf16 (3.39e38) would round to infinity and is held at that bf16.
 __device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)
 {
@@ -135,13 +135,16 @@ __device__ __forceinline__ int acc_row(int v, int half) { return (v & 3) + 4 * h
 // width without rounding, so an accumulator that has grown over thousands of rows loses
 // the low bits of every product it takes in, always downwards: measured on uniform data
 // the sum over 2048 rows comes out 1.7e-6 low, over 4096 rows 1.1e-5, while up to 512 rows
-// the loss is below 1e-7.  The pass kernels therefore keep a matrix accumulator for at most
-// kFlushSteps 16-row steps and then add it, with ordinary rounded fp32 adds, into a total
-// that the wave keeps in its own 16 KiB of LDS (64 accumulator registers x 64 lanes; no
-// other wave touches it, so no barrier).  Slot of register r of tile q for a lane: the
+// the loss is below 1e-7.  Where A repeats one value down a column, all products of that column
+// lose the same bits: 4.0e-7 of the result with 512 rows to an accumulator (32768 x 16384, k = 32),
+// 1.8e-7 with 256.  The pass kernels therefore keep a matrix accumulator for at most kFlushSteps
+// 16-row steps (the kernels further down for as long, or for 96 rows) and then add it, with
+// ordinary rounded fp32 adds, into a total that the wave keeps in its own 16 KiB of LDS (64
+// accumulator registers x 64 lanes; no other wave touches it, so no barrier); 16 steps instead of
+// 32 cost 0.1 % of an iteration.  Slot of register r of tile q for a lane: the
 // lane index is flipped by 8 q so that the epilogue, which walks columns 4 jj + q, reads
 // 32 different banks.
-constexpr int kFlushSteps = 32;
+constexpr int kFlushSteps = 16;
 
 // Cache policy of the buffer loads that stream A: the non-temporal bit.  Every element of A is
 // used once per pass, so its lines are marked for early eviction and leave the L2 and the
@@ -656,7 +659,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
     const int64_t step = 16 * NW;
     Stage s0, s1;
     int64_t i = r0 + 16 * w;
-    int pairs = 4 * w;   // the waves of a workgroup flush at different times
+    int pairs = 2 * w;   // the waves of a workgroup flush at different times
     load_stage(s0, i);
     while (i < r1) {
         load_stage(s1, i + step);
@@ -1381,7 +1384,8 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
     if (KT == 2)
         for (int e = tid; e < 4096; e += 64 * NW) Grun[e] = 0.f;   // first read after many barriers
     double dacc = 0.0;
-    const int rounds = (int)((nchunks + 63) >> 6);   // a round = up to 8 chunks per wave
+    // a round = up to 4 chunks per wave (8: rows of one value 4.2e-7 off at 16384 columns, 4: 1.8e-7, in the same time)
+    const int rounds = (int)((nchunks + 31) >> 5);
 
     for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         const int64_t i0 = blk * RB;
@@ -1452,15 +1456,15 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
                 }
             };
             // Sub-tiles in the order (chunk, row tile); the loads of the next one are requested as soon
-            // as the current one has gone to LDS.  After every round (8 chunks = 32 products deep) the
+            // as the current one has gone to LDS.  After every round (4 chunks = 256 columns) the
             // matrix accumulators are added, in rounded fp32, to totals in LDS that the waves w and w + 4
             // share: first the lower four waves, then the upper four, a barrier after each.
             Stage s0;
             load_stage(s0, w, 0);
             float *Tp = T + (w & 3) * RT;
             for (int r = 0; r < rounds; ++r) {
-                for (int t = 0; t < 8; ++t) {
-                    const int64_t ch = w + 8 * (int64_t)(8 * r + t);
+                for (int t = 0; t < 4; ++t) {
+                    const int64_t ch = w + 8 * (int64_t)(4 * r + t);
                     if (ch >= nchunks) break;        // this wave has no more chunks (loads already requested nothing)
                     load_b(ch);
 #pragma unroll
@@ -1635,8 +1639,9 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
 //      block's rows (factor = lane % 32), for which it has formed W H H^T meanwhile; it
 //      updates them, and leaves the pieces of the new rows in LDS.
 //   3. Every wave reads its tile again, columns by lane, for W^T A.
-// Two barriers per block.  An accumulator of W^T A takes in at most kOnePassFlush blocks (512 rows)
-// before it is added, in rounded fp32, to ppart.
+// Two barriers per block.  An accumulator of W^T A takes in at most kOnePassFlush blocks (256 rows a
+// wave) before it is added, in rounded fp32, to ppart (twice as many: columns of one value 4.5e-7 off
+// instead of 1.9e-7, for 1 to 3 % less time).
 // The pieces of W never leave the chip, and A comes from memory once per iteration instead of
 // twice.  One workgroup (8 waves, 116 KiB of LDS) fills a compute unit; its chain of LDS round
 // trips, not the memory, bounds it: 314 us on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
@@ -1644,7 +1649,7 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
 // per wave (n up to 1024), with the second reading from the caches, gained 0.95 to 1.15x only,
 // three lost to the row plan (0.73 to 1.01x): hence the limit.
 // ---------------------------------------------------------------------------
-constexpr int kOnePassFlush = 16;
+constexpr int kOnePassFlush = 8;
 template <int NRW, int POLICY, bool update, bool product>
 __global__ __launch_bounds__(512, 2) void one_pass_kernel(
     const float *__restrict__ A, const u32x4 *__restrict__ planesH, const float *__restrict__ GH,

@@ -63,3 +63,28 @@ def test_misaligned_matrices_at_33_to_64_factors(m, n, k):
     # with the products on the fp32 matrix instruction 7.7e-8 to 9.0e-8: one and a half roundings of 2^-24
     assert orc.rel_fro(Hd.cpu().numpy(), Hr) < 1.5 * 2.0 ** -24
     assert orc.rel_fro(Wd.cpu().numpy(), Wr) < 1.5 * 2.0 ** -24
+
+
+# few splits and a whole chain of each pass: W^T A of the row plan, A H^T of the row plan, W^T A of the one-pass plan
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k,same", [(4096, 33024, 32, "columns"), (12288, 4096, 20, "rows"), (300000, 132, 16, "columns")])
+def test_up_to_32_factors_and_one_value_per_column_or_row(m, n, k, same):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    W, H = torch.rand((m, k), generator=g, device="cuda"), torch.rand((k, n), generator=g, device="cuda")
+    A = torch.rand((1, n) if same == "columns" else (m, 1), generator=g, device="cuda").expand(m, n).contiguous()
+    Wd, Hd = W.clone(), H.clone()
+    nmf.nmf_mu_dense(A, m, n, k, Wd, Hd, 1, EPS)
+    A, W, H = A.double(), W.double(), H.double()
+    # the factor whose long sums are over the equal values, W with the H that the library has
+    if same == "columns":
+        Wt = W.t().contiguous()
+        got, want = Hd, H * (Wt @ A) / ((Wt @ W) @ H + EPS)
+    else:
+        Ht = Hd.double().t().contiguous()
+        got, want = Wd, W * (A @ Ht) / (W @ (Hd.double() @ Ht) + EPS)
+    # four roundings of 2^-24 as above, and a loss of two more in sums of up to 256 equal terms
+    assert ((got - want).norm() / want.norm()).item() < 2.0 ** -22
