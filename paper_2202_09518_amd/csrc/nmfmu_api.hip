@@ -639,9 +639,10 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
     return NMF_OK;
 }
 
-// Upper bound on splits x 64 x cols over every X with at most `cols` columns: the split count is
-// at most 32 and at most 512 / slabs + 1 with cols <= 256 slabs (64-factor slices; 32-factor
-// slices have 128-column slabs and half the factors).
+// Upper bound on splits x 64 x cols over every X with at most `cols` rows and columns (64-factor slices;
+// 32-factor slices have 128-column slabs and half the factors).  wta_splits keeps splits x slabs <= 512 with
+// cols <= 256 slabs, or two splits on fewer than 384 slabs, or one: splits x cols <= 131072 + cols.  And more than
+// 32 splits need fewer than 16 slabs and 256 rows each: at most cols / 256 splits of 15 x 256 columns.
 size_t sliced_ppart_elems(int64_t cols)
 {
     const int64_t a = 32 * cols, b = 131072 + cols;

@@ -710,7 +710,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
 // 32 t + row(v), column 2 jj + q, so (q = 0, q = 1) pair up to 8-byte stores, 256
 // contiguous bytes per row.  Loads of A run two steps ahead of the arithmetic (three register
 // stages), held there by scheduling barriers.  Measured in the iteration on 32768 x 16384:
-// 480 -> 400 us (5.4 TB/s; its bare 8-byte loads take 338), on 16384 x 8192 131 -> 107 us.
+// 480 -> 400 us (5.4 TB/s; its bare 8-byte loads take 338), on 16384 x 8192 131 -> 110 us.
 // ---------------------------------------------------------------------------
 // Several 64-factor slices of a wider factor in one launch (SLICES; ranks above 64): a
 // one-dimensional grid whose workgroup L stands for (tile, slice) with the slices of one
@@ -897,7 +897,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
 // thread loads only its own factors' old values (the column meets in LDS), and short factors are
 // cut into narrower chunks so that more workgroups share the splits (see factor_update_width).
 // With every thread loading the whole column, batches of 2 to 4 splits and G as 16 partial sums:
-// 25 us at k = 50 on 9998 columns and 12 splits, now 17; 10.5 at k = 20 on 4096, now 6.7; 27 at
+// 25 us at k = 50 on 9998 columns and 12 splits, now 19; 10.5 at k = 20 on 4096, now 6.7; 27 at
 // k = 16 on 512 columns and 128 splits, now 10; 13 at k = 32 on 16384, now 9.6.
 // ---------------------------------------------------------------------------
 template <int KP, int CW, bool BIG>
@@ -1324,8 +1324,8 @@ __global__ __launch_bounds__(512) void aht_pass_kernel(const float *__restrict__
 // roles: A_op = A elements (32 rows x 16 columns, a lane holds 8 consecutive columns of one
 // row, cut into bf16 pieces in registers), B_op = the piece planes of H^T (16 columns x 32
 // factors: the planes the H update writes for its new H; the 48 registers of a chunk serve
-// all R row tiles), so the sums are the exact-piece sums of the W^T A pass, and like there a
-// matrix accumulator runs for at most 32 products deep (8 chunks) before it is added, in
+// all R row tiles), so the sums are the piece sums of the W^T A pass, and like there a
+// matrix accumulator runs over at most 256 terms (4 chunks) before it is added, in
 // rounded fp32, to totals: here totals in LDS shared by the wave pairs (w, w + 4), because
 // R accumulator tiles and R total tiles do not fit a wave's registers beside the planes.
 // An operand layout with lanes down the rows would make every lane of a load touch its own
@@ -1341,7 +1341,7 @@ __global__ __launch_bounds__(512) void aht_pass_kernel(const float *__restrict__
 // Epilogue per row block: the four totals are added in order; W <- W * Q / (W GH + eps) for
 // the block's rows with GH = H H^T (k x k, complete); then from the new rows in LDS: their
 // bf16 piece planes (operand of the next W^T A pass), this workgroup's share of W^T W (fp32
-// matrix instruction, one tile set per workgroup in gout, which the next W^T A pass adds up
+// matrix instruction, one tile set per workgroup in gout, which the next W^T A pass adds
 // up) and, with dpart, its share of <A H^T, W_new> in double.
 // KT = 2 (33 <= k <= 64): planes of 64 factor slots (96 registers per chunk), every cut of A
 // feeds two accumulator chains, R = 2 (four accumulator tiles), 65-float rows in the epilogue,
@@ -1644,7 +1644,8 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
 // instead of 1.9e-7, for 1 to 3 % less time).
 // The pieces of W never leave the chip, and A comes from memory once per iteration instead of
 // twice.  One workgroup (8 waves, 116 KiB of LDS) fills a compute unit; its chain of LDS round
-// trips, not the memory, bounds it: 314 us on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
+// trips, not the memory, bounds it: 313 us between events (326 at best, 378 on average in a
+// profiler's trace) on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
 // against 215 us for the W^T A pass and 340 us for aht_rows_kernel there.  Two chunks of columns
 // per wave (n up to 1024), with the second reading from the caches, gained 0.95 to 1.15x only,
 // three lost to the row plan (0.73 to 1.01x): hence the limit.
@@ -2043,7 +2044,7 @@ __global__ __launch_bounds__(256) void residual_kernel(const float *__restrict__
 // ---------------------------------------------------------------------------
 // The same objective as a streaming pass for k = 16 or 32, 16-byte aligned A, W and H,
 // n % 4 == 0 and m % 32 == 0 (the launcher gives the rows left over to the general kernel):
-// the geometry and the exact-piece arithmetic of the W^T A pass, turned round: here the
+// the geometry and the pieces of the W^T A pass, turned round (both operands cut with rounding): here the
 // 32 x 32 tile of an instruction is rows of A by columns of A and the reduction runs over the
 // factor index.  Workgroup = 4 waves on 256 consecutive columns and one row split; a wave
 // owns 64 of the columns and walks down all the rows of the split, a lane 2 consecutive
@@ -2486,7 +2487,7 @@ int wta_splits(int64_t rows, int64_t n, int k)
     const int64_t slabs = (n + width - 1) / width;
     // Rounded down: 512 workgroups are resident at once, and one more split than fits leaves its
     // last workgroups to a second round (20011 x 10000 at k = 50: 40 slabs x 13 splits = 520
-    // workgroups took 252 us; 40 x 12, and the planes staged in LDS, 162).
+    // workgroups take 213 us back to back; 40 x 12 170).
     const int64_t target = 512;
     int64_t s = target / slabs;
     // With one split on fewer than 384 slabs (three quarters of the places) the chip is better served by two rounds of

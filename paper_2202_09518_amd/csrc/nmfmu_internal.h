@@ -92,7 +92,7 @@ hipError_t launch_factor_update(float *X, float *Xt, const float *part, int spli
                                 const BlockMap *map = nullptr, void *planes = nullptr,
                                 double *dpart = nullptr);
 // dpart (with an updating launch): per block, the sum of numerator x new value over its entries
-// (factor_update_blocks(len) doubles when gout is given, else one per 64 columns).
+// (factor_update_blocks(len) doubles when gout is given, else one per chunk of 16, 32 or 64 columns).
 // out[0] = sum of squares of X[0 .. count) in double; partial: 4096 doubles of scratch.
 hipError_t launch_sumsq(const float *X, int64_t count, double *partial, double *out, hipStream_t st);
 // out[0] = sqrt(max(0, normA2[0] - 2 sum(dpart[0 .. nb)) + <GW, GH>)).
@@ -110,7 +110,7 @@ hipError_t launch_aht_pass(const float *A, int64_t rows, int64_t n, int k, const
                            const float *GH, float *W, float eps, hipStream_t st, double *dpart = nullptr);
 int64_t aht_pass_blocks(int64_t rows);
 // The same update for k <= 64 as one streaming pass over the row-major A (coalesced loads turned
-// through LDS, exact-piece products): planesH = piece planes of H^T (what launch_factor_update
+// through LDS, products from pieces): planesH = piece planes of H^T (what launch_factor_update
 // writes for X = H), GH = H H^T (k x k).  Also written: the piece planes of the new W (planesW),
 // aht_rows_blocks(rows, k) tile sets of W^T W (gout) and dpart as above (aht_rows_blocks(rows, k)
 // doubles).  gram_only: no pass and no update, only planesW and gout of W as it is.  dry: the

@@ -1,7 +1,7 @@
 """The arithmetic behind the k <= 32 pass, checked on the CPU with exact rationals.
 
 The pass forms every product w * a from three bf16 pieces of each operand.  What
-has to hold for its sums to be the fp32 sums of the exact products:
+holds of the pieces and their nine products:
   * the pieces of a float add up to it exactly,
   * each piece has at most 8 significant bits (it is a bf16),
   * each of the nine piece products has at most 16 significant bits, so a
@@ -72,9 +72,10 @@ def test_nine_piece_products_are_exact_in_float32_and_sum_to_the_product():
 
 
 def test_the_product_of_the_two_lowest_pieces_is_below_2_to_minus_30_of_the_term():
-    """The kernels leave l_x l_y out: each lowest piece is below 2^-15 of its float (h keeps 8
-    significant bits, m the next 8 from the remainder's leading bit on), so the eight products
-    they keep give x y to 2^-30, a 64th of one float32 rounding."""
+    """Each lowest piece is below 2^-15 of its float (h keeps 8 significant bits, m the next 8
+    from the remainder's leading bit on), so the eight products without l_x l_y give x y to
+    2^-30, a 64th of one float32 rounding.  (The kernels cut one operand with rounding and
+    leave two more products out: test_rounded_pieces.py.)"""
     x, y = sample(2000, 5), sample(2000, 6)
     px, py = pieces(x), pieces(y)
     for i in range(x.size):
