@@ -1644,8 +1644,8 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
 // instead of 1.9e-7, for 1 to 3 % less time).
 // The pieces of W never leave the chip, and A comes from memory once per iteration instead of
 // twice.  One workgroup (8 waves, 116 KiB of LDS) fills a compute unit; its chain of LDS round
-// trips, not the memory, bounds it: 313 us between events (326 at best, 378 on average in a
-// profiler's trace) on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
+// trips, not the memory, bounds it: 314 us at best and 357 on average in a profiler's trace
+// on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
 // against 215 us for the W^T A pass and 340 us for aht_rows_kernel there.  Two chunks of columns
 // per wave (n up to 1024), with the second reading from the caches, gained 0.95 to 1.15x only,
 // three lost to the row plan (0.73 to 1.01x): hence the limit.
