@@ -15,6 +15,14 @@ extern "C" {
 #endif
 
 /*
+ * The resident plan of nmf_mu_dense with one workgroup doing the run of all, as the
+ * kernel does by itself when the device has no room for all of them at once: the same
+ * bits, many times slower.  NMF_EUNSUPPORTED for a shape that this plan does not take.
+ */
+int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H,
+                          int32_t iters, float eps, void *stream);
+
+/*
  * nmf_mu_dense with timing, on A as it is (no copy of a misaligned A is made, so such
  * an A takes the slower kernels here): the same launches on `stream`, with a HIP event
  * recorded between them; synchronises `stream` before returning.  On return
@@ -27,7 +35,9 @@ extern "C" {
  * both passes stream the row-major A, [0], [3] and [5] are 0 because the Gram
  * matrices and the W update are by-products of the other three kernels; with
  * n <= 512 columns both products of an iteration are one launch, which is then
- * [1] except for the run's last W update, whose launch is [4]), 1 the
+ * [1] except for the run's last W update, whose launch is [4]; on the resident plan
+ * [1] is W^T A and the H update, [4] A H^T and the W update, each as a launch of its
+ * own), 1 the
  * mirrored plan (see nmf_mu_workspace_bytes), 0 the small plan.  kernel_ms[7] and
  * [8]: milliseconds per launch of the W^T A pass and (plans 1 and 2, else 0) of
  * the A H^T pass, from 20 launches back to back between two events after the

@@ -140,6 +140,9 @@ int check_common(const void *a, const void *w, const void *h, int64_t m, int64_t
 struct DensePlan {
     bool mirrored;
     bool one_pass = false;     // both products in one reading of A: ppart and planes2 only
+    int resident = 0;          // the run in one launch, this many row tiles per workgroup: `res` and dry only
+    ResidentArgs res;          // its exchange buffers
+    float *dry;                // room for factors that a timing run leaves behind
     int64_t a_rows = 0;        // mirrored: rows of A itself when those of W are padded (0: the same)
     Common c;
     float *ppart;              // row-split partials of either pass
@@ -187,6 +190,28 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
 size_t one_pass_bytes(int64_t m, int64_t n, int k)
 {
     return common_bytes(k) + align_up((size_t)one_pass_blocks(m, n) * k * n * sizeof(float)) + align_up(planes_bytes(n));
+}
+
+DensePlan carve_resident(Carve &cv, int64_t m, int64_t n, int k, int tiles)
+{
+    const size_t R = (size_t)(m + 16 * tiles - 1) / (16 * tiles), C = (size_t)(n + 255) / 256, wgs = R * C;
+    DensePlan p{};
+    p.resident = tiles;
+    p.c = carve_common(cv, k);
+    p.res.part = cv.take<float>(wgs * kResidentPRec);
+    p.res.qpart = cv.take<float>(wgs * resident_qrec(tiles));
+    p.res.hx = cv.take<float>(C * 4096);
+    p.res.wx = cv.take<float>(R * 256 * tiles);
+    p.res.sync = cv.take<unsigned>((size_t)resident_sync_words((int64_t)R, (int64_t)C));
+    p.dry = cv.take<float>((size_t)(m + n) * k);
+    return p;
+}
+
+size_t resident_bytes(int64_t m, int64_t n, int k)
+{
+    Carve c(nullptr);
+    carve_resident(c, m, n, k, resident_tiles(m, n, k));
+    return c.off;
 }
 
 DensePlan carve_one_pass(void *ws, int64_t m, int64_t n, int k)
@@ -255,12 +280,20 @@ bool have_workspace(size_t need, hipStream_t st)
     return can;
 }
 
-// The plan of a dense run with `extra` bytes behind it (*tail): the one-pass plan where it applies,
-// else the row or the mirrored plan, else the small one; whatever the workspace can hold.
+// The plan of a dense run with `extra` bytes behind it (*tail): the resident plan where it applies, then the
+// one-pass plan, else the row or the mirrored plan, else the small one; whatever the workspace can hold.
 int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStream_t st, DensePlan *p, char **tail)
 {
     void *ws = nullptr;
-    size_t bytes = one_pass_bytes(m, n, k);
+    const int tiles = resident_tiles(m, n, k);
+    size_t bytes = tiles ? resident_bytes(m, n, k) : 0;
+    if (tiles && have_workspace(bytes + extra, st)) {
+        Carve cv(g.ws);
+        *p = carve_resident(cv, m, n, k, tiles);
+        if (tail) *tail = static_cast<char *>(g.ws) + bytes;
+        return NMF_OK;
+    }
+    bytes = one_pass_bytes(m, n, k);
     if (one_pass_ok(A, n, k) && have_workspace(bytes + extra, st)) {
         *p = carve_one_pass(g.ws, m, n, k);
     } else {
@@ -315,6 +348,8 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
     r->n = n;
     bool padded = false, pad_w = false;
     size_t base = 0;
+    if (resident_tiles(m, n, k) && have_workspace(resident_bytes(m, n, k) + extra, st))      // takes any A
+        return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
     if (eps >= 1.17549435e-38f && (copy_a || m != m4) && iters > 0) {
         const bool one = one_pass_ok(nullptr, n4, k), rows = rows_plan_first(nullptr, m, n4, k);
         if (one || rows) {
@@ -380,7 +415,7 @@ int close_run(const DenseRun &r, int k, float *W, float *H, int64_t m, int64_t n
 // A dense_body on this plan streams A itself for both products and leaves the plan's A^T alone.
 bool takes_row_plan(const DensePlan &p, const float *A, int64_t m, int64_t n, int k)
 {
-    return !p.one_pass && !p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored);
+    return !p.one_pass && !p.resident && !p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored);
 }
 
 constexpr int kDenseKernels = 6;
@@ -403,6 +438,40 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
                hipEvent_t *ev = nullptr, const BlockMap *map = nullptr, const Monitor *mon = nullptr)
 {
     const Common &c = p.c;
+    if (p.resident) {
+        ResidentArgs a = p.res;
+        a.A = A;
+        a.Win = a.W = W;
+        a.Hin = a.H = H;
+        a.m = m;
+        a.n = n;
+        a.k = k;
+        a.eps = eps;
+        if (ev) {      // the halves of an iteration one by one: the same sums
+            NMF_HIP(hipEventRecord(*ev++, st));
+            for (int it = 0; it < iters; ++it)
+                for (int slot = 0; slot < kDenseKernels; ++slot) {
+                    a.nprod = slot == 1;
+                    a.lead = slot == 4;
+                    if (slot == 1 || slot == 4) NMF_HIP(launch_resident(a, p.resident, st));
+                    NMF_HIP(hipEventRecord(*ev++, st));
+                }
+            return NMF_OK;
+        }
+        const int calls = mon && !mon->last_only ? iters : 1;
+        a.nprod = iters / calls;
+        a.trail = 1;
+        const int R = (int)((m + 16 * p.resident - 1) / (16 * p.resident)), C = (int)((n + 255) / 256);
+        if (mon) a.dpart = mon->dpart, a.gout = c.gwp, a.gh = c.gh;
+        for (int i = 0; i < calls; ++i) {
+            NMF_HIP(launch_resident(a, p.resident, st));
+            if (mon) {
+                NMF_HIP(launch_gram_sum(c.gwp, R, k, c.gw, st));
+                NMF_HIP(launch_objective(mon->dpart, R * C, c.gw, c.gh, k, mon->normA2, mon->out + i, st));
+            }
+        }
+        return NMF_OK;
+    }
     if (p.one_pass) {
         // Per iteration: the pass that finishes the previous one (A H^T, the W update) and leaves W^T A
         // and W^T W of the new W as one share per workgroup, then the H update; the last W update has a
@@ -1007,7 +1076,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
     std::lock_guard<std::mutex> lock(g.mu);
     DensePlan p;
     if (int rc = dense_plan(A, m, n, k, 0, st, &p, nullptr)) return rc;
-    const bool mirrored = p.mirrored, one_pass = p.one_pass;
+    const bool mirrored = p.mirrored, one_pass = p.one_pass, resident = p.resident != 0;
     constexpr int NK = kDenseKernels;
     std::vector<hipEvent_t> ev((size_t)iters * NK + 1, nullptr);
     int rc = NMF_OK;
@@ -1027,7 +1096,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
                 sum[j] += ms;
             }
         for (int j = 0; j < NK; ++j) kernel_ms[j] = (float)(sum[j] / iters);
-        kernel_ms[NK] = one_pass || rows_plan_runs(A, m, n, k, mirrored) ? 2.f : (mirrored ? 1.f : 0.f);
+        kernel_ms[NK] = resident || one_pass || rows_plan_runs(A, m, n, k, mirrored) ? 2.f : (mirrored ? 1.f : 0.f);
         kernel_ms[NK + 1] = kernel_ms[NK + 2] = 0.f;
     }
     // The pass kernels once more, `reps` launches back to back between two events: the
@@ -1037,15 +1106,21 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
         const int reps = 20;
         const int s1 = wta_splits(m, n, k), s2 = wta_splits(n, m, k);
         const int64_t rps1 = wta_rows_per_split(m, s1), rps2 = wta_rows_per_split(n, s2);
-        const bool rows_plan = !one_pass && rows_plan_runs(A, m, n, k, mirrored);
+        const bool rows_plan = !resident && !one_pass && rows_plan_runs(A, m, n, k, mirrored);
         const Common &c = p.c;
-        for (int which = 0; which < ((mirrored || rows_plan || one_pass) ? 2 : 1) && rc == NMF_OK; ++which) {
-            if (one_pass) (void)0;
+        for (int which = 0; which < ((mirrored || rows_plan || one_pass || resident) ? 2 : 1) && rc == NMF_OK; ++which) {
+            if (one_pass || resident) (void)0;
             else if (which == 0) (void)launch_split_planes(W, m, k, p.planes, st);
             else if (!rows_plan) (void)launch_split_planes(p.Ht, n, k, p.planes, st);
+            ResidentArgs dry = p.res;
+            if (resident) {
+                dry.A = A, dry.Win = W, dry.Hin = H, dry.W = p.dry, dry.H = p.dry + m * k;
+                dry.m = m, dry.n = n, dry.k = k, dry.eps = eps, dry.nprod = which == 0, dry.lead = which == 1;
+            }
             hipError_t e = hipEventRecord(ev[0], st);
             for (int r = 0; r < reps && e == hipSuccess; ++r)
-                e = one_pass ? launch_one_pass(A, m, n, k, p.planes2, nullptr, c.ghp, factor_update_blocks(n), W, nullptr, p.ppart,
+                e = resident ? launch_resident(dry, p.resident, st)
+                    : one_pass ? launch_one_pass(A, m, n, k, p.planes2, nullptr, c.ghp, factor_update_blocks(n), W, nullptr, p.ppart,
                                                c.gwp, eps, st, which == 1, which == 0)
                     : which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, nullptr, 0, nullptr, mirrored)
                     : rows_plan  // the fused pass without its stores to W
@@ -1714,7 +1789,7 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     if (int rc = open_run(A, m, n, k, W, H, max_iters, eps, extra, st, &r)) return rc;
     const bool mirrored = r.p.mirrored;
     // plans whose W update leaves the objective's terms behind
-    const bool fast = mirrored || r.p.one_pass || rows_plan_runs(r.A, m, r.n, k, mirrored);
+    const bool fast = mirrored || r.p.one_pass || r.p.resident || rows_plan_runs(r.A, m, r.n, k, mirrored);
     Carve cv(r.tail);
     double *scratch = cv.take<double>(run_scratch_bytes(m, n) / sizeof(double));
     Monitor mon;
@@ -1786,7 +1861,7 @@ int nmf_mu_dense_monitor(const float *A, int64_t m, int64_t n, int32_t k, float 
     mon.out = cv.take<double>((size_t)iters);
     mon.res = cv.take<double>(run_scratch_bytes(m, n) / sizeof(double));
     mon.last_only = false;
-    if (r.p.mirrored || r.p.one_pass || rows_plan_runs(r.A, m, r.n, k, r.p.mirrored))
+    if (r.p.mirrored || r.p.one_pass || r.p.resident || rows_plan_runs(r.A, m, r.n, k, r.p.mirrored))
         NMF_HIP(launch_sumsq(r.A, m * r.n, mon.normA2 + 1, mon.normA2, st));
     if (int rc = dense_body(r.A, r.m, r.n, k, r.W, r.H, iters, eps, r.p, st, r.have_at, nullptr, nullptr, &mon)) return rc;
     if (int rc = close_run(r, k, W, H, m, n, st)) return rc;
@@ -1812,12 +1887,35 @@ int nmf_mu_dense_noalloc(const float *A, int64_t m, int64_t n, int32_t k, float 
     // the kernels restore that, but an earlier call may have been cut short.  A fill kernel, not
     // a memset: the call may be under graph capture.
     NMF_HIP(launch_fill_f32(static_cast<float *>(ws), 64, 0.f, st));
+    const int tiles = resident_tiles(m, n, k);
+    if (tiles && resident_bytes(m, n, k) <= kScratchBytes) {
+        Carve cv(ws);
+        return dense_body(A, m, n, k, W, H, iters, eps, carve_resident(cv, m, n, k, tiles), st);
+    }
     const bool one = one_pass_ok(A, n, k) && one_pass_bytes(m, n, k) <= kScratchBytes;
     const DensePlan p = one ? carve_one_pass(ws, m, n, k) : carve_dense(ws, m, n, k, false);
     return dense_body(A, m, n, k, W, H, iters, eps, p, st);
 }
 
 // ---- single steps ----------------------------------------------------------
+
+int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
+                          void *stream)
+{
+    if (int rc = check_common(A, W, H, m, n, k, iters, eps)) return rc;
+    const int tiles = resident_tiles(m, n, k);
+    if (!tiles) return fail(NMF_EUNSUPPORTED, "not a shape of the resident plan%s");
+    if (iters == 0) return NMF_OK;
+    std::lock_guard<std::mutex> lock(g.mu);
+    void *ws = nullptr;
+    if (int rc = ensure_workspace(resident_bytes(m, n, k), &ws)) return rc;
+    Carve cv(ws);
+    ResidentArgs a = carve_resident(cv, m, n, k, tiles).res;
+    a.A = A, a.Win = a.W = W, a.Hin = a.H = H;
+    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters, a.trail = 1;
+    NMF_HIP(launch_resident(a, tiles, static_cast<hipStream_t>(stream), true));
+    return NMF_OK;
+}
 
 int nmf_csr_partition(const int64_t *rowptr, int64_t m, int32_t nparts, int64_t *part, void *stream)
 {

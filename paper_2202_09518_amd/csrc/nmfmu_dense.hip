@@ -28,6 +28,8 @@
 //   A_op (32 x 2):  lane l holds A_op[l % 32][l / 32]
 //   B_op (2 x 32):  lane l holds B_op[l / 32][l % 32]
 //   D    (32 x 32): lane l, register v holds D[(v % 4) + 4 (l / 32) + 8 (v / 4)][l % 32]
+#include <atomic>
+
 #include "nmfmu_internal.h"
 
 namespace nmfmu {
@@ -61,6 +63,12 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma_bf16_16(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
@@ -1954,6 +1962,530 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// A whole run in one launch, for matrices that the chip holds on its compute units (k <= 16; the "resident
+// plan").  What such a run costs otherwise is launches and trips to L2: four dependent kernels of 3 to 12 us
+// per iteration whatever the work in them.  Here a workgroup keeps a tile of A, 16 RT rows x 256 columns, on its
+// compute unit over all iterations; workgroup (r, c) of R x C has rows 16 RT r .. and columns 256 c ...
+//   product:   the share of its rows in W^T A (its columns) and in W^T W, for column group c;
+//   H update:  the 16-column tiles of group c are dealt to its R workgroups, which add up the R shares;
+//   A H^T:     the share of its columns in A H^T (its rows) and in H H^T, for row group r;
+//   W update:  the 16-row tiles of group r are dealt to its C workgroups, which add up the C shares.
+// Each of the four hands its result through memory to the other workgroups of the group (with C = 1 the last two
+// stay on chip): the workgroup posts a flag behind its stores and waits for the flags of its group.  Cutting
+// A both ways keeps what is handed over small: with 16-row blocks of whole rows, 2000 x 1201 at k = 12 wrote
+// and read 9.6 MB of shares of W^T A per iteration, against 2.4 MB in all, and took 18.4 us.
+//
+// The arithmetic is that of the other passes, on 16 x 16 x 32 instructions: six products of pieces, A cut with
+// rounding once per run.  For A H^T (operand: lane = row, 8 columns) the pieces stay in registers: wave
+// (rt, cw) has row tile rt and RT of the tile's eight 32-column steps.  For W^T A (lane = column, 8 rows) they
+// stay in LDS: wave w has columns 32 w .. 32 w + 31.  16 rows fill only half of an instruction's depth, so its
+// halves take two different piece products: three instructions for the six.  H H^T and W^T W are on the
+// fp32 instruction.  A matrix accumulator takes in at most 256 terms, and the largest products have one of their own
+// that meets the others in a rounded add: what the instruction drops when they join it is always downwards and shows
+// as a drift of the factors' scale over many iterations.
+//
+// Who waits for a flag must know that its writer runs: the workgroups first report in, and only when all
+// have (all hold their compute units then) does the run start.  If they have not after `patience` ticks of
+// the 100 MHz counter (other kernels, or several such launches that hold part of the device each), the first
+// that reported in does the whole run by itself, tile after tile, and the others leave.  So every wait ends
+// whatever else the device does; the sums, and so the bits, are the same.  Only a caller that breaks the rule of
+// one call at a time per workspace can take flags away from a run that waits for them: a thread has kLostPolls
+// looks (seconds) for all its waits, then waits no more, and the kernel ends and leaves a NaN in W and H.
+// Stores and loads of what workgroups exchange carry the sc1 bit: they meet behind the L2s of the XCDs.
+// (Plain loads after an acquire at the flags, which drops the L2's copies, were slower: 19.5 for 18.4 us.)
+// ---------------------------------------------------------------------------
+constexpr int kExchange = 16;            // sc1: coherent over the whole device
+constexpr int kLostPolls = 1 << 24;      // looks, not time: a process that is switched out does not look
+constexpr int kPRec = kResidentPRec;
+__host__ __device__ constexpr int resident_lds_floats(int rt)
+{
+    return 8 * 2 * rt * 384 + 3 * 32 * 16 * 4 + 2 * 2048 + rt * 16 * 20 + 3 * 16 * 20 + 3 * rt * 128 + 24;
+}
+
+__device__ __forceinline__ unsigned peek(const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+template <int RT>
+__global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
+{
+    constexpr int kRsrcFlags = 0x00020000;         // raw buffer, 32-bit data format (gfx9 family)
+    constexpr unsigned kOut = 0x7fffffffu;         // an offset outside every extent: reads as zero, stores nothing
+    constexpr int LD = 20, RB = 16 * RT, CW = 8 / RT, NE = (RT * 256 + 511) / 512, kQRec = resident_qrec(RT);
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};   // smallest first
+    float *lds = aht_rows_lds;
+    u32x4 *Ap = reinterpret_cast<u32x4 *>(lds);                    // [wave][2 tiles][RT][3 pieces][2][16 columns]
+    u32x4 *Hp = Ap + 8 * 2 * RT * 96;                              // pieces of H: [3][32 groups of 8 columns][16]
+    float *Qs = reinterpret_cast<float *>(Hp + 3 * 32 * 16);       // shares of the waves: [8][256]
+    float *Gq = Qs + 2048;
+    float *Ws = Gq + 2048;                                         // [RB rows][LD]
+    float *Gs = Ws + RB * LD;                                      // H H^T or W^T W [16][LD]
+    float *Gl = Gs + 16 * LD;                                      // what the float of an entry of Gs leaves out
+    float *Hs = Gl + 16 * LD;                                      // [16 columns][LD]
+    unsigned short *Wp = reinterpret_cast<unsigned short *>(Hs + 16 * LD);   // pieces of the rows [3][RB / 8][16][8]
+    unsigned *word = reinterpret_cast<unsigned *>(Hs + 16 * LD + 3 * RT * 128);
+    double *dsum = reinterpret_cast<double *>(word + 2);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, quad = lane >> 4, hr = quad & 1, half = lane >> 5;
+    const int er = (tid >> 4) & 15, ec = tid & 15;
+    const int nwg = gridDim.x, k = a.k, R = a.R, C = a.C, n = (int)a.n;
+    const int nt = (n + 15) >> 4;                                  // 16-column tiles in all
+    const int rpad = (R + 31) & ~31, box = rpad + 32;              // words of a workgroup's letter box: column group, row group
+
+    // ---- all here, or one for all
+    bool solo = nwg < R * C;
+    if (!solo && nwg > 1) {
+        if (tid == 0) {
+            const unsigned ticket = __hip_atomic_fetch_add(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned none = 0u;
+            if (ticket == (unsigned)nwg - 1)
+                __hip_atomic_compare_exchange_strong(a.sync + 1, &none, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // the low bits of the clock: of several launches that wait for each other's compute units one gives up first
+            const long long t0 = wall_clock64(), end = t0 + a.patience + (t0 & 0xfffff);
+            unsigned mode;
+            for (int looks = 0; (mode = peek(a.sync + 1)) == 0u && looks < kLostPolls; ++looks) {
+                __builtin_amdgcn_s_sleep(1);
+                if (ticket == 0 && (long long)wall_clock64() > end) {
+                    none = 0u;
+                    __hip_atomic_compare_exchange_strong(a.sync + 1, &none, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (ticket == 0) looks = 0;
+            }
+            word[0] = mode == 1u ? 1u : (ticket == 0 ? 2u : 0u);
+        }
+        __syncthreads();
+        const unsigned mode = __builtin_amdgcn_readfirstlane(word[0]);
+        if (mode == 0u) return;
+        solo = mode == 2u;
+    }
+    const int v0 = solo ? 0 : (int)blockIdx.x, v1 = solo ? R * C : v0 + 1;     // the workgroups this one stands for
+    const int r0 = v0 / C, c0 = v0 % C;
+    unsigned epoch = 0;
+    unsigned *boxes = a.sync + 32;
+    // Posts a flag behind all stores of this workgroup to every other of its column or row group, then waits for
+    // theirs.  Each has its own letter box: with one array of flags that all poll, the few lines of it are what a
+    // wait of 125 workgroups waits for (9000 cycles instead of 3000 of 16).
+    int looks = kLostPolls;            // left to this thread
+    auto meet = [&](bool column) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        ++epoch;
+        if (solo) return;
+        if (tid < (column ? R : C)) {
+            unsigned *to = boxes + (column ? (tid * C + c0) * box + r0 : (r0 * C + tid) * box + rpad + c0);
+            const unsigned *from = boxes + v0 * box + (column ? 0 : rpad) + tid;
+            __hip_atomic_store(to, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while (peek(from) < epoch && looks > 0) {
+                __builtin_amdgcn_s_sleep(1);
+                --looks;
+            }
+        }
+        asm volatile("" ::: "memory");
+        __syncthreads();
+    };
+
+    u32x4 at[RT][3];                   // operand of A H^T
+    auto load_tile = [&](int r, int c) {
+        const int64_t row0 = (int64_t)r * RB;
+        int64_t av = a.m - row0;
+        av = av > RB ? RB : av;
+        const int col0 = c * 256, rt = w / CW;
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(a.A + row0 * n), 0, (int)(av * n * 4), kRsrcFlags);
+        int opaque = 0;
+        asm volatile("" : "+s"(opaque));      // the offsets are formed here, once, and not kept in registers over the run
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            const int cc = opaque + col0 + 32 * (w % CW + CW * i) + 8 * quad;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                x[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, cc + e < n ? (unsigned)((16 * rt + l16) * n + cc + e) * 4u : kOut, 0, 0));
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) cut2(x[2 * pr], x[2 * pr + 1], at[i], pr);
+            __builtin_amdgcn_sched_barrier(0);     // one group of loads at a time: all of them would spill
+        }
+        const int cc = opaque + col0 + 32 * w + 16 * half + l16;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {             // columns by lane: 8 rows of one of the wave's two tiles
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                x[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, cc < n ? (unsigned)((16 * i + 8 * hr + e) * n + cc) * 4u : kOut, 0, 0));
+            u32x4 p[3];
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) cut2(x[2 * pr], x[2 * pr + 1], p, pr);
+            u32x4 *dst = Ap + ((w * 2 + half) * RT + i) * 96;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) dst[(q * 2 + hr) * 16 + l16] = p[q];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // a row of W in LDS: the float and its pieces
+    auto put_w = [&](int row, int f, float x) {
+        Ws[row * LD + f] = x;
+        unsigned h, mm, l;
+        split3(x, h, mm, l);
+        unsigned short *dst = Wp + ((row >> 3) * 16 + f) * 8 + (row & 7);
+        dst[0] = (unsigned short)(h >> 16);
+        dst[RT * 256] = (unsigned short)(mm >> 16);
+        dst[2 * RT * 256] = (unsigned short)(l >> 16);
+    };
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(a.wx, 0, R * RB * 64, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(a.hx, 0, nt * 1024, kRsrcFlags);
+    // the rows of row group r: as handed in, or as exchanged
+    auto load_w = [&](int r, bool handed_in) {
+        float x[NE];
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int e = tid + 512 * i, row = e >> 4, f = e & 15;
+            const int64_t grow = (int64_t)r * RB + row;
+            if (handed_in) x[i] = row < RB && grow < a.m && f < k ? a.Win[grow * k + f] : 0.f;
+            else x[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, row < RB ? (unsigned)(r * RB * 16 + e) * 4u : kOut, 0, kExchange));
+        }
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int e = tid + 512 * i;
+            if (e < RT * 256) put_w(e >> 4, e & 15, x[i]);
+        }
+    };
+    // The Gram matrix of either update, up to 8 factors in two floats an entry: an entry's rounding is the same in all
+    // rows or columns and, near a fixed point, in all iterations, so that the factors' scale drifts by it (256 x 192,
+    // k = 4, 100 iterations, median of 48 inputs: 4.2e-7 off with one float, 3.6 with two, 3.7 on the one-pass plan;
+    // 1000 x 300, k = 12, 50 iterations: 3.5, 3.4, 3.7).
+    auto put_g = [&](double x) {
+        const float hi = (float)x;
+        Gs[er * LD + ec] = hi;
+        Gl[er * LD + ec] = (float)(x - (double)hi);
+    };
+    auto dot = [&](const float *x, int row) -> float {     // x . row of the Gram matrix
+        const float *gh = Gs + row * LD, *gl = Gl + row * LD;
+        float s0 = 0.f, s1 = 0.f, l = 0.f;
+        auto four = [&](int d) {
+            const f32x4 u = *reinterpret_cast<const f32x4 *>(x + d), v = *reinterpret_cast<const f32x4 *>(gh + d);
+            s0 += u.x * v.x;
+            s1 += u.y * v.y;
+            s0 += u.z * v.z;
+            s1 += u.w * v.w;
+        };
+        auto rest = [&](int d) {
+            const f32x4 u = *reinterpret_cast<const f32x4 *>(x + d), v = *reinterpret_cast<const f32x4 *>(gl + d);
+            l += u.x * v.x + u.y * v.y + u.z * v.z + u.w * v.w;
+        };
+        if (k <= 8) {
+            four(0), rest(0);
+            four(4), rest(4);
+        } else {
+            four(0), four(4), four(8), four(12);
+        }
+        return (s0 + s1) + l;
+    };
+    // new entry of W; with the last update also to the caller's W and the objective's terms
+    auto update_w = [&](int r, int row, int f, float num, bool last, double &dacc) -> float {
+        const int64_t grow = (int64_t)r * RB + row;
+        if (grow >= a.m || f >= k) return 0.f;
+        const float x = Ws[row * LD + f] * num / (dot(Ws + row * LD, f) + a.eps);   // H H^T is symmetric
+        if (last) a.W[grow * k + f] = x;
+        dacc += (double)num * (double)x;
+        return x;
+    };
+    // what the last update of W leaves for the objective; `owner` of the row group's first tile: also its W^T W
+    auto report = [&](int v, double dacc) {
+        for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
+        __syncthreads();
+        if (lane == 0) dsum[w] = dacc;
+        __syncthreads();
+        if (tid == 0) {
+            double t = 0.0;
+            for (int i = 0; i < 8; ++i) t += dsum[i];
+            a.dpart[v] = t;
+        }
+        if (v == 0 && tid < 256 && er < k && ec < k) a.gh[er * k + ec] = Gs[er * LD + ec];
+    };
+
+    for (int v = v0; v < v1; ++v)      // H as handed in, to where its owners look for it
+        for (int t = v / C; t < 16; t += R) {
+            const int tile = 16 * (v % C) + t, col = 16 * tile + ec;
+            if (tid < 256)
+                __builtin_amdgcn_raw_buffer_store_b32(er < k && col < n ? __float_as_uint(a.Hin[(int64_t)er * n + col]) : 0u, rh,
+                                                      (unsigned)((2 * tile + (ec >> 3)) * 128 + er * 8 + (ec & 7)) * 4u, 0, kExchange);
+        }
+    if (a.lead) meet(true);
+    bool have_tile = false, stored = false;      // stored: wx holds the rows
+    for (int s = 0; s <= a.nprod; ++s) {
+        const bool product = s < a.nprod, update = s ? (product || a.trail) : a.lead;
+        if (!product && !update) break;
+        const bool last_w = update && (!product || (s == a.nprod - 1 && !a.trail));
+        const bool last_h = s == a.nprod - 1;
+        if (update) {
+            // ---- A H^T
+            for (int v = v0; v < v1; ++v) {
+                const int r = v / C, c = v % C;
+                if (solo) __syncthreads();
+                if (solo || !have_tile) {
+                    load_tile(r, c);
+                    load_w(r, !stored);
+                }
+                // thread tid: group tid / 16 of 8 columns, factor tid % 16; the floats are its wave's operand of H H^T
+                const unsigned off = (tid & 15) < k ? (unsigned)(c * 4096 + tid * 8) * 4u : kOut;
+                const u32x4 x0 = __builtin_amdgcn_raw_buffer_load_b128(rh, off, 0, kExchange);
+                const u32x4 x1 = __builtin_amdgcn_raw_buffer_load_b128(rh, off + 16, 0, kExchange);
+                {
+                    u32x4 p[3];
+                    cut2(__uint_as_float(x0.x), __uint_as_float(x0.y), p, 0);
+                    cut2(__uint_as_float(x0.z), __uint_as_float(x0.w), p, 1);
+                    cut2(__uint_as_float(x1.x), __uint_as_float(x1.y), p, 2);
+                    cut2(__uint_as_float(x1.z), __uint_as_float(x1.w), p, 3);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) Hp[q * 512 + tid] = p[q];
+                }
+                __syncthreads();
+                f32x4 q[2], g = {0.f, 0.f, 0.f, 0.f};
+                q[0] = q[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    u32x4 b[3];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) b[p] = Hp[p * 512 + (4 * (w % CW + CW * i) + quad) * 16 + l16];
+#pragma unroll
+                    for (int e = 0; e < 6; ++e) q[e / 5] = mfma_bf16_16(at[i][PA[e]], b[PB[e]], q[e / 5]);
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float x = __uint_as_float(e < 4 ? x0[e & 3] : x1[e & 3]);
+                    g = __builtin_amdgcn_mfma_f32_16x16x4f32(x, x, g, 0, 0, 0);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    Qs[w * 256 + (4 * quad + i) * 16 + l16] = q[0][i] + q[1][i];
+                    Gq[w * 256 + (4 * quad + i) * 16 + l16] = g[i];
+                }
+                __syncthreads();
+                float num[NE];
+                double gsum = 0.0;
+#pragma unroll
+                for (int i = 0; i < NE; ++i) {
+                    const int e = tid + 512 * i;
+                    float t[CW];
+#pragma unroll
+                    for (int u = 0; u < CW; ++u) t[u] = e < RT * 256 ? Qs[((e >> 8) * CW + u) * 256 + (e & 255)] : 0.f;
+                    num[i] = tree_sum(t);
+                }
+                if (RT > 1 ? tid < 256 : tid >= 256) {      // one row tile: the threads without an entry of it
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) gsum += (double)Gq[u * 256 + (tid & 255)];
+                }
+                const bool has_g = RT > 1 ? tid < 256 : tid >= 256;
+                if (C == 1) {
+                    if (has_g) put_g(gsum);
+                    __syncthreads();
+                    double dacc = 0.0;
+                    float x[NE];
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) {
+                        const int e = tid + 512 * i;
+                        x[i] = e < RT * 256 ? update_w(r, e >> 4, e & 15, num[i], last_w, dacc) : 0.f;
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) {
+                        const int e = tid + 512 * i;
+                        if (e < RT * 256) {
+                            put_w(e >> 4, e & 15, x[i]);
+                            if (solo) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), rw, (unsigned)(r * RB * 16 + e) * 4u, 0, kExchange);
+                        }
+                    }
+                    if (last_w && a.dpart) report(v, dacc);
+                } else {
+                    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(a.qpart + (int64_t)v * kQRec, 0, kQRec * 4, kRsrcFlags);
+#pragma unroll
+                    for (int i = 0; i < NE; ++i)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(num[i]), rq, tid + 512 * i < RT * 256 ? (unsigned)(tid + 512 * i) * 4u : kOut, 0, kExchange);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)gsum), rq, has_g ? (unsigned)(RT * 256 + (tid & 255)) * 4u : kOut, 0, kExchange);
+                }
+            }
+            if (C > 1) {
+                meet(false);
+                // ---- W update: the 16-row tiles dealt to the workgroups of the row group
+                for (int v = v0; v < v1; ++v) {
+                    const int r = v / C, c = v % C;
+                    if (solo) {
+                        __syncthreads();
+                        load_w(r, !stored);
+                    }
+                    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(a.qpart + (int64_t)r * C * kQRec, 0, C * kQRec * 4, kRsrcFlags);
+                    // first tile of this workgroup: threads 0 .. 255, H H^T: the others; shares in batches of 8
+                    const int t = c;
+                    float sum = 0.f;
+                    double gsum = 0.0;
+                    unsigned qo = tid >= 256 ? (unsigned)(RT * 256 + tid - 256) * 4u : t < RT ? (unsigned)(t * 256 + tid) * 4u : kOut;
+                    for (int b = 0; b < C; b += 8) {
+                        float x[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            x[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rq, qo + (unsigned)((b + u) * kQRec) * 4u, 0, kExchange));
+                        if (tid >= 256) {
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) gsum += (double)x[u];
+                        }
+                        sum += tree_sum(x);
+                    }
+                    if (tid >= 256) put_g(gsum);
+                    __syncthreads();
+                    double dacc = 0.0;
+                    for (int tt = t; tt < RT; tt += C) {
+                        if (tt != t && tid < 256) {
+                            sum = 0.f;
+                            for (int u = 0; u < C; ++u)
+                                sum += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rq, (unsigned)(u * kQRec + tt * 256 + tid) * 4u, 0, kExchange));
+                        }
+                        if (tid < 256) {
+                            const float x = update_w(r, 16 * tt + er, ec, sum, last_w, dacc);
+                            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rw, (unsigned)((r * RB + 16 * tt) * 16 + tid) * 4u, 0, kExchange);
+                        }
+                    }
+                    if (last_w && a.dpart) report(v, dacc);
+                }
+                if (product || a.gout) meet(false);
+            }
+        }
+        if (!product && !a.gout) break;
+        // ---- product
+        for (int v = v0; v < v1; ++v) {
+            const int r = v / C, c = v % C;
+            if (solo) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the rows of an update that did not wait for others
+                __syncthreads();
+            }
+            if (solo || !have_tile) {
+                if (solo || !update) load_tile(r, c);
+                if (solo || !update) load_w(r, !(stored || update));
+            }
+            if (!solo && update && C > 1) load_w(r, false);
+            __syncthreads();
+            if (product) {
+                f32x4 d[2][2];         // [tile][small products, large ones]
+#pragma unroll
+                for (int t = 0; t < 2; ++t) d[t][0] = d[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                const u32x4 *wsrc = reinterpret_cast<const u32x4 *>(Wp);
+                const int p0 = half ? 1 : 2, p1 = half ? 1 : 0;
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    u32x4 wf[3];
+                    wf[0] = wsrc[(p0 * 2 * RT + 2 * i + hr) * 16 + l16];    // l | m   against h | m
+                    wf[1] = wsrc[(p1 * 2 * RT + 2 * i + hr) * 16 + l16];    // h | m           l | h
+                    wf[2] = wsrc[(2 * i + hr) * 16 + l16];                  // h | h           m | h
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const u32x4 *src = Ap + ((w * 2 + t) * RT + i) * 96;
+                        u32x4 af[3];
+                        af[0] = src[((half ? 1 : 0) * 2 + hr) * 16 + l16];
+                        af[1] = src[((half ? 0 : 2) * 2 + hr) * 16 + l16];
+                        af[2] = src[((half ? 0 : 1) * 2 + hr) * 16 + l16];
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) d[t][e / 2] = mfma_bf16_16(af[e], wf[e], d[t][e / 2]);
+                    }
+                }
+                const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(a.part + (int64_t)v * kPRec, 0, kPRec * 4, kRsrcFlags);
+                const unsigned off = l16 < k ? (unsigned)(l16 * 16 + 4 * quad) * 4u + (unsigned)w * 2048u : kOut;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, d[t][0] + d[t][1]), rp, off + t * 1024u, 0, kExchange);
+            }
+            if (w == 7) {              // the rows' W^T W
+                f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 4 * RT; ++i) {
+                    const float x = Ws[(4 * i + quad) * LD + l16];
+                    d = __builtin_amdgcn_mfma_f32_16x16x4f32(x, x, d, 0, 0, 0);
+                }
+                if (product) {
+                    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(a.part + (int64_t)v * kPRec, 0, kPRec * 4, kRsrcFlags);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {      // the lower triangle
+                        const int row = 4 * quad + i;
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d[i]), rp, row >= l16 && row < k ? (unsigned)(4096 + row * (row + 1) / 2 + l16) * 4u : kOut, 0, kExchange);
+                    }
+                }
+                if (last_w && a.gout && c == 0) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int row = 4 * quad + i;
+                        a.gout[(int64_t)r * 1024 + ((row & 3) + 4 * (row >> 3)) * 64 + l16 + 32 * ((row >> 2) & 1)] = d[i];
+                    }
+                }
+            }
+        }
+        have_tile = true;
+        stored = stored || update;
+        if (!product) break;
+        meet(true);
+        // ---- H update: the 16-column tiles dealt to the workgroups of the column group
+        for (int v = v0; v < v1; ++v) {
+            const int r = v / C, c = v % C;
+            for (int t = r; t < 16 && 16 * c + t < nt; t += R) {
+                const int tile = 16 * c + t, col = 16 * tile + ec;
+                const unsigned hoff = (unsigned)((2 * tile + (ec >> 3)) * 128 + er * 8 + (ec & 7)) * 4u;
+                const float hold = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rh, tid < 256 ? hoff : kOut, 0, kExchange));
+                constexpr int B = 8;
+                const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(a.part + (int64_t)c * kPRec, 0, ((R - 1) * C + 1) * kPRec * 4, kRsrcFlags);
+                f32x4 ps = {0.f, 0.f, 0.f, 0.f}, gs = {0.f, 0.f, 0.f, 0.f};
+                for (int g0 = w; g0 < R; g0 += 8 * B) {
+                    u32x4 p[B], gg[B];
+                    unsigned pstep = (unsigned)(8 * C * kPRec) * 4u, po = (unsigned)(g0 * C * kPRec) * 4u, go = po;
+                    po = l16 < k ? po + (unsigned)(t * 256 + l16 * 16 + 4 * quad) * 4u : kOut;
+                    go = 8 * lane < k * (k + 1) ? go + (unsigned)(4096 + 4 * lane) * 4u : kOut;
+                    asm volatile("" : "+v"(po), "+v"(go), "+s"(pstep));
+#pragma unroll
+                    for (int i = 0; i < B; ++i) {
+                        p[i] = gg[i] = u32x4{0u, 0u, 0u, 0u};
+                        if (g0 + 8 * i < R) {
+                            p[i] = __builtin_amdgcn_raw_buffer_load_b128(rp, po + i * pstep, 0, kExchange);
+                            gg[i] = __builtin_amdgcn_raw_buffer_load_b128(rp, go + i * pstep, 0, kExchange);
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float x[B], y[B];
+#pragma unroll
+                        for (int i = 0; i < B; ++i) x[i] = __uint_as_float(p[i][j]), y[i] = __uint_as_float(gg[i][j]);
+                        ps[j] += tree_sum(x);
+                        gs[j] += tree_sum(y);
+                    }
+                }
+                __syncthreads();       // the last readers of these
+                *reinterpret_cast<f32x4 *>(Qs + w * 256 + l16 * 16 + 4 * quad) = ps;
+                *reinterpret_cast<f32x4 *>(Gq + w * 256 + lane * 4) = gs;
+                if (tid < 256) Hs[ec * LD + er] = hold;
+                __syncthreads();
+                float sum = 0.f;
+                if (tid < 256) {
+                    float x[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[i] = Qs[i * 256 + tid];
+                    sum = tree_sum(x);
+                } else {
+                    const int hi = er > ec ? er : ec, lo = er > ec ? ec : er;
+                    double x = 0.0;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x += (double)Gq[i * 256 + hi * (hi + 1) / 2 + lo];
+                    put_g(hi < k ? x : 0.0);
+                }
+                __syncthreads();
+                if (tid < 256) {
+                    const float den = dot(Hs + ec * LD, er);
+                    const float h = er < k && col < n ? hold * sum / (den + a.eps) : 0.f;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h), rh, hoff, 0, kExchange);
+                    if (last_h && er < k && col < n) a.H[(int64_t)er * n + col] = h;
+                }
+            }
+        }
+        if (last_h && !a.trail) break;
+        meet(true);
+    }
+    if (looks <= 0) a.W[0] = a.H[0] = __builtin_nanf("");
+}
+
 // G (k x k, ld k) = sum over nb sets of partial 32 x 32 tiles (accumulator layout).
 // Eight lanes share one entry: lane q adds sets q, q+8, ..., a batch of 16 at a time, then the
 // eight sums are combined in a fixed tree, so the result does not depend on timing.
@@ -3036,6 +3568,63 @@ hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const
     if (stream) NMFMU_ONE_PASS(1, kStreamLoad);
     NMFMU_ONE_PASS(1, 0);
 #undef NMFMU_ONE_PASS
+}
+
+// Compute units of the current device (asked for once per device).
+static int compute_units()
+{
+    static std::atomic<int> known[64];
+    int dev = -1, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    if ((cus = known[dev].load(std::memory_order_relaxed)) == 0) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        known[dev].store(cus, std::memory_order_relaxed);
+    }
+    return cus;
+}
+
+// Row tiles per workgroup of the resident plan, 0: the plan does not apply.
+int resident_tiles(int64_t m, int64_t n, int k)
+{
+    if (k > 16 || m > 1 << 16 || n > 1 << 12) return 0;
+    const int64_t cols = (n + 255) / 256, most = compute_units() < 256 ? compute_units() : 256;
+    for (int rt = 1; rt <= 4; rt *= 2) {
+        const int64_t groups = (m + 16 * rt - 1) / (16 * rt);
+        if (groups * cols <= most && (groups <= 32 || rt == 4)) return rt;
+    }
+    return 0;
+}
+
+template <int RT>
+static hipError_t resident_launch(unsigned blocks, hipStream_t st, const ResidentArgs &a)
+{
+    constexpr int kLdsBytes = resident_lds_floats(RT) * (int)sizeof(float);
+    static bool raised = false;      // more dynamic LDS than the default limit: asked for once per process
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&resident_kernel<RT>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    hipLaunchKernelGGL((resident_kernel<RT>), dim3(blocks), dim3(512), kLdsBytes, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool one_for_all)
+{
+    ResidentArgs a = args;
+    if (a.k < 1 || a.k > 16 || a.m < 1 || a.n < 1 || !a.A || !a.part || !a.qpart || !a.hx || !a.wx || !a.sync ||
+        (a.dpart && (!a.gout || !a.gh)) || (tiles != 1 && tiles != 2 && tiles != 4))
+        return hipErrorInvalidValue;
+    const int64_t R = (a.m + 16 * tiles - 1) / (16 * tiles), C = (a.n + 255) / 256;
+    if (R * C > 256) return hipErrorInvalidValue;
+    a.R = (int)R;
+    a.C = (int)C;
+    a.patience = 10000000;     // 100 ms: longer than most kernels that may be in the way
+    const unsigned blocks = one_for_all ? 1u : (unsigned)(R * C);
+    hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync), resident_sync_words(R, C), 0.f, st);
+    if (e != hipSuccess) return e;
+    return tiles == 1 ? resident_launch<1>(blocks, st, a) : tiles == 2 ? resident_launch<2>(blocks, st, a) : resident_launch<4>(blocks, st, a);
 }
 
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st)

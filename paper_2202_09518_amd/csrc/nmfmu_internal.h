@@ -137,6 +137,32 @@ hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const
                            const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, float eps,
                            hipStream_t st, bool update, bool product, double *dpart = nullptr);
 
+// A whole run in one launch (see resident_kernel): up to 16 factors, R x C workgroups, each with a tile of A of
+// 16 * tiles rows (tiles: 1, 2, 4) x 256 columns.
+struct ResidentArgs {
+    const float *A, *Win, *Hin;      // the matrix and the factors as handed in
+    float *W, *H;                    // where they go
+    float *part;                     // shares of W^T A and W^T W: per workgroup [16 tiles][16 factors][16 columns], lower triangle
+    float *qpart;                    // shares of A H^T and H H^T: per workgroup [16 tiles rows][16], [16][16]
+    float *hx;                       // the new H: [group of 8 columns][16 factors][8]
+    float *wx;                       // the new W: [row][16]
+    unsigned *sync;                  // reported in, decision; from word 32 on the letter boxes; zero at the start
+    double *dpart;                   // optional, of the last W update: <A H^T, W> in R C shares,
+    float *gout, *gh;                // R tile sets of W^T W (32 x 32 accumulator layout) and H H^T (k x k)
+    int64_t m, n;
+    int k, R, C;
+    float eps;
+    int nprod;                       // updates of H; updates of W: between them,
+    int lead, trail;                 // one before the first (lead) and one after the last (trail)
+    long long patience;
+};
+constexpr int kResidentPRec = 4096 + 160;     // floats of a workgroup's record in part,
+constexpr int resident_qrec(int tiles) { return 256 * (tiles + 1); }     // and in qpart
+inline int64_t resident_sync_words(int64_t R, int64_t C) { return 32 + R * C * (((R + 31) & ~(int64_t)31) + 32); }
+int resident_tiles(int64_t m, int64_t n, int k);
+// Fills in R, C and patience and clears sync.  one_for_all: one workgroup does the run of all.
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool one_for_all = false);
+
 // out[0] = sum of in[0 .. count), added in a fixed order (strided per thread, then the threads in order).
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st);
 

@@ -1,0 +1,118 @@
+"""A whole run in one launch (up to 16 factors, A on the compute units): edges of the row and column tiles, of the groups
+that exchange and of the factor count, against the oracle; the same bits from a run cut in two, from the allocation-free
+call, from a monitored and a stopped run, and from one workgroup that does the run of all."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from oracle import nmf_oracle as orc
+
+EPS = 1e-16
+# one group of columns and 1, 2, 4 row tiles per workgroup (1, 32, 33, 63, 65 row groups, an odd rest); two to 16 groups
+# of columns; more groups of rows than 16 (owners of no column tile), more groups of columns than row tiles
+SHAPES = [(1, 1), (16, 16), (17, 15), (256, 192), (513, 255), (1000, 256), (1025, 31), (4161, 97), (16380, 256), (40, 257),
+          (100, 513), (600, 1003), (2000, 1201), (1030, 2047), (63, 4096), (4096, 1024)]
+
+
+def data(m, n, k):
+    r = np.random.default_rng(m + 3 * n + 7 * k)
+    return r.random((m, n), dtype=np.float32), r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+
+
+def by_one(nmf, A, m, n, k, W, H, iters):
+    import torch
+
+    fn = nmf.lib().nmfmu_resident_by_one
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
+                   ctypes.c_int32, ctypes.c_float, ctypes.c_void_p]
+    assert fn(A.data_ptr(), m, n, k, W.data_ptr(), H.data_ptr(), iters, EPS, torch.cuda.current_stream().cuda_stream) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n", SHAPES)
+@pytest.mark.parametrize("k", [1, 5, 16])
+def test_runs_of_the_resident_plan(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A, W, H = data(m, n, k)
+    Ad = torch.empty(m * n + 1, device="cuda")[1:]        # not 16-byte aligned: the plan takes any A
+    Ad.copy_(torch.from_numpy(A).reshape(-1))
+    eps = float(np.float32(EPS))
+
+    def run(fn, *iters):
+        Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+        for it in iters:
+            fn(Wd, Hd, it)
+        torch.cuda.synchronize()
+        return Wd, Hd
+
+    ref = run(lambda w, h, it: nmf.nmf_mu_dense(Ad, m, n, k, w, h, it, EPS), 3)
+    Wr, Hr = orc.mu_dense(A, W, H, 3, eps)
+    # three updates of each factor, sums of one sign: a few roundings of 2^-24 per sum
+    assert orc.rel_fro(ref[0].cpu().numpy(), Wr) < 3e-6 and orc.rel_fro(ref[1].cpu().numpy(), Hr) < 3e-6
+    res = {}
+    others = [run(lambda w, h, it: nmf.nmf_mu_dense(Ad, m, n, k, w, h, it, EPS), 2, 1),
+              run(lambda w, h, it: nmf.nmf_mu_dense_noalloc(Ad, m, n, k, w, h, it, EPS), 3),
+              run(lambda w, h, it: by_one(nmf, Ad, m, n, k, w, h, it), 3),
+              run(lambda w, h, it: res.update(mon=nmf.nmf_mu_dense_monitor(Ad, m, n, k, w, h, it, EPS)), 3)]
+    for Wd, Hd in others:
+        assert torch.equal(Wd, ref[0]) and torch.equal(Hd, ref[1])
+    Wd, Hd = run(lambda w, h, it: res.update(tol=nmf.nmf_mu_dense_tol(Ad, m, n, k, w, h, it, EPS, 0.0, 2)), 3)
+    if res["tol"][0] == 3 or (m, n) != (1, 1):            # one entry may be met exactly
+        assert res["tol"][0] == 3 and torch.equal(Wd, ref[0]) and torch.equal(Hd, ref[1])
+    normA2 = float((A.astype(np.float64) ** 2).sum())
+    for it in range(3):
+        W, H = orc.mu_dense(A, W, H, 1, eps)
+        want = orc.residual_dense(A, W, H)
+        # ||A||^2 - 2 <A H^T, W> + <H H^T, W^T W>: three sums of relative error 2^-21 or less that cancel
+        assert abs(res["mon"][it] ** 2 - want ** 2) <= 1e-6 * normA2 + 1e-5 * want ** 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("eps", [0.0, EPS])
+def test_zeros_of_the_resident_plan(eps):
+    """A zero row and a zero column of A empty their row of W and column of H; with eps = 0 padded factors and columns
+    (0 / 0) stay out of the result."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    m, n, k = 70, 300, 3
+    A, W, H = data(m, n, k)
+    if eps:
+        A[5] = 0
+        A[:, 270] = 0
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    nmf.nmf_mu_dense(torch.from_numpy(A).cuda(), m, n, k, Wd, Hd, 3, eps)
+    Wr, Hr = orc.mu_dense(A, W, H, 3, float(np.float32(eps)))
+    assert orc.rel_fro(Wd.cpu().numpy(), Wr) < 3e-6 and orc.rel_fro(Hd.cpu().numpy(), Hr) < 3e-6
+    if eps:
+        assert not Wd[5].any() and not Hd[:, 270].any()
+
+
+@pytest.mark.gpu
+def test_replays_of_a_captured_resident_run():
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    m, n, k = 600, 1003, 7
+    A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+    We, He = W.clone(), H.clone()
+    nmf.nmf_mu_dense(A, m, n, k, We, He, 5, EPS)
+    torch.cuda.synchronize()
+    Wd, Hd = W.clone(), H.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        Wd.copy_(W)
+        Hd.copy_(H)
+        nmf.nmf_mu_dense(A, m, n, k, Wd, Hd, 5, EPS)
+    for _ in range(4):
+        Wd.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Wd, We) and torch.equal(Hd, He)
+        W2, H2 = W.clone(), H.clone()
+        nmf.nmf_mu_dense(A, m, n, k, W2, H2, 5, EPS)      # the same workspace between the replays
+        torch.cuda.synchronize()
+        assert torch.equal(W2, We) and torch.equal(H2, He)
