@@ -1963,6 +1963,265 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// one_pass_kernel for up to 16 factors and many rows, on 16 x 16 x 32 instructions: the same block of 32 NRW rows, the
+// same partials and tile sets per workgroup, but 16 waves with 32 columns and 32 rows each.  With 32 factor slots half
+// of the matrix work, of the planes and of the accumulators would be padding, and 8 waves that pass through a chain of
+// LDS round trips in step left the memory idle for half of it: 357 us per pass on 524288 x 512 at k = 16.  Here a
+// wave's share of a block is half as long, and its registers (four loads, one step of planes, two column tiles) leave room
+// for 16 waves; the running totals stay in registers (8 per lane) instead of going to ppart every 8 blocks.
+//   1. A arrives coalesced (8 rows x 128 bytes per instruction, a block ahead) and goes to the wave's 4 KiB of LDS, 16-byte
+//      chunks flipped by (row / 2) % 8; read back row by lane for A H^T: two 16-row tiles, one step of 32 columns.
+//   2. The column groups' shares of A H^T meet in LDS; thread tid owns entry (row tid / 16, factor tid % 16).
+//   3. The wave reads its tile again, columns by lane (two per lane), all 32 rows the depth of one instruction.
+// The largest products have an accumulator of their own (see resident_kernel).
+// ---------------------------------------------------------------------------
+template <int NRW, int POLICY, bool update, bool product>
+__global__ __launch_bounds__(1024, 1) void one_pass16_kernel(
+    const float *__restrict__ A, const u32x4 *__restrict__ planesH, const float *__restrict__ GH,
+    const float *__restrict__ ghsets, int nbh, const float *W, float *Wnew, float *__restrict__ ppart,
+    float *__restrict__ gout, double *__restrict__ dpart, int64_t rows, int64_t n, int k, float eps)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int NW = 16, NCW = NW / NRW, RB = 32 * NRW, LD = 20;
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    constexpr unsigned kOut = 0x7fffffffu;   // an offset outside every extent: reads as zero
+    float *lds = aht_rows_lds;               // staging tiles: 16 x 1024 floats
+    float *Qp = lds + NW * 1024;             // the waves' shares of A H^T: 16 x 512
+    float *Ws = Qp + NW * 512;               // old rows [RB][LD]
+    float *Gs = Ws + RB * LD;                // H H^T [16][LD]
+    unsigned short *Wp = reinterpret_cast<unsigned short *>(Gs + 16 * LD);   // pieces of the new rows [3][RB / 8][16][8]
+    __shared__ double dsum[NW];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = w / NCW, cw = w % NCW;
+    const int l16 = lane & 15, quad = lane >> 4;
+    float *stg = lds + w * 1024;
+    const unsigned rowb = (unsigned)(n * 4);
+    const int64_t nblocks = (rows + RB - 1) / RB;
+    const bool has_cols = cw * 32 < n;
+    const int lrow = lane >> 3, lch = lane & 7;
+
+    struct Rows { u32x4 a[4]; };       // coalesced: instruction u = rows 8 u .. 8 u + 7, lane = (row, 16-byte chunk)
+    auto load_rows = [&](Rows &s, int64_t blk) {
+        const int64_t rbase = blk * RB + 32 * rw;
+        int64_t av = rows - rbase;                  // rows of this wave's tile that exist
+        av = av < 0 || blk >= nblocks || !has_cols ? 0 : (av > 32 ? 32 : av);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(A + (av ? rbase * n + cw * 32 : 0)), 0,
+            (int)(av ? av * (int64_t)rowb - cw * 128 : 0), kRsrcFlags);
+        unsigned lo = (cw * 32 + lch * 4 < n) ? (unsigned)lrow * rowb + (unsigned)lch * 16 : kOut;
+        asm volatile("" : "+v"(lo));   // the rows' offsets are added here, not kept in registers across the block
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s.a[u] = __builtin_amdgcn_raw_buffer_load_b128(r, lo + (unsigned)(8 * u) * rowb, 0, POLICY);
+    };
+    const int er = tid >> 4, ec = tid & 15;         // this thread's entry of the block's rows of W
+    const bool entry = tid < RB * 16;
+    float wnext;
+    auto load_w = [&](int64_t blk) {
+        int64_t av = rows - blk * RB;
+        av = av < 0 || blk >= nblocks ? 0 : (av > RB ? RB : av);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(W + (av ? blk * RB * k : 0)), 0, (int)(av * k * 4), kRsrcFlags);
+        wnext = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, entry && ec < k ? (unsigned)(er * k + ec) * 4u : kOut, 0, 0));
+    };
+    u32x4 bp[3];                       // planes of H^T (32 factor slots), this wave's 32 columns
+    if (update) {
+        const int64_t ngroups = (n + 7) >> 3, g = (int64_t)cw * 4;
+        int64_t ng = ngroups - g;                   // 8-column groups of planes that exist
+        ng = ng < 0 ? 0 : (ng > 4 ? 4 : ng);
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u32x4 *>(planesH + (ng ? g : 0) * 3 * 32), 0, (int)(ng * 3 * 32 * 16), kRsrcFlags);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+            bp[pl] = __builtin_amdgcn_raw_buffer_load_b128(rp, (unsigned)((quad * 3 + pl) * 32 + l16) * 16, 0, 0);
+    }
+    Rows ra;
+    int64_t blk = blockIdx.x;
+    load_rows(ra, blk);
+    load_w(blk);
+    if (update) {
+        // H H^T: complete, or the H update's tile sets added up, a batch of 16 at a time
+        constexpr int B = 16;
+        if (tid < 256) {
+            const bool in = ec < k && er < k;
+            const int pos = ((er & 3) + 4 * (er >> 3)) * 64 + ec + 32 * ((er >> 2) & 1);
+            float g = 0.f;
+            if (GH) {
+                g = GH[in ? er * k + ec : 0];
+            } else {
+                for (int b = 0; b < nbh; b += B) {
+                    float t[B];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) t[u] = ghsets[(b + u < nbh ? b + u : 0) * 1024 + pos];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) t[u] = b + u < nbh ? t[u] : 0.f;
+                    g += tree_sum(t);
+                }
+            }
+            Gs[er * LD + ec] = in ? g : 0.f;
+        }
+        __syncthreads();
+    }
+
+    f32x4 acc[2][2], tot[2], gacc = {0.f, 0.f, 0.f, 0.f};      // acc: [column parity][small products, large ones]
+#pragma unroll
+    for (int q = 0; q < 2; ++q) acc[q][0] = acc[q][1] = tot[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    double dacc = 0.0;
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};   // smallest first
+    int done = 0;
+    auto settle = [&]() {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            tot[q] += acc[q][0] + acc[q][1];
+            acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        done = 0;
+    };
+    for (; blk < nblocks; blk += gridDim.x) {
+        const int64_t i0 = blk * RB, next = blk + gridDim.x;
+        const float wold = wnext;
+        if (entry) Ws[er * LD + ec] = wold;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int row = 8 * u + lrow;
+            *reinterpret_cast<f32x4 *>(stg + row * 32 + ((lch ^ ((row >> 1) & 7)) << 2)) = __builtin_bit_cast(f32x4, ra.a[u]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(ra, next);
+        load_w(next);
+        __builtin_amdgcn_sched_barrier(0);
+        float wn = wold;
+        if (update) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int row = 16 * t + l16, sw = (row >> 1) & 7;
+                const f32x4 x0 = *reinterpret_cast<const f32x4 *>(stg + row * 32 + (((2 * quad) ^ sw) << 2));
+                const f32x4 x1 = *reinterpret_cast<const f32x4 *>(stg + row * 32 + (((2 * quad + 1) ^ sw) << 2));
+                u32x4 at[3];
+                cut2(x0.x, x0.y, at, 0);
+                cut2(x0.z, x0.w, at, 1);
+                cut2(x1.x, x1.y, at, 2);
+                cut2(x1.z, x1.w, at, 3);
+                f32x4 q[2];
+                q[0] = q[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 6; ++e) q[e / 5] = mfma_bf16_16(at[PA[e]], bp[PB[e]], q[e / 5]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) Qp[w * 512 + (16 * t + 4 * quad + v) * 16 + l16] = q[0][v] + q[1][v];
+            }
+            float den = 0.f;           // W H H^T of this thread's entry (its wave wrote the row above)
+            if (entry) {
+                float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+                for (int d = 0; d < 16; d += 4) {
+                    const f32x4 g = *reinterpret_cast<const f32x4 *>(Gs + ec * LD + d);
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(Ws + er * LD + d);
+                    s0 += x.x * g.x;
+                    s1 += x.y * g.y;
+                    s0 += x.z * g.z;
+                    s1 += x.w * g.w;
+                }
+                den = s0 + s1;
+            }
+            __syncthreads();
+            if (entry) {
+                const float *src = Qp + (er >> 5) * NCW * 512 + (er & 31) * 16 + ec;
+                float t[NCW];
+#pragma unroll
+                for (int c = 0; c < NCW; ++c) t[c] = src[c * 512];
+                const float qs = tree_sum(t);
+                wn = 0.f;
+                if (i0 + er < rows && ec < k) {
+                    wn = wold * qs / (den + eps);
+                    if (Wnew) Wnew[(i0 + er) * k + ec] = wn;
+                    dacc += (double)qs * (double)wn;
+                }
+            }
+        } else {
+            __syncthreads();           // the last block's readers of Wp are done
+        }
+        gacc = __builtin_amdgcn_mfma_f32_16x16x4f32(wn, wn, gacc, 0, 0, 0);     // the wave's four rows (no entry: zeros)
+        if (product) {
+            if (entry) {
+                unsigned h, m, l;
+                split3(wn, h, m, l);
+                unsigned short *dst = Wp + ((er >> 3) * 16 + ec) * 8 + (er & 7);
+                dst[0] = (unsigned short)(h >> 16);
+                dst[(RB / 8) * 128] = (unsigned short)(m >> 16);
+                dst[2 * (RB / 8) * 128] = (unsigned short)(l >> 16);
+            }
+            __syncthreads();
+            u32x2 x[8];                // columns 2 l16, 2 l16 + 1 of rows 8 quad + e
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int row = 8 * quad + e;
+                x[e] = *reinterpret_cast<const u32x2 *>(stg + row * 32 + (((l16 >> 1) ^ ((row >> 1) & 7)) << 2) + ((l16 & 1) << 1));
+            }
+            u32x4 wt[3];
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) wt[pl] = reinterpret_cast<const u32x4 *>(Wp)[(pl * (RB / 8) + 4 * rw + quad) * 16 + l16];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                u32x4 at[3];
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) cut2(__uint_as_float(x[2 * pr][q]), __uint_as_float(x[2 * pr + 1][q]), at, pr);
+#pragma unroll
+                for (int e = 0; e < 6; ++e) acc[q][e / 5] = mfma_bf16_16(at[PA[e]], wt[PB[e]], acc[q][e / 5]);
+            }
+            if (++done == kOnePassFlush) settle();
+        } else {
+            __syncthreads();           // the shares of A H^T are read; the next block writes its own
+        }
+    }
+    if (product) {
+        settle();
+        if (NRW > 1) {                 // the row tiles of a column group in order
+            __syncthreads();
+            if (rw > 0) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) *reinterpret_cast<f32x4 *>(stg + (q * 64 + lane) * 4) = tot[q];
+            }
+            __syncthreads();
+            if (rw == 0) {
+#pragma unroll
+                for (int r = 1; r < NRW; ++r)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) tot[q] += *reinterpret_cast<const f32x4 *>(lds + (r * NCW + cw) * 1024 + (q * 64 + lane) * 4);
+            }
+        }
+        if (rw == 0) {                 // lane: factor l16, columns 8 quad .. 8 quad + 7 of the wave's
+            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(ppart + (int64_t)blockIdx.x * k * n, 0, k * (int)rowb, kRsrcFlags);
+#pragma unroll
+            for (int v = 0; v < 4; v += 2) {
+                const int col = cw * 32 + 8 * quad + 2 * v;
+                const f32x4 val = {tot[0][v], tot[1][v], tot[0][v + 1], tot[1][v + 1]};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), ro, l16 < k && col < n ? (unsigned)l16 * rowb + (unsigned)col * 4u : kOut, 0, 0);
+            }
+        }
+    }
+    if (dpart) {
+        for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
+        if (lane == 0) dsum[w] = dacc;
+    }
+    // this workgroup's W^T W: the waves' tiles added in wave order
+    __syncthreads();
+    *reinterpret_cast<f32x4 *>(Qp + w * 256 + l16 * 16 + 4 * quad) = gacc;
+    __syncthreads();
+    {
+        // a tile set in the layout of the 32 x 32 accumulators; beyond 16 factors zero
+        const int v = tid >> 6, r = acc_row(v, (tid >> 5) & 1), c = tid & 31;
+        float t = 0.f;
+        if (r < 16 && c < 16)
+            for (int ww = 0; ww < NW; ++ww) t += Qp[ww * 256 + c * 16 + r];
+        gout[(int64_t)blockIdx.x * 1024 + tid] = t;
+    }
+    if (dpart && tid == 0) {
+        double t = 0.0;
+        for (int i = 0; i < NW; ++i) t += dsum[i];
+        dpart[blockIdx.x] = t;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // A whole run in one launch, for matrices that the chip holds on its compute units (k <= 16; the "resident
 // plan").  What such a run costs otherwise is launches and trips to L2: four dependent kernels of 3 to 12 us
 // per iteration whatever the work in them.  Here a workgroup keeps a tile of A, 16 RT rows x 256 columns, on its
@@ -3548,6 +3807,24 @@ static hipError_t one_pass_launch(dim3 grid, hipStream_t st, const float *A, con
     return hipGetLastError();
 }
 
+template <int NRW, int POLICY, bool update, bool product>
+static hipError_t one_pass16_launch(dim3 grid, hipStream_t st, const float *A, const u32x4 *planesH, const float *GH,
+                                    const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, double *dpart,
+                                    int64_t rows, int64_t n, int k, float eps)
+{
+    constexpr int kLdsBytes = (16 * 1024 + 16 * 512 + 32 * NRW * 20 + 16 * 20 + 3 * 4 * NRW * 64) * (int)sizeof(float);
+    static bool raised = false;      // more dynamic LDS than the default limit: asked for once per process
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&one_pass16_kernel<NRW, POLICY, update, product>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    hipLaunchKernelGGL((one_pass16_kernel<NRW, POLICY, update, product>), grid, dim3(1024), kLdsBytes, st, A, planesH, GH, ghsets, nbh, W, Wnew,
+                       ppart, gout, dpart, rows, n, k, eps);
+    return hipGetLastError();
+}
+
 hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const void *planesH, const float *GH,
                            const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, float eps,
                            hipStream_t st, bool update, bool product, double *dpart)
@@ -3556,11 +3833,24 @@ hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)one_pass_blocks(rows, n));
     const u32x4 *ph = static_cast<const u32x4 *>(planesH);
+    const bool stream = stream_a(rows, n);
+#define NMFMU_ONE_PASS16(NRW, POL) \
+    return !update ? one_pass16_launch<NRW, POL, false, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
+         : product ? one_pass16_launch<NRW, POL, true, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
+                   : one_pass16_launch<NRW, POL, true, false>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps)
+    if (k <= 16) {
+        if (n <= 256) {
+            if (stream) NMFMU_ONE_PASS16(2, kStreamLoad);
+            NMFMU_ONE_PASS16(2, 0);
+        }
+        if (stream) NMFMU_ONE_PASS16(1, kStreamLoad);
+        NMFMU_ONE_PASS16(1, 0);
+    }
+#undef NMFMU_ONE_PASS16
 #define NMFMU_ONE_PASS(NRW, POL) \
     return !update ? one_pass_launch<NRW, POL, false, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
          : product ? one_pass_launch<NRW, POL, true, true>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps) \
                    : one_pass_launch<NRW, POL, true, false>(grid, st, A, ph, GH, ghsets, nbh, W, Wnew, ppart, gout, dpart, rows, n, k, eps)
-    const bool stream = stream_a(rows, n);
     if (n <= 256) {
         if (stream) NMFMU_ONE_PASS(2, kStreamLoad);
         NMFMU_ONE_PASS(2, 0);
