@@ -146,6 +146,7 @@ struct DensePlan {
     int64_t a_rows = 0;        // mirrored: rows of A itself when those of W are padded (0: the same)
     Common c;
     float *ppart;              // row-split partials of either pass
+    float *psum;               // one-pass plan: the workgroups' shares of W^T A added up to kShareGroups
     void *planes;              // bf16 piece planes of the factor a pass contracts with
     void *planes2;             // row plan: piece planes of H^T (planes then holds those of W)
     float *At, *Wt, *Ht;       // mirrored only
@@ -187,9 +188,13 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
     return p;
 }
 
+// One-pass plan: up to this many shares and tile sets are added by the H update's workgroups themselves.
+constexpr int kFewSets = 32;
+
 size_t one_pass_bytes(int64_t m, int64_t n, int k)
 {
-    return common_bytes(k) + align_up((size_t)one_pass_blocks(m, n) * k * n * sizeof(float)) + align_up(planes_bytes(n));
+    return common_bytes(k) + align_up((size_t)one_pass_blocks(m, n) * k * n * sizeof(float)) + align_up(planes_bytes(n)) +
+           align_up(one_pass_blocks(m, n) > kFewSets ? (size_t)kShareGroups * k * n * sizeof(float) : 0);
 }
 
 DensePlan carve_resident(Carve &cv, int64_t m, int64_t n, int k, int tiles)
@@ -223,6 +228,7 @@ DensePlan carve_one_pass(void *ws, int64_t m, int64_t n, int k)
     p.c = carve_common(cv, k);
     p.ppart = cv.take<float>((size_t)one_pass_blocks(m, n) * k * n);
     p.planes2 = cv.take<char>(planes_bytes(n));
+    p.psum = cv.take<float>(one_pass_blocks(m, n) > kFewSets ? (size_t)kShareGroups * k * n : 0);
     p.planes = nullptr;
     p.At = p.Wt = p.Ht = nullptr;
     p.s1 = p.s2 = 0;
@@ -476,8 +482,7 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         // Per iteration: the pass that finishes the previous one (A H^T, the W update) and leaves W^T A
         // and W^T W of the new W as one share per workgroup, then the H update; the last W update has a
         // pass of its own without W^T A.  Up to kFewSets tile sets are added by the consumer's
-        // workgroups themselves, more by a launch of their own.
-        constexpr int kFewSets = 32;
+        // workgroups themselves, more by a launch of their own (for W^T W: with the shares of W^T A).
         const int nbw = one_pass_blocks(m, n), nbh = factor_update_blocks(n);
         auto pass = [&](int done, bool product) -> int {       // `done` H updates so far
             const bool report = done && mon && (!mon->last_only || done == iters);
@@ -497,9 +502,10 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (int rc = pass(it, true)) return rc;
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-            if (nbw > kFewSets) NMF_HIP(launch_gram_sum(c.gwp, nbw, k, c.gw, st));
-            NMF_HIP(launch_factor_update(H, nullptr, p.ppart, nbw, nbw > kFewSets ? c.gw : nullptr, c.gwp, nbw, c.ghp, k, n,
-                                         eps, st, map, p.planes2));
+            const bool many = nbw > kFewSets;
+            if (many) NMF_HIP(launch_share_sum(p.ppart, nbw, k, n, p.psum, c.gwp, c.gw, st));
+            NMF_HIP(launch_factor_update(H, nullptr, many ? p.psum : p.ppart, many ? kShareGroups : nbw, many ? c.gw : nullptr, c.gwp,
+                                         nbw, c.ghp, k, n, eps, st, map, p.planes2));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (it == iters - 1)

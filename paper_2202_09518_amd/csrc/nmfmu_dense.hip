@@ -2748,12 +2748,11 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
 // G (k x k, ld k) = sum over nb sets of partial 32 x 32 tiles (accumulator layout).
 // Eight lanes share one entry: lane q adds sets q, q+8, ..., a batch of 16 at a time, then the
 // eight sums are combined in a fixed tree, so the result does not depend on timing.
-__global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__ gpart, int nb, int k,
-                                                       float *__restrict__ G)
+__device__ __forceinline__ void gram_sum(const float *__restrict__ gpart, int nb, int k, float *__restrict__ G, int block)
 {
     const int kt = (k + 31) >> 5;
     const int64_t stride = (int64_t)kt * kt * 1024;
-    const int gid = blockIdx.x * 256 + threadIdx.x;
+    const int gid = block * 256 + threadIdx.x;
     const int entry = gid >> 3, q = gid & 7;
     const bool ok = entry < kt * kt * 1024;
     const float *src = gpart + (ok ? entry : 0);
@@ -2776,6 +2775,41 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__
         const int r1 = 32 * (tile / kt) + acc_row(v, l >> 5), r2 = 32 * (tile % kt) + (l & 31);
         if (r1 < k && r2 < k) G[r1 * k + r2] = s;
     }
+}
+__global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__ gpart, int nb, int k,
+                                                       float *__restrict__ G)
+{
+    gram_sum(gpart, nb, k, G, blockIdx.x);
+}
+
+// The shares of W^T A that the workgroups of a one-pass launch leave (nb of count4 x 4 floats), added up to kShareGroups
+// for the H update, and beside them the sum of their Gram tile sets.  The H update alone, 16 or 32 columns a workgroup,
+// has 10 to 32 of them for the 8 MiB of 256 shares: 17.5 us at k = 16, n = 512.
+__global__ __launch_bounds__(256) void share_sum_kernel(const float *__restrict__ ppart, int nb, int count4, f32x4 *__restrict__ psum,
+                                                        int pblocks, const float *__restrict__ gpart, int k, float *__restrict__ G)
+{
+    if ((int)blockIdx.x >= pblocks) {
+        gram_sum(gpart, nb, k, G, (int)blockIdx.x - pblocks);
+        return;
+    }
+    const int t = blockIdx.x * 256 + threadIdx.x, e = t % count4, g = t / count4;
+    if (g >= kShareGroups) return;
+    const int per = (nb + kShareGroups - 1) / kShareGroups, s0 = g * per, s1 = s0 + per < nb ? s0 + per : nb;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(ppart) + e;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int b = s0; b < s1; b += 16) {
+        f32x4 x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = src[(int64_t)(b + u < s1 ? b + u : s0) * count4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float y[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) y[u] = b + u < s1 ? x[u][j] : 0.f;
+            sum[j] += tree_sum(y);
+        }
+    }
+    psum[(int64_t)g * count4 + e] = sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -3915,6 +3949,15 @@ hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, 
     hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync), resident_sync_words(R, C), 0.f, st);
     if (e != hipSuccess) return e;
     return tiles == 1 ? resident_launch<1>(blocks, st, a) : tiles == 2 ? resident_launch<2>(blocks, st, a) : resident_launch<4>(blocks, st, a);
+}
+
+hipError_t launch_share_sum(const float *ppart, int nb, int k, int64_t n, float *psum, const float *gtiles, float *G, hipStream_t st)
+{
+    if (k < 1 || k > 32 || n % 4 || nb < 1) return hipErrorInvalidValue;
+    const int count4 = (int)(k * n / 4), pblocks = (count4 * kShareGroups + 255) / 256;
+    hipLaunchKernelGGL(share_sum_kernel, dim3((unsigned)pblocks + 32u), dim3(256), 0, st, ppart, nb, count4, reinterpret_cast<f32x4 *>(psum),
+                       pblocks, gtiles, k, G);
+    return hipGetLastError();
 }
 
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st)

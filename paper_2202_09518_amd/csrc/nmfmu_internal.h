@@ -137,6 +137,11 @@ hipError_t launch_one_pass(const float *A, int64_t rows, int64_t n, int k, const
                            const float *ghsets, int nbh, const float *W, float *Wnew, float *ppart, float *gout, float eps,
                            hipStream_t st, bool update, bool product, double *dpart = nullptr);
 
+// psum (kShareGroups x k x n) = the nb shares of W^T A of a one-pass launch, added up group by group; G = the sum of its
+// nb tile sets.
+constexpr int kShareGroups = 16;
+hipError_t launch_share_sum(const float *ppart, int nb, int k, int64_t n, float *psum, const float *gtiles, float *G, hipStream_t st);
+
 // A whole run in one launch (see resident_kernel): up to 16 factors, R x C workgroups, each with a tile of A of
 // 16 * tiles rows (tiles: 1, 2, 4) x 256 columns.
 struct ResidentArgs {
