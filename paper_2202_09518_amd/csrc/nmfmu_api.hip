@@ -46,6 +46,7 @@ struct State {
     hipEvent_t ev_copied[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev_freed[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev_entry = nullptr;
+    double *pinned = nullptr;   // host memory that kernels write: results of blocking calls
     // rank-sliced out-of-memory path: up to kMaxSlots staging slots, factor rows copied back
     void *sl_stage = nullptr;
     size_t sl_stage_bytes = 0;
@@ -1040,6 +1041,8 @@ int nmf_mu_release(void)
     }
     if (g.ev_entry) NMF_HIP(hipEventDestroy(g.ev_entry));
     g.ev_entry = nullptr;
+    if (g.pinned) NMF_HIP(hipHostFree(g.pinned));
+    g.pinned = nullptr;
     if (g.copy_stream) NMF_HIP(hipStreamDestroy(g.copy_stream));
     g.copy_stream = nullptr;
     for (int i = 0; i < 16; ++i) {
@@ -1745,16 +1748,35 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
 // ---- objective and tolerance-driven run ---------------------------------------
 
 namespace {
+// Host memory for the few doubles a blocking call waits for, written by the kernel that has them: a copy to the caller's
+// pageable memory costs 8 us more.  Null if there is none (the value is then copied).  Used under the lock only, which a
+// blocking call holds until it has read the value.
+double *pinned_doubles()
+{
+    if (!g.pinned && hipHostMalloc(reinterpret_cast<void **>(&g.pinned), kAlign, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        g.pinned = nullptr;
+    }
+    return g.pinned;
+}
+
+// Waits for `st` and reads the double that a kernel on it wrote to `at` (pinned host memory or device memory).
+int read_double(const double *at, double *out_host, hipStream_t st)
+{
+    const bool host = g.pinned && at >= g.pinned && at < g.pinned + kAlign / sizeof(double);
+    if (!host) NMF_HIP(hipMemcpyAsync(out_host, at, sizeof(double), hipMemcpyDeviceToHost, st));
+    NMF_HIP(hipStreamSynchronize(st));
+    if (host) *out_host = *static_cast<const volatile double *>(at);
+    return NMF_OK;
+}
+
 // ||A - W H||_F into *out_host; synchronises `st`.  Scratch sits behind the dense plan.
 int residual_to_host(const float *A, int64_t m, int64_t n, int k, const float *W, const float *H,
                      double *scratch, double *out_host, hipStream_t st)
 {
-    const int64_t blocks = (m + 31) / 32;
-    NMF_HIP(launch_residual(A, m, n, k, W, H, scratch + 1, scratch, st));
-    NMF_HIP(hipMemcpyAsync(out_host, scratch, sizeof(double), hipMemcpyDeviceToHost, st));
-    NMF_HIP(hipStreamSynchronize(st));
-    (void)blocks;
-    return NMF_OK;
+    double *pin = pinned_doubles(), *out = pin ? pin : scratch;
+    NMF_HIP(launch_residual(A, m, n, k, W, H, scratch + 1, out, st));
+    return read_double(out, out_host, st);
 }
 // the same for a run that may work on a copy of A with padded columns
 size_t run_scratch_bytes(int64_t m, int64_t n)
@@ -1802,6 +1824,7 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     mon.dpart = cv.take<double>(kFinMaxBlocks);
     mon.normA2 = cv.take<double>(4097);
     mon.out = cv.take<double>(1);
+    if (double *pin = pinned_doubles()) mon.out = pin + 1;
     mon.res = scratch;
     mon.last_only = true;
     int done = 0;
@@ -1826,8 +1849,7 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
             // (no pass over A); its error is bounded by the fp32 sums of its three terms.  Only
             // when it comes within that bound of the tolerance is the exact value needed.
             double approx = 0.0;
-            NMF_HIP(hipMemcpyAsync(&approx, mon.out, sizeof(double), hipMemcpyDeviceToHost, st));
-            NMF_HIP(hipStreamSynchronize(st));
+            if (int rc = read_double(mon.out, &approx, st)) return rc;
             const double slack = 1e-3 * approx + 2e-6 * normA2 / (approx > 1e-300 ? approx : 1e-300);
             if (approx > tol + slack) {
                 res = approx;
