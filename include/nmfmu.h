@@ -129,7 +129,7 @@ int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k,
  * nmf_mu_dense for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments and result as nmf_mu_dense on its plans without copies of A (the
- * one-pass plan where it applies and fits, else the row plan, else the small
+ * resident and the one-pass plan where they apply and fit, else the row plan, else the small
  * plan), k <= NMF_MU_MAX_K.  The scratch memory
  * (row-split partial sums, operand planes of W, Gram scratch) is a fixed array
  * of NMF_MU_NOALLOC_SCRATCH_BYTES in the library's device image instead of

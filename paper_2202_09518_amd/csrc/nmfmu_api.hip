@@ -1528,13 +1528,13 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     // leaves behind: <A H^T, W>, H H^T, and W^T W of the new W (computed here; the next iteration
     // computes the same matrix again for its H update).
     auto iteration = [&](double *out) -> int {
-        NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, st, ld));
+        NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, c.counters, st, ld));
         NMF_HIP(launch_aht_csr(colptr, rowidx, cvals, part_c, long_c, long_n + 1, k, Wx, c.gw, Ht, eps, nnz, n, m, st, false, nullptr, false, ld, ld));   // H update on H^T
-        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st, ld));
+        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, c.counters, st, ld));
         NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, Wx, eps, nnz, m, n, st, false,
                                out ? dpart : nullptr, false, ld, ld));                                                       // W update
         if (out) {
-            NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, st, ld));
+            NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, c.counters, st, ld));
             NMF_HIP(launch_objective(dpart, kCsrDparts, c.gw, c.gh, k, normA2, out, st));
         }
         return NMF_OK;
@@ -1542,8 +1542,8 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
     if (tolp) {
         // objective of the factors as given: the W pass without its update
         double res = 0.0;
-        NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, st, ld));
-        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st, ld));
+        NMF_HIP(launch_gram_w_wide(Wx, m, k, c.gw, c.gwp, c.counters, st, ld));
+        NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, c.counters, st, ld));
         NMF_HIP(launch_aht_csr(rowptr, colidx, vals, part_r, long_r, long_n, k, Ht, c.gh, Wx, eps, nnz, m, n, st, false, dpart, true, ld, ld));
         NMF_HIP(launch_objective(dpart, kCsrDparts, c.gw, c.gh, k, normA2, obj, st));
         NMF_HIP(hipMemcpyAsync(&res, obj, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1736,9 +1736,9 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
             NMF_HIP(hipEventRecord(g.sl_freed[slot], st));
         }
         if (s < iters) {
-            NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, st));
+            NMF_HIP(launch_gram_w_wide(W, m, k, c.gw, c.gwp, c.counters, st));
             NMF_HIP(launch_row_update(Ht, Num, c.gw, k, n, eps, st));
-            NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, st));
+            NMF_HIP(launch_gram_w_wide(Ht, n, k, c.gh, c.ghp, c.counters, st));
         }
     }
     NMF_HIP(launch_transpose(Ht, n, k, H, st));

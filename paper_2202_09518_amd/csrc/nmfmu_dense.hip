@@ -11,8 +11,9 @@
 //       reduction of the matrix instruction
 //   factor_update_kernel : sums the partials, updates H (or W^T in the mirrored
 //       plan), writes the operand planes and the Gram tiles of the new factor
-//   one_pass_kernel : up to 512 columns, A H^T, the W update and W^T A of the next iteration in one
-//       reading of A
+//   one_pass_kernel, one_pass16_kernel : up to 512 columns, A H^T, the W update and W^T A of the next
+//       iteration in one reading of A
+//   resident_kernel : up to 16 factors, a whole run in one launch while the compute units hold A
 //   aht_rows_kernel : A H^T on the row-major A (coalesced loads turned through
 //       LDS) with the W update, the planes and the Gram tiles of the new W fused
 //   aht_pass_kernel : the older direct A H^T kernel (lanes down the rows), for
@@ -329,6 +330,79 @@ __global__ __launch_bounds__(512) void gram_kernel(const float *__restrict__ X, 
         if (r1 < k && r2 < k) G[r1 * k + r2] = s;
     }
     if (tid == 0) counters[blockIdx.y] = 0u;
+}
+
+// X^T X of a factor of up to 16 columns (rows ld apart) in one launch: 16 x 16 x 4 instructions, a share (lower triangle)
+// per workgroup, the last workgroup to arrive adds the shares up, all its loads in flight together.  Sums of
+// more than 16 rows are in double: an entry's error is the same for all rows of the other factor.  A tile set per
+// workgroup and a launch for their sum took 4.8 + 3.9 us on 65536 x 12, a chain of trips to memory each.
+constexpr int kGram16Blocks = 64;
+__global__ __launch_bounds__(512) void gram16_kernel(const float *__restrict__ X, int64_t rows, int k, int ld, float *__restrict__ G,
+                                                     float *shares, unsigned *counter)
+{
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    constexpr unsigned kOut = 0x7fffffffu;   // an offset outside the extent: reads as zero, stores nothing
+    constexpr int kExchange = 16;            // sc1: coherent over the whole device
+    constexpr int UN = 16, ROW = 136, GR = 15;     // ROW: floats of a share; GR x ROW / 4 threads add them up
+    __shared__ double sums[8 * 256];         // of the waves, then of groups of shares
+    __shared__ unsigned ticket;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, quad = lane >> 4;
+    const int64_t per = (rows + gridDim.x - 1) / gridDim.x, r0 = blockIdx.x * per, r1 = r0 + per < rows ? r0 + per : rows;
+    double tot[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t base = r0 + 4 * w; base < r1; base += 32 * UN) {
+        f32x4 acc[4];          // 16 rows each
+        float x[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int64_t row = base + 32 * u + quad;
+            const bool in = row < r1 && l16 < k;
+            const float v = X[in ? row * ld + l16 : 0];
+            x[u] = in ? v : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) acc[u & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u], x[u], u < 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[u & 3], 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tot[v] += ((double)acc[0][v] + (double)acc[1][v]) + ((double)acc[2][v] + (double)acc[3][v]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sums[w * 256 + l16 * 16 + 4 * quad + v] = tot[v];
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(shares, 0, (int)(gridDim.x * ROW * 4), kRsrcFlags);
+    const int er = (tid >> 4) & 15, ec = tid & 15;
+    if (tid < 256) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += sums[i * 256 + tid];
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)s), rs, er >= ec && er < k ? (unsigned)(blockIdx.x * ROW + er * (er + 1) / 2 + ec) * 4u : kOut, 0, kExchange);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (ticket != gridDim.x - 1) return;
+    const int vec = tid % (ROW / 4), g = tid / (ROW / 4);
+    if (g < GR) {
+        constexpr int M = (kGram16Blocks + GR - 1) / GR;
+        u32x4 x[M];
+#pragma unroll
+        for (int i = 0; i < M; ++i) x[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)((g + GR * i) * ROW + 4 * vec) * 4u, 0, kExchange);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < M; ++i) s += (double)__uint_as_float(x[i][j]);
+            sums[g * ROW + 4 * vec + j] = s;
+        }
+    }
+    __syncthreads();
+    if (tid < 256 && er < k && ec < k) {
+        const int hi = er > ec ? er : ec, lo = er > ec ? ec : er;
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < GR; ++i) s += sums[i * ROW + hi * (hi + 1) / 2 + lo];
+        G[er * k + ec] = (float)s;
+    }
+    if (tid == 0) *counter = 0u;
 }
 
 // Side job of the pass kernels: the Gram tiles a finisher left behind (nsets sets of
@@ -1652,9 +1726,9 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
 // instead of 1.9e-7, for 1 to 3 % less time).
 // The pieces of W never leave the chip, and A comes from memory once per iteration instead of
 // twice.  One workgroup (8 waves, 116 KiB of LDS) fills a compute unit; its chain of LDS round
-// trips, not the memory, bounds it: 314 us at best and 357 on average in a profiler's trace
-// on 524288 x 512 at k = 16 (3.4 TB/s of A, read once)
-// against 215 us for the W^T A pass and 340 us for aht_rows_kernel there.  Two chunks of columns
+// trips, not the memory, bounds it: 200000 x 400 at k = 30 takes 141 us per iteration.  It runs for 17 to 32
+// factors; up to 16 one_pass16_kernel does (524288 x 512, k = 16, per pass: 215 us for the W^T A pass and 340 for
+// aht_rows_kernel, 357 for this kernel, about 210 for that one).  Two chunks of columns
 // per wave (n up to 1024), with the second reading from the caches, gained 0.95 to 1.15x only,
 // three lost to the row plan (0.73 to 1.01x): hence the limit.
 // ---------------------------------------------------------------------------
@@ -3378,8 +3452,16 @@ hipError_t launch_gram_w(const float *X, int64_t rows, int k, float *G, float *g
     return hipGetLastError();
 }
 
-hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, hipStream_t st, int ld)
+// 1024 rows per workgroup, two trips; beyond, 256 workgroups and a launch for the sum read faster.
+constexpr int64_t kGram16Rows = 1 << 16;
+hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, unsigned *counters, hipStream_t st, int ld)
 {
+    if (k <= 16 && rows <= kGram16Rows) {
+        int64_t nb = (rows + 63) / 64;
+        if (nb > kGram16Blocks) nb = kGram16Blocks;
+        hipLaunchKernelGGL(gram16_kernel, dim3((unsigned)nb), dim3(512), 0, st, X, rows, k, ld ? ld : k, G, tiles, counters);
+        return hipGetLastError();
+    }
     const int kt = k_tiles(k);
     // 256 rows per workgroup: two trips of eight row pairs per wave (65536 x 12: 7.8 us with 512 rows)
     int64_t nb = (rows + 255) / 256;
@@ -3907,7 +3989,13 @@ static int compute_units()
     return cus;
 }
 
-// Row tiles per workgroup of the resident plan, 0: the plan does not apply.
+// Row tiles per workgroup of the resident plan, 0: the plan does not apply.  One workgroup per compute unit, so the tiles
+// of A must be at most 256; within that the plan was faster at every size tried (us per iteration of 50, other plans ->
+// this one): 200 x 150 16.8 -> 6.6, 512 x 512 17.4 -> 10.1, 64 x 4096 33.4 -> 12.7, 2048 x 2048 31.9 -> 12.2, 8000 x 512
+// 34.8 -> 17.0, 16384 x 256 33.4 -> 18.0, 16384 x 64 25.5 -> 15.0; two iterations per call 18.2 -> 10.6 to 40.5 -> 20.2.
+// Low tiles first, as a workgroup's own work is shorter, but not more than 32 row groups if higher ones avoid that:
+// every owner of columns adds up a share per group (2000 x 192: 125 groups 10.4 us, 32 groups 8.4; 4096 x 256: 256 groups
+// 15.8, 64 groups 9.6).
 int resident_tiles(int64_t m, int64_t n, int k)
 {
     if (k > 16 || m > 1 << 16 || n > 1 << 12) return 0;

@@ -40,7 +40,9 @@ hipError_t launch_gram_w(const float *X, int64_t rows, int k, float *G, float *g
                          unsigned *counters, hipStream_t st);
 // The same for a long factor (millions of rows): up to kFinMaxBlocks blocks write partial tiles
 // (tiles: kFinMaxBlocks sets), summed by launch_gram_sum.
-hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, hipStream_t st, int ld = 0);
+// counters: as for launch_gram_w.
+hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, unsigned *counters, hipStream_t st,
+                              int ld = 0);
 // G (k x k, ld k) = X X^T for X k x cols (row-major, ld cols).
 hipError_t launch_gram_h(const float *X, int k, int64_t cols, float *G, float *gpart,
                          unsigned *counters, hipStream_t st);
