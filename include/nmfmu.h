@@ -89,10 +89,10 @@ const char *nmf_last_error(void);
  *   iters  >= 0;  eps >= 0 and finite
  * Asynchronous on `stream`.  Five plans, chosen per call; they give the same
  * iteration and differ in low-order bits.  Resident plan (k <= 16, any alignment,
- * ceil(m / 64) ceil(n / 256) <= 256 and n <= 4096): the whole run in one launch, A on the
+ * ceil(m / 64) ceil(n / 256) <= 256 and n <= 4096): 256 to 4096 iterations in one launch, A on the
  * compute units, at most one workgroup on each; the workgroups wait for each other,
  * so calls that overlap on one workspace (which race on any plan) may take seconds
- * until they give up; workspace kind 4 plus 48 KiB for each of the at most 256
+ * until they give up, W[0] and H[0] are a NaN then; workspace kind 4 plus 48 KiB for each of the at most 256
  * workgroups, else the next plan.  One-pass plan (k <= 32, 16-byte aligned
  * A, n % 4 == 0, n <= 512): both products of an iteration in one reading of A;
  * workspace kind 4 plus 1024 k n bytes at most.  Row plan (16-byte aligned A,

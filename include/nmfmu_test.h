@@ -23,6 +23,13 @@ int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float
                           int32_t iters, float eps, void *stream);
 
 /*
+ * The resident plan of nmf_mu_dense with `polls` looks for each wait of its workgroups (0: the usual number, seconds)
+ * before the run counts as lost, whose W[0] and H[0] are NaN.  NMF_EUNSUPPORTED as above.
+ */
+int nmfmu_resident_polls(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H,
+                         int32_t iters, float eps, uint32_t polls, void *stream);
+
+/*
  * nmf_mu_dense with timing, on A as it is (no copy of a misaligned A is made, so such
  * an A takes the slower kernels here): the same launches on `stream`, with a HIP event
  * recorded between them; synchronises `stream` before returning.  On return

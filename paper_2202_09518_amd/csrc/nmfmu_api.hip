@@ -446,6 +446,7 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
 {
     const Common &c = p.c;
     if (p.resident) {
+        if (iters < 1) return NMF_OK;
         ResidentArgs a = p.res;
         a.A = A;
         a.Win = a.W = W;
@@ -460,23 +461,24 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
                 for (int slot = 0; slot < kDenseKernels; ++slot) {
                     a.nprod = slot == 1;
                     a.lead = slot == 4;
-                    if (slot == 1 || slot == 4) NMF_HIP(launch_resident(a, p.resident, st));
+                    if (slot == 1 || slot == 4) NMF_HIP(launch_resident(a, p.resident, st, it == 0 && slot == 1));
                     NMF_HIP(hipEventRecord(*ev++, st));
                 }
+            NMF_HIP(launch_resident_mark(a, st));
             return NMF_OK;
         }
         const int calls = mon && !mon->last_only ? iters : 1;
         a.nprod = iters / calls;
-        a.trail = 1;
         const int R = (int)((m + 16 * p.resident - 1) / (16 * p.resident)), C = (int)((n + 255) / 256);
         if (mon) a.dpart = mon->dpart, a.gout = c.gwp, a.gh = c.gh;
         for (int i = 0; i < calls; ++i) {
-            NMF_HIP(launch_resident(a, p.resident, st));
+            NMF_HIP(launch_resident_run(a, p.resident, st, i == 0));
             if (mon) {
                 NMF_HIP(launch_gram_sum(c.gwp, R, k, c.gw, st));
                 NMF_HIP(launch_objective(mon->dpart, R * C, c.gw, c.gh, k, mon->normA2, mon->out + i, st));
             }
         }
+        NMF_HIP(launch_resident_mark(a, st));
         return NMF_OK;
     }
     if (p.one_pass) {
@@ -1940,8 +1942,28 @@ int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float
     Carve cv(ws);
     ResidentArgs a = carve_resident(cv, m, n, k, tiles).res;
     a.A = A, a.Win = a.W = W, a.Hin = a.H = H;
-    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters, a.trail = 1;
-    NMF_HIP(launch_resident(a, tiles, static_cast<hipStream_t>(stream), true));
+    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters;
+    NMF_HIP(launch_resident_run(a, tiles, static_cast<hipStream_t>(stream), true, true));
+    return NMF_OK;
+}
+
+int nmfmu_resident_polls(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
+                         uint32_t polls, void *stream)
+{
+    if (int rc = check_common(A, W, H, m, n, k, iters, eps)) return rc;
+    const int tiles = resident_tiles(m, n, k);
+    if (!tiles) return fail(NMF_EUNSUPPORTED, "not a shape of the resident plan%s");
+    if (iters == 0) return NMF_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    std::lock_guard<std::mutex> lock(g.mu);
+    void *ws = nullptr;
+    if (int rc = ensure_workspace(resident_bytes(m, n, k), &ws)) return rc;
+    Carve cv(ws);
+    ResidentArgs a = carve_resident(cv, m, n, k, tiles).res;
+    a.A = A, a.Win = a.W = W, a.Hin = a.H = H;
+    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters, a.polls = polls;
+    NMF_HIP(launch_resident_run(a, tiles, st));
+    NMF_HIP(launch_resident_mark(a, st));
     return NMF_OK;
 }
 

@@ -2323,13 +2323,15 @@ __global__ __launch_bounds__(1024, 1) void one_pass16_kernel(
 // the 100 MHz counter (other kernels, or several such launches that hold part of the device each), the first
 // that reported in does the whole run by itself, tile after tile, and the others leave.  So every wait ends
 // whatever else the device does; the sums, and so the bits, are the same.  Only a caller that breaks the rule of
-// one call at a time per workspace can take flags away from a run that waits for them: a thread has kLostPolls
-// looks (seconds) for all its waits, then waits no more, and the kernel ends and leaves a NaN in W and H.
+// one call at a time per workspace can take flags away from a run that waits for them: each wait has `polls`
+// looks (ten seconds or more), then the run is marked as lost, nobody waits for it any longer and it ends; a launch behind
+// it (resident_mark_kernel) leaves a NaN in W and H.
+// A launch does a bounded number of iterations (resident_piece): a longer run is cut, which gives the same bits.
 // Stores and loads of what workgroups exchange carry the sc1 bit: they meet behind the L2s of the XCDs.
 // (Plain loads after an acquire at the flags, which drops the L2's copies, were slower: 19.5 for 18.4 us.)
 // ---------------------------------------------------------------------------
 constexpr int kExchange = 16;            // sc1: coherent over the whole device
-constexpr int kLostPolls = 1 << 24;      // looks, not time: a process that is switched out does not look
+constexpr unsigned kLostPolls = 1u << 24;     // looks, not time: a process that is switched out does not look
 constexpr int kPRec = kResidentPRec;
 __host__ __device__ constexpr int resident_lds_floats(int rt)
 {
@@ -2369,18 +2371,18 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     bool solo = nwg < R * C;
     if (!solo && nwg > 1) {
         if (tid == 0) {
-            const unsigned ticket = __hip_atomic_fetch_add(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned ticket = __hip_atomic_fetch_add(a.sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             unsigned none = 0u;
             if (ticket == (unsigned)nwg - 1)
-                __hip_atomic_compare_exchange_strong(a.sync + 1, &none, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_compare_exchange_strong(a.sync + 2, &none, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // the low bits of the clock: of several launches that wait for each other's compute units one gives up first
             const long long t0 = wall_clock64(), end = t0 + a.patience + (t0 & 0xfffff);
             unsigned mode;
-            for (int looks = 0; (mode = peek(a.sync + 1)) == 0u && looks < kLostPolls; ++looks) {
+            for (unsigned looks = 0; (mode = peek(a.sync + 2)) == 0u && looks < kLostPolls; ++looks) {
                 __builtin_amdgcn_s_sleep(1);
                 if (ticket == 0 && (long long)wall_clock64() > end) {
                     none = 0u;
-                    __hip_atomic_compare_exchange_strong(a.sync + 1, &none, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_compare_exchange_strong(a.sync + 2, &none, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 if (ticket == 0) looks = 0;
             }
@@ -2398,7 +2400,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     // Posts a flag behind all stores of this workgroup to every other of its column or row group, then waits for
     // theirs.  Each has its own letter box: with one array of flags that all poll, the few lines of it are what a
     // wait of 125 workgroups waits for (9000 cycles instead of 3000 of 16).
-    int looks = kLostPolls;            // left to this thread
+    bool lost = false;                 // this thread waits no more
     auto meet = [&](bool column) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
@@ -2408,9 +2410,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
             unsigned *to = boxes + (column ? (tid * C + c0) * box + r0 : (r0 * C + tid) * box + rpad + c0);
             const unsigned *from = boxes + v0 * box + (column ? 0 : rpad) + tid;
             __hip_atomic_store(to, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while (peek(from) < epoch && looks > 0) {
+            for (unsigned looks = 1; !lost && peek(from) < epoch; ++looks) {
                 __builtin_amdgcn_s_sleep(1);
-                --looks;
+                lost = looks >= a.polls || (looks % 4096 == 0 && peek(a.sync + kResidentLost) != 0u);
+                if (lost) __hip_atomic_store(a.sync + kResidentLost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         asm volatile("" ::: "memory");
@@ -2816,7 +2819,12 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
         if (last_h && !a.trail) break;
         meet(true);
     }
-    if (looks <= 0) a.W[0] = a.H[0] = __builtin_nanf("");
+}
+
+// Behind all launches of a run: the owners of W[0] and H[0] have stored what they had.
+__global__ void resident_mark_kernel(const unsigned *sync, float *W, float *H)
+{
+    if (sync[kResidentLost]) W[0] = H[0] = __builtin_nanf("");
 }
 
 // G (k x k, ld k) = sum over nb sets of partial 32 x 32 tiles (accumulator layout).
@@ -4022,7 +4030,7 @@ static hipError_t resident_launch(unsigned blocks, hipStream_t st, const Residen
     return hipGetLastError();
 }
 
-hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool one_for_all)
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first, bool one_for_all)
 {
     ResidentArgs a = args;
     if (a.k < 1 || a.k > 16 || a.m < 1 || a.n < 1 || !a.A || !a.part || !a.qpart || !a.hx || !a.wx || !a.sync ||
@@ -4033,10 +4041,34 @@ hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, 
     a.R = (int)R;
     a.C = (int)C;
     a.patience = 10000000;     // 100 ms: longer than most kernels that may be in the way
+    if (!a.polls) a.polls = kLostPolls;
     const unsigned blocks = one_for_all ? 1u : (unsigned)(R * C);
-    hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync), resident_sync_words(R, C), 0.f, st);
+    const int64_t from = first ? 0 : kResidentLost + 1;       // the mark of a lost run stays for all its launches
+    hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync + from), resident_sync_words(R, C) - from, 0.f, st);
     if (e != hipSuccess) return e;
     return tiles == 1 ? resident_launch<1>(blocks, st, a) : tiles == 2 ? resident_launch<2>(blocks, st, a) : resident_launch<4>(blocks, st, a);
+}
+
+hipError_t launch_resident_mark(const ResidentArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL(resident_mark_kernel, dim3(1), dim3(1), 0, st, a.sync, a.W, a.H);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first, bool one_for_all)
+{
+    const int piece = resident_piece((args.m + 16 * tiles - 1) / (16 * tiles) * ((args.n + 255) / 256));
+    ResidentArgs a = args;
+    a.trail = 1;
+    for (int left = args.nprod; left > 0; left -= a.nprod, first = false) {
+        a.nprod = left < piece ? left : piece;
+        a.dpart = a.nprod == left ? args.dpart : nullptr;
+        a.gout = a.nprod == left ? args.gout : nullptr;
+        if (hipError_t e = launch_resident(a, tiles, st, first, one_for_all)) return e;
+        a.Win = a.W;
+        a.Hin = a.H;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_share_sum(const float *ppart, int nb, int k, int64_t n, float *psum, const float *gtiles, float *G, hipStream_t st)

@@ -153,7 +153,7 @@ struct ResidentArgs {
     float *qpart;                    // shares of A H^T and H H^T: per workgroup [16 tiles rows][16], [16][16]
     float *hx;                       // the new H: [group of 8 columns][16 factors][8]
     float *wx;                       // the new W: [row][16]
-    unsigned *sync;                  // reported in, decision; from word 32 on the letter boxes; zero at the start
+    unsigned *sync;                  // lost, reported in, decision; from word 32 on the letter boxes; zero at the start
     double *dpart;                   // optional, of the last W update: <A H^T, W> in R C shares,
     float *gout, *gh;                // R tile sets of W^T W (32 x 32 accumulator layout) and H H^T (k x k)
     int64_t m, n;
@@ -162,13 +162,24 @@ struct ResidentArgs {
     int nprod;                       // updates of H; updates of W: between them,
     int lead, trail;                 // one before the first (lead) and one after the last (trail)
     long long patience;
+    unsigned polls;                  // looks of one wait before the run is given up (0: the default)
 };
+constexpr int kResidentLost = 0;     // word of sync that is set when a wait has run out of them
 constexpr int kResidentPRec = 4096 + 160;     // floats of a workgroup's record in part,
 constexpr int resident_qrec(int tiles) { return 256 * (tiles + 1); }     // and in qpart
 inline int64_t resident_sync_words(int64_t R, int64_t C) { return 32 + R * C * (((R + 31) & ~(int64_t)31) + 32); }
 int resident_tiles(int64_t m, int64_t n, int k);
-// Fills in R, C and patience and clears sync.  one_for_all: one workgroup does the run of all.
-hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool one_for_all = false);
+// Iterations of one launch of R * C = `groups` workgroups: it holds its compute units for up to some 30 ms, or seconds if one
+// workgroup does the run of all, and the flags (four an iteration) and looks stay far from their ends.  Loading A
+// again costs 10 to 20 us.
+inline int resident_piece(int64_t groups) { return (int)(groups > 256 ? 256 : groups < 16 ? 4096 : 65536 / groups); }
+// Fills in R, C, patience and polls and clears sync, the mark of a lost run only with `first`.  one_for_all: one
+// workgroup does the run of all.
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, bool one_for_all = false);
+// nprod updates of H, each followed by one of W, in launches of resident_piece iterations.
+hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, bool one_for_all = false);
+// A NaN in W and H if a launch since the last `first` was lost.
+hipError_t launch_resident_mark(const ResidentArgs &a, hipStream_t st);
 
 // out[0] = sum of in[0 .. count), added in a fixed order (strided per thread, then the threads in order).
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st);

@@ -116,3 +116,54 @@ def test_replays_of_a_captured_resident_run():
         nmf.nmf_mu_dense(A, m, n, k, W2, H2, 5, EPS)      # the same workspace between the replays
         torch.cuda.synchronize()
         assert torch.equal(W2, We) and torch.equal(H2, He)
+
+
+def polled(nmf, A, m, n, k, W, H, iters, polls):
+    import torch
+
+    fn = nmf.lib().nmfmu_resident_polls
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
+                   ctypes.c_int32, ctypes.c_float, ctypes.c_uint32, ctypes.c_void_p]
+    assert fn(A.data_ptr(), m, n, k, W.data_ptr(), H.data_ptr(), iters, EPS, polls, torch.cuda.current_stream().cuda_stream) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k,iters", [(16, 16, 2, 9000), (256, 192, 4, 9000), (100, 513, 5, 9000), (4096, 1024, 16, 1500)])
+def test_long_runs(m, n, k, iters):
+    """More iterations than a launch does: the bits of short calls.  The looks of all waits together are many times the
+    looks that a wait has, which belong to each wait (2^13: milliseconds, where a wait takes one or two microseconds)."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+    runs = []
+    for calls, fn in ((1, lambda *a: polled(nmf, *a, 1 << 13)), (1, lambda *a: nmf.nmf_mu_dense(*a, EPS)),
+                      (30, lambda *a: nmf.nmf_mu_dense(*a, EPS))):
+        Wd, Hd = W.clone(), H.clone()
+        for _ in range(calls):
+            fn(A, m, n, k, Wd, Hd, iters // calls)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(Wd).all()) and bool(torch.isfinite(Hd).all())
+        runs.append((Wd, Hd))
+    for Wd, Hd in runs[1:]:
+        assert torch.equal(Wd, runs[0][0]) and torch.equal(Hd, runs[0][1])
+
+
+@pytest.mark.gpu
+def test_a_lost_run_is_marked():
+    """One look a wait: a run of many workgroups does not get by with that, ends all the same and says so."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    m, n, k = 4096, 1024, 16
+    A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+    Wd, Hd = W.clone(), H.clone()
+    polled(nmf, A, m, n, k, Wd, Hd, 300, 1)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(Wd[0, 0])) and bool(torch.isnan(Hd[0, 0]))
+    runs = [(W.clone(), H.clone()) for _ in range(2)]
+    polled(nmf, A, m, n, k, *runs[0], 3, 0)         # the next run on the same workspace is none the worse for it
+    by_one(nmf, A, m, n, k, *runs[1], 3)
+    torch.cuda.synchronize()
+    assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
+    assert bool(torch.isfinite(runs[0][0]).all())
