@@ -2492,7 +2492,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     auto put_g = [&](double x) {
         const float hi = (float)x;
         Gs[er * LD + ec] = hi;
-        Gl[er * LD + ec] = (float)(x - (double)hi);
+        Gl[er * LD + ec] = fabsf(hi) < __builtin_inff() ? (float)(x - (double)hi) : 0.f;     // an infinite denominator stays one
     };
     auto dot = [&](const float *x, int row) -> float {     // x . row of the Gram matrix
         const float *gh = Gs + row * LD, *gl = Gl + row * LD;

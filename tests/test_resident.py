@@ -167,3 +167,27 @@ def test_a_lost_run_is_marked():
     torch.cuda.synchronize()
     assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
     assert bool(torch.isfinite(runs[0][0]).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n", [(300, 200), (600, 1003)])
+@pytest.mark.parametrize("k", [3, 8, 9])
+def test_gram_matrices_beyond_the_largest_float(m, n, k):
+    """W^T W overflows: the denominators are infinite and H becomes zero, and W with it, as on the plan of a workspace without
+    room for this one."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A, W, H = (torch.from_numpy(x + np.float32(0.1)).cuda() for x in data(m, n, k))
+    A *= 1e-3
+    W *= 1e20
+    small = torch.empty(nmf.nmf_mu_workspace_bytes(4, m, n, 0, k, 0), dtype=torch.uint8, device="cuda")
+    for ws in (None, small):
+        Wd, Hd = W.clone(), H.clone()
+        nmf.nmf_mu_set_workspace(ws)
+        try:
+            nmf.nmf_mu_dense(A, m, n, k, Wd, Hd, 2, EPS)
+            torch.cuda.synchronize()
+        finally:
+            nmf.nmf_mu_set_workspace(None)
+        assert torch.equal(Wd, torch.zeros_like(W)) and torch.equal(Hd, torch.zeros_like(H))
