@@ -1494,6 +1494,8 @@ static int csr_run(const int64_t *rowptr, const int32_t *colidx, const float *va
         dup = cv.take<double>(65536 + 1);      // one share per block of the copy's last kernel, then the sum of squares
     }
     const int ndup = csc_finish_blocks(nnz);
+    // The Gram kernel's arrival counter reads zero at the start also after a call that was cut short.
+    NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(c.counters), 64, 0.f, st));
 
     // Column-ordered copy of A, once per call, enqueued like everything else.
     NMF_HIP(launch_csc_build(rowptr, colidx, vals, m, n, nnz, sorted_cols, payload, sorted_payload, sort_temp,
@@ -1697,6 +1699,7 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
     NMF_HIP(hipEventRecord(g.ev_entry, st));
     NMF_HIP(hipStreamWaitEvent(g.copy_stream, g.ev_entry, 0));
 
+    NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(c.counters), 64, 0.f, st));      // as in csr_run
     NMF_HIP(launch_transpose(H, k, n, Ht, st));
     int64_t issued = 0;
     for (int s = 0; s <= iters; ++s) {
