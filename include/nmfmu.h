@@ -90,8 +90,12 @@ const char *nmf_last_error(void);
  * Asynchronous on `stream`.  Five plans, chosen per call; they give the same
  * iteration and differ in low-order bits.  Resident plan (k <= 16, any alignment,
  * ceil(m / 64) ceil(n / 256) <= 256 and n <= 4096): 256 to 4096 iterations in one launch, A on the
- * compute units, at most one workgroup on each; the workgroups wait for each other,
- * so calls that overlap on one workspace (which race on any plan) may take seconds
+ * compute units, at most one workgroup on each, which other work on the device does
+ * not get meanwhile (up to some 30 ms).  Where other work holds compute units when a
+ * launch begins, its workgroups wait 200 us for each other; those that are there then
+ * begin without the rest, who join in when they come (same bits; two to four times
+ * slower with half or more of them, in proportion with fewer).  Calls
+ * that overlap on one workspace (which race on any plan) may take seconds
  * until they give up, W[0] and H[0] are a NaN then; workspace kind 4 plus 48 KiB for each of the at most 256
  * workgroups, else the next plan.  One-pass plan (k <= 32, 16-byte aligned
  * A, n % 4 == 0, n <= 512): both products of an iteration in one reading of A;

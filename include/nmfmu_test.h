@@ -15,12 +15,21 @@ extern "C" {
 #endif
 
 /*
- * The resident plan of nmf_mu_dense with one workgroup doing the run of all, as the
- * kernel does by itself when the device has no room for all of them at once: the same
+ * The resident plan of nmf_mu_dense with one workgroup doing the run of all: the same
  * bits, many times slower.  NMF_EUNSUPPORTED for a shape that this plan does not take.
  */
 int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H,
                           int32_t iters, float eps, void *stream);
+
+/*
+ * The resident plan of nmf_mu_dense on `workgroups` of its workgroups (0, or more than it
+ * has: all), which share the run as the kernel does by itself when the device has no room
+ * for all of them at once; patience: ticks of 10 ns until those that are there start
+ * without the others, who join in when they come (0: the usual 200 us; negative: at once).
+ * The same bits.  NMF_EUNSUPPORTED as above.
+ */
+int nmfmu_resident_shared(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H,
+                          int32_t iters, float eps, int32_t workgroups, int64_t patience, void *stream);
 
 /*
  * The resident plan of nmf_mu_dense with `polls` looks for each wait of its workgroups (0: the usual number, seconds)

@@ -1932,8 +1932,8 @@ int nmf_mu_dense_noalloc(const float *A, int64_t m, int64_t n, int32_t k, float 
 
 // ---- single steps ----------------------------------------------------------
 
-int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
-                          void *stream)
+static int resident_hook(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters, float eps, int workgroups,
+                         long long patience, unsigned polls, hipStream_t st)
 {
     if (int rc = check_common(A, W, H, m, n, k, iters, eps)) return rc;
     const int tiles = resident_tiles(m, n, k);
@@ -1945,29 +1945,28 @@ int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float
     Carve cv(ws);
     ResidentArgs a = carve_resident(cv, m, n, k, tiles).res;
     a.A = A, a.Win = a.W = W, a.Hin = a.H = H;
-    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters;
-    NMF_HIP(launch_resident_run(a, tiles, static_cast<hipStream_t>(stream), true, true));
+    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters, a.patience = patience, a.polls = polls;
+    NMF_HIP(launch_resident_run(a, tiles, st, true, workgroups));
+    NMF_HIP(launch_resident_mark(a, st));
     return NMF_OK;
+}
+
+int nmfmu_resident_by_one(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
+                          void *stream)
+{
+    return resident_hook(A, m, n, k, W, H, iters, eps, 1, 0, 0, static_cast<hipStream_t>(stream));
+}
+
+int nmfmu_resident_shared(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
+                          int32_t workgroups, int64_t patience, void *stream)
+{
+    return resident_hook(A, m, n, k, W, H, iters, eps, workgroups, patience, 0, static_cast<hipStream_t>(stream));
 }
 
 int nmfmu_resident_polls(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
                          uint32_t polls, void *stream)
 {
-    if (int rc = check_common(A, W, H, m, n, k, iters, eps)) return rc;
-    const int tiles = resident_tiles(m, n, k);
-    if (!tiles) return fail(NMF_EUNSUPPORTED, "not a shape of the resident plan%s");
-    if (iters == 0) return NMF_OK;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    std::lock_guard<std::mutex> lock(g.mu);
-    void *ws = nullptr;
-    if (int rc = ensure_workspace(resident_bytes(m, n, k), &ws)) return rc;
-    Carve cv(ws);
-    ResidentArgs a = carve_resident(cv, m, n, k, tiles).res;
-    a.A = A, a.Win = a.W = W, a.Hin = a.H = H;
-    a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters, a.polls = polls;
-    NMF_HIP(launch_resident_run(a, tiles, st));
-    NMF_HIP(launch_resident_mark(a, st));
-    return NMF_OK;
+    return resident_hook(A, m, n, k, W, H, iters, eps, 0, 0, polls, static_cast<hipStream_t>(stream));
 }
 
 int nmf_csr_partition(const int64_t *rowptr, int64_t m, int32_t nparts, int64_t *part, void *stream)

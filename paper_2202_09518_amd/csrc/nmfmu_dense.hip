@@ -2318,14 +2318,19 @@ __global__ __launch_bounds__(1024, 1) void one_pass16_kernel(
 // that meets the others in a rounded add: what the instruction drops when they join it is always downwards and shows
 // as a drift of the factors' scale over many iterations.
 //
-// Who waits for a flag must know that its writer runs: the workgroups first report in, and only when all
-// have (all hold their compute units then) does the run start.  If they have not after `patience` ticks of
-// the 100 MHz counter (other kernels, or several such launches that hold part of the device each), the first
-// that reported in does the whole run by itself, tile after tile, and the others leave.  So every wait ends
-// whatever else the device does; the sums, and so the bits, are the same.  Only a caller that breaks the rule of
-// one call at a time per workspace can take flags away from a run that waits for them: each wait has `polls`
-// looks (ten seconds or more), then the run is marked as lost, nobody waits for it any longer and it ends; a launch behind
-// it (resident_mark_kernel) leaves a NaN in W and H.
+// Who waits for a flag must know that its writer runs.  The workgroups first report in, and when all have (all hold
+// their compute units then) the run starts.  If they have not after `patience` ticks of the 100 MHz counter (other
+// kernels, another such launch, a stream with few compute units), those that have start without the others: an
+// iteration's work of all R C is dealt to them in ranges, which they do one after the other, tiles loaded anew,
+// with barriers of all (the "shared" run).  After each iteration the first looks who has reported in meanwhile and
+// deals again; as soon as all have, each keeps its own tile from there on.  So every wait is for a
+// workgroup that runs, whatever else the device does; the sums, and so the bits, are the same.  Microseconds per iteration
+// with all, all but one, half and a quarter of the workgroups, and with one: 2000 x 1201, k = 12 11.4, 31.9, 38.6, 68, 2300;
+// 16384 x 256, k = 16 17.5, 40.9, 48.2, 90, 4100 (the other plans on the whole device: 27.5 and 33.4).  The two bodies apart
+// also took a tenth off the iterations of all (256 x 192, k = 4: 7.3 -> 6.5 us): fewer scalar registers to spill.
+// Only a caller that breaks the rule of one call at a time per workspace can take flags away from a run that waits for
+// them: each wait has `polls` looks (ten seconds or more), then the run is marked as lost, nobody waits for it any
+// longer and it ends; a launch behind it (resident_mark_kernel) leaves a NaN in W and H.
 // A launch does a bounded number of iterations (resident_piece): a longer run is cut, which gives the same bits.
 // Stores and loads of what workgroups exchange carry the sc1 bit: they meet behind the L2s of the XCDs.
 // (Plain loads after an acquire at the flags, which drops the L2's copies, were slower: 19.5 for 18.4 us.)
@@ -2339,9 +2344,33 @@ __host__ __device__ constexpr int resident_lds_floats(int rt)
 }
 
 __device__ __forceinline__ unsigned peek(const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void post(unsigned *p, unsigned x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ unsigned add_one(unsigned *p) { return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ bool decide(unsigned *p, unsigned x)      // if nobody has
+{
+    unsigned none = 0u;
+    return __hip_atomic_compare_exchange_strong(p, &none, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
-template <int RT>
-__global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
+// Waits of one thread for a word to reach a value.
+struct Patient {
+    unsigned *lost_word;
+    unsigned polls;
+    unsigned lost;                     // this thread waits no more
+    __device__ __forceinline__ void await(const unsigned *from, unsigned least)
+    {
+        for (unsigned looks = 1; !lost && peek(from) < least; ++looks) {
+            __builtin_amdgcn_s_sleep(1);
+            lost = looks >= polls || (looks % 4096 == 0 && peek(lost_word) != 0u);
+            if (lost) post(lost_word, 1u);
+        }
+    }
+};
+
+// Iterations `s` .. of the workgroup.  SHARED: a range of the workgroups' work, dealt anew after every iteration; returns
+// the iteration from which all workgroups are there, or -1 after the last.
+template <int RT, bool SHARED>
+__device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s, unsigned ticket, unsigned deal)
 {
     constexpr int kRsrcFlags = 0x00020000;         // raw buffer, 32-bit data format (gfx9 family)
     constexpr unsigned kOut = 0x7fffffffu;         // an offset outside every extent: reads as zero, stores nothing
@@ -2363,58 +2392,48 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, quad = lane >> 4, hr = quad & 1, half = lane >> 5;
     const int er = (tid >> 4) & 15, ec = tid & 15;
-    const int nwg = gridDim.x, k = a.k, R = a.R, C = a.C, n = (int)a.n;
+    const int k = a.k, R = a.R, C = a.C, nwg = R * C, n = (int)a.n;
     const int nt = (n + 15) >> 4;                                  // 16-column tiles in all
     const int rpad = (R + 31) & ~31, box = rpad + 32;              // words of a workgroup's letter box: column group, row group
 
-    // ---- all here, or one for all
-    bool solo = nwg < R * C;
-    if (!solo && nwg > 1) {
-        if (tid == 0) {
-            const unsigned ticket = __hip_atomic_fetch_add(a.sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            unsigned none = 0u;
-            if (ticket == (unsigned)nwg - 1)
-                __hip_atomic_compare_exchange_strong(a.sync + 2, &none, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // the low bits of the clock: of several launches that wait for each other's compute units one gives up first
-            const long long t0 = wall_clock64(), end = t0 + a.patience + (t0 & 0xfffff);
-            unsigned mode;
-            for (unsigned looks = 0; (mode = peek(a.sync + 2)) == 0u && looks < kLostPolls; ++looks) {
-                __builtin_amdgcn_s_sleep(1);
-                if (ticket == 0 && (long long)wall_clock64() > end) {
-                    none = 0u;
-                    __hip_atomic_compare_exchange_strong(a.sync + 2, &none, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                if (ticket == 0) looks = 0;
-            }
-            word[0] = mode == 1u ? 1u : (ticket == 0 ? 2u : 0u);
+    int v0, v1, r0, c0;                                            // the workgroups this one stands for
+    auto take = [&]() {
+        if (SHARED) {
+            const int here = deal & 511;
+            v0 = (int)ticket * nwg / here;
+            v1 = ((int)ticket + 1) * nwg / here;
+        } else {
+            v0 = blockIdx.x;
+            v1 = v0 + 1;
         }
-        __syncthreads();
-        const unsigned mode = __builtin_amdgcn_readfirstlane(word[0]);
-        if (mode == 0u) return;
-        solo = mode == 2u;
-    }
-    const int v0 = solo ? 0 : (int)blockIdx.x, v1 = solo ? R * C : v0 + 1;     // the workgroups this one stands for
-    const int r0 = v0 / C, c0 = v0 % C;
-    unsigned epoch = 0;
-    unsigned *boxes = a.sync + 32;
+        r0 = v0 / C;
+        c0 = v0 % C;
+    };
+    take();
+    unsigned epoch = 0, target = 0;
+    unsigned *boxes = a.sync + kResidentHead;
     // Posts a flag behind all stores of this workgroup to every other of its column or row group, then waits for
     // theirs.  Each has its own letter box: with one array of flags that all poll, the few lines of it are what a
     // wait of 125 workgroups waits for (9000 cycles instead of 3000 of 16).
-    bool lost = false;                 // this thread waits no more
+    Patient thread{a.sync + kResidentLost, a.polls, 0u};
     auto meet = [&](bool column) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         ++epoch;
-        if (solo) return;
-        if (tid < (column ? R : C)) {
-            unsigned *to = boxes + (column ? (tid * C + c0) * box + r0 : (r0 * C + tid) * box + rpad + c0);
-            const unsigned *from = boxes + v0 * box + (column ? 0 : rpad) + tid;
-            __hip_atomic_store(to, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (unsigned looks = 1; !lost && peek(from) < epoch; ++looks) {
-                __builtin_amdgcn_s_sleep(1);
-                lost = looks >= a.polls || (looks % 4096 == 0 && peek(a.sync + kResidentLost) != 0u);
-                if (lost) __hip_atomic_store(a.sync + kResidentLost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (SHARED) {                  // all that are here
+            if (tid == 0) {
+                add_one(a.sync + kResidentArrived);
+                if (ticket == 0) {
+                    target += deal & 511;
+                    thread.await(a.sync + kResidentArrived, target);
+                    post(a.sync + kResidentRelease, epoch);
+                } else {
+                    thread.await(a.sync + kResidentRelease, epoch);
+                }
             }
+        } else if (tid < (column ? R : C)) {
+            post(boxes + (column ? (tid * C + c0) * box + r0 : (r0 * C + tid) * box + rpad + c0), epoch);
+            thread.await(boxes + v0 * box + (column ? 0 : rpad) + tid, epoch);
         }
         asm volatile("" ::: "memory");
         __syncthreads();
@@ -2539,16 +2558,20 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
         if (v == 0 && tid < 256 && er < k && ec < k) a.gh[er * k + ec] = Gs[er * LD + ec];
     };
 
-    for (int v = v0; v < v1; ++v)      // H as handed in, to where its owners look for it
-        for (int t = v / C; t < 16; t += R) {
-            const int tile = 16 * (v % C) + t, col = 16 * tile + ec;
-            if (tid < 256)
-                __builtin_amdgcn_raw_buffer_store_b32(er < k && col < n ? __float_as_uint(a.Hin[(int64_t)er * n + col]) : 0u, rh,
-                                                      (unsigned)((2 * tile + (ec >> 3)) * 128 + er * 8 + (ec & 7)) * 4u, 0, kExchange);
+    bool have_tile = false;
+    for (; s <= a.nprod; ++s) {
+        epoch = 8 * s;                 // more than an iteration's meetings
+        if (s == 0) {
+            for (int v = v0; v < v1; ++v)      // H as handed in, to where its owners look for it
+                for (int t = v / C; t < 16; t += R) {
+                    const int tile = 16 * (v % C) + t, col = 16 * tile + ec;
+                    if (tid < 256)
+                        __builtin_amdgcn_raw_buffer_store_b32(er < k && col < n ? __float_as_uint(a.Hin[(int64_t)er * n + col]) : 0u, rh,
+                                                              (unsigned)((2 * tile + (ec >> 3)) * 128 + er * 8 + (ec & 7)) * 4u, 0, kExchange);
+                }
+            if (a.lead) meet(true);
         }
-    if (a.lead) meet(true);
-    bool have_tile = false, stored = false;      // stored: wx holds the rows
-    for (int s = 0; s <= a.nprod; ++s) {
+        const bool stored = s > 1 || (s == 1 && a.lead);     // wx holds the rows
         const bool product = s < a.nprod, update = s ? (product || a.trail) : a.lead;
         if (!product && !update) break;
         const bool last_w = update && (!product || (s == a.nprod - 1 && !a.trail));
@@ -2557,8 +2580,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
             // ---- A H^T
             for (int v = v0; v < v1; ++v) {
                 const int r = v / C, c = v % C;
-                if (solo) __syncthreads();
-                if (solo || !have_tile) {
+                if (SHARED) __syncthreads();
+                if (SHARED || !have_tile) {
                     load_tile(r, c);
                     load_w(r, !stored);
                 }
@@ -2628,7 +2651,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
                         const int e = tid + 512 * i;
                         if (e < RT * 256) {
                             put_w(e >> 4, e & 15, x[i]);
-                            if (solo) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), rw, (unsigned)(r * RB * 16 + e) * 4u, 0, kExchange);
+                            if (SHARED) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), rw, (unsigned)(r * RB * 16 + e) * 4u, 0, kExchange);
                         }
                     }
                     if (last_w && a.dpart) report(v, dacc);
@@ -2645,7 +2668,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
                 // ---- W update: the 16-row tiles dealt to the workgroups of the row group
                 for (int v = v0; v < v1; ++v) {
                     const int r = v / C, c = v % C;
-                    if (solo) {
+                    if (SHARED) {
                         __syncthreads();
                         load_w(r, !stored);
                     }
@@ -2689,15 +2712,15 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
         // ---- product
         for (int v = v0; v < v1; ++v) {
             const int r = v / C, c = v % C;
-            if (solo) {
+            if (SHARED) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the rows of an update that did not wait for others
                 __syncthreads();
             }
-            if (solo || !have_tile) {
-                if (solo || !update) load_tile(r, c);
-                if (solo || !update) load_w(r, !(stored || update));
+            if (SHARED || !have_tile) {
+                if (SHARED || !update) load_tile(r, c);
+                if (SHARED || !update) load_w(r, !(stored || update));
             }
-            if (!solo && update && C > 1) load_w(r, false);
+            if (!SHARED && update && C > 1) load_w(r, false);
             __syncthreads();
             if (product) {
                 f32x4 d[2][2];         // [tile][small products, large ones]
@@ -2753,7 +2776,6 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
             }
         }
         have_tile = true;
-        stored = stored || update;
         if (!product) break;
         meet(true);
         // ---- H update: the 16-column tiles dealt to the workgroups of the column group
@@ -2818,7 +2840,58 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
         }
         if (last_h && !a.trail) break;
         meet(true);
+        if (SHARED) {
+            if (tid == 0) {
+                const unsigned next = (unsigned)(s + 2) << 9;
+                unsigned now;
+                if (ticket == 0) {
+                    now = next | peek(a.sync + kResidentHere);
+                    post(a.sync + kResidentDeal, now);
+                } else {
+                    thread.await(a.sync + kResidentDeal, next);
+                    now = peek(a.sync + kResidentDeal);
+                }
+                word[0] = now >> 9 == next >> 9 ? now : deal;      // a lost run
+            }
+            __syncthreads();
+            deal = __builtin_amdgcn_readfirstlane(word[0]);
+            if ((int)(deal & 511) >= nwg) return s + 1;
+            take();
+        }
     }
+    if (SHARED && ticket == 0 && tid == 0) post(a.sync + kResidentDeal, kResidentOver);
+    return -1;
+}
+
+template <int RT>
+__global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
+{
+    unsigned *word = reinterpret_cast<unsigned *>(aht_rows_lds);
+    if (threadIdx.x == 0) {
+        const unsigned ticket = add_one(a.sync + kResidentHere);
+        if (ticket == gridDim.x - 1) decide(a.sync + kResidentDeal, 1u << 9 | gridDim.x);
+        const long long end = wall_clock64() + a.patience;
+        unsigned deal;
+        // the low nine bits: how many of those that have reported in are at work; the others: from which iteration on, plus one
+        for (unsigned looks = 1; ((deal = peek(a.sync + kResidentDeal)) & 511) <= ticket; ++looks) {
+            if (ticket == 0 && (long long)wall_clock64() >= end) decide(a.sync + kResidentDeal, 1u << 9 | peek(a.sync + kResidentHere));
+            __builtin_amdgcn_s_sleep(1);
+            if (ticket && looks >= a.polls) {
+                post(a.sync + kResidentLost, 1u);
+                deal = kResidentOver;
+                break;
+            }
+        }
+        word[0] = deal;
+        word[1] = ticket;
+    }
+    __syncthreads();
+    const unsigned deal = __builtin_amdgcn_readfirstlane(word[0]), ticket = __builtin_amdgcn_readfirstlane(word[1]);
+    __syncthreads();
+    if (deal == kResidentOver) return;
+    int s = (int)(deal >> 9) - 1;
+    if ((int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, true>(a, s, ticket, deal);
+    if (s >= 0) resident_iterations<RT, false>(a, s, 0u, 0u);
 }
 
 // Behind all launches of a run: the owners of W[0] and H[0] have stored what they had.
@@ -4030,7 +4103,7 @@ static hipError_t resident_launch(unsigned blocks, hipStream_t st, const Residen
     return hipGetLastError();
 }
 
-hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first, bool one_for_all)
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first, int workgroups)
 {
     ResidentArgs a = args;
     if (a.k < 1 || a.k > 16 || a.m < 1 || a.n < 1 || !a.A || !a.part || !a.qpart || !a.hx || !a.wx || !a.sync ||
@@ -4040,9 +4113,10 @@ hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, 
     if (R * C > 256) return hipErrorInvalidValue;
     a.R = (int)R;
     a.C = (int)C;
-    a.patience = 10000000;     // 100 ms: longer than most kernels that may be in the way
+    // 200 us: a launch's workgroups are all there after 10 to 20 if nothing is in the way, and who comes later joins in
+    if (!a.patience) a.patience = 20000;
     if (!a.polls) a.polls = kLostPolls;
-    const unsigned blocks = one_for_all ? 1u : (unsigned)(R * C);
+    const unsigned blocks = workgroups > 0 && workgroups < R * C ? (unsigned)workgroups : (unsigned)(R * C);
     const int64_t from = first ? 0 : kResidentLost + 1;       // the mark of a lost run stays for all its launches
     hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync + from), resident_sync_words(R, C) - from, 0.f, st);
     if (e != hipSuccess) return e;
@@ -4055,7 +4129,7 @@ hipError_t launch_resident_mark(const ResidentArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first, bool one_for_all)
+hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first, int workgroups)
 {
     const int piece = resident_piece((args.m + 16 * tiles - 1) / (16 * tiles) * ((args.n + 255) / 256));
     ResidentArgs a = args;
@@ -4064,7 +4138,7 @@ hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t 
         a.nprod = left < piece ? left : piece;
         a.dpart = a.nprod == left ? args.dpart : nullptr;
         a.gout = a.nprod == left ? args.gout : nullptr;
-        if (hipError_t e = launch_resident(a, tiles, st, first, one_for_all)) return e;
+        if (hipError_t e = launch_resident(a, tiles, st, first, workgroups)) return e;
         a.Win = a.W;
         a.Hin = a.H;
     }

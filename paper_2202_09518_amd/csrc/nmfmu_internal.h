@@ -153,7 +153,7 @@ struct ResidentArgs {
     float *qpart;                    // shares of A H^T and H H^T: per workgroup [16 tiles rows][16], [16][16]
     float *hx;                       // the new H: [group of 8 columns][16 factors][8]
     float *wx;                       // the new W: [row][16]
-    unsigned *sync;                  // lost, reported in, decision; from word 32 on the letter boxes; zero at the start
+    unsigned *sync;                  // kResidentLost ..; from kResidentHead on the letter boxes; zero at the start
     double *dpart;                   // optional, of the last W update: <A H^T, W> in R C shares,
     float *gout, *gh;                // R tile sets of W^T W (32 x 32 accumulator layout) and H H^T (k x k)
     int64_t m, n;
@@ -161,23 +161,29 @@ struct ResidentArgs {
     float eps;
     int nprod;                       // updates of H; updates of W: between them,
     int lead, trail;                 // one before the first (lead) and one after the last (trail)
-    long long patience;
+    long long patience;              // ticks until those that are there start without the others (0: the default)
     unsigned polls;                  // looks of one wait before the run is given up (0: the default)
 };
-constexpr int kResidentLost = 0;     // word of sync that is set when a wait has run out of them
+// Words of sync, a cache line each:
+constexpr int kResidentLost = 0,     // set when a wait has run out of looks
+    kResidentHere = 32,              // workgroups that have reported in
+    kResidentDeal = 64,              // how many of them are at work, from which iteration on
+    kResidentArrived = 96, kResidentRelease = 128,     // barriers of a shared run
+    kResidentHead = 160;
+constexpr unsigned kResidentOver = ~0u;     // in kResidentDeal: who comes now is not needed
 constexpr int kResidentPRec = 4096 + 160;     // floats of a workgroup's record in part,
 constexpr int resident_qrec(int tiles) { return 256 * (tiles + 1); }     // and in qpart
-inline int64_t resident_sync_words(int64_t R, int64_t C) { return 32 + R * C * (((R + 31) & ~(int64_t)31) + 32); }
+inline int64_t resident_sync_words(int64_t R, int64_t C) { return kResidentHead + R * C * (((R + 31) & ~(int64_t)31) + 32); }
 int resident_tiles(int64_t m, int64_t n, int k);
 // Iterations of one launch of R * C = `groups` workgroups: it holds its compute units for up to some 30 ms, or seconds if one
-// workgroup does the run of all, and the flags (four an iteration) and looks stay far from their ends.  Loading A
-// again costs 10 to 20 us.
+// workgroup does the run of all, and the flags (8 an iteration) stay far from their end.  Loading A again costs 10
+// to 20 us.
 inline int resident_piece(int64_t groups) { return (int)(groups > 256 ? 256 : groups < 16 ? 4096 : 65536 / groups); }
-// Fills in R, C, patience and polls and clears sync, the mark of a lost run only with `first`.  one_for_all: one
-// workgroup does the run of all.
-hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, bool one_for_all = false);
+// Fills in R, C and the defaults and clears sync, the mark of a lost run only with `first`.  workgroups > 0: that many
+// are launched instead of R * C (and share the run).
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, int workgroups = 0);
 // nprod updates of H, each followed by one of W, in launches of resident_piece iterations.
-hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, bool one_for_all = false);
+hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, int workgroups = 0);
 // A NaN in W and H if a launch since the last `first` was lost.
 hipError_t launch_resident_mark(const ResidentArgs &a, hipStream_t st);
 

@@ -191,3 +191,71 @@ def test_gram_matrices_beyond_the_largest_float(m, n, k):
         finally:
             nmf.nmf_mu_set_workspace(None)
         assert torch.equal(Wd, torch.zeros_like(W)) and torch.equal(Hd, torch.zeros_like(H))
+
+
+def shared(nmf, A, m, n, k, W, H, iters, workgroups, patience):
+    import torch
+
+    fn = nmf.lib().nmfmu_resident_shared
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
+                   ctypes.c_float, ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p]
+    assert fn(A.data_ptr(), m, n, k, W.data_ptr(), H.data_ptr(), iters, EPS, workgroups, patience,
+              torch.cuda.current_stream().cuda_stream) == 0
+
+
+# 1, 2 and 4 row tiles per workgroup with one and with several groups of columns; (1100, 300) and (2001, 700): second row
+# tiles of one owner; launched: a few workgroups, half, all but one, and all, who start at once with those that are there
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(256, 192, 4), (513, 255, 9), (4161, 97, 16), (40, 257, 5), (600, 1003, 8), (1100, 300, 12),
+                                   (2001, 700, 3), (4096, 1024, 16), (16380, 256, 10)])
+def test_runs_shared_by_those_that_are_there(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+    iters = 12
+    We, He = W.clone(), H.clone()
+    nmf.nmf_mu_dense(A, m, n, k, We, He, iters, EPS)
+    torch.cuda.synchronize()
+    Wr, Hr = orc.mu_dense(A.cpu().numpy(), W.cpu().numpy(), H.cpu().numpy(), iters, float(np.float32(EPS)))
+    # twelve updates of each factor: as for three, times their number
+    assert orc.rel_fro(We.cpu().numpy(), Wr) < 1.2e-5 and orc.rel_fro(He.cpu().numpy(), Hr) < 1.2e-5
+    rows = 16
+    while -(-m // rows) > 32 and rows < 64:
+        rows *= 2
+    groups = -(-m // rows) * -(-n // 256)
+    for workgroups, patience in ((2, 0), (3, -1), (max(1, groups // 2), 0), (max(1, groups - 1), 0), (0, -1), (0, 1), (0, 100)):
+        Wd, Hd = W.clone(), H.clone()
+        shared(nmf, A, m, n, k, Wd, Hd, iters, workgroups, patience)
+        torch.cuda.synchronize()
+        assert torch.equal(Wd, We) and torch.equal(Hd, He), (workgroups, patience)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("first,second", [((16380, 256, 16), (16380, 256, 16)), ((6400, 256, 8), (16380, 256, 16)),
+                                          ((2000, 1201, 12), (4096, 1024, 5))])
+def test_two_runs_at_once(first, second):
+    """A run on the library's workspace and one on the fixed scratch array, on two streams: together they want more
+    compute units than there are."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    problems, results = [], []
+    for m, n, k in (first, second):
+        A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+        problems.append((A, m, n, k, W, H))
+    calls = (nmf.nmf_mu_dense, nmf.nmf_mu_dense_noalloc)
+    streams = [torch.cuda.Stream() for _ in calls]
+    for together in (False, True):
+        factors = [(p[4].clone(), p[5].clone()) for p in problems]
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for call, st, (A, m, n, k, _, _), (Wd, Hd) in zip(calls, streams, problems, factors):
+                with torch.cuda.stream(st):
+                    call(A, m, n, k, Wd, Hd, 400, EPS)
+                if not together:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        results.append(factors)
+    for (Wa, Ha), (Wb, Hb) in zip(*results):
+        assert torch.equal(Wa, Wb) and torch.equal(Ha, Hb)
