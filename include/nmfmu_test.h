@@ -39,6 +39,14 @@ int nmfmu_resident_polls(const float *A, int64_t m, int64_t n, int32_t k, float 
                          int32_t iters, float eps, uint32_t polls, void *stream);
 
 /*
+ * The plan that nmf_mu_dense would run with these arguments and the workspace as it is, in *plan: 0 the small plan, 1 the
+ * mirrored, 2 the row, 3 the one-pass, 4 the resident plan; 8 more if it runs on padded copies (which are made).
+ * k <= NMF_MU_MAX_K; W and H are read.
+ */
+int nmfmu_dense_plan(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
+                     int32_t *plan, void *stream);
+
+/*
  * nmf_mu_dense with timing, on A as it is (no copy of a misaligned A is made, so such
  * an A takes the slower kernels here): the same launches on `stream`, with a HIP event
  * recorded between them; synchronises `stream` before returning.  On return

@@ -1932,6 +1932,19 @@ int nmf_mu_dense_noalloc(const float *A, int64_t m, int64_t n, int32_t k, float 
 
 // ---- single steps ----------------------------------------------------------
 
+int nmfmu_dense_plan(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
+                     int32_t *plan, void *stream)
+{
+    if (int rc = check_common(A, W, H, m, n, k, iters, eps)) return rc;
+    if (!plan) return fail(NMF_EINVAL, "null pointer%s");
+    std::lock_guard<std::mutex> lock(g.mu);
+    DenseRun r;
+    if (int rc = open_run(A, m, n, k, W, H, iters, eps, 0, static_cast<hipStream_t>(stream), &r)) return rc;
+    *plan = r.p.resident ? 4 : r.p.one_pass ? 3 : takes_row_plan(r.p, r.A, r.m, r.n, k) ? 2 : r.p.mirrored ? 1 : 0;
+    if (r.A != A || r.W != W || r.H != H) *plan += 8;
+    return NMF_OK;
+}
+
 static int resident_hook(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters, float eps, int workgroups,
                          long long patience, unsigned polls, hipStream_t st)
 {
