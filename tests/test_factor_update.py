@@ -1,5 +1,6 @@
 """The factor update at the edges of its chunk widths (16, 32 and 64 columns), factor counts and split
-batches, and on a factor of more than 2^31 bytes."""
+batches, and on a factor of more than 2^31 bytes.  Up to 16 factors the smaller ones run in one launch
+(test_resident.py) unless the workspace is short (test_short_workspaces.py)."""
 import numpy as np
 import pytest
 

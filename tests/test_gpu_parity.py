@@ -142,7 +142,8 @@ def test_mu_dense_one_iteration(m, n, k):
 def test_row_plan_shapes(m, n, k, iters):
     """Run twice: as the library plans it (the row plan for 12288 rows and 512 columns or more and for
     small problems, a transposed copy otherwise), and with a workspace that has no room for a copy,
-    which leaves every one of these shapes to the row kernel."""
+    which leaves these shapes to the plans on A itself (all reported as 2): the row kernel, up to 512 columns a one-pass
+    kernel if it fits, up to 16 factors the resident one if it does; test_short_workspaces.py names them."""
     A, W, H = case(m, n, k, 300 + k)
     Wr, Hr = orc.mu_dense(A, W, H, iters, float(np.float32(EPS)))
     Wg, Hg = run_dense(A, W, H, iters)

@@ -1,6 +1,7 @@
 """Both products in one reading of A (up to 32 factors, up to 512 columns): edges of the row tiles,
 the column groups, the factor count and the rows an accumulator may take in, against the oracle;
-a run cut in two; the objective from its by-products."""
+a run cut in two; the objective from its by-products.  Up to 16 factors the smaller ones run in one launch
+(test_resident.py) unless the workspace is short (test_short_workspaces.py)."""
 import numpy as np
 import pytest
 

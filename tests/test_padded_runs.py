@@ -1,6 +1,7 @@
 """Dense runs on copies with padded rows or columns (m % 4, n % 4 or the base of A not what the streaming
 kernels take), against the oracle: all three plans, the monitored and the stopped run, and
-a workspace that cannot hold the copies."""
+a workspace that cannot hold the copies.  At 12 factors the smaller ones need no copies (test_resident.py) unless the
+workspace is short (test_short_workspaces.py)."""
 import numpy as np
 import pytest
 

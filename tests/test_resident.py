@@ -10,9 +10,11 @@ from oracle import nmf_oracle as orc
 
 EPS = 1e-16
 # one group of columns and 1, 2, 4 row tiles per workgroup (1, 32, 33, 63, 65 row groups, an odd rest); two to 16 groups
-# of columns; more groups of rows than 16 (owners of no column tile), more groups of columns than row tiles
+# of columns; more groups of rows than 16 (owners of no column tile), more groups of columns than row tiles; 4 row tiles
+# on two or three groups of columns (an owner's second tile in the W update)
 SHAPES = [(1, 1), (16, 16), (17, 15), (256, 192), (513, 255), (1000, 256), (1025, 31), (4161, 97), (16380, 256), (40, 257),
-          (100, 513), (600, 1003), (2000, 1201), (1030, 2047), (63, 4096), (4096, 1024)]
+          (100, 513), (600, 1003), (2000, 1201), (1030, 2047), (63, 4096), (4096, 1024),
+          (1100, 300), (8192, 512), (2001, 700)]
 
 
 def data(m, n, k):
