@@ -3533,8 +3533,11 @@ hipError_t launch_gram_w(const float *X, int64_t rows, int k, float *G, float *g
     return hipGetLastError();
 }
 
-// 1024 rows per workgroup, two trips; beyond, 256 workgroups and a launch for the sum read faster.
-constexpr int64_t kGram16Rows = 1 << 16;
+// Up to 2048 rows per workgroup, four trips; beyond, 256 workgroups and a launch for the sum read faster.  Sparse iterations
+// (two Gram matrices of this many rows, one entry per row), gram16_kernel against the two launches, in us: k = 12 16384 rows 29.0, 31.3,
+// 65536 38.9, 41.3, 98304 51.9, 53.2, 131072 55.4, 55.9, 262144 93.3, 89.9; k = 4 131072 39.8, 40.5, 262144 53.8, 51.2; k = 16 131072
+// 58.7, 58.9, 262144 99.5, 96.2.
+constexpr int64_t kGram16Rows = 1 << 17;
 hipError_t launch_gram_w_wide(const float *X, int64_t rows, int k, float *G, float *tiles, unsigned *counters, hipStream_t st, int ld)
 {
     if (k <= 16 && rows <= kGram16Rows) {

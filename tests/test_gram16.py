@@ -1,4 +1,4 @@
-"""Gram matrices of up to 16 factors in one launch: row counts around the shares and the line to the other kernels, through
+"""Gram matrices of up to 16 factors in one launch: row counts around the shares and the line to the other kernels (131072), through
 sparse runs against the oracle; a run cut in two gives the same bits."""
 import numpy as np
 import pytest
@@ -9,7 +9,8 @@ EPS = 1e-16
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("m,n,k", [(1, 5, 3), (63, 65, 1), (64, 129, 16), (1000, 4097, 15), (65536, 70, 12), (65537, 90, 16)])
+@pytest.mark.parametrize("m,n,k", [(1, 5, 3), (63, 65, 1), (64, 129, 16), (1000, 4097, 15), (65536, 70, 12), (65537, 90, 16), (131072, 60, 5),
+                                   (131073, 60, 9)])
 def test_sparse_runs(m, n, k):
     import torch
 
