@@ -461,10 +461,9 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
                 for (int slot = 0; slot < kDenseKernels; ++slot) {
                     a.nprod = slot == 1;
                     a.lead = slot == 4;
-                    if (slot == 1 || slot == 4) NMF_HIP(launch_resident(a, p.resident, st, it == 0 && slot == 1));
+                    if (slot == 1 || slot == 4) NMF_HIP(launch_resident(a, p.resident, st));
                     NMF_HIP(hipEventRecord(*ev++, st));
                 }
-            NMF_HIP(launch_resident_mark(a, st));
             return NMF_OK;
         }
         const int calls = mon && !mon->last_only ? iters : 1;
@@ -472,13 +471,12 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         const int R = (int)((m + 16 * p.resident - 1) / (16 * p.resident)), C = (int)((n + 255) / 256);
         if (mon) a.dpart = mon->dpart, a.gout = c.gwp, a.gh = c.gh;
         for (int i = 0; i < calls; ++i) {
-            NMF_HIP(launch_resident_run(a, p.resident, st, i == 0));
+            NMF_HIP(launch_resident_run(a, p.resident, st));
             if (mon) {
                 NMF_HIP(launch_gram_sum(c.gwp, R, k, c.gw, st));
                 NMF_HIP(launch_objective(mon->dpart, R * C, c.gw, c.gh, k, mon->normA2, mon->out + i, st));
             }
         }
-        NMF_HIP(launch_resident_mark(a, st));
         return NMF_OK;
     }
     if (p.one_pass) {
@@ -1959,8 +1957,7 @@ static int resident_hook(const float *A, int64_t m, int64_t n, int k, float *W, 
     ResidentArgs a = carve_resident(cv, m, n, k, tiles).res;
     a.A = A, a.Win = a.W = W, a.Hin = a.H = H;
     a.m = m, a.n = n, a.k = k, a.eps = eps, a.nprod = iters, a.patience = patience, a.polls = polls;
-    NMF_HIP(launch_resident_run(a, tiles, st, true, workgroups));
-    NMF_HIP(launch_resident_mark(a, st));
+    NMF_HIP(launch_resident_run(a, tiles, st, workgroups));
     return NMF_OK;
 }
 

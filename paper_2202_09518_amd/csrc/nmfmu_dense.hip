@@ -2329,8 +2329,9 @@ __global__ __launch_bounds__(1024, 1) void one_pass16_kernel(
 // 16384 x 256, k = 16 17.5, 40.9, 48.2, 90, 4100 (the other plans on the whole device: 27.5 and 33.4).  The two bodies apart
 // also took a tenth off the iterations of all (256 x 192, k = 4: 7.3 -> 6.5 us): fewer scalar registers to spill.
 // Only a caller that breaks the rule of one call at a time per workspace can take flags away from a run that waits for
-// them: each wait has `polls` looks (ten seconds or more), then the run is marked as lost, nobody waits for it any
-// longer and it ends; a launch behind it (resident_mark_kernel) leaves a NaN in W and H.
+// them: each wait has `polls` looks (ten seconds or more), then the launch is marked as lost, nobody waits in it any
+// longer and it ends; the last workgroup to leave stores a NaN in W[0] and H[0].  The last updates store to W and H behind the
+// L2s, so that no line of an L2 is written back over it.  (A launch behind the run for this: 2 to 6 us more per call.)
 // A launch does a bounded number of iterations (resident_piece): a longer run is cut, which gives the same bits.
 // Stores and loads of what workgroups exchange carry the sc1 bit: they meet behind the L2s of the XCDs.
 // (Plain loads after an acquire at the flags, which drops the L2's copies, were slower: 19.5 for 18.4 us.)
@@ -2346,6 +2347,7 @@ __host__ __device__ constexpr int resident_lds_floats(int rt)
 __device__ __forceinline__ unsigned peek(const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void post(unsigned *p, unsigned x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ unsigned add_one(unsigned *p) { return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void put_through(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ bool decide(unsigned *p, unsigned x)      // if nobody has
 {
     unsigned none = 0u;
@@ -2388,10 +2390,21 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
     unsigned short *Wp = reinterpret_cast<unsigned short *>(Hs + 16 * LD);   // pieces of the rows [3][RB / 8][16][8]
     unsigned *word = reinterpret_cast<unsigned *>(Hs + 16 * LD + 3 * RT * 128);
     double *dsum = reinterpret_cast<double *>(word + 2);
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, quad = lane >> 4, hr = quad & 1, half = lane >> 5;
     const int er = (tid >> 4) & 15, ec = tid & 15;
+    // The lane, with 4 row tiles found again in every iteration: what follows from it (offsets, masks) would else be kept in
+    // registers over the loop, 15 more than there are (2000 x 1201, k = 12: 12.3 us an iteration instead of 11.2).
+    int lane, l16, quad, hr, half;
+    auto place = [&]() {
+        lane = tid & 63;
+        if (RT > 2) asm volatile("" : "+v"(lane));
+        l16 = lane & 15;
+        quad = lane >> 4;
+        hr = quad & 1;
+        half = lane >> 5;
+    };
+    place();
     const int k = a.k, R = a.R, C = a.C, nwg = R * C, n = (int)a.n;
     const int nt = (n + 15) >> 4;                                  // 16-column tiles in all
     const int rpad = (R + 31) & ~31, box = rpad + 32;              // words of a workgroup's letter box: column group, row group
@@ -2540,7 +2553,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         const int64_t grow = (int64_t)r * RB + row;
         if (grow >= a.m || f >= k) return 0.f;
         const float x = Ws[row * LD + f] * num / (dot(Ws + row * LD, f) + a.eps);   // H H^T is symmetric
-        if (last) a.W[grow * k + f] = x;
+        if (last) put_through(a.W + grow * k + f, x);
         dacc += (double)num * (double)x;
         return x;
     };
@@ -2560,6 +2573,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
 
     bool have_tile = false;
     for (; s <= a.nprod; ++s) {
+        place();
         epoch = 8 * s;                 // more than an iteration's meetings
         if (s == 0) {
             for (int v = v0; v < v1; ++v)      // H as handed in, to where its owners look for it
@@ -2834,7 +2848,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                     const float den = dot(Hs + ec * LD, er);
                     const float h = er < k && col < n ? hold * sum / (den + a.eps) : 0.f;
                     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h), rh, hoff, 0, kExchange);
-                    if (last_h && er < k && col < n) a.H[(int64_t)er * n + col] = h;
+                    if (last_h && er < k && col < n) put_through(a.H + (int64_t)er * n + col, h);
                 }
             }
         }
@@ -2888,17 +2902,19 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     __syncthreads();
     const unsigned deal = __builtin_amdgcn_readfirstlane(word[0]), ticket = __builtin_amdgcn_readfirstlane(word[1]);
     __syncthreads();
-    if (deal == kResidentOver) return;
-    int s = (int)(deal >> 9) - 1;
-    if ((int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, true>(a, s, ticket, deal);
-    if (s >= 0) resident_iterations<RT, false>(a, s, 0u, 0u);
+    if (deal != kResidentOver) {
+        int s = (int)(deal >> 9) - 1;
+        if ((int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, true>(a, s, ticket, deal);
+        if (s >= 0) resident_iterations<RT, false>(a, s, 0u, 0u);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // what this workgroup has stored, marks among it
+    __syncthreads();
+    if (threadIdx.x == 0 && add_one(a.sync + kResidentOut) == gridDim.x - 1 && peek(a.sync + kResidentLost)) {
+        put_through(a.W, __builtin_nanf(""));
+        put_through(a.H, __builtin_nanf(""));
+    }
 }
 
-// Behind all launches of a run: the owners of W[0] and H[0] have stored what they had.
-__global__ void resident_mark_kernel(const unsigned *sync, float *W, float *H)
-{
-    if (sync[kResidentLost]) W[0] = H[0] = __builtin_nanf("");
-}
 
 // G (k x k, ld k) = sum over nb sets of partial 32 x 32 tiles (accumulator layout).
 // Eight lanes share one entry: lane q adds sets q, q+8, ..., a batch of 16 at a time, then the
@@ -4106,7 +4122,7 @@ static hipError_t resident_launch(unsigned blocks, hipStream_t st, const Residen
     return hipGetLastError();
 }
 
-hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first, int workgroups)
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, int workgroups)
 {
     ResidentArgs a = args;
     if (a.k < 1 || a.k > 16 || a.m < 1 || a.n < 1 || !a.A || !a.part || !a.qpart || !a.hx || !a.wx || !a.sync ||
@@ -4120,28 +4136,21 @@ hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, 
     if (!a.patience) a.patience = 20000;
     if (!a.polls) a.polls = kLostPolls;
     const unsigned blocks = workgroups > 0 && workgroups < R * C ? (unsigned)workgroups : (unsigned)(R * C);
-    const int64_t from = first ? 0 : kResidentLost + 1;       // the mark of a lost run stays for all its launches
-    hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync + from), resident_sync_words(R, C) - from, 0.f, st);
+    hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync), resident_sync_words(R, C), 0.f, st);
     if (e != hipSuccess) return e;
     return tiles == 1 ? resident_launch<1>(blocks, st, a) : tiles == 2 ? resident_launch<2>(blocks, st, a) : resident_launch<4>(blocks, st, a);
 }
 
-hipError_t launch_resident_mark(const ResidentArgs &a, hipStream_t st)
-{
-    hipLaunchKernelGGL(resident_mark_kernel, dim3(1), dim3(1), 0, st, a.sync, a.W, a.H);
-    return hipGetLastError();
-}
-
-hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first, int workgroups)
+hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, int workgroups)
 {
     const int piece = resident_piece((args.m + 16 * tiles - 1) / (16 * tiles) * ((args.n + 255) / 256));
     ResidentArgs a = args;
     a.trail = 1;
-    for (int left = args.nprod; left > 0; left -= a.nprod, first = false) {
+    for (int left = args.nprod; left > 0; left -= a.nprod) {
         a.nprod = left < piece ? left : piece;
         a.dpart = a.nprod == left ? args.dpart : nullptr;
         a.gout = a.nprod == left ? args.gout : nullptr;
-        if (hipError_t e = launch_resident(a, tiles, st, first, workgroups)) return e;
+        if (hipError_t e = launch_resident(a, tiles, st, workgroups)) return e;
         a.Win = a.W;
         a.Hin = a.H;
     }

@@ -169,7 +169,8 @@ constexpr int kResidentLost = 0,     // set when a wait has run out of looks
     kResidentHere = 32,              // workgroups that have reported in
     kResidentDeal = 64,              // how many of them are at work, from which iteration on
     kResidentArrived = 96, kResidentRelease = 128,     // barriers of a shared run
-    kResidentHead = 160;
+    kResidentOut = 160,              // workgroups that are done
+    kResidentHead = 192;
 constexpr unsigned kResidentOver = ~0u;     // in kResidentDeal: who comes now is not needed
 constexpr int kResidentPRec = 4096 + 160;     // floats of a workgroup's record in part,
 constexpr int resident_qrec(int tiles) { return 256 * (tiles + 1); }     // and in qpart
@@ -179,13 +180,11 @@ int resident_tiles(int64_t m, int64_t n, int k);
 // workgroup does the run of all, and the flags (8 an iteration) stay far from their end.  Loading A again costs 10
 // to 20 us.
 inline int resident_piece(int64_t groups) { return (int)(groups > 256 ? 256 : groups < 16 ? 4096 : 65536 / groups); }
-// Fills in R, C and the defaults and clears sync, the mark of a lost run only with `first`.  workgroups > 0: that many
-// are launched instead of R * C (and share the run).
-hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, int workgroups = 0);
+// Fills in R, C and the defaults and clears sync.  workgroups > 0: that many are launched instead of R * C (and share
+// the run).
+hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, int workgroups = 0);
 // nprod updates of H, each followed by one of W, in launches of resident_piece iterations.
-hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, bool first = true, int workgroups = 0);
-// A NaN in W and H if a launch since the last `first` was lost.
-hipError_t launch_resident_mark(const ResidentArgs &a, hipStream_t st);
+hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, int workgroups = 0);
 
 // out[0] = sum of in[0 .. count), added in a fixed order (strided per thread, then the threads in order).
 hipError_t launch_sum_f64(const double *in, int64_t count, double *out, hipStream_t st);
