@@ -429,12 +429,20 @@ constexpr int kDenseKernels = 6;
 
 // Per-iteration objective of a dense run (device memory): out[it] after iteration it.
 struct Monitor {
-    double *dpart;      // kFinMaxBlocks: <numerator, new W> per finisher block
+    double *dpart;      // kFinMaxBlocks: <numerator, new W> per finisher block (batch times that, batch > 1)
     double *normA2;     // [0] = ||A||_F^2, followed by 4096 doubles of scratch for its sum
     double *out;        // iters values
     double *res;        // direct plan: scratch of the tiled evaluation (ceil(m / 32) + 1 doubles)
     bool last_only;     // only the last iteration of the call reports (into out[0])
+    int batch = 1;      // resident plan: iterations per launch that reports them all, with
+    float *gw = nullptr, *gh = nullptr;      // batch Gram matrices each
 };
+// 32 iterations: what a launch costs beyond its iterations (20 us) no longer shows.
+constexpr int kMonitored = 32;
+size_t monitored_bytes(int batch, int k)
+{
+    return align_up((size_t)(batch - 1) * kFinMaxBlocks * sizeof(double)) + 2 * align_up((size_t)batch * k * k * sizeof(float));
+}
 
 // One resident dense run on `st`.  With `ev` (kDenseKernels * iters + 1 events)
 // an event is recorded before the first kernel of the loop and after every
@@ -466,15 +474,19 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
                 }
             return NMF_OK;
         }
-        const int calls = mon && !mon->last_only ? iters : 1;
-        a.nprod = iters / calls;
+        const bool all = mon && !mon->last_only;
+        const int step = all ? mon->batch : iters;
         const int R = (int)((m + 16 * p.resident - 1) / (16 * p.resident)), C = (int)((n + 255) / 256);
+        float *gw = c.gw;
         if (mon) a.dpart = mon->dpart, a.gout = c.gwp, a.gh = c.gh;
-        for (int i = 0; i < calls; ++i) {
+        if (all && step > 1) a.gw = gw = mon->gw, a.gh = mon->gh;
+        for (int i = 0; i < iters; i += step) {
+            const int some = iters - i < step ? iters - i : step, report = all ? some : 1;
+            a.nprod = some;
             NMF_HIP(launch_resident_run(a, p.resident, st));
             if (mon) {
-                NMF_HIP(launch_gram_sum(c.gwp, R, k, c.gw, st));
-                NMF_HIP(launch_objective(mon->dpart, R * C, c.gw, c.gh, k, mon->normA2, mon->out + i, st));
+                NMF_HIP(launch_gram_sum(c.gwp, R, k, gw + (size_t)(report - 1) * k * k, st));
+                NMF_HIP(launch_objective(mon->dpart, R * C, gw, a.gh, k, mon->normA2, mon->out + i, st, report));
             }
         }
         return NMF_OK;
@@ -1881,13 +1893,25 @@ int nmf_mu_dense_monitor(const float *A, int64_t m, int64_t n, int32_t k, float 
     if (iters == 0) return NMF_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
-    const size_t extra = align_up((size_t)kFinMaxBlocks * sizeof(double)) + align_up(4097 * sizeof(double)) +
-                         align_up((size_t)iters * sizeof(double)) + run_scratch_bytes(m, n);
+    size_t extra = align_up((size_t)kFinMaxBlocks * sizeof(double)) + align_up(4097 * sizeof(double)) +
+                   align_up((size_t)iters * sizeof(double)) + run_scratch_bytes(m, n);
+    Monitor mon;
+    if (resident_tiles(m, n, k) && iters > 1) {
+        const int batch = iters < kMonitored ? iters : kMonitored;
+        const size_t more = monitored_bytes(batch, k);
+        if (have_workspace(resident_bytes(m, n, k) + extra + more, st)) {
+            mon.batch = batch;
+            extra += more;
+        }
+    }
     DenseRun r;
     if (int rc = open_run(A, m, n, k, W, H, iters, eps, extra, st, &r)) return rc;
     Carve cv(r.tail);
-    Monitor mon;
-    mon.dpart = cv.take<double>(kFinMaxBlocks);
+    mon.dpart = cv.take<double>((size_t)mon.batch * kFinMaxBlocks);
+    if (mon.batch > 1) {
+        mon.gw = cv.take<float>((size_t)mon.batch * k * k);
+        mon.gh = cv.take<float>((size_t)mon.batch * k * k);
+    }
     mon.normA2 = cv.take<double>(4097);
     mon.out = cv.take<double>((size_t)iters);
     mon.res = cv.take<double>(run_scratch_bytes(m, n) / sizeof(double));

@@ -2557,8 +2557,9 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         dacc += (double)num * (double)x;
         return x;
     };
-    // what the last update of W leaves for the objective; `owner` of the row group's first tile: also its W^T W
+    // what the last update of W, or every one (lead = 0), leaves for the objective
     auto report = [&](int v, double dacc) {
+        const int u = a.gw ? s - 1 : 0;
         for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
         __syncthreads();
         if (lane == 0) dsum[w] = dacc;
@@ -2566,9 +2567,9 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         if (tid == 0) {
             double t = 0.0;
             for (int i = 0; i < 8; ++i) t += dsum[i];
-            a.dpart[v] = t;
+            a.dpart[u * nwg + v] = t;
         }
-        if (v == 0 && tid < 256 && er < k && ec < k) a.gh[er * k + ec] = Gs[er * LD + ec];
+        if (v == 0 && tid < 256 && er < k && ec < k) a.gh[(u * k + er) * k + ec] = Gs[er * LD + ec];
     };
 
     bool have_tile = false;
@@ -2668,7 +2669,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                             if (SHARED) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), rw, (unsigned)(r * RB * 16 + e) * 4u, 0, kExchange);
                         }
                     }
-                    if (last_w && a.dpart) report(v, dacc);
+                    if (a.dpart && (last_w || a.gw)) report(v, dacc);
                 } else {
                     const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(a.qpart + (int64_t)v * kQRec, 0, kQRec * 4, kRsrcFlags);
 #pragma unroll
@@ -2717,7 +2718,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rw, (unsigned)((r * RB + 16 * tt) * 16 + tid) * 4u, 0, kExchange);
                         }
                     }
-                    if (last_w && a.dpart) report(v, dacc);
+                    if (a.dpart && (last_w || a.gw)) report(v, dacc);
                 }
                 if (product || a.gout) meet(false);
             }
@@ -2842,6 +2843,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
 #pragma unroll
                     for (int i = 0; i < 8; ++i) x += (double)Gq[i * 256 + hi * (hi + 1) / 2 + lo];
                     put_g(hi < k ? x : 0.0);
+                    if (a.gw && s > 0 && v == 0 && t == 0 && hi < k) a.gw[((s - 1) * k + er) * k + ec] = (float)x;
                 }
                 __syncthreads();
                 if (tid < 256) {
@@ -3408,6 +3410,10 @@ __global__ __launch_bounds__(256) void objective_kernel(const double *__restrict
 {
     __shared__ double part[256], dsum[256];
     double gg = 0.0, dd = 0.0;
+    dpart += (int64_t)blockIdx.x * nb;       // a workgroup per iteration
+    GW += blockIdx.x * k * k;
+    GH += blockIdx.x * k * k;
+    out += blockIdx.x;
     for (int e = threadIdx.x; e < k * k; e += 256) gg += (double)GW[e] * (double)GH[e];
     // shares b, b + 256, ... per thread, then the threads in order (the sparse and the streamed
     // runs hand over thousands of shares: one thread alone would spend 0.3 ms on them)
@@ -3798,9 +3804,9 @@ hipError_t launch_sumsq(const float *X, int64_t count, double *partial, double *
 }
 
 hipError_t launch_objective(const double *dpart, int nb, const float *GW, const float *GH, int k,
-                            const double *normA2, double *out, hipStream_t st)
+                            const double *normA2, double *out, hipStream_t st, int iters)
 {
-    hipLaunchKernelGGL(objective_kernel, dim3(1), dim3(256), 0, st, dpart, nb, GW, GH, k, normA2, out);
+    hipLaunchKernelGGL(objective_kernel, dim3((unsigned)iters), dim3(256), 0, st, dpart, nb, GW, GH, k, normA2, out);
     return hipGetLastError();
 }
 
@@ -4126,7 +4132,7 @@ hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, 
 {
     ResidentArgs a = args;
     if (a.k < 1 || a.k > 16 || a.m < 1 || a.n < 1 || !a.A || !a.part || !a.qpart || !a.hx || !a.wx || !a.sync ||
-        (a.dpart && (!a.gout || !a.gh)) || (tiles != 1 && tiles != 2 && tiles != 4))
+        (a.dpart && (!a.gout || !a.gh)) || (a.gw && (!a.dpart || a.lead || !a.trail)) || (tiles != 1 && tiles != 2 && tiles != 4))
         return hipErrorInvalidValue;
     const int64_t R = (a.m + 16 * tiles - 1) / (16 * tiles), C = (a.n + 255) / 256;
     if (R * C > 256) return hipErrorInvalidValue;

@@ -98,8 +98,9 @@ hipError_t launch_factor_update(float *X, float *Xt, const float *part, int spli
 // out[0] = sum of squares of X[0 .. count) in double; partial: 4096 doubles of scratch.
 hipError_t launch_sumsq(const float *X, int64_t count, double *partial, double *out, hipStream_t st);
 // out[0] = sqrt(max(0, normA2[0] - 2 sum(dpart[0 .. nb)) + <GW, GH>)).
+// iters: of that many iterations, their nb shares and matrices one behind the other.
 hipError_t launch_objective(const double *dpart, int nb, const float *GW, const float *GH, int k,
-                            const double *normA2, double *out, hipStream_t st);
+                            const double *normA2, double *out, hipStream_t st, int iters = 1);
 int factor_update_blocks(int64_t len);
 // G (k x k, ld k) = sum of nb sets of partial tiles.
 hipError_t launch_gram_sum(const float *gpart, int nb, int k, float *G, hipStream_t st);
@@ -156,6 +157,8 @@ struct ResidentArgs {
     unsigned *sync;                  // kResidentLost ..; from kResidentHead on the letter boxes; zero at the start
     double *dpart;                   // optional, of the last W update: <A H^T, W> in R C shares,
     float *gout, *gh;                // R tile sets of W^T W (32 x 32 accumulator layout) and H H^T (k x k)
+    float *gw;                       // optional: dpart and gh of every update of W, one behind the other, and here W^T W (k x k) of
+                                     // all but the last (lead = 0, trail = 1, one launch)
     int64_t m, n;
     int k, R, C;
     float eps;

@@ -261,3 +261,33 @@ def test_two_runs_at_once(first, second):
         results.append(factors)
     for (Wa, Ha), (Wb, Hb) in zip(*results):
         assert torch.equal(Wa, Wb) and torch.equal(Ha, Hb)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(256, 192, 4), (40, 257, 5), (16380, 256, 16), (2000, 1201, 12)])
+def test_objectives_of_several_launches(m, n, k):
+    """More iterations than a launch reports: the factors of a plain run and its objectives, also from a workspace that has no
+    room to report several iterations at once."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+    iters, want = 70, {}
+    We, He = W.clone(), H.clone()
+    for it in range(iters):
+        nmf.nmf_mu_dense(A, m, n, k, We, He, 1, EPS)
+        if it in (0, 30, 31, 32, 63, 64, 69):
+            want[it] = nmf.nmf_residual_dense(A, m, n, k, We, He)
+    normA2 = float(A.double().square().sum())
+    short = nmf.nmf_mu_workspace_bytes(4, m, n, 0, k, 0) + (48 << 10) * (-(-m // 16) * -(-n // 256))
+    for size in (None, short):
+        Wd, Hd = W.clone(), H.clone()
+        nmf.nmf_mu_set_workspace(None if size is None else torch.empty(size, dtype=torch.uint8, device="cuda"))
+        try:
+            got = nmf.nmf_mu_dense_monitor(A, m, n, k, Wd, Hd, iters, EPS)
+        finally:
+            nmf.nmf_mu_set_workspace(None)
+        assert torch.equal(Wd, We) and torch.equal(Hd, He)
+        for it, f in want.items():
+            # ||A||^2 - 2 <A H^T, W> + <H H^T, W^T W>: three sums of relative error 2^-21 or less that cancel
+            assert abs(got[it] ** 2 - f ** 2) <= 1e-6 * normA2 + 1e-5 * f ** 2, (size, it)
