@@ -2370,8 +2370,10 @@ struct Patient {
 };
 
 // Iterations `s` .. of the workgroup.  SHARED: a range of the workgroups' work, dealt anew after every iteration; returns
-// the iteration from which all workgroups are there, or -1 after the last.
-template <int RT, bool SHARED>
+// the iteration from which all workgroups are there, or -1 after the last.  EVERY: all updates of W leave their part of the
+// objective (a.gw), not only the last (if a.dpart).  (A launch per reported iteration took 20 us more each: 4096 x 1024,
+// k = 8, 20 iterations 903 us a call, 802 on the row plan, 340 so.  As a run-time case: 3 % on runs that report nothing.)
+template <int RT, bool EVERY, bool SHARED>
 __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s, unsigned ticket, unsigned deal)
 {
     constexpr int kRsrcFlags = 0x00020000;         // raw buffer, 32-bit data format (gfx9 family)
@@ -2559,7 +2561,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
     };
     // what the last update of W, or every one (lead = 0), leaves for the objective
     auto report = [&](int v, double dacc) {
-        const int u = a.gw ? s - 1 : 0;
+        const int u = EVERY ? s - 1 : 0;
         for (int off = 32; off > 0; off >>= 1) dacc += __shfl_xor(dacc, off);
         __syncthreads();
         if (lane == 0) dsum[w] = dacc;
@@ -2669,7 +2671,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                             if (SHARED) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), rw, (unsigned)(r * RB * 16 + e) * 4u, 0, kExchange);
                         }
                     }
-                    if (a.dpart && (last_w || a.gw)) report(v, dacc);
+                    if (a.dpart && (last_w || EVERY)) report(v, dacc);
                 } else {
                     const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(a.qpart + (int64_t)v * kQRec, 0, kQRec * 4, kRsrcFlags);
 #pragma unroll
@@ -2718,7 +2720,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rw, (unsigned)((r * RB + 16 * tt) * 16 + tid) * 4u, 0, kExchange);
                         }
                     }
-                    if (a.dpart && (last_w || a.gw)) report(v, dacc);
+                    if (a.dpart && (last_w || EVERY)) report(v, dacc);
                 }
                 if (product || a.gout) meet(false);
             }
@@ -2843,7 +2845,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
 #pragma unroll
                     for (int i = 0; i < 8; ++i) x += (double)Gq[i * 256 + hi * (hi + 1) / 2 + lo];
                     put_g(hi < k ? x : 0.0);
-                    if (a.gw && s > 0 && v == 0 && t == 0 && hi < k) a.gw[((s - 1) * k + er) * k + ec] = (float)x;
+                    if (EVERY && s > 0 && v == 0 && t == 0 && hi < k) a.gw[((s - 1) * k + er) * k + ec] = (float)x;
                 }
                 __syncthreads();
                 if (tid < 256) {
@@ -2879,7 +2881,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
     return -1;
 }
 
-template <int RT>
+template <int RT, bool EVERY>
 __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
 {
     unsigned *word = reinterpret_cast<unsigned *>(aht_rows_lds);
@@ -2906,8 +2908,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     __syncthreads();
     if (deal != kResidentOver) {
         int s = (int)(deal >> 9) - 1;
-        if ((int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, true>(a, s, ticket, deal);
-        if (s >= 0) resident_iterations<RT, false>(a, s, 0u, 0u);
+        if ((int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, EVERY, true>(a, s, ticket, deal);
+        if (s >= 0) resident_iterations<RT, EVERY, false>(a, s, 0u, 0u);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // what this workgroup has stored, marks among it
     __syncthreads();
@@ -4113,18 +4115,18 @@ int resident_tiles(int64_t m, int64_t n, int k)
     return 0;
 }
 
-template <int RT>
+template <int RT, bool EVERY>
 static hipError_t resident_launch(unsigned blocks, hipStream_t st, const ResidentArgs &a)
 {
     constexpr int kLdsBytes = resident_lds_floats(RT) * (int)sizeof(float);
     static bool raised = false;      // more dynamic LDS than the default limit: asked for once per process
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&resident_kernel<RT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&resident_kernel<RT, EVERY>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    hipLaunchKernelGGL((resident_kernel<RT>), dim3(blocks), dim3(512), kLdsBytes, st, a);
+    hipLaunchKernelGGL((resident_kernel<RT, EVERY>), dim3(blocks), dim3(512), kLdsBytes, st, a);
     return hipGetLastError();
 }
 
@@ -4144,7 +4146,8 @@ hipError_t launch_resident(const ResidentArgs &args, int tiles, hipStream_t st, 
     const unsigned blocks = workgroups > 0 && workgroups < R * C ? (unsigned)workgroups : (unsigned)(R * C);
     hipError_t e = launch_fill_f32(reinterpret_cast<float *>(a.sync), resident_sync_words(R, C), 0.f, st);
     if (e != hipSuccess) return e;
-    return tiles == 1 ? resident_launch<1>(blocks, st, a) : tiles == 2 ? resident_launch<2>(blocks, st, a) : resident_launch<4>(blocks, st, a);
+    if (a.gw) return tiles == 1 ? resident_launch<1, true>(blocks, st, a) : tiles == 2 ? resident_launch<2, true>(blocks, st, a) : resident_launch<4, true>(blocks, st, a);
+    return tiles == 1 ? resident_launch<1, false>(blocks, st, a) : tiles == 2 ? resident_launch<2, false>(blocks, st, a) : resident_launch<4, false>(blocks, st, a);
 }
 
 hipError_t launch_resident_run(const ResidentArgs &args, int tiles, hipStream_t st, int workgroups)
