@@ -291,3 +291,27 @@ def test_objectives_of_several_launches(m, n, k):
         for it, f in want.items():
             # ||A||^2 - 2 <A H^T, W> + <H H^T, W^T W>: three sums of relative error 2^-21 or less that cancel
             assert abs(got[it] ** 2 - f ** 2) <= 1e-6 * normA2 + 1e-5 * f ** 2, (size, it)
+
+
+@pytest.mark.gpu
+def test_monitored_run_beside_another():
+    """Its launches find part of the compute units taken: the factors and objectives of an undisturbed run."""
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    m, n, k = 4096, 1024, 7
+    A, W, H = (torch.from_numpy(x).cuda() for x in data(m, n, k))
+    A2, W2, H2 = (torch.from_numpy(x).cuda() for x in data(6400, 256, 16))
+    side, runs = torch.cuda.Stream(), []
+    for disturbed in (False, True, True):
+        Wd, Hd = W.clone(), H.clone()
+        torch.cuda.synchronize()
+        if disturbed:
+            with torch.cuda.stream(side):
+                for _ in range(20):
+                    nmf.nmf_mu_dense_noalloc(A2, 6400, 256, 16, W2, H2, 100, EPS)
+        got = nmf.nmf_mu_dense_monitor(A, m, n, k, Wd, Hd, 70, EPS)
+        runs.append((Wd, Hd, list(got)))
+    torch.cuda.synchronize()
+    for Wd, Hd, got in runs[1:]:
+        assert torch.equal(Wd, runs[0][0]) and torch.equal(Hd, runs[0][1]) and got == runs[0][2]
