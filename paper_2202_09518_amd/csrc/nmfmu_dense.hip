@@ -1728,7 +1728,8 @@ __global__ __launch_bounds__(512, 2) void aht_rows_kernel(
 // twice.  One workgroup (8 waves, 116 KiB of LDS) fills a compute unit; its chain of LDS round
 // trips, not the memory, bounds it: 200000 x 400 at k = 30 takes 141 us per iteration.  It runs for 17 to 32
 // factors; up to 16 one_pass16_kernel does (524288 x 512, k = 16, per pass: 215 us for the W^T A pass and 340 for
-// aht_rows_kernel, 357 for this kernel, about 210 for that one).  Two chunks of columns
+// aht_rows_kernel; averages of a trace of three ten-iteration calls, and the shortest: 357 and 314 for this kernel, 259 and
+// 212 for that one).  Two chunks of columns
 // per wave (n up to 1024), with the second reading from the caches, gained 0.95 to 1.15x only,
 // three lost to the row plan (0.73 to 1.01x): hence the limit.
 // ---------------------------------------------------------------------------
@@ -2040,7 +2041,7 @@ __global__ __launch_bounds__(512, 2) void one_pass_kernel(
 // one_pass_kernel for up to 16 factors and many rows, on 16 x 16 x 32 instructions: the same block of 32 NRW rows, the
 // same partials and tile sets per workgroup, but 16 waves with 32 columns and 32 rows each.  With 32 factor slots half
 // of the matrix work, of the planes and of the accumulators would be padding, and 8 waves that pass through a chain of
-// LDS round trips in step left the memory idle for half of it: 357 us per pass on 524288 x 512 at k = 16.  Here a
+// LDS round trips in step left the memory idle for half of it: 357 us per pass on 524288 x 512 at k = 16 on average.  Here a
 // wave's share of a block is half as long, and its registers (four loads, one step of planes, two column tiles) leave room
 // for 16 waves; the running totals stay in registers (8 per lane) instead of going to ppart every 8 blocks.
 //   1. A arrives coalesced (8 rows x 128 bytes per instruction, a block ahead) and goes to the wave's 4 KiB of LDS, 16-byte
@@ -4099,11 +4100,12 @@ static int compute_units()
 
 // Row tiles per workgroup of the resident plan, 0: the plan does not apply.  One workgroup per compute unit, so the tiles
 // of A must be at most 256; within that the plan was faster at every size tried (us per iteration of 50, other plans ->
-// this one): 200 x 150 16.8 -> 6.6, 512 x 512 17.4 -> 10.1, 64 x 4096 33.4 -> 12.7, 2048 x 2048 31.9 -> 12.2, 8000 x 512
-// 34.8 -> 17.0, 16384 x 256 33.4 -> 18.0, 16384 x 64 25.5 -> 15.0; two iterations per call 18.2 -> 10.6 to 40.5 -> 20.2.
+// this one): 200 x 150 17.0 -> 6.4, 512 x 512 17.3 -> 9.8, 64 x 4096 33.7 -> 12.9, 2048 x 2048 31.9 -> 12.4, 8000 x 512
+// 34.8 -> 16.2, 16384 x 256 33.6 -> 17.3, 16384 x 64 31.7 -> 16.1; two iterations in a call, with its wait, 47 -> 36 us to 89 -> 68.
+// One iteration in a call takes as long as on the others, 4 us less to 2 more; it stays here for the bits of a run cut in pieces.
 // Low tiles first, as a workgroup's own work is shorter, but not more than 32 row groups if higher ones avoid that:
-// every owner of columns adds up a share per group (2000 x 192: 125 groups 10.4 us, 32 groups 8.4; 4096 x 256: 256 groups
-// 15.8, 64 groups 9.6).
+// every owner of columns adds up a share per group (2000 x 192: 125 groups 10.4 us, 32 groups 8.5; 4096 x 256: 256 groups
+// 15.8, 64 groups 9.9).
 int resident_tiles(int64_t m, int64_t n, int k)
 {
     if (k > 16 || m > 1 << 16 || n > 1 << 12) return 0;
