@@ -96,7 +96,7 @@ const char *nmf_last_error(void);
  * begin without the rest, who join in when they come (same bits; two to four times
  * slower with half or more of them, in proportion with fewer).  Calls
  * that overlap on one workspace (which race on any plan) may take seconds
- * until they give up, W[0] and H[0] are a NaN then; workspace kind 4 plus 48 KiB for each of the at most 256
+ * until they give up, W[0] and H[0] are normally a NaN then; workspace kind 4 plus 48 KiB for each of the at most 256
  * workgroups, else the next plan.  One-pass plan (k <= 32, 16-byte aligned
  * A, n % 4 == 0, n <= 512): both products of an iteration in one reading of A;
  * workspace kind 4 plus 1024 k n bytes at most.  Row plan (16-byte aligned A,

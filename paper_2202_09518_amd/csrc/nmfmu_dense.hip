@@ -2355,6 +2355,13 @@ __device__ __forceinline__ bool decide(unsigned *p, unsigned x)      // if nobod
     return __hip_atomic_compare_exchange_strong(p, &none, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// How many have reported in, within what a deal may say whatever other calls do to the word.
+__device__ __forceinline__ unsigned resident_here(const ResidentArgs &a, int most)
+{
+    const int here = (int)peek(a.sync + kResidentHere);
+    return (unsigned)(here < 1 ? 1 : here > most ? most : here);
+}
+
 // Waits of one thread for a word to reach a value.
 struct Patient {
     unsigned *lost_word;
@@ -2864,13 +2871,13 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                 const unsigned next = (unsigned)(s + 2) << 9;
                 unsigned now;
                 if (ticket == 0) {
-                    now = next | peek(a.sync + kResidentHere);
+                    now = next | resident_here(a, nwg);
                     post(a.sync + kResidentDeal, now);
                 } else {
                     thread.await(a.sync + kResidentDeal, next);
                     now = peek(a.sync + kResidentDeal);
                 }
-                word[0] = now >> 9 == next >> 9 ? now : deal;      // a lost run
+                word[0] = now >> 9 == next >> 9 && (now & 511) > ticket ? now : deal;      // else a lost run
             }
             __syncthreads();
             deal = __builtin_amdgcn_readfirstlane(word[0]);
@@ -2893,9 +2900,9 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
         unsigned deal;
         // the low nine bits: how many of those that have reported in are at work; the others: from which iteration on, plus one
         for (unsigned looks = 1; ((deal = peek(a.sync + kResidentDeal)) & 511) <= ticket; ++looks) {
-            if (ticket == 0 && (long long)wall_clock64() >= end) decide(a.sync + kResidentDeal, 1u << 9 | peek(a.sync + kResidentHere));
+            if (ticket == 0 && (long long)wall_clock64() >= end) decide(a.sync + kResidentDeal, 1u << 9 | resident_here(a, gridDim.x));
             __builtin_amdgcn_s_sleep(1);
-            if (ticket && looks >= a.polls) {
+            if (looks >= a.polls) {
                 post(a.sync + kResidentLost, 1u);
                 deal = kResidentOver;
                 break;
@@ -2908,8 +2915,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(const ResidentArgs a)
     const unsigned deal = __builtin_amdgcn_readfirstlane(word[0]), ticket = __builtin_amdgcn_readfirstlane(word[1]);
     __syncthreads();
     if (deal != kResidentOver) {
-        int s = (int)(deal >> 9) - 1;
-        if ((int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, EVERY, true>(a, s, ticket, deal);
+        int s = (int)(deal >> 9) - 1;      // beyond the last iteration, if it is not this run's deal: nothing is done
+        if (s >= 0 && (int)(deal & 511) < a.R * a.C) s = resident_iterations<RT, EVERY, true>(a, s, ticket, deal);
         if (s >= 0) resident_iterations<RT, EVERY, false>(a, s, 0u, 0u);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // what this workgroup has stored, marks among it
