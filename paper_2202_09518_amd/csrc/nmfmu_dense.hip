@@ -2322,12 +2322,12 @@ __global__ __launch_bounds__(1024, 1) void one_pass16_kernel(
 // Who waits for a flag must know that its writer runs.  The workgroups first report in, and when all have (all hold
 // their compute units then) the run starts.  If they have not after `patience` ticks of the 100 MHz counter (other
 // kernels, another such launch, a stream with few compute units), those that have start without the others: an
-// iteration's work of all R C is dealt to them in ranges, which they do one after the other, tiles loaded anew,
+// iteration's work of all R C is dealt to them, each does its share one workgroup's after the other, tiles loaded anew,
 // with barriers of all (the "shared" run).  After each iteration the first looks who has reported in meanwhile and
 // deals again; as soon as all have, each keeps its own tile from there on.  So every wait is for a
 // workgroup that runs, whatever else the device does; the sums, and so the bits, are the same.  Microseconds per iteration
-// with all, all but one, half and a quarter of the workgroups, and with one: 2000 x 1201, k = 12 11.4, 31.9, 38.6, 68, 2300;
-// 16384 x 256, k = 16 17.5, 40.9, 48.2, 90, 4100 (the other plans on the whole device: 27.5 and 33.4).  The two bodies apart
+// with all, all but one, half and a quarter of the workgroups, and with one: 2000 x 1201, k = 12 11.5, 29.6, 35.2, 59, 1900;
+// 16384 x 256, k = 16 17.2, 37.3, 38.5, 63, 3500 (the other plans on the whole device: 27.8 and 33.6; on half of it 28.5 and 43).  The two bodies apart
 // also took a tenth off the iterations of all (256 x 192, k = 4: 7.3 -> 6.5 us): fewer scalar registers to spill.
 // Only a caller that breaks the rule of one call at a time per workspace can take flags away from a run that waits for
 // them: each wait has `polls` looks (ten seconds or more), then the launch is marked as lost, nobody waits in it any
@@ -2377,7 +2377,7 @@ struct Patient {
     }
 };
 
-// Iterations `s` .. of the workgroup.  SHARED: a range of the workgroups' work, dealt anew after every iteration; returns
+// Iterations `s` .. of the workgroup.  SHARED: the work of several, dealt anew after every iteration; returns
 // the iteration from which all workgroups are there, or -1 after the last.  EVERY: all updates of W leave their part of the
 // objective (a.gw), not only the last (if a.dpart).  (A launch per reported iteration took 20 us more each: 4096 x 1024,
 // k = 8, 20 iterations 903 us a call, 802 on the row plan, 340 so.  As a run-time case: 3 % on runs that report nothing.)
@@ -2419,20 +2419,9 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
     const int nt = (n + 15) >> 4;                                  // 16-column tiles in all
     const int rpad = (R + 31) & ~31, box = rpad + 32;              // words of a workgroup's letter box: column group, row group
 
-    int v0, v1, r0, c0;                                            // the workgroups this one stands for
-    auto take = [&]() {
-        if (SHARED) {
-            const int here = deal & 511;
-            v0 = (int)ticket * nwg / here;
-            v1 = ((int)ticket + 1) * nwg / here;
-        } else {
-            v0 = blockIdx.x;
-            v1 = v0 + 1;
-        }
-        r0 = v0 / C;
-        c0 = v0 % C;
-    };
-    take();
+    // The workgroups this one stands for.  Shared: far apart, as the first ones own the column tiles.
+    const int v0 = SHARED ? (int)ticket : (int)blockIdx.x, v1 = SHARED ? nwg : v0 + 1, r0 = v0 / C, c0 = v0 % C;
+    int step = SHARED ? (int)(deal & 511) : 1;
     unsigned epoch = 0, target = 0;
     unsigned *boxes = a.sync + kResidentHead;
     // Posts a flag behind all stores of this workgroup to every other of its column or row group, then waits for
@@ -2463,7 +2452,8 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
     };
 
     u32x4 at[RT][3];                   // operand of A H^T
-    auto load_tile = [&](int r, int c) {
+    // The tile as the operand of A H^T, of W^T A, or both (a shared run loads what the half it is at needs).
+    auto load_tile = [&](int r, int c, bool for_aht, bool for_wta) {
         const int64_t row0 = (int64_t)r * RB;
         int64_t av = a.m - row0;
         av = av > RB ? RB : av;
@@ -2473,7 +2463,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         int opaque = 0;
         asm volatile("" : "+s"(opaque));      // the offsets are formed here, once, and not kept in registers over the run
 #pragma unroll
-        for (int i = 0; i < RT; ++i) {
+        for (int i = 0; i < (for_aht ? RT : 0); ++i) {
             const int cc = opaque + col0 + 32 * (w % CW + CW * i) + 8 * quad;
             float x[8];
 #pragma unroll
@@ -2481,11 +2471,11 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
                 x[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, cc + e < n ? (unsigned)((16 * rt + l16) * n + cc + e) * 4u : kOut, 0, 0));
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) cut2(x[2 * pr], x[2 * pr + 1], at[i], pr);
-            __builtin_amdgcn_sched_barrier(0);     // one group of loads at a time: all of them would spill
+            if (!SHARED) __builtin_amdgcn_sched_barrier(0);     // one group of loads at a time: all of them would spill
         }
         const int cc = opaque + col0 + 32 * w + 16 * half + l16;
 #pragma unroll
-        for (int i = 0; i < RT; ++i) {             // columns by lane: 8 rows of one of the wave's two tiles
+        for (int i = 0; i < (for_wta ? RT : 0); ++i) {      // columns by lane: 8 rows of one of the wave's two tiles
             float x[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e)
@@ -2496,7 +2486,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
             u32x4 *dst = Ap + ((w * 2 + half) * RT + i) * 96;
 #pragma unroll
             for (int q = 0; q < 3; ++q) dst[(q * 2 + hr) * 16 + l16] = p[q];
-            __builtin_amdgcn_sched_barrier(0);
+            if (!SHARED) __builtin_amdgcn_sched_barrier(0);
         }
     };
     // a row of W in LDS: the float and its pieces
@@ -2587,7 +2577,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         place();
         epoch = 8 * s;                 // more than an iteration's meetings
         if (s == 0) {
-            for (int v = v0; v < v1; ++v)      // H as handed in, to where its owners look for it
+            for (int v = v0; v < v1; v += step)      // H as handed in, to where its owners look for it
                 for (int t = v / C; t < 16; t += R) {
                     const int tile = 16 * (v % C) + t, col = 16 * tile + ec;
                     if (tid < 256)
@@ -2603,11 +2593,11 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         const bool last_h = s == a.nprod - 1;
         if (update) {
             // ---- A H^T
-            for (int v = v0; v < v1; ++v) {
+            for (int v = v0; v < v1; v += step) {
                 const int r = v / C, c = v % C;
                 if (SHARED) __syncthreads();
                 if (SHARED || !have_tile) {
-                    load_tile(r, c);
+                    load_tile(r, c, true, !SHARED);
                     load_w(r, !stored);
                 }
                 // thread tid: group tid / 16 of 8 columns, factor tid % 16; the floats are its wave's operand of H H^T
@@ -2691,7 +2681,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
             if (C > 1) {
                 meet(false);
                 // ---- W update: the 16-row tiles dealt to the workgroups of the row group
-                for (int v = v0; v < v1; ++v) {
+                for (int v = v0; v < v1; v += step) {
                     const int r = v / C, c = v % C;
                     if (SHARED) {
                         __syncthreads();
@@ -2735,14 +2725,14 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         }
         if (!product && !a.gout) break;
         // ---- product
-        for (int v = v0; v < v1; ++v) {
+        for (int v = v0; v < v1; v += step) {
             const int r = v / C, c = v % C;
             if (SHARED) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the rows of an update that did not wait for others
                 __syncthreads();
             }
             if (SHARED || !have_tile) {
-                if (SHARED || !update) load_tile(r, c);
+                if (SHARED || !update) load_tile(r, c, !SHARED, true);
                 if (SHARED || !update) load_w(r, !(stored || update));
             }
             if (!SHARED && update && C > 1) load_w(r, false);
@@ -2804,7 +2794,7 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
         if (!product) break;
         meet(true);
         // ---- H update: the 16-column tiles dealt to the workgroups of the column group
-        for (int v = v0; v < v1; ++v) {
+        for (int v = v0; v < v1; v += step) {
             const int r = v / C, c = v % C;
             for (int t = r; t < 16 && 16 * c + t < nt; t += R) {
                 const int tile = 16 * c + t, col = 16 * tile + ec;
@@ -2881,8 +2871,8 @@ __device__ __forceinline__ int resident_iterations(const ResidentArgs &a, int s,
             }
             __syncthreads();
             deal = __builtin_amdgcn_readfirstlane(word[0]);
-            if ((int)(deal & 511) >= nwg) return s + 1;
-            take();
+            step = deal & 511;
+            if (step >= nwg) return s + 1;
         }
     }
     if (SHARED && ticket == 0 && tid == 0) post(a.sync + kResidentDeal, kResidentOver);
