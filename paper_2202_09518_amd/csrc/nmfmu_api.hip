@@ -675,6 +675,13 @@ struct Sliced {
     void *planes;     // planes_bytes(max rows of any F)
     float *ppart;     // row-split partials of one slice: splits x 64 x max cols
     size_t planes_cap, ppart_elems;
+    unsigned *maxima; // of the columns of W, H^T and the two Gram matrices, k words each
+};
+
+// The largest magnitudes of a factor's columns, which scale its pair planes: where they go, and whether they are there.
+struct Maxima {
+    unsigned *at;
+    bool there;
 };
 
 // Row splits of a pass whose slices run side by side: every split of every slice is a partial result
@@ -698,8 +705,14 @@ int sliced_splits(int64_t rows, int64_t cols, int width, int nslices)
     return best;
 }
 
+// Whether a product over X runs on pairs of halves, all slices in one launch each.
+bool sliced_pairs(const float *X, int64_t cols, int k) { return k > NMF_MU_MAX_K && wta_planes_only_width(X, cols) == 64; }
+
+// fm: maxima of F's columns, found here if they are not there.  split: the planes do not hold F yet; clear1, clear2: maxima to
+// set to zero with the split.  gm: takes the maxima of the columns of out (zero before).
 int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float *X, int64_t cols,
-               float *out, bool accumulate, hipStream_t st)
+               float *out, bool accumulate, hipStream_t st, Maxima &fm, bool split = true, unsigned *clear1 = nullptr,
+               unsigned *clear2 = nullptr, Maxima *gm = nullptr)
 {
     // factor columns per pass: the widest the pass kernels take from planes alone for this X
     // (the slices of F are not contiguous, so the kernel that reads the factor itself is out)
@@ -707,13 +720,20 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
     const int nslices = (k + 63) / 64;
     const int splits = sliced_splits(rows, cols, kSlice, kSlice == 64 ? nslices : 1);
     const int64_t rps = wta_rows_per_split(rows, splits);
-    if (kSlice == 64 && k > 64) {
+    if (gm) gm->there = false;
+    if (sliced_pairs(X, cols, k)) {
         // all slices in one launch each: the slices of a tile of X run side by side and share its bytes
-        if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems || planes_bytes(rows) * nslices > e.planes_cap)
+        if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems || pair_planes_bytes(rows) * nslices > e.planes_cap)
             return fail(NMF_EHIP, "internal: sliced scratch too small%s");
-        NMF_HIP(launch_split_planes_slices(F, rows, k, e.planes, st));
-        NMF_HIP(launch_wta_pass_slices(X, rows, cols, k, e.planes, e.ppart, splits, rps, st));
-        NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate));
+        if (!fm.there) {
+            NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(fm.at), k, 0.f, st));
+            NMF_HIP(launch_factor_max(F, rows, k, fm.at, st));
+            fm.there = true;
+        }
+        if (split) NMF_HIP(launch_split_pairs(F, rows, k, fm.at, e.planes, st, clear1, clear2));
+        NMF_HIP(launch_pair_slices(X, rows, cols, k, e.planes, fm.at, e.ppart, splits, rps, st));
+        NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate, gm ? gm->at : nullptr));
+        if (gm) gm->there = true;
         return NMF_OK;
     }
     if ((size_t)splits * kSlice * (size_t)cols > e.ppart_elems || planes_bytes(rows) > e.planes_cap)
@@ -740,7 +760,7 @@ size_t sliced_ppart_elems(int64_t cols)
 // Resident run of rank k > NMF_MU_MAX_K.
 struct SlicedDense {
     Sliced e;
-    float *At, *Wt, *Ht, *num, *den, *gw, *gh;
+    float *At, *Wt, *Ht, *num, *den, *g;
 };
 
 template <class T> T max3(T a, T b, T c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
@@ -752,6 +772,7 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, size_t *by
     cv.take<unsigned>(64);
     const int64_t big = m > n ? m : n;
     const size_t nslices = (size_t)(k + 63) / 64;
+    p.e.maxima = cv.take<unsigned>(4 * (size_t)k);
     p.e.planes_cap = planes_bytes(max3<int64_t>(m, n, k)) * nslices;
     p.e.ppart_elems = sliced_ppart_elems(max3<int64_t>(m, n, k)) * nslices;
     p.e.planes = cv.take<char>(p.e.planes_cap);
@@ -762,8 +783,7 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, size_t *by
     p.Ht = cv.take<float>((size_t)n * k);
     p.num = cv.take<float>((size_t)k * big);
     p.den = cv.take<float>((size_t)k * big);
-    p.gw = cv.take<float>((size_t)k * k);
-    p.gh = cv.take<float>((size_t)k * k);
+    p.g = cv.take<float>((size_t)k * k);
     if (bytes) *bytes = cv.off;
     return p;
 }
@@ -775,23 +795,31 @@ size_t sliced_dense_bytes(int64_t m, int64_t n, int k)
     return b;
 }
 
+// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps), F rows x k, X rows x cols.
+int sliced_update(const SlicedDense &p, const float *F, int64_t rows, int k, const float *X, int64_t cols, float *Y, float eps,
+                  Maxima &fF, Maxima &fY, Maxima &fG, hipStream_t st)
+{
+    const bool first = sliced_pairs(X, cols, k), second = sliced_pairs(F, k, k);
+    if (int rc = sliced_ftx(p.e, F, rows, k, X, cols, p.num, false, st, fF, true, fG.at, fY.at)) return rc;
+    if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, fF, !first, fG.at, fY.at, &fG)) return rc;
+    if (int rc = sliced_ftx(p.e, p.g, k, k, Y, cols, p.den, false, st, fG)) return rc;
+    fY.there = first || second;      // set to zero on the way
+    NMF_HIP(launch_mu_apply(Y, p.num, p.den, eps, k, cols, st, fY.there ? fY.at : nullptr));
+    return NMF_OK;
+}
+
 int sliced_dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters,
                       float eps, const SlicedDense &p, hipStream_t st)
 {
+    Maxima fw{p.e.maxima, false}, fh{p.e.maxima + k, false}, fg{p.e.maxima + 2 * k, false};
     NMF_HIP(launch_transpose(A, m, n, p.At, st));
     NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
     for (int it = 0; it < iters; ++it) {
         // H update (Algorithm 3 order): numerator W^T A, denominator (W^T W) H
-        if (int rc = sliced_ftx(p.e, W, m, k, A, n, p.num, false, st)) return rc;
-        if (int rc = sliced_ftx(p.e, W, m, k, W, k, p.gw, false, st)) return rc;
-        if (int rc = sliced_ftx(p.e, p.gw, k, k, H, n, p.den, false, st)) return rc;
-        NMF_HIP(launch_mu_apply(H, p.num, p.den, eps, (int64_t)k * n, st));
+        if (int rc = sliced_update(p, W, m, k, A, n, H, eps, fw, fh, fg, st)) return rc;
         NMF_HIP(launch_transpose(H, k, n, p.Ht, st));
         // W update with the new H, on the transposes: (A H^T)^T = H A^T, (W H H^T)^T = (H H^T) W^T
-        if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.At, m, p.num, false, st)) return rc;
-        if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Ht, k, p.gh, false, st)) return rc;
-        if (int rc = sliced_ftx(p.e, p.gh, k, k, p.Wt, m, p.den, false, st)) return rc;
-        NMF_HIP(launch_mu_apply(p.Wt, p.num, p.den, eps, (int64_t)k * m, st));
+        if (int rc = sliced_update(p, p.Ht, n, k, p.At, m, p.Wt, eps, fh, fw, fg, st)) return rc;
         NMF_HIP(launch_transpose(p.Wt, k, m, W, st));
     }
     return NMF_OK;
@@ -813,6 +841,7 @@ SlicedOoc carve_sliced_ooc(void *ws, int64_t rb, int64_t n, int k, size_t *bytes
     SlicedOoc p;
     cv.take<unsigned>(64);
     const size_t nslices = (size_t)(k + 63) / 64;
+    p.e.maxima = cv.take<unsigned>(4 * (size_t)k);
     p.e.planes_cap = planes_bytes(max3<int64_t>(rb, n, k)) * nslices;
     p.e.ppart_elems = sliced_ppart_elems(max3<int64_t>(rb, n, k)) * nslices;
     p.e.planes = cv.take<char>(p.e.planes_cap);
@@ -874,6 +903,7 @@ int sliced_ooc_run(const float *A_host, float *W_host, float *W_dev, int64_t m, 
     NMF_HIP(hipStreamWaitEvent(g.copy_stream, g.ev_entry, 0));
 
     const int64_t nb = (m + batch_rows - 1) / batch_rows;
+    Maxima fw{p.e.maxima, false}, fh{p.e.maxima + k, false}, fgw{p.e.maxima + 2 * k, false}, fgh{p.e.maxima + 3 * k, false};
     int64_t issued = 0;
     for (int s = 0; s <= iters; ++s) {
         for (int64_t b = 0; b < nb; ++b, ++issued) {
@@ -895,15 +925,17 @@ int sliced_ooc_run(const float *A_host, float *W_host, float *W_dev, int64_t m, 
                 // W_b <- W_b * (A_b H^T) / (W_b H H^T + eps) on the transposes of the batch
                 NMF_HIP(launch_transpose(Ab, rb, n, p.Abt, st));
                 NMF_HIP(launch_transpose(Wb, rb, k, p.Wbt, st));
-                if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Abt, rb, p.num_b, false, st)) return rc;
-                if (int rc = sliced_ftx(p.e, p.gh, k, k, p.Wbt, rb, p.den_b, false, st)) return rc;
-                NMF_HIP(launch_mu_apply(p.Wbt, p.num_b, p.den_b, eps, (int64_t)k * rb, st));
+                if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Abt, rb, p.num_b, false, st, fh, true, fw.at)) return rc;
+                if (int rc = sliced_ftx(p.e, p.gh, k, k, p.Wbt, rb, p.den_b, false, st, fgh)) return rc;
+                fw.there = sliced_pairs(p.Abt, rb, k);      // set to zero on the way
+                NMF_HIP(launch_mu_apply(p.Wbt, p.num_b, p.den_b, eps, k, rb, st, fw.there ? fw.at : nullptr));
                 NMF_HIP(launch_transpose(p.Wbt, k, rb, Wb, st));
             }
             if (s < iters) {
                 // accumulate W_b^T A_b and W_b^T W_b with the W_b just updated
-                if (int rc = sliced_ftx(p.e, Wb, rb, k, Ab, n, p.num, b > 0, st)) return rc;
-                if (int rc = sliced_ftx(p.e, Wb, rb, k, Wb, k, p.gw, b > 0, st)) return rc;
+                if (s == 0) fw.there = false;
+                if (int rc = sliced_ftx(p.e, Wb, rb, k, Ab, n, p.num, b > 0, st, fw)) return rc;
+                if (int rc = sliced_ftx(p.e, Wb, rb, k, Wb, k, p.gw, b > 0, st, fw, !sliced_pairs(Ab, n, k))) return rc;
             }
             if (hostw) {
                 NMF_HIP(hipEventRecord(g.sl_done[slot], st));
@@ -917,10 +949,12 @@ int sliced_ooc_run(const float *A_host, float *W_host, float *W_dev, int64_t m, 
             }
         }
         if (s < iters) {
-            if (int rc = sliced_ftx(p.e, p.gw, k, k, H, n, p.den, false, st)) return rc;
-            NMF_HIP(launch_mu_apply(H, p.num, p.den, eps, (int64_t)k * n, st));
+            fgw.there = false;
+            if (int rc = sliced_ftx(p.e, p.gw, k, k, H, n, p.den, false, st, fgw, true, fh.at, fgh.at)) return rc;
+            fh.there = sliced_pairs(H, n, k);
+            NMF_HIP(launch_mu_apply(H, p.num, p.den, eps, k, n, st, fh.there ? fh.at : nullptr));
             NMF_HIP(launch_transpose(H, k, n, p.Ht, st));
-            if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Ht, k, p.gh, false, st)) return rc;
+            if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Ht, k, p.gh, false, st, fh, true, fgh.at, nullptr, &fgh)) return rc;
         }
     }
     if (hostw) {

@@ -68,22 +68,26 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
 // two: A is read in turn with its transpose (what the last-level cache would have to keep).
 // gtiles (optional): nsets sets of partial Gram tiles for rank k that the first workgroups of
 // the pass add up into gsum (one set).
-// Ranks above 64, all ceil(k / 64) slices of 64 factors in one launch each: planes of every slice of X
-// (rows x k; slice z at planes + z * planes_bytes(rows)), the pass over A for every slice (aligned A,
-// n % 4 == 0; partials of slice z at ppart + z * splits * 64 * n, packed for that slice's width), and
-// P (k x cols) (+)= the sums over the splits.  The slices of one tile of A run side by side, so A is
-// fetched from HBM about once per product.
-hipError_t launch_split_planes_slices(const float *X, int64_t rows, int k, void *planes, hipStream_t st);
-hipError_t launch_wta_pass_slices(const float *A, int64_t rows, int64_t n, int k, const void *planes, float *ppart,
-                                  int splits, int64_t rps, hipStream_t st);
+// Ranks above 64, all ceil(k / 64) slices of 64 factors in one launch each: pair planes of every slice of X
+// (rows x k; slice z at planes + z * pair_planes_bytes(rows)) scaled by fmax, the k largest magnitudes of X's columns (bits),
+// the pass over A for every slice (aligned A, n % 4 == 0; partials of slice z at ppart + z * splits * 64 * n, packed for that
+// slice's width), and P (k x cols) (+)= the sums over the splits.  The slices of one tile of A run side by side, so A is
+// fetched from HBM about once per product.  launch_factor_max: fmax of X (zero before); clear1, clear2: k words each that
+// launch_split_pairs sets to zero; most: the largest magnitudes of P's columns (zero before).
+size_t pair_planes_bytes(int64_t rows);
+hipError_t launch_factor_max(const float *X, int64_t rows, int k, unsigned *fmax, hipStream_t st);
+hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const unsigned *fmax, void *planes, hipStream_t st,
+                              unsigned *clear1 = nullptr, unsigned *clear2 = nullptr);
+hipError_t launch_pair_slices(const float *A, int64_t rows, int64_t n, int k, const void *planes, const unsigned *fmax, float *ppart,
+                              int splits, int64_t rps, hipStream_t st);
 hipError_t launch_sum_partials_slices(const float *ppart, int splits, int k, int64_t cols, float *P, hipStream_t st,
-                                      bool accumulate = false);
+                                      bool accumulate = false, unsigned *most = nullptr);
 // P[e] (+)= sum_s ppart[s][e], e < count.
 hipError_t launch_sum_partials(const float *ppart, int splits, int64_t count, float *P,
                                hipStream_t st, bool accumulate = false);
-// X[e] <- X[e] * P[e] / (D[e] + eps), e < count.
-hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, int64_t count,
-                           hipStream_t st);
+// X[e] <- X[e] * P[e] / (D[e] + eps), X k x len; most (optional): the largest magnitudes of its k rows (zero before).
+hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, int k, int64_t len, hipStream_t st,
+                           unsigned *most = nullptr);
 // X (k x len) <- X * (sum_s part[s]) / (G X + eps), in place.  G is given complete (Gfull, ld k)
 // or as nbin partial tiles (gin).  Optional: Xt (len x k) = new X^T; gout = partial Gram tiles
 // of the new X, one set per block (factor_update_blocks(len) blocks); planes = the bf16 piece

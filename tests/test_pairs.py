@@ -1,0 +1,104 @@
+"""Pairs of halves: what the two pieces of a scaled float hold, and the scales that follow the data."""
+import numpy as np
+import pytest
+
+EPS = 1e-16
+
+
+def cut(x, e):
+    """Pieces of x under the scale 2^(14 - e), as the kernels cut them."""
+    s = np.ldexp(x.astype(np.float64), 14 - e)
+    h = s.astype(np.float16)
+    low = (s - h.astype(np.float64)).astype(np.float32).astype(np.float16)
+    return s, h.astype(np.float64), low.astype(np.float64)
+
+
+def test_two_halves_hold_a_float_to_its_last_bit():
+    r = np.random.default_rng(1)
+    x = r.random(200000).astype(np.float32) + np.float32(1)           # [1, 2): exponent 0 under any scale above its own
+    for e in (0, 3, 10):
+        s, h, low = cut(x, e)
+        ulp = np.ldexp(1.0, 14 - e - 23)
+        err = s - h - low
+        assert np.abs(err).max() <= ulp                                # the neighbour at worst,
+        assert (err == 0).mean() > 0.7                                 # and three quarters exact
+        assert abs(err.mean()) < 0.01 * ulp                            # of either sign
+        # the product left out: the lower pieces of both operands
+        assert np.abs(low).max() <= np.ldexp(1.0, 14 - e - 11)
+
+
+def test_small_entries_keep_an_absolute_error_of_the_largest():
+    r = np.random.default_rng(2)
+    x = np.ldexp(r.random(200000) + 1, r.integers(-60, 1, 200000)).astype(np.float32)
+    s, h, low = cut(x, 0)
+    err = np.abs(s - h - low)
+    assert (err <= np.maximum(np.ldexp(s, -23), np.ldexp(1.0, -25))).all()
+
+
+def reference(A, W, H):
+    A, W, H = (x.astype(np.float64) for x in (A, W, H))
+    eps = float(np.float32(EPS))
+    H = H * (W.T @ A) / ((W.T @ W) @ H + eps)
+    W = W * (A @ H.T) / (W @ (H @ H.T) + eps)
+    return W, H
+
+
+def columns_off(got, want):
+    """Largest relative error of a column (2-norm)."""
+    d = np.linalg.norm(got.astype(np.float64) - want, axis=0) / np.linalg.norm(want, axis=0)
+    return d.max()
+
+
+# odd sizes, ranks that fill one slice and part of the next; sizes at which the other paths of a product run
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["plain", "columns", "rows", "growing", "late", "spikes"])
+@pytest.mark.parametrize("m,n,k", [(1300, 516, 68), (517, 1028, 132), (700, 333, 96)])
+def test_scales_follow_the_data(m, n, k, kind):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(7)
+    A = (r.random((m, 8)) @ r.random((8, n))).astype(np.float32)
+    W, H = r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+    if kind == "columns":       # units of their own
+        A *= np.ldexp(np.float32(1), r.integers(-30, 30, n)).astype(np.float32)
+    elif kind == "rows":
+        A *= np.ldexp(np.float32(1), r.integers(-12, 12, m)).astype(np.float32)[:, None]
+        W *= np.ldexp(np.float32(1), r.integers(-20, 20, k)).astype(np.float32)
+    elif kind == "growing":     # every few rows leave the scale of those before
+        A *= np.ldexp(np.float32(1), np.arange(m) * 60 // m - 30).astype(np.float32)[:, None]
+    elif kind == "late":        # nothing, and then something
+        A[: m // 2] = 0
+        A[:, n // 3] = 0
+        A[m - 1, n // 3] = 1
+    elif kind == "spikes":
+        A[r.random((m, n)) < 0.001] *= 1000
+    Wr, Hr = reference(A, W, H)
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    nmf.nmf_mu_dense(torch.from_numpy(A).cuda(), m, n, k, Wd, Hd, 1, EPS)
+    Wd, Hd = Wd.cpu().numpy(), Hd.cpu().numpy()
+    # sums of up to 1300 positive terms in single precision, a product of three of them and a quotient
+    live = np.linalg.norm(Hr, axis=0) > 0
+    assert columns_off(Hd[:, live], Hr[:, live]) < 4e-6
+    live = np.linalg.norm(Wr, axis=1) > 0
+    assert columns_off(Wd.T[:, live], Wr.T[:, live]) < 4e-6
+    assert not Hd[:, np.linalg.norm(Hr, axis=0) == 0].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_infinities_and_nan_reach_their_columns_only(bad):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    m, n, k = 600, 260, 68
+    r = np.random.default_rng(3)
+    A = r.random((m, n)).astype(np.float32)
+    W, H = r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+    A[400, 17] = bad
+    P = torch.from_numpy(A).cuda()
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+    nmf.nmf_mu_dense(P, m, n, k, Wd, Hd, 1, EPS)
+    Hd = Hd.cpu().numpy()
+    assert not np.isfinite(Hd[:, 17]).any()
+    assert np.isfinite(np.delete(Hd, 17, axis=1)).all()
