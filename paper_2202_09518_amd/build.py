@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnmfmu.so")
-SOURCES = ["nmfmu_dense.hip", "nmfmu_csr.hip", "nmfmu_api.hip"]
+SOURCES = ["nmfmu_dense.hip", "nmfmu_pairs.hip", "nmfmu_csr.hip", "nmfmu_api.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -24,7 +24,7 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "nmfmu_internal.h"), os.path.join(ROOT, "include", "nmfmu.h"),
+    deps = sources() + [os.path.join(CSRC, "nmfmu_internal.h"), os.path.join(CSRC, "nmfmu_device.h"), os.path.join(ROOT, "include", "nmfmu.h"),
                         os.path.join(ROOT, "include", "nmfmu_test.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 

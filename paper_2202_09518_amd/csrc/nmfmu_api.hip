@@ -141,6 +141,9 @@ int check_common(const void *a, const void *w, const void *h, int64_t m, int64_t
 struct DensePlan {
     bool mirrored;
     bool one_pass = false;     // both products in one reading of A: ppart and planes2 only
+    bool pairs = false;        // mirrored, with A and A^T as pairs of halves: ppart, pa, pt, fw, fh and Wt
+    PairMatrix pa, pt;         // A' and (A^T)'
+    PairFactor fw, fh;         // planes of W and of H^T
     int resident = 0;          // the run in one launch, this many row tiles per workgroup: `res` and dry only
     ResidentArgs res;          // its exchange buffers
     float *dry;                // room for factors that a timing run leaves behind
@@ -187,6 +190,55 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
         p.Ht = cv.take<float>((size_t)n * k);
     }
     return p;
+}
+
+// 33 to 64 factors: the mirrored plan on pairs of halves.
+bool pairs_ok(int64_t m, int64_t n, int k) { return k > 32 && k <= NMF_MU_MAX_K && m < (int64_t)1 << 25 && n < (int64_t)1 << 25; }
+
+PairMatrix carve_pair_matrix(Carve &cv, int64_t rows, int64_t cols)
+{
+    PairMatrix x;
+    x.ld = pair_matrix_ld(cols);
+    x.units = cv.take<char>(pair_matrix_units(rows, x.ld));
+    x.inv = cv.take<float>(pair_matrix_scales(rows, x.ld) / sizeof(float));
+    return x;
+}
+
+PairFactor carve_pair_factor(Carve &cv, int64_t rows, int64_t ld)
+{
+    PairFactor f;
+    f.units = cv.take<char>(pair_units_bytes(rows, ld));
+    f.exps = cv.take<unsigned char>(pair_exps_bytes(rows, ld));
+    f.most = nullptr;
+    return f;
+}
+
+DensePlan carve_pairs(Carve &cv, int64_t m, int64_t n, int k)
+{
+    DensePlan p{};
+    p.mirrored = p.pairs = true;
+    p.c = carve_common(cv, k);
+    p.s1 = pair_splits(m, n, 2, 1);
+    p.rps1 = pair_rows_per_split(m, p.s1);
+    p.s2 = pair_splits(n, m, 2, 1);
+    p.rps2 = pair_rows_per_split(n, p.s2);
+    const size_t p1 = (size_t)p.s1 * k * n, p2 = (size_t)p.s2 * k * m;
+    p.ppart = cv.take<float>(p1 > p2 ? p1 : p2);
+    p.pa = carve_pair_matrix(cv, m, n);
+    p.pt = carve_pair_matrix(cv, n, m);
+    p.fw = carve_pair_factor(cv, m, 64);
+    p.fh = carve_pair_factor(cv, n, 64);
+    p.fw.most = cv.take<unsigned>(128);
+    p.fh.most = p.fw.most + 64;
+    p.Wt = cv.take<float>((size_t)k * m);
+    return p;
+}
+
+size_t pairs_bytes(int64_t m, int64_t n, int k)
+{
+    Carve c(nullptr);
+    carve_pairs(c, m, n, k);
+    return c.off;
 }
 
 // One-pass plan: up to this many shares and tile sets are added by the H update's workgroups themselves.
@@ -303,6 +355,10 @@ int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStr
     bytes = one_pass_bytes(m, n, k);
     if (one_pass_ok(A, n, k) && have_workspace(bytes + extra, st)) {
         *p = carve_one_pass(g.ws, m, n, k);
+    } else if (pairs_ok(m, n, k) && have_workspace(pairs_bytes(m, n, k) + extra, st)) {
+        bytes = pairs_bytes(m, n, k);
+        Carve cv(g.ws);
+        *p = carve_pairs(cv, m, n, k);
     } else {
         bool mirrored = false;
         bytes = dense_bytes(m, n, k, true);
@@ -340,8 +396,10 @@ struct DenseRun {
 // 32768 x 16382, k = 32: 1020 -> 800 (row plan); mirrored plan: 20011 x 9998, k = 50 634 -> 424;
 // 20011 x 10000, k = 40 788 -> 409; 2001 x 6001, k = 50 169 -> 68; 5001 x 3000, k = 12 62 -> 50;
 // one iteration: 5001 x 3001, k = 12 117 -> 119, k = 40 192 -> 124.
+// The mirrored plan on pairs of halves takes any A as it is; with `aligned` it works on the copies all the same
+// (a caller that evaluates the objective on r->A).
 int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters, float eps, size_t extra,
-             hipStream_t st, DenseRun *r)
+             hipStream_t st, DenseRun *r, bool aligned = false)
 {
     const int64_t n4 = (n + 3) & ~(int64_t)3, m4 = (m + 3) & ~(int64_t)3;
     const bool copy_a = (reinterpret_cast<uintptr_t>(A) & 15u) != 0 || n != n4;
@@ -357,7 +415,19 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
     size_t base = 0;
     if (resident_tiles(m, n, k) && have_workspace(resident_bytes(m, n, k) + extra, st))      // takes any A
         return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
-    if (eps >= 1.17549435e-38f && (copy_a || m != m4) && iters > 0) {
+    // large matrices of more than 32 factors: one iteration alone does not earn a second layout of A
+    const bool can_rows = aht_rows_ok(nullptr, m, n4, k), copies_can = eps >= 1.17549435e-38f && iters > 0;
+    if (pairs_ok(m, n, k) && !(iters == 1 && copy_a && can_rows && copies_can)) {
+        if (aligned && copy_a && copies_can && have_workspace(pairs_bytes(m, n4, k) + copies + extra, st)) {
+            base = pairs_bytes(m, n4, k);
+            Carve cv(g.ws);
+            r->p = carve_pairs(cv, m, n4, k);
+            padded = true;
+        } else if (have_workspace(pairs_bytes(m, n, k) + extra, st)) {
+            return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
+        }
+    }
+    if (!padded && copies_can && (copy_a || m != m4)) {
         const bool one = one_pass_ok(nullptr, n4, k), rows = rows_plan_first(nullptr, m, n4, k);
         if (one || rows) {
             if (copy_a) {
@@ -371,8 +441,6 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
                 }
             }
         } else {
-            // large matrices of more than 32 factors: one iteration alone does not earn the transposed copy
-            const bool can_rows = aht_rows_ok(nullptr, m, n4, k);
             pad_w = m != m4;
             base = dense_bytes(m4, n4, k, true);
             const size_t wcopy = pad_w ? align_up((size_t)m4 * k * sizeof(float)) : 0;
@@ -392,9 +460,9 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
     Carve cv(static_cast<char *>(g.ws) + base);
     if (copy_a) {
         float *Ap = cv.take<float>((size_t)m * n4);
-        if (r->p.mirrored) NMF_HIP(launch_transpose(A, m, n, r->p.At, st, r->m, Ap, n4));
+        if (r->p.mirrored && !r->p.pairs) NMF_HIP(launch_transpose(A, m, n, r->p.At, st, r->m, Ap, n4));
         else NMF_HIP(launch_pad_copy(A, n, Ap, n4, m, n, st));
-        r->have_at = r->p.mirrored;
+        r->have_at = r->p.mirrored && !r->p.pairs;
         r->A = Ap;
         r->n = n4;
     }
@@ -422,7 +490,7 @@ int close_run(const DenseRun &r, int k, float *W, float *H, int64_t m, int64_t n
 // A dense_body on this plan streams A itself for both products and leaves the plan's A^T alone.
 bool takes_row_plan(const DensePlan &p, const float *A, int64_t m, int64_t n, int k)
 {
-    return !p.one_pass && !p.resident && !p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored);
+    return !p.one_pass && !p.resident && !p.pairs && !p.a_rows && rows_plan_runs(A, m, n, k, p.mirrored);
 }
 
 constexpr int kDenseKernels = 6;
@@ -442,6 +510,32 @@ constexpr int kMonitored = 32;
 size_t monitored_bytes(int batch, int k)
 {
     return align_up((size_t)(batch - 1) * kFinMaxBlocks * sizeof(double)) + 2 * align_up((size_t)batch * k * k * sizeof(float));
+}
+
+// A pass of a run on pairs: over A' with the planes of W, or (transposed) over (A^T)' with those of H^T.  The maxima of the planes
+// that come next are set to zero on the way: those planes were read by the pass before.
+hipError_t pass_over(const DensePlan &p, int64_t m, int64_t n, int k, bool transposed, const float *gtiles, int nsets, float *gsum,
+                     hipStream_t st)
+{
+    PairPass a{};
+    a.F = transposed ? p.fh : p.fw;
+    a.ldf = 64;
+    a.X = transposed ? p.pt : p.pa;
+    a.ppart = p.ppart;
+    a.rows = transposed ? n : m;
+    a.n = transposed ? m : n;
+    a.splits = transposed ? p.s2 : p.s1;
+    a.rps = transposed ? p.rps2 : p.rps1;
+    a.nslices = 1;
+    a.k[0] = (short)k;
+    a.gtiles = gtiles;
+    a.nsets = nsets;
+    a.gsum = gsum;
+    if (gtiles) {
+        a.clear = transposed ? p.fw.most : p.fh.most;
+        a.nclear = 64;
+    }
+    return launch_pair_pass(a, 2, stream_a(m, n, true), st);
 }
 
 // One resident dense run on `st`.  With `ev` (kDenseKernels * iters + 1 events)
@@ -525,6 +619,38 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
                 if (int rc = pass(iters, false)) return rc;
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
             if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+        }
+        return NMF_OK;
+    }
+    if (p.pairs) {
+        // As the mirrored plan below, on A' and (A^T)'; the finishers write the planes that the next pass contracts
+        // with, and W itself only when the run is over.
+        if (!a_is_mirrored) NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, p.fw.most, 128, st));
+        else NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.fw.most), 128, 0.f, st));
+        NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
+        NMF_HIP(launch_factor_update(p.Wt, nullptr, nullptr, 0, nullptr, nullptr, 0, c.gwp, k, m, eps, st, nullptr, nullptr, nullptr,
+                                     &p.fw));
+        const int nbw = factor_update_blocks(m), nbh = factor_update_blocks(n);
+        if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+        for (int it = 0; it < iters; ++it) {
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            NMF_HIP(pass_over(p, m, n, k, false, c.gwp, nbw, c.gws, st));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            NMF_HIP(launch_factor_update(H, nullptr, p.ppart, p.s1, nullptr, c.gws, 1, c.ghp, k, n, eps, st, map, nullptr, nullptr, &p.fh));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            NMF_HIP(pass_over(p, m, n, k, true, c.ghp, nbh, c.ghs, st));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            const bool report = mon && (!mon->last_only || it == iters - 1);
+            NMF_HIP(launch_factor_update(p.Wt, it == iters - 1 ? W : nullptr, p.ppart, p.s2, nullptr, c.ghs, 1, c.gwp, k, m, eps, st, map,
+                                         nullptr, report ? mon->dpart : nullptr, &p.fw));
+            if (ev) NMF_HIP(hipEventRecord(*ev++, st));
+            if (report) {
+                NMF_HIP(launch_gram_sum(c.gwp, nbw, k, c.gw, st));
+                NMF_HIP(launch_gram_sum(c.ghs, 1, k, c.gh, st));
+                NMF_HIP(launch_objective(mon->dpart, nbw, c.gw, c.gh, k, mon->normA2,
+                                         mon->out + (mon->last_only ? 0 : it), st));
+            }
         }
         return NMF_OK;
     }
@@ -665,24 +791,28 @@ int build_csc(const int64_t *rowptr, const int32_t *colidx, const float *vals, i
 
 // ---- rank-sliced engine (ranks above NMF_MU_MAX_K, and the host-resident-W pipeline) ----
 // Every product of the iteration is written as F^T X with F (rows x k) and X (rows x cols)
-// row-major, i.e. a reduction over the rows of both, and computed 64 factor columns at a
-// time by the k <= 64 pass kernel on the piece planes of that slice of F:
+// row-major, i.e. a reduction over the rows of both, and computed for slices of 64 or 128 columns of F side by side
+// on the planes of F:
 //   W^T A, W^T W                      F = W,  X = A or W
 //   (W^T W) H                         F = W^T W (symmetric), X = H
 //   A H^T, H H^T, W (H H^T)           the same three on the transposes A^T, H^T, W^T
-// followed by the element-wise update.  X is read once per slice.
+// followed by the element-wise update.
 struct Sliced {
-    void *planes;     // planes_bytes(max rows of any F)
+    void *planes;     // pair planes of F (or, up to 64 factors and for X that is not aligned, the bf16 planes of a slice)
     float *ppart;     // row-split partials of one slice: splits x 64 x max cols
     size_t planes_cap, ppart_elems;
-    unsigned *maxima; // of the columns of W, H^T and the two Gram matrices, k words each
+    unsigned *most;   // the largest magnitudes of the columns of F
 };
 
-// The largest magnitudes of a factor's columns, which scale its pair planes: where they go, and whether they are there.
-struct Maxima {
-    unsigned *at;
-    bool there;
-};
+// The pair planes of F in e.planes.
+PairFactor sliced_factor(const Sliced &e, int64_t rows, int ld)
+{
+    return PairFactor{e.planes, reinterpret_cast<unsigned char *>(e.planes) + pair_units_bytes(rows, ld), e.most};
+}
+// Columns per row group: whole slices of 128.
+int sliced_ld(int k) { return (k + 127) / 128 * 128; }
+
+template <class T> T max3(T a, T b, T c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 
 // Row splits of a pass whose slices run side by side: every split of every slice is a partial result
 // written and read again, and the slices already fill the chip (512 workgroups at a time), so the fewest
@@ -708,11 +838,17 @@ int sliced_splits(int64_t rows, int64_t cols, int width, int nslices)
 // Whether a product over X runs on pairs of halves, all slices in one launch each.
 bool sliced_pairs(const float *X, int64_t cols, int k) { return k > NMF_MU_MAX_K && wta_planes_only_width(X, cols) == 64; }
 
-// fm: maxima of F's columns, found here if they are not there.  split: the planes do not hold F yet; clear1, clear2: maxima to
-// set to zero with the split.  gm: takes the maxima of the columns of out (zero before).
+hipError_t sliced_split(const Sliced &e, const float *F, int64_t rows, int k, hipStream_t st)
+{
+    const int ld = sliced_ld(k);
+    if (pair_units_bytes(rows, ld) + pair_exps_bytes(rows, ld) > e.planes_cap) return hipErrorInvalidValue;
+    hipError_t rc = launch_fill_f32(reinterpret_cast<float *>(e.most), k, 0.f, st);
+    return rc != hipSuccess ? rc : launch_split_pairs(F, rows, k, sliced_factor(e, rows, ld), ld, st);
+}
+
+// split: the planes do not hold F yet.
 int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float *X, int64_t cols,
-               float *out, bool accumulate, hipStream_t st, Maxima &fm, bool split = true, unsigned *clear1 = nullptr,
-               unsigned *clear2 = nullptr, Maxima *gm = nullptr)
+               float *out, bool accumulate, hipStream_t st, bool split = true)
 {
     // factor columns per pass: the widest the pass kernels take from planes alone for this X
     // (the slices of F are not contiguous, so the kernel that reads the factor itself is out)
@@ -720,20 +856,12 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
     const int nslices = (k + 63) / 64;
     const int splits = sliced_splits(rows, cols, kSlice, kSlice == 64 ? nslices : 1);
     const int64_t rps = wta_rows_per_split(rows, splits);
-    if (gm) gm->there = false;
     if (sliced_pairs(X, cols, k)) {
         // all slices in one launch each: the slices of a tile of X run side by side and share its bytes
-        if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems || pair_planes_bytes(rows) * nslices > e.planes_cap)
-            return fail(NMF_EHIP, "internal: sliced scratch too small%s");
-        if (!fm.there) {
-            NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(fm.at), k, 0.f, st));
-            NMF_HIP(launch_factor_max(F, rows, k, fm.at, st));
-            fm.there = true;
-        }
-        if (split) NMF_HIP(launch_split_pairs(F, rows, k, fm.at, e.planes, st, clear1, clear2));
-        NMF_HIP(launch_pair_slices(X, rows, cols, k, e.planes, fm.at, e.ppart, splits, rps, st));
-        NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate, gm ? gm->at : nullptr));
-        if (gm) gm->there = true;
+        if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems) return fail(NMF_EHIP, "internal: sliced scratch too small%s");
+        if (split) NMF_HIP(sliced_split(e, F, rows, k, st));
+        NMF_HIP(launch_pair_slices(X, rows, cols, k, sliced_factor(e, rows, sliced_ld(k)), sliced_ld(k), e.ppart, splits, rps, st));
+        NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate));
         return NMF_OK;
     }
     if ((size_t)splits * kSlice * (size_t)cols > e.ppart_elems || planes_bytes(rows) > e.planes_cap)
@@ -751,6 +879,14 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
 // 32-factor slices have 128-column slabs and half the factors).  wta_splits keeps splits x slabs <= 512 with
 // cols <= 256 slabs, or two splits on fewer than 384 slabs, or one: splits x cols <= 131072 + cols.  And more than
 // 32 splits need fewer than 16 slabs and 256 rows each: at most cols / 256 splits of 15 x 256 columns.
+// Partials of the passes over A': slices of 128 and one of 64.
+size_t sliced_pass_elems(int64_t rows, int64_t cols, int k)
+{
+    const int wide = (k + 63) / 128;
+    const size_t a = wide ? (size_t)pair_splits(rows, cols, 4, wide) * wide * 128 : 0, b = (size_t)pair_splits(rows, cols, 2, 1) * 64;
+    return (a > b ? a : b) * (size_t)cols;
+}
+
 size_t sliced_ppart_elems(int64_t cols)
 {
     const int64_t a = 32 * cols, b = 131072 + cols;
@@ -761,24 +897,40 @@ size_t sliced_ppart_elems(int64_t cols)
 struct SlicedDense {
     Sliced e;
     float *At, *Wt, *Ht, *num, *den, *g;
+    bool pairs;             // A' and (A^T)' instead of At
+    PairMatrix pa, pt;
 };
 
-template <class T> T max3(T a, T b, T c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 
-SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, size_t *bytes)
+// Bytes of planes for any F of up to `rows` rows.
+size_t sliced_planes_cap(int64_t rows, int k)
+{
+    const size_t pairs = pair_units_bytes(rows, sliced_ld(k)) + pair_exps_bytes(rows, sliced_ld(k)), pieces = planes_bytes(rows);
+    return pairs > pieces ? pairs : pieces;
+}
+
+SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, bool pairs, size_t *bytes)
 {
     Carve cv(ws);
-    SlicedDense p;
-    cv.take<unsigned>(64);
-    const int64_t big = m > n ? m : n;
+    SlicedDense p{};
+    const int64_t big = m > n ? m : n, all = max3<int64_t>(m, n, k);
     const size_t nslices = (size_t)(k + 63) / 64;
-    p.e.maxima = cv.take<unsigned>(4 * (size_t)k);
-    p.e.planes_cap = planes_bytes(max3<int64_t>(m, n, k)) * nslices;
-    p.e.ppart_elems = sliced_ppart_elems(max3<int64_t>(m, n, k)) * nslices;
+    p.e.most = cv.take<unsigned>((size_t)sliced_ld(k));
+    p.e.planes_cap = sliced_planes_cap(all, k);
     p.e.planes = cv.take<char>(p.e.planes_cap);
     // X is one of A (m x n), W (m x k), H (k x n) or a transpose of those
+    p.e.ppart_elems = sliced_ppart_elems(all) * nslices;
+    if ((p.pairs = pairs)) {
+        const size_t p1 = sliced_pass_elems(m, n, k), p2 = sliced_pass_elems(n, m, k);
+        p.e.ppart_elems = max3(p.e.ppart_elems, p1, p2);
+    }
     p.e.ppart = cv.take<float>(p.e.ppart_elems);
-    p.At = cv.take<float>((size_t)m * n);
+    if (pairs) {
+        p.pa = carve_pair_matrix(cv, m, n);
+        p.pt = carve_pair_matrix(cv, n, m);
+    } else {
+        p.At = cv.take<float>((size_t)m * n);
+    }
     p.Wt = cv.take<float>((size_t)k * m);
     p.Ht = cv.take<float>((size_t)n * k);
     p.num = cv.take<float>((size_t)k * big);
@@ -788,38 +940,74 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, size_t *by
     return p;
 }
 
-size_t sliced_dense_bytes(int64_t m, int64_t n, int k)
+bool sliced_cut_ok(int64_t m, int64_t n, int k) { return k > NMF_MU_MAX_K && m < (int64_t)1 << 25 && n < (int64_t)1 << 25; }
+
+size_t sliced_dense_bytes(int64_t m, int64_t n, int k, bool pairs)
 {
     size_t b = 0;
-    carve_sliced_dense(nullptr, m, n, k, &b);
+    carve_sliced_dense(nullptr, m, n, k, pairs, &b);
     return b;
 }
 
-// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps), F rows x k, X rows x cols.
-int sliced_update(const SlicedDense &p, const float *F, int64_t rows, int k, const float *X, int64_t cols, float *Y, float eps,
-                  Maxima &fF, Maxima &fY, Maxima &fG, hipStream_t st)
+// P (k x cols) = F^T X over X' = x, the planes of F in e.planes: slices of 128 factors, and one of 64 for up to 64 that are left.
+int sliced_pass(const Sliced &e, int64_t rows, int k, const PairMatrix &x, int64_t cols, bool stream, float *out, hipStream_t st)
 {
-    const bool first = sliced_pairs(X, cols, k), second = sliced_pairs(F, k, k);
-    if (int rc = sliced_ftx(p.e, F, rows, k, X, cols, p.num, false, st, fF, true, fG.at, fY.at)) return rc;
-    if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, fF, !first, fG.at, fY.at, &fG)) return rc;
-    if (int rc = sliced_ftx(p.e, p.g, k, k, Y, cols, p.den, false, st, fG)) return rc;
-    fY.there = first || second;      // set to zero on the way
-    NMF_HIP(launch_mu_apply(Y, p.num, p.den, eps, k, cols, st, fY.there ? fY.at : nullptr));
+    const int ld = sliced_ld(k);
+    for (int c0 = 0; c0 < k;) {
+        const bool wide = k - c0 > 64;
+        const int width = wide ? 128 : 64, tiles = wide ? 4 : 2, kc = wide ? (k - c0 > 64 + (k - c0) / 128 * 128 ? k - c0 : (k - c0) / 128 * 128) : k - c0;
+        PairPass a{};
+        a.F = sliced_factor(e, rows, ld);
+        a.F.units = static_cast<char *>(a.F.units) + (size_t)c0 * 16;
+        a.F.exps += c0;
+        a.F.most += c0;
+        a.ldf = ld;
+        a.slice_units = a.slice_exps = a.slice_most = width;
+        a.X = x;
+        a.ppart = e.ppart;
+        a.rows = rows;
+        a.n = cols;
+        a.nslices = (kc + width - 1) / width;
+        for (int z = 0; z < a.nslices; ++z) a.k[z] = (short)(kc - width * z < width ? kc - width * z : width);
+        a.splits = pair_splits(rows, cols, tiles, a.nslices);
+        a.rps = pair_rows_per_split(rows, a.splits);
+        a.slice_ppart = (int64_t)a.splits * width * cols;
+        NMF_HIP(launch_pair_pass(a, tiles, stream, st));
+        NMF_HIP(launch_sum_partials_slices(e.ppart, a.splits, kc, cols, out + (int64_t)c0 * cols, st, false, width));
+        c0 += kc;
+    }
+    return NMF_OK;
+}
+
+// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps), F rows x k, X rows x cols (x: X').
+int sliced_update(const SlicedDense &p, const float *F, int64_t rows, int k, const float *X, const PairMatrix &x, int64_t cols, float *Y,
+                  float eps, bool stream, hipStream_t st)
+{
+    if (p.pairs) {
+        NMF_HIP(sliced_split(p.e, F, rows, k, st));
+        if (int rc = sliced_pass(p.e, rows, k, x, cols, stream, p.num, st)) return rc;
+    } else if (int rc = sliced_ftx(p.e, F, rows, k, X, cols, p.num, false, st)) {
+        return rc;
+    }
+    if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, !p.pairs && !sliced_pairs(X, cols, k))) return rc;
+    if (int rc = sliced_ftx(p.e, p.g, k, k, Y, cols, p.den, false, st)) return rc;
+    NMF_HIP(launch_mu_apply(Y, p.num, p.den, eps, (int64_t)k * cols, st));
     return NMF_OK;
 }
 
 int sliced_dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters,
                       float eps, const SlicedDense &p, hipStream_t st)
 {
-    Maxima fw{p.e.maxima, false}, fh{p.e.maxima + k, false}, fg{p.e.maxima + 2 * k, false};
-    NMF_HIP(launch_transpose(A, m, n, p.At, st));
+    const bool stream = stream_a(m, n, true);
+    if (p.pairs) NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, nullptr, 0, st));
+    else NMF_HIP(launch_transpose(A, m, n, p.At, st));
     NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
     for (int it = 0; it < iters; ++it) {
         // H update (Algorithm 3 order): numerator W^T A, denominator (W^T W) H
-        if (int rc = sliced_update(p, W, m, k, A, n, H, eps, fw, fh, fg, st)) return rc;
+        if (int rc = sliced_update(p, W, m, k, A, p.pa, n, H, eps, stream, st)) return rc;
         NMF_HIP(launch_transpose(H, k, n, p.Ht, st));
         // W update with the new H, on the transposes: (A H^T)^T = H A^T, (W H H^T)^T = (H H^T) W^T
-        if (int rc = sliced_update(p, p.Ht, n, k, p.At, m, p.Wt, eps, fh, fw, fg, st)) return rc;
+        if (int rc = sliced_update(p, p.Ht, n, k, p.At, p.pt, m, p.Wt, eps, stream, st)) return rc;
         NMF_HIP(launch_transpose(p.Wt, k, m, W, st));
     }
     return NMF_OK;
@@ -841,8 +1029,8 @@ SlicedOoc carve_sliced_ooc(void *ws, int64_t rb, int64_t n, int k, size_t *bytes
     SlicedOoc p;
     cv.take<unsigned>(64);
     const size_t nslices = (size_t)(k + 63) / 64;
-    p.e.maxima = cv.take<unsigned>(4 * (size_t)k);
-    p.e.planes_cap = planes_bytes(max3<int64_t>(rb, n, k)) * nslices;
+    p.e.most = cv.take<unsigned>((size_t)sliced_ld(k));
+    p.e.planes_cap = sliced_planes_cap(max3<int64_t>(rb, n, k), k);
     p.e.ppart_elems = sliced_ppart_elems(max3<int64_t>(rb, n, k)) * nslices;
     p.e.planes = cv.take<char>(p.e.planes_cap);
     p.e.ppart = cv.take<float>(p.e.ppart_elems);
@@ -903,7 +1091,6 @@ int sliced_ooc_run(const float *A_host, float *W_host, float *W_dev, int64_t m, 
     NMF_HIP(hipStreamWaitEvent(g.copy_stream, g.ev_entry, 0));
 
     const int64_t nb = (m + batch_rows - 1) / batch_rows;
-    Maxima fw{p.e.maxima, false}, fh{p.e.maxima + k, false}, fgw{p.e.maxima + 2 * k, false}, fgh{p.e.maxima + 3 * k, false};
     int64_t issued = 0;
     for (int s = 0; s <= iters; ++s) {
         for (int64_t b = 0; b < nb; ++b, ++issued) {
@@ -925,17 +1112,15 @@ int sliced_ooc_run(const float *A_host, float *W_host, float *W_dev, int64_t m, 
                 // W_b <- W_b * (A_b H^T) / (W_b H H^T + eps) on the transposes of the batch
                 NMF_HIP(launch_transpose(Ab, rb, n, p.Abt, st));
                 NMF_HIP(launch_transpose(Wb, rb, k, p.Wbt, st));
-                if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Abt, rb, p.num_b, false, st, fh, true, fw.at)) return rc;
-                if (int rc = sliced_ftx(p.e, p.gh, k, k, p.Wbt, rb, p.den_b, false, st, fgh)) return rc;
-                fw.there = sliced_pairs(p.Abt, rb, k);      // set to zero on the way
-                NMF_HIP(launch_mu_apply(p.Wbt, p.num_b, p.den_b, eps, k, rb, st, fw.there ? fw.at : nullptr));
+                if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Abt, rb, p.num_b, false, st)) return rc;
+                if (int rc = sliced_ftx(p.e, p.gh, k, k, p.Wbt, rb, p.den_b, false, st)) return rc;
+                NMF_HIP(launch_mu_apply(p.Wbt, p.num_b, p.den_b, eps, (int64_t)k * rb, st));
                 NMF_HIP(launch_transpose(p.Wbt, k, rb, Wb, st));
             }
             if (s < iters) {
                 // accumulate W_b^T A_b and W_b^T W_b with the W_b just updated
-                if (s == 0) fw.there = false;
-                if (int rc = sliced_ftx(p.e, Wb, rb, k, Ab, n, p.num, b > 0, st, fw)) return rc;
-                if (int rc = sliced_ftx(p.e, Wb, rb, k, Wb, k, p.gw, b > 0, st, fw, !sliced_pairs(Ab, n, k))) return rc;
+                if (int rc = sliced_ftx(p.e, Wb, rb, k, Ab, n, p.num, b > 0, st)) return rc;
+                if (int rc = sliced_ftx(p.e, Wb, rb, k, Wb, k, p.gw, b > 0, st, !sliced_pairs(Ab, n, k))) return rc;
             }
             if (hostw) {
                 NMF_HIP(hipEventRecord(g.sl_done[slot], st));
@@ -949,12 +1134,10 @@ int sliced_ooc_run(const float *A_host, float *W_host, float *W_dev, int64_t m, 
             }
         }
         if (s < iters) {
-            fgw.there = false;
-            if (int rc = sliced_ftx(p.e, p.gw, k, k, H, n, p.den, false, st, fgw, true, fh.at, fgh.at)) return rc;
-            fh.there = sliced_pairs(H, n, k);
-            NMF_HIP(launch_mu_apply(H, p.num, p.den, eps, k, n, st, fh.there ? fh.at : nullptr));
+            if (int rc = sliced_ftx(p.e, p.gw, k, k, H, n, p.den, false, st)) return rc;
+            NMF_HIP(launch_mu_apply(H, p.num, p.den, eps, (int64_t)k * n, st));
             NMF_HIP(launch_transpose(H, k, n, p.Ht, st));
-            if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Ht, k, p.gh, false, st, fh, true, fgh.at, nullptr, &fgh)) return rc;
+            if (int rc = sliced_ftx(p.e, p.Ht, n, k, p.Ht, k, p.gh, false, st)) return rc;
         }
     }
     if (hostw) {
@@ -1021,14 +1204,21 @@ size_t nmf_mu_workspace_bytes(int kind, int64_t m, int64_t n, int64_t nnz, int32
                               int64_t batch_rows)
 {
     if (m < 1 || n < 1 || k < 1) return 0;
-    if (kind == 5) return k > NMF_MU_MAX_K_SLICED ? 0 : sliced_dense_bytes(m, n, k);
+    if (kind == 5) {
+        if (k > NMF_MU_MAX_K_SLICED) return 0;
+        const size_t plain = sliced_dense_bytes(m, n, k, false), pairs = sliced_cut_ok(m, n, k) ? sliced_dense_bytes(m, n, k, true) : 0;
+        return plain > pairs ? plain : pairs;
+    }
     if (kind == 6) {
         if (batch_rows < 1 || k > NMF_MU_MAX_K_SLICED) return 0;
         return sliced_ooc_bytes(batch_rows < m ? batch_rows : m, n, k);
     }
     if (k > NMF_MU_MAX_K) return 0;
     switch (kind) {
-    case 0: return dense_bytes(m, n, k, true);
+    case 0: {
+        const size_t mirrored = dense_bytes(m, n, k, true), pairs = pairs_ok(m, n, k) ? pairs_bytes(m, n, k) : 0;
+        return mirrored > pairs ? mirrored : pairs;
+    }
     case 3:   // stacks of runs up to the largest supported rank, plus their packed factors
         return dense_bytes(m, n, NMF_MU_MAX_K, true) + align_up((size_t)m * NMF_MU_MAX_K * sizeof(float)) +
                align_up((size_t)NMF_MU_MAX_K * n * sizeof(float));
@@ -1110,9 +1300,11 @@ int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k, float *W, floa
     std::lock_guard<std::mutex> lock(g.mu);
     void *ws = nullptr;
     if (k > NMF_MU_MAX_K) {
-        if (int rc = ensure_workspace(sliced_dense_bytes(m, n, k), &ws)) return rc;
-        const SlicedDense p = carve_sliced_dense(ws, m, n, k, nullptr);
-        return sliced_dense_body(A, m, n, k, W, H, iters, eps, p, static_cast<hipStream_t>(stream));
+        hipStream_t st = static_cast<hipStream_t>(stream);
+        const bool pairs = sliced_cut_ok(m, n, k) && have_workspace(sliced_dense_bytes(m, n, k, true), st);
+        if (int rc = ensure_workspace(sliced_dense_bytes(m, n, k, pairs), &ws)) return rc;
+        const SlicedDense p = carve_sliced_dense(ws, m, n, k, pairs, nullptr);
+        return sliced_dense_body(A, m, n, k, W, H, iters, eps, p, st);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     DenseRun r;
@@ -1164,7 +1356,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
         const bool rows_plan = !resident && !one_pass && rows_plan_runs(A, m, n, k, mirrored);
         const Common &c = p.c;
         for (int which = 0; which < ((mirrored || rows_plan || one_pass || resident) ? 2 : 1) && rc == NMF_OK; ++which) {
-            if (one_pass || resident) (void)0;
+            if (one_pass || resident || p.pairs) (void)0;
             else if (which == 0) (void)launch_split_planes(W, m, k, p.planes, st);
             else if (!rows_plan) (void)launch_split_planes(p.Ht, n, k, p.planes, st);
             ResidentArgs dry = p.res;
@@ -1177,6 +1369,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
                 e = resident ? launch_resident(dry, p.resident, st)
                     : one_pass ? launch_one_pass(A, m, n, k, p.planes2, nullptr, c.ghp, factor_update_blocks(n), W, nullptr, p.ppart,
                                                c.gwp, eps, st, which == 1, which == 0)
+                    : p.pairs ? pass_over(p, m, n, k, which == 1, nullptr, 0, nullptr, st)
                     : which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, nullptr, 0, nullptr, mirrored)
                     : rows_plan  // the fused pass without its stores to W
                         ? launch_aht_rows(A, m, n, k, p.planes2, c.gh, W, p.planes, c.gwp, eps, st, false, nullptr,
@@ -1863,7 +2056,7 @@ int nmf_mu_dense_tol(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     const size_t extra = run_scratch_bytes(m, n) + align_up((size_t)kFinMaxBlocks * sizeof(double)) +
                          align_up(4097 * sizeof(double)) + kAlign;
     DenseRun r;
-    if (int rc = open_run(A, m, n, k, W, H, max_iters, eps, extra, st, &r)) return rc;
+    if (int rc = open_run(A, m, n, k, W, H, max_iters, eps, extra, st, &r, true)) return rc;
     const bool mirrored = r.p.mirrored;
     // plans whose W update leaves the objective's terms behind
     const bool fast = mirrored || r.p.one_pass || r.p.resident || rows_plan_runs(r.A, m, r.n, k, mirrored);

@@ -31,12 +31,10 @@
 //   D    (32 x 32): lane l, register v holds D[(v % 4) + 4 (l / 32) + 8 (v / 4)][l % 32]
 #include <atomic>
 
-#include "nmfmu_internal.h"
+#include "nmfmu_device.h"
 
 namespace nmfmu {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
 {
@@ -59,7 +57,6 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
 // A_op[l % 32][8 (l / 32) .. 8 (l / 32) + 7]; B_op (16 x 32): lane l holds
 // B_op[8 (l / 32) .. + 7][l % 32]; D as for the fp32 instruction.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
 {
@@ -123,59 +120,6 @@ __device__ __forceinline__ void cut2(float x0, float x1, u32x4 (&at)[3], int pr)
     at[1][pr] = m;
     at[2][pr] = cvt_pk_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
-
-// ---- the same from pairs of halves --------------------------------------------------
-// A float scaled by a power of two into the range of a half (11 significant bits) is cut into h = x rounded to nearest
-// even and l = (x - h) rounded likewise: 22 bits and the two signs, so h + l is x or, for a quarter of all floats, its
-// neighbour; below 2^-1 of the scaled range the halves' denormals end the second piece at 2^-25 instead.  THREE products,
-// l h, h l and h h, do the work of the six of bf16 pieces (the one left out is below 2^-24 of the term, of either sign),
-// and the cut is shorter.  The products have up to 22 bits, and fewer of them join an accumulator: against 64
-// bits, root mean square over 4096 terms of U[0,1) in chains of 256, bf16 pieces 7.5e-8 and pairs 6.7e-8 (fp32
-// instruction 8.0e-8); with one value down a column 1.9e-7 and 8.4e-8; one value on either side 6.3e-7 and 4.4e-7.
-//
-// Scales: a factor's column c has one for all of a pass, 2^(14 - exponent of its largest entry) (half_exponent of fmax[c]).
-// The streamed operand's columns belong to lanes, and a lane's scale follows its data (see the pass).
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ f32x16 mfma_f16(u32x4 a, u32x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-// Exponent of the power of two below |x|, from the bits of |x|; held where 2^(14 - e) and its inverse are floats.  What is
-// smaller than 2^-112 meets a scale of 2^126, under which the last bit of a denormal float is a half.
-__device__ __forceinline__ int half_exponent(unsigned bits)
-{
-    const int e = (int)(bits >> 23) - 127;
-    return e < -112 ? -112 : e;
-}
-__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
-
-// Halves of two consecutive elements of an operand, times s, into register pr of its two planes.
-__device__ __forceinline__ void cut2h(float x0, float x1, float s, u32x4 (&at)[2], int pr)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const f16x2 h = __builtin_convertvector(f32x2{x0 * s, x1 * s}, f16x2);
-    const float r0 = __builtin_fmaf(x0, s, -(float)h[0]), r1 = __builtin_fmaf(x1, s, -(float)h[1]);
-    at[0][pr] = __builtin_bit_cast(unsigned, h);
-    at[1][pr] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{r0, r1}, f16x2));
-}
-
-// Sum of N requested values, added in a fixed tree: long lists of partial results meet in batches of this
-// kind, so that no value passes through a chain of more roundings than there are batches plus log2 N.
-template <int N>
-__device__ __forceinline__ float tree_sum(float (&t)[N])
-{
-#pragma unroll
-    for (int w = N / 2; w > 0; w >>= 1)
-#pragma unroll
-        for (int i = 0; i < w; ++i) t[i] += t[i + w];
-    return t[0];
-}
-
-// Row of the 32 x 32 accumulator held in register v of a lane in half `half`.
-__device__ __forceinline__ int acc_row(int v, int half) { return (v & 3) + 4 * half + 8 * (v >> 2); }
 
 // Running totals of the piece passes.  The bf16 matrix instruction aligns its 16 products
 // and the accumulator on the largest exponent and drops what falls below its adder's
@@ -443,36 +387,6 @@ __global__ __launch_bounds__(512) void gram16_kernel(const float *__restrict__ X
     if (tid == 0) *counter = 0u;
 }
 
-// Side job of the pass kernels: the Gram tiles a finisher left behind (nsets sets of
-// kt x kt tiles of 1024 floats) are needed, summed, by the finisher AFTER this pass.  The
-// first workgroups of the pass add them up so that no separate launch is needed: job j = entries
-// 64 j .. 64 j + 63, dealt to the workgroups in order; four lanes share an entry, lane q adds sets
-// q, q + 4, ... a batch of 16 at a time, and the four sums meet in a fixed tree.  (Sums of 16 sets each, left to the
-// finisher's workgroups to finish, cost every one of them 256 KiB of reads at 33 to 64 factors.)
-__device__ __forceinline__ void sum_tile_sets(const float *__restrict__ gtiles, int nsets, int k,
-                                              float *__restrict__ gsum)
-{
-    constexpr int B = 16;
-    const int kt = (k + 31) >> 5;
-    const int stride = kt * kt * 1024;
-    const int nwg = gridDim.x * gridDim.y, q = threadIdx.x & 3;
-    for (int job = blockIdx.y * gridDim.x + blockIdx.x; job < stride / 64; job += nwg) {
-        const float *src = gtiles + job * 64 + (threadIdx.x >> 2);
-        float sum = 0.f;
-        for (int s = q; s < nsets; s += 4 * B) {
-            float t[B];
-#pragma unroll
-            for (int b = 0; b < B; ++b) t[b] = src[(int64_t)(s + 4 * b < nsets ? s + 4 * b : 0) * stride];
-#pragma unroll
-            for (int b = 0; b < B; ++b) t[b] = s + 4 * b < nsets ? t[b] : 0.f;
-            sum += tree_sum(t);
-        }
-        sum += __shfl_xor(sum, 1);
-        sum += __shfl_xor(sum, 2);
-        if (q == 0) gsum[job * 64 + (threadIdx.x >> 2)] = sum;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // W^T A pass.  Workgroup = 4 waves on one 128-column slab of A and one row
 // split; wave w takes row pairs w, w+4, ... of the split.  Per row pair a lane
@@ -498,7 +412,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void wta_pass_kernel(const flo
     constexpr int NW = kWtaWaves;
     constexpr int LD = 132;
     __shared__ float red[KT * 32 * LD];
-    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int jj = lane & 31, half = lane >> 5;
     const int64_t j0 = (int64_t)blockIdx.x * kWtaCols;
@@ -631,7 +545,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_kernel(
 {
     constexpr int NW = kWtaWaves;
     __shared__ float tot[NW * kTotFloats];
-    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     float *mytot = tot + w * kTotFloats;
     tot_clear(mytot, lane);
@@ -721,7 +635,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split_buf_kernel(
     constexpr int NW = kWtaWaves;
     constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
     __shared__ float tot[NW * kTotFloats];
-    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *mytot = tot + w * kTotFloats;
@@ -846,7 +760,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
     constexpr int kUnits = kSteps * 2 * 3 * KP;        // 16-byte units of planes in a group
     __shared__ u32x4 pst[2][kUnits];
     const int bx = blockIdx.x, by = blockIdx.y;
-    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum);
+    if (gtiles) sum_tile_sets(gtiles, nsets, k, gsum, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int jj = lane & 31, half = lane >> 5;
@@ -971,244 +885,6 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
 }
 
 // ---------------------------------------------------------------------------
-// Ranks above 64: the largest magnitude of every column of X (rows x k), as bits, into fmax (zero before; an infinity or a
-// NaN is the largest).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void factor_max_kernel(const float *__restrict__ X, int64_t rows, int k, unsigned *__restrict__ fmax)
-{
-    // a thread walks one column of 64 rows, eight requested together
-    const int64_t c = (int64_t)blockIdx.y * 256 + threadIdx.x;
-    if (c >= k) return;
-    const int64_t r0 = (int64_t)blockIdx.x * 64;
-    unsigned most = 0;
-    for (int i = 0; i < 64; i += 8) {
-        unsigned v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t r = r0 + i + u < rows ? r0 + i + u : rows - 1;
-            v[u] = __float_as_uint(X[r * k + c]) & 0x7fffffffu;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) most = v[u] > most ? v[u] : most;
-    }
-    if (most) atomicMax(fmax + c, most);
-}
-
-// Pair planes of all slices of 64 columns of X (rows x k, row-major), scaled by fmax:
-// planes[slice * slice_planes + (g * 2 + p) * 64 + c] = the eight halves (p = 0: h, 1: l) of
-// X[8 g .. 8 g + 7][64 slice + c]; rows beyond `rows` and columns beyond k are zero.
-// clear1, clear2 (optional): arrays of k words to set to zero on the way, for the maxima that come next.
-__global__ __launch_bounds__(256) void split_pairs_kernel(const float *__restrict__ X, int64_t rows, int k,
-                                                          const unsigned *__restrict__ fmax, u32x4 *__restrict__ planes,
-                                                          int64_t slice_planes, unsigned *__restrict__ clear1,
-                                                          unsigned *__restrict__ clear2)
-{
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int cw = (int)(t & 63), c = 64 * (int)blockIdx.y + cw;
-    const int64_t g = t >> 6;
-    if (g == 0 && c < k) {
-        if (clear1) clear1[c] = 0u;
-        if (clear2) clear2[c] = 0u;
-    }
-    if (g * 8 >= rows) return;
-    float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = (g * 8 + e < rows && c < k) ? X[(g * 8 + e) * k + c] : 0.f;
-    const float sc = c < k ? power_of_two(14 - half_exponent(fmax[c])) : 0.f;
-    u32x4 o[2];
-#pragma unroll
-    for (int pr = 0; pr < 4; ++pr) cut2h(x[2 * pr], x[2 * pr + 1], sc, o, pr);
-    u32x4 *dst = planes + (int64_t)blockIdx.y * slice_planes + g * 128 + cw;
-    dst[0] = o[0];
-    dst[64] = o[1];
-}
-
-// ---------------------------------------------------------------------------
-// The pass for slices of 64 factors on pairs of halves (aligned A, n % 4 == 0, 64 n < 2^31; pair planes).  Geometry of
-// wta_pass_split64_wide_kernel: workgroup = 256 columns, wave = 64 of them (lane = 2 consecutive columns), the planes of a
-// group of steps staged in LDS for the four waves, three register stages of A.  12 matrix instructions per 16 rows x 64
-// columns x 64 factors instead of 24.  The accumulators join the totals every second group, after 192 terms.
-// Ranks above 64 were bound by the matrix cores (power) on bf16 pieces; rank 256 on 16384 x 8192: 380 -> 270 us per product
-// (of which loads without the matrix work 210, the matrix work without the loads 220), whole iterations 937 -> 718,
-// error against 64 bits after five iterations 2.4 -> 2.3e-7.
-//
-// Scale of a column of A: a column of the accumulators belongs to a lane pair (l, l + 32), so the scale may change from group to
-// group as long as the accumulators are unscaled when they join the totals (one fused multiply-add each).  The running maximum
-// of a column's magnitudes costs half an instruction per element; if an element would leave the halves' range
-// (2^15), the wave joins what it has to the totals and scales anew: the largest entry seen goes to 2^11, so that entries up to
-// 8 times as large come without another change, and after every join the scale follows the maximum since the last one.
-// ---------------------------------------------------------------------------
-// Several 64-factor slices of a wider factor in one launch: workgroup L of a one-dimensional grid stands for (tile, slice) with
-// the slices of one tile of A (slab x row split) 8 workgroups apart, i.e. on the same XCD at about the same time, so that A
-// comes from HBM once and from that XCD's L2 for the other slices (default cache policy).  Slice z reads planes + z *
-// slice_planes and writes ppart + z * slice_ppart; it holds min(64, ktotal - 64 z) factors.
-__global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
-    const float *__restrict__ A, const u32x4 *__restrict__ planes, const unsigned *__restrict__ fmax, float *__restrict__ ppart,
-    int64_t rows, int64_t n, int k, int64_t rps, int gx, int gy, int nslices, int64_t slice_planes, int64_t slice_ppart)
-{
-    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    constexpr int KP = 64;
-    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
-    constexpr int kSteps = 6;                          // 16-row steps per group of staged planes
-    constexpr int kUnits = kSteps * 2 * 2 * KP;        // 16-byte units of planes in a group
-    constexpr float kMost = 32768.f;
-    __shared__ u32x4 pst[2][kUnits];
-    __shared__ int fexp[KP];
-    const int L = blockIdx.x, within = L >> 3;
-    const int z = within % nslices;
-    const int t8 = (within / nslices) * 8 + (L & 7);
-    if (t8 >= gx * gy) return;
-    const int bx = t8 % gx, by = t8 / gx;
-    planes += (int64_t)z * slice_planes;
-    ppart += (int64_t)z * slice_ppart;
-    fmax += 64 * z;
-    k = (k - 64 * z < 64) ? k - 64 * z : 64;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int jj = lane & 31, half = lane >> 5;
-    const int64_t jw = (int64_t)bx * 256 + 64 * w;
-    const bool live = jw < n;   // a wave wholly past the edge only helps to stage the planes
-    const int64_t colr = jw + 2 * jj;
-    const int64_t col = colr < n ? colr : 0;   // lanes past the edge read valid data that is never stored
-    const int64_t r0 = (int64_t)by * rps;
-    const int64_t r1 = (r0 + rps < rows) ? r0 + rps : rows;
-    const unsigned rowb = (unsigned)(n * 4);
-    const unsigned loff = (unsigned)(half * 8) * rowb + (unsigned)col * 4;
-    const int64_t ngroups = (rows + 7) >> 3;
-    if (tid < KP) fexp[tid] = tid < k ? half_exponent(fmax[tid]) - 14 : 0;     // read after the first barrier
-
-    f32x16 acc[2][2], tot[2][2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[t][q] = f32x16{0}, tot[t][q] = f32x16{0};
-    // per column: scale, its inverse, largest magnitude since the last join
-    float sc[2], inv[2], most[2] = {0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) sc[q] = power_of_two(126), inv[q] = power_of_two(-126);
-
-    struct Stage { u32x2 a[8]; };
-    auto load_stage = [&](Stage &s, int64_t ib) {
-        int64_t av = live ? r1 - ib : 0;            // rows of this step inside the split
-        av = av < 0 ? 0 : (av > 16 ? 16 : av);
-        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(A + (av ? ib : 0) * n), 0, (int)(av * rowb), kRsrcFlags);
-#pragma unroll
-        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b64(ra, loff + r * rowb, 0, 0);
-    };
-    // a third of the planes of the group of rows from ib on: 2 units per thread
-    struct Third { u32x4 u[2]; };
-    auto load_third = [&](Third &p, int64_t ib, int part) {
-        const int64_t g = ib >> 3;
-        int64_t ng = ib < r1 ? ngroups - g : 0;     // 8-row groups of planes that exist
-        ng = ng < 0 ? 0 : (ng > 2 * kSteps ? 2 * kSteps : ng);
-        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<u32x4 *>(planes + (ng ? g : 0) * 2 * KP), 0, (int)(ng * 2 * KP * 16), kRsrcFlags);
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-            p.u[e] = __builtin_amdgcn_raw_buffer_load_b128(rp, (unsigned)((2 * part + e) * 256 + tid) * 16, 0, 0);
-    };
-    auto store_third = [&](const Third &p, int buf, int part) {
-#pragma unroll
-        for (int e = 0; e < 2; ++e) pst[buf][(2 * part + e) * 256 + tid] = p.u[e];
-    };
-    // the accumulators join the totals; the scales follow the maxima
-    auto join = [&]() {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    tot[t][q][v] = __builtin_fmaf(acc[t][q][v], inv[q], tot[t][q][v]);
-                    acc[t][q][v] = 0.f;
-                }
-            const float both = fmaxf(most[q], __shfl_xor(most[q], 32));
-            if (both > 0.f) {
-                const int e = half_exponent(__float_as_uint(both));
-                sc[q] = power_of_two(11 - e > 126 ? 126 : 11 - e);
-                inv[q] = power_of_two(11 - e > 126 ? -126 : e - 11);
-            }
-            most[q] = 0.f;
-        }
-    };
-    auto compute = [&](const Stage &c, int buf, int st) {
-        u32x4 wt[2][2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int pl = 0; pl < 2; ++pl) wt[t][pl] = pst[buf][((2 * st + half) * 2 + pl) * KP + 32 * t + jj];
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) most[q] = fmaxf(most[q], __builtin_fabsf(__uint_as_float(c.a[r][q])));
-        if (__any(most[0] * sc[0] >= kMost || most[1] * sc[1] >= kMost)) join();
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            u32x4 at[2];
-#pragma unroll
-            for (int pr = 0; pr < 4; ++pr)
-                cut2h(__uint_as_float(c.a[2 * pr][q]), __uint_as_float(c.a[2 * pr + 1][q]), sc[q], at, pr);
-            constexpr int PW[3] = {1, 0, 0}, PA[3] = {0, 1, 0};   // smallest first
-#pragma unroll
-            for (int e = 0; e < 3; ++e)
-#pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t][q] = mfma_f16(wt[t][PW[e]], at[PA[e]], acc[t][q]);
-        }
-    };
-    Stage s0, s1, s2;
-    Third th;
-    load_stage(s0, r0);
-    __builtin_amdgcn_sched_barrier(0);   // issue order = age order, also here: the waits in the loop count loads in flight
-    load_stage(s1, r0 + 16);
-#pragma unroll
-    for (int part = 0; part < 3; ++part) {
-        load_third(th, r0, part);
-        store_third(th, 0, part);
-    }
-    __syncthreads();
-    int buf = 0;
-    for (int64_t i = r0; i < r1; i += 16 * kSteps) {
-#pragma unroll
-        for (int part = 0; part < 3; ++part) {
-            const int64_t ib = i + 32 * part;
-            Stage &x = part == 0 ? s0 : (part == 1 ? s2 : s1);
-            Stage &y = part == 0 ? s1 : (part == 1 ? s0 : s2);
-            Stage &z2 = part == 0 ? s2 : (part == 1 ? s1 : s0);
-            load_third(th, i + 16 * kSteps, part);
-            load_stage(z2, ib + 32);
-            __builtin_amdgcn_sched_barrier(0);
-            if (live && ib < r1) compute(x, buf, 2 * part);
-            __builtin_amdgcn_sched_barrier(0);
-            load_stage(x, ib + 48);
-            __builtin_amdgcn_sched_barrier(0);
-            if (live && ib + 16 < r1) compute(y, buf, 2 * part + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            store_third(th, buf ^ 1, part);
-        }
-        if (buf) join();
-        __syncthreads();    // the next group's planes are written, this group's are read
-        buf ^= 1;
-    }
-    join();
-
-    if (colr < n) {
-        float *dst = ppart + (int64_t)by * k * n + colr;
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int c = 32 * t + acc_row(v, half);
-                if (c < k) {
-                    const int e = fexp[c];
-                    *reinterpret_cast<f32x2 *>(dst + (int64_t)c * n) = f32x2{ldexpf(tot[t][0][v], e), ldexpf(tot[t][1][v], e)};
-                }
-            }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Factor update ("finisher").  For X (k x len), partials of its numerator and
 // the Gram matrix G of the other factor:
 //     X[c][j] <- X[c][j] * (sum_s part[s][c][j]) / (sum_d G[c][d] X[d][j] + eps).
@@ -1238,7 +914,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
 // 25 us at k = 50 on 9998 columns and 12 splits, now 19; 10.5 at k = 20 on 4096, now 6.7; 27 at
 // k = 16 on 512 columns and 128 splits, now 10; 13 at k = 32 on 16384, now 9.6.
 // ---------------------------------------------------------------------------
-template <int KP, int CW, bool BIG>
+template <int KP, int CW, bool BIG, bool PAIRS>
 __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                                                             const float *__restrict__ part,
                                                             int splits,
@@ -1247,7 +923,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                                                             float *__restrict__ gout,
                                                             u32x4 *__restrict__ planes,
                                                             double *__restrict__ dpart, int k,
-                                                            int64_t len, float eps, BlockMap bm)
+                                                            int64_t len, float eps, BlockMap bm, PairFactor pf)
 {
     constexpr int NW = 8, KT = KP / 32 > 0 ? KP / 32 : 1, LD = KP + 4;
     constexpr int NG = 512 / CW, FG = NG < KP ? NG : KP, SPL = NG / FG, NC = KP / FG;
@@ -1367,6 +1043,8 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
     f32x16 acc = {0};
 
     double dacc = 0.0;   // sum over this thread's entries of numerator x new value (objective monitor)
+    __shared__ unsigned most[64];    // of each factor, over this block's chunks (pair planes)
+    if (PAIRS && tid < 64) most[tid] = 0u;    // the barriers of the first chunk come before its use
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
         const int64_t j = ch * CW + jl;
         const bool okj = j < len;
@@ -1447,7 +1125,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
             }
         }
         constexpr int PKP = KP <= 32 ? 32 : 64;   // factor slots per row group of the planes
-        if (planes && tid < (CW / 8) * PKP) {
+        if (!PAIRS && planes && tid < (CW / 8) * PKP) {
             // bf16 piece planes of the new X^T rows of this chunk (layout of split_planes_kernel)
             const int gl = tid / PKP, c = tid % PKP;
             const int64_t grow = ch * (CW / 8) + gl;
@@ -1467,6 +1145,18 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                 }
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) planes[(grow * 3 + pl) * PKP + c] = o[pl];
+            }
+        }
+        if (PAIRS && tid < (CW / 8) * PKP) {
+            // pair planes of the same rows (layout of split_pairs_kernel)
+            const int gl = tid / PKP, c = tid % PKP;
+            const int64_t grow = ch * (CW / 8) + gl;
+            if (grow * 8 < len) {
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = c < k ? Ts[(8 * gl + e) * LDT + c] : 0.f;
+                const unsigned top = put_pairs(x, static_cast<u32x4 *>(pf.units) + grow * 2 * PKP + c, PKP, pf.exps + grow * PKP + c);
+                if (top) atomicMax(&most[c], top);
             }
         }
         if (gout && G2) {
@@ -1501,6 +1191,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
     }
     if (!gout) return;
     __syncthreads();   // the last chunk's readers of Ts are done: Sm changes hands
+    if (PAIRS && tid < k && most[tid]) atomicMax(pf.most + tid, most[tid]);
     // Rows and columns of a tile at factor indices >= k hold whatever LDS held;
     // consumers never read them.
     // every wave parks its tile, then all threads add the copies in wave order: the two halves
@@ -3687,17 +3378,15 @@ __global__ __launch_bounds__(256) void objective_kernel(const double *__restrict
 }
 
 // P = sum over the row splits of the partial W^T A results (test entry point only).
-// blockIdx.y = slice of 64 factors (ranks above 64): partials at ppart + slice * slice_ppart, `count`
+// blockIdx.y = slice of 64 or 128 factors (ranks above 64): partials at ppart + slice * slice_ppart, `count`
 // floats of P per full slice, count_last for the last one.
-// most (optional, small P only): the largest magnitude of each of the cols columns of P, as bits (zero before).
 // Eight splits are requested together and added in split order: one load at a time, a 256 x 256
 // Gram matrix over 32 splits took 35 us on 64 workgroups per slice, a chain of trips to memory
 // (rank 256 on 16384 x 8192: 1041 -> 977 us per iteration).
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float *__restrict__ ppart,
                                                            int splits, int64_t count,
                                                            float *__restrict__ P, int accumulate,
-                                                           int64_t slice_ppart, int64_t count_last, int cols,
-                                                           unsigned *__restrict__ most)
+                                                           int64_t slice_ppart, int64_t count_last)
 {
     ppart += (int64_t)blockIdx.y * slice_ppart;
     P += (int64_t)blockIdx.y * count;
@@ -3713,41 +3402,18 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float *__restri
             for (int u = 0; u < 8; ++u) s += v[u];
         }
         for (; t < splits; ++t) s += ppart[(int64_t)t * count + e];
-        if (accumulate) s += P[e];
-        P[e] = s;
-        if (most) atomicMax(most + (int)((unsigned)e % (unsigned)cols), __float_as_uint(s) & 0x7fffffffu);
+        P[e] = accumulate ? P[e] + s : s;
     }
 }
 
 // X <- X * P / (D + eps) element by element: the multiplicative update with its numerator P
 // and the product D of the other factor's Gram matrix with X already formed (ranks above 64).
-// blockIdx.y = row of X (len entries); most (optional): the largest magnitude of each row of the new X, as bits (zero before).
 __global__ __launch_bounds__(256) void mu_apply_kernel(float *__restrict__ X, const float *__restrict__ P,
                                                        const float *__restrict__ D, float eps,
-                                                       int64_t len, unsigned *__restrict__ most)
+                                                       int64_t count)
 {
-    const int64_t row = (int64_t)blockIdx.y * len;
-    unsigned top = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) {
-        const int64_t e = row + i;
-        const float x = X[e] * P[e] / (D[e] + eps);
-        X[e] = x;
-        const unsigned b = __float_as_uint(x) & 0x7fffffffu;
-        top = b > top ? b : top;
-    }
-    if (!most) return;
-    __shared__ unsigned part[4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned b = __shfl_xor(top, o);
-        top = b > top ? b : top;
-    }
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = top;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 0; i < 4; ++i) top = part[i] > top ? part[i] : top;
-        atomicMax(most + blockIdx.y, top);
-    }
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256)
+        X[e] = X[e] * P[e] / (D[e] + eps);
 }
 
 // ---------------------------------------------------------------------------
@@ -3764,7 +3430,7 @@ static inline bool vec_ok(const void *p, int64_t ld)
 // 2000 x 1204, k = 12: 13.7 -> 11.7 and 8.3 -> 8.0.  A run that reads A and A^T in turn has two matrices to
 // keep; per iteration there, marked against kept: 2 x 120 MiB, k = 40 102 and 97 us, 2 x 144 110 and 110 (k = 20 83 and
 // 81), 2 x 160, k = 64 124 and 128, 2 x 192, k = 40 132 and 137, 2 x 220, k = 64 147 and 155.
-static bool stream_a(int64_t rows, int64_t n, bool two = false)
+bool stream_a(int64_t rows, int64_t n, bool two)
 {
     return rows * n * 4 > ((int64_t)(two ? 152 : 224) << 20);
 }
@@ -3902,47 +3568,16 @@ hipError_t launch_split_planes_slice(const float *X, int64_t rows, int64_t ld, i
     return hipGetLastError();
 }
 
-size_t pair_planes_bytes(int64_t rows) { return (size_t)((rows + 7) / 8) * 2 * 64 * 16; }
-
-hipError_t launch_factor_max(const float *X, int64_t rows, int k, unsigned *fmax, hipStream_t st)
-{
-    hipLaunchKernelGGL(factor_max_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)((k + 255) / 256)), dim3(256), 0, st, X, rows, k,
-                       fmax);
-    return hipGetLastError();
-}
-
-hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const unsigned *fmax, void *planes, hipStream_t st,
-                              unsigned *clear1, unsigned *clear2)
-{
-    const int64_t threads = ((rows + 7) / 8) * 64;
-    hipLaunchKernelGGL(split_pairs_kernel, dim3((unsigned)((threads + 255) / 256), (unsigned)((k + 63) / 64)), dim3(256), 0, st, X,
-                       rows, k, fmax, static_cast<u32x4 *>(planes), (int64_t)(pair_planes_bytes(rows) / 16), clear1, clear2);
-    return hipGetLastError();
-}
-
-hipError_t launch_pair_slices(const float *A, int64_t rows, int64_t n, int k, const void *planes, const unsigned *fmax, float *ppart,
-                              int splits, int64_t rps, hipStream_t st)
-{
-    if (!vec_ok(A, n) || n >= ((int64_t)1 << 25) || rps % 16) return hipErrorInvalidValue;
-    const int nslices = (k + 63) / 64;
-    const int gx = (int)((n + 255) / 256), gy = splits;
-    const int64_t tiles8 = ((int64_t)gx * gy + 7) / 8 * 8;
-    hipLaunchKernelGGL(wta_pass_pair_kernel, dim3((unsigned)(tiles8 * nslices)), dim3(64 * kWtaWaves), 0, st, A,
-                       static_cast<const u32x4 *>(planes), fmax, ppart, rows, n, k, rps, gx, gy, nslices,
-                       (int64_t)(pair_planes_bytes(rows) / 16), (int64_t)splits * 64 * n);
-    return hipGetLastError();
-}
-
 hipError_t launch_sum_partials_slices(const float *ppart, int splits, int k, int64_t cols, float *P, hipStream_t st,
-                                      bool accumulate, unsigned *most)
+                                      bool accumulate, int width)
 {
-    const int nslices = (k + 63) / 64;
-    const int64_t count = 64 * cols, count_last = (int64_t)(k - 64 * (nslices - 1)) * cols;
+    const int nslices = (k + width - 1) / width;
+    const int64_t count = width * cols, count_last = (int64_t)(k - width * (nslices - 1)) * cols;
     int64_t b = (count + 255) / 256;
     if (b > 4096) b = 4096;
     // the partials of slice z hold splits x (factors of z) x cols floats, packed for that slice's width
     hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)b, (unsigned)nslices), dim3(256), 0, st, ppart, splits, count, P,
-                       accumulate ? 1 : 0, (int64_t)splits * 64 * cols, count_last, (int)cols, most);
+                       accumulate ? 1 : 0, (int64_t)splits * width * cols, count_last);
     return hipGetLastError();
 }
 
@@ -3952,12 +3587,12 @@ hipError_t launch_split_planes(const float *X, int64_t rows, int k, void *planes
     return launch_split_planes_slice(X, rows, k, 0, k, planes, st);
 }
 
-hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, int k, int64_t len, hipStream_t st, unsigned *most)
+hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, int64_t count,
+                           hipStream_t st)
 {
-    // four elements a thread, 8192 workgroups at most
-    int64_t b = (len + 1023) / 1024;
-    if (b > 8192 / k) b = 8192 / k;
-    hipLaunchKernelGGL(mu_apply_kernel, dim3((unsigned)b, (unsigned)k), dim3(256), 0, st, X, P, D, eps, len, most);
+    int64_t b = (count + 255) / 256;
+    if (b > 8192) b = 8192;
+    hipLaunchKernelGGL(mu_apply_kernel, dim3((unsigned)b), dim3(256), 0, st, X, P, D, eps, count);
     return hipGetLastError();
 }
 
@@ -4036,24 +3671,26 @@ int factor_update_blocks(int64_t len)
 template <int CW, bool BIG>
 static void factor_update_dispatch(dim3 grid, hipStream_t st, float *X, float *Xt, const float *part, int splits,
                                    const float *Gfull, const float *gin, int nbin, float *gout, u32x4 *pl,
-                                   double *dpart, int k, int64_t len, float eps, const BlockMap &bm)
+                                   double *dpart, int k, int64_t len, float eps, const BlockMap &bm, const PairFactor &pf)
 {
     const dim3 block(512);
-    if (k <= 8)
-        hipLaunchKernelGGL((factor_update_kernel<8, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else if (k <= 16)
-        hipLaunchKernelGGL((factor_update_kernel<16, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else if (k <= 32)
-        hipLaunchKernelGGL((factor_update_kernel<32, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else
-        hipLaunchKernelGGL((factor_update_kernel<64, CW, BIG>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+#define NMFMU_FINISHER(KP, PAIRS) \
+    hipLaunchKernelGGL((factor_update_kernel<KP, CW, BIG, PAIRS>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf)
+    if (k <= 8) NMFMU_FINISHER(8, false);
+    else if (k <= 16) NMFMU_FINISHER(16, false);
+    else if (k <= 32) NMFMU_FINISHER(32, false);
+    else if (pf.units) NMFMU_FINISHER(64, true);
+    else NMFMU_FINISHER(64, false);
+#undef NMFMU_FINISHER
 }
 
 hipError_t launch_factor_update(float *X, float *Xt, const float *part, int splits,
                                 const float *Gfull, const float *gin, int nbin, float *gout, int k,
                                 int64_t len, float eps, hipStream_t st, const BlockMap *map,
-                                void *planes, double *dpart)
+                                void *planes, double *dpart, const PairFactor *pairs)
 {
+    const PairFactor pf = pairs ? *pairs : PairFactor{};
+    if (pairs && (k <= 32 || !gout)) return hipErrorInvalidValue;
     u32x4 *pl = wta_uses_planes(k) ? static_cast<u32x4 *>(planes) : nullptr;
     BlockMap bm;
     if (map) bm = *map;
@@ -4063,10 +3700,10 @@ hipError_t launch_factor_update(float *X, float *Xt, const float *part, int spli
     int64_t blocks = gout ? factor_update_blocks(len) : (len + cw - 1) / cw;
     if (blocks > 65535) blocks = 65535;
     const dim3 grid((unsigned)blocks);
-    if (cw == 16) factor_update_dispatch<16, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else if (cw == 32) factor_update_dispatch<32, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else if (k * len < ((int64_t)1 << 29)) factor_update_dispatch<64, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
-    else factor_update_dispatch<64, true>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm);
+    if (cw == 16) factor_update_dispatch<16, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
+    else if (cw == 32) factor_update_dispatch<32, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
+    else if (k * len < ((int64_t)1 << 29)) factor_update_dispatch<64, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
+    else factor_update_dispatch<64, true>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
     return hipGetLastError();
 }
 
@@ -4076,7 +3713,7 @@ hipError_t launch_sum_partials(const float *ppart, int splits, int64_t count, fl
     int64_t b = (count + 255) / 256;
     if (b > 4096) b = 4096;
     hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)b), dim3(256), 0, st, ppart, splits, count, P, accumulate ? 1 : 0,
-                       (int64_t)0, count, 1, static_cast<unsigned *>(nullptr));
+                       (int64_t)0, count);
     return hipGetLastError();
 }
 

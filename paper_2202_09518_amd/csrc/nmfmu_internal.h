@@ -68,26 +68,76 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
 // two: A is read in turn with its transpose (what the last-level cache would have to keep).
 // gtiles (optional): nsets sets of partial Gram tiles for rank k that the first workgroups of
 // the pass add up into gsum (one set).
-// Ranks above 64, all ceil(k / 64) slices of 64 factors in one launch each: pair planes of every slice of X
-// (rows x k; slice z at planes + z * pair_planes_bytes(rows)) scaled by fmax, the k largest magnitudes of X's columns (bits),
-// the pass over A for every slice (aligned A, n % 4 == 0; partials of slice z at ppart + z * splits * 64 * n, packed for that
-// slice's width), and P (k x cols) (+)= the sums over the splits.  The slices of one tile of A run side by side, so A is
-// fetched from HBM about once per product.  launch_factor_max: fmax of X (zero before); clear1, clear2: k words each that
-// launch_split_pairs sets to zero; most: the largest magnitudes of P's columns (zero before).
-size_t pair_planes_bytes(int64_t rows);
-hipError_t launch_factor_max(const float *X, int64_t rows, int k, unsigned *fmax, hipStream_t st);
-hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const unsigned *fmax, void *planes, hipStream_t st,
+// Whether a pass marks A (rows x n) for early eviction; two: A^T is read in turn with it.
+bool stream_a(int64_t rows, int64_t n, bool two = false);
+// ---- pairs of halves ----
+// Planes of a factor (rows x k) in units of 8 rows x 1 column, ld columns per row group (see put_pairs).
+struct PairFactor {
+    void *units;              // pair_units_bytes(rows, ld)
+    unsigned char *exps;      // pair_exps_bytes(rows, ld)
+    unsigned *most;           // ld words; zero before the planes are written
+};
+inline size_t pair_units_bytes(int64_t rows, int64_t ld) { return (size_t)((rows + 7) / 8) * 2 * ld * 16; }
+inline size_t pair_exps_bytes(int64_t rows, int64_t ld) { return (size_t)((rows + 7) / 8) * ld; }
+// X' of a matrix X (rows x cols, contracted over its rows): the same units, cut under one scale per column and kPairBlock
+// rows, whose inverse is inv[(row / kPairBlock) * ld + column]; rows are filled up to whole blocks with zeros.
+constexpr int kPairBlock = 128;
+struct PairMatrix {
+    void *units;              // pair_matrix_units(rows, ld) bytes
+    float *inv;               // pair_matrix_scales(rows, ld) bytes
+    int64_t ld;               // pair_matrix_ld(cols)
+};
+inline int64_t pair_matrix_ld(int64_t cols) { return (cols + 63) / 64 * 64; }
+inline size_t pair_matrix_units(int64_t rows, int64_t ld) { return (size_t)((rows + kPairBlock - 1) / kPairBlock) * kPairBlock * ld * 4; }
+inline size_t pair_matrix_scales(int64_t rows, int64_t ld) { return (size_t)((rows + kPairBlock - 1) / kPairBlock) * ld * 4; }
+// A' and (A^T)' of A (m x n, any alignment) in one reading; clear (optional): words to set to zero on the way.
+hipError_t launch_cut_pairs(const float *A, int64_t m, int64_t n, const PairMatrix &a, const PairMatrix &at, unsigned *clear, int nclear,
+                            hipStream_t st);
+// Planes of X (rows x k, row-major) with ld columns per row group, ld >= k a multiple of 64; clear1, clear2 (optional): k words
+// each to set to zero on the way.
+hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const PairFactor &f, int ld, hipStream_t st,
                               unsigned *clear1 = nullptr, unsigned *clear2 = nullptr);
-hipError_t launch_pair_slices(const float *A, int64_t rows, int64_t n, int k, const void *planes, const unsigned *fmax, float *ppart,
+// One pass: F^T X for slices of `tiles` * 32 factors side by side, slice z with k[z] factors, its operands the z-th along the
+// strides, its partials (splits x k[z] x n) at ppart + z * slice_ppart.
+constexpr int kPairSlices = 16;
+struct PairPass {
+    PairFactor F;
+    int ldf;
+    int64_t slice_units, slice_exps, slice_most;      // from slice to slice: in units of 16 bytes, bytes and words
+    PairMatrix X;
+    float *ppart;
+    int64_t slice_ppart;
+    int64_t rows, n, rps;                             // rps: rows of a split, a multiple of kPairBlock
+    int splits, nslices;
+    short k[kPairSlices];
+    const float *gtiles;                              // optional, as in launch_wta_pass: tile sets to add up,
+    int nsets;
+    float *gsum;
+    int64_t slice_gtiles, slice_gsum;
+    unsigned *clear;                                  // optional: words to set to zero on the way
+    int nclear;
+};
+// tiles: 2 or 4.  stream: X' is marked for early eviction.
+hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream_t st);
+int pair_splits(int64_t rows, int64_t cols, int tiles, int nslices);
+inline int64_t pair_rows_per_split(int64_t rows, int splits)
+{
+    const int64_t blocks = (rows + kPairBlock - 1) / kPairBlock;
+    return (blocks + splits - 1) / splits * kPairBlock;
+}
+// The same product with X itself, cut as it is loaded (16-byte aligned, n % 4 == 0), for all slices of 64 of k factors whose
+// planes have ld columns per row group; partials of slice z at ppart + z * splits * 64 * n.  rps: a multiple of 16.
+hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const PairFactor &f, int ld, float *ppart,
                               int splits, int64_t rps, hipStream_t st);
+// P (k x cols) (+)= the sums over the splits.  width: factors of a slice.
 hipError_t launch_sum_partials_slices(const float *ppart, int splits, int k, int64_t cols, float *P, hipStream_t st,
-                                      bool accumulate = false, unsigned *most = nullptr);
+                                      bool accumulate = false, int width = 64);
 // P[e] (+)= sum_s ppart[s][e], e < count.
 hipError_t launch_sum_partials(const float *ppart, int splits, int64_t count, float *P,
                                hipStream_t st, bool accumulate = false);
-// X[e] <- X[e] * P[e] / (D[e] + eps), X k x len; most (optional): the largest magnitudes of its k rows (zero before).
-hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, int k, int64_t len, hipStream_t st,
-                           unsigned *most = nullptr);
+// X[e] <- X[e] * P[e] / (D[e] + eps), e < count.
+hipError_t launch_mu_apply(float *X, const float *P, const float *D, float eps, int64_t count,
+                           hipStream_t st);
 // X (k x len) <- X * (sum_s part[s]) / (G X + eps), in place.  G is given complete (Gfull, ld k)
 // or as nbin partial tiles (gin).  Optional: Xt (len x k) = new X^T; gout = partial Gram tiles
 // of the new X, one set per block (factor_update_blocks(len) blocks); planes = the bf16 piece
@@ -96,7 +146,8 @@ hipError_t launch_factor_update(float *X, float *Xt, const float *part, int spli
                                 const float *Gfull, const float *gin, int nbin, float *gout, int k,
                                 int64_t len, float eps, hipStream_t st,
                                 const BlockMap *map = nullptr, void *planes = nullptr,
-                                double *dpart = nullptr);
+                                double *dpart = nullptr, const PairFactor *pairs = nullptr);
+// pairs (optional, 33 <= k <= 64, with gout): the pair planes of the new X^T instead, 64 columns per row group.
 // dpart (with an updating launch): per block, the sum of numerator x new value over its entries
 // (factor_update_blocks(len) doubles when gout is given, else one per chunk of 16, 32 or 64 columns).
 // out[0] = sum of squares of X[0 .. count) in double; partial: 4096 doubles of scratch.

@@ -1,0 +1,590 @@
+// Products of two fp32 matrices as pairs of halves on the fp16 matrix cores: more than 32 factors (see nmfmu_device.h for the
+// arithmetic and the formats).
+//   cut_pairs_kernel : A and A^T in the order in which the pass loads them, once per call
+//   split_pairs_kernel : the planes of a factor (factor_update_kernel writes them itself)
+//   pair_pass_kernel : the pass over A' or (A^T)' for slices of 64 or 128 factors
+//   wta_pass_pair_kernel : the same over a matrix that is cut as it is loaded
+#include "nmfmu_device.h"
+
+namespace nmfmu {
+
+// ---------------------------------------------------------------------------
+// A itself as pairs of halves, in the order in which the pass loads its operands, so that nothing is cut more than once a call:
+// A' and (A^T)' (see PairMatrix; a column's largest magnitude in a block of 128 rows goes to 2^14).  A workgroup takes a tile of
+// 128 x 128 of A through LDS and writes it into both.  16384 x 8192: 300 us (a transposed copy alone: 200); 20011 x 9998: 480 (a
+// transposed and an aligned copy: 595).
+// clear: words to set to zero on the way.
+// ---------------------------------------------------------------------------
+constexpr int kCutTile = kPairBlock;
+template <bool VEC>
+__global__ __launch_bounds__(512) void cut_pairs_kernel(const float *__restrict__ A, int64_t m, int64_t n, PairMatrix a, PairMatrix at_,
+                                                        unsigned *__restrict__ clear, int nclear)
+{
+    __shared__ float tile[kCutTile][kCutTile + 1];
+    __shared__ unsigned part[4][kCutTile];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0)
+        for (int i = tid; i < nclear; i += 512) clear[i] = 0u;
+    const int64_t tc = (n + kCutTile - 1) / kCutTile;
+    const int64_t br = blockIdx.x / tc, bc = blockIdx.x % tc;
+    const int64_t r0 = br * kCutTile, c0 = bc * kCutTile;
+    if (VEC) {
+        const int x = (tid & 31) * 4, y = tid >> 5;
+        f32x4 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t r = r0 + y + 16 * i;
+            const bool ok = r < m && c0 + x < n;
+            v[i] = *reinterpret_cast<const f32x4 *>(A + (ok ? r * n + c0 + x : 0));
+            if (!ok) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tile[y + 16 * i][x + e] = v[i][e];
+    } else {
+        const int x = tid & 127, y = tid >> 7;
+#pragma unroll
+        for (int b = 0; b < 32; b += 16) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int64_t r = r0 + y + 4 * (b + i);
+                const bool ok = r < m && c0 + x < n;
+                v[i] = A[ok ? r * n + c0 + x : 0];
+                v[i] = ok ? v[i] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) tile[y + 4 * (b + i)][x] = v[i];
+        }
+    }
+    __syncthreads();
+    const int at = tid & 127, quarter = tid >> 7;     // a column (then a row) of the tile and 32 of its entries
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        float v[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = side ? tile[at][32 * quarter + i] : tile[32 * quarter + i][at];
+        unsigned top = 0;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            const unsigned b = __float_as_uint(v[i]) & 0x7fffffffu;
+            top = b > top ? b : top;
+        }
+        part[quarter][at] = top;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) top = part[i][at] > top ? part[i][at] : top;
+        const int e = half_exponent(top);
+        const float sc = power_of_two(14 - e);
+        const PairMatrix &x = side ? at_ : a;
+        const int64_t col = (side ? r0 : c0) + at, ld = x.ld, block = side ? bc : br;
+        if (col < ld) {
+            u32x4 *dst = static_cast<u32x4 *>(x.units) + (block * 16 + 4 * quarter) * 2 * ld + col;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                u32x4 o[2];
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) cut2h(v[8 * g + 2 * pr], v[8 * g + 2 * pr + 1], sc, o, pr);
+                dst[(2 * g) * ld] = o[0];
+                dst[(2 * g + 1) * ld] = o[1];
+            }
+            if (quarter == 0) x.inv[block * ld + col] = power_of_two(e - 14);
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Pair planes of X (rows x k, row-major), see put_pairs; rows beyond `rows` and columns beyond k are zero.  blockIdx.y = 64 columns;
+// a thread takes eight of a block's 32 row groups, so that a column's maximum costs one atomic per block.
+// clear1, clear2 (optional): k words each to set to zero on the way.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void split_pairs_kernel(const float *__restrict__ X, int64_t rows, int k, PairFactor f, int ld,
+                                                          unsigned *__restrict__ clear1, unsigned *__restrict__ clear2)
+{
+    __shared__ unsigned most[4][64];
+    const int cw = threadIdx.x & 63, w = threadIdx.x >> 6, c = 64 * (int)blockIdx.y + cw;
+    if (blockIdx.x == 0 && w == 0 && c < k) {
+        if (clear1) clear1[c] = 0u;
+        if (clear2) clear2[c] = 0u;
+    }
+    unsigned top = 0;
+    for (int i = 0; i < 8; ++i) {
+        const int64_t g = (int64_t)blockIdx.x * 32 + 4 * i + w;
+        if (g * 8 >= rows) break;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = (g * 8 + e < rows && c < k) ? X[(g * 8 + e) * k + c] : 0.f;
+        const unsigned t = put_pairs(x, static_cast<u32x4 *>(f.units) + g * 2 * ld + c, ld, f.exps + g * ld + c);
+        top = t > top ? t : top;
+    }
+    most[w][cw] = top;
+    __syncthreads();
+    if (w == 0 && c < k) {
+#pragma unroll
+        for (int i = 1; i < 4; ++i) top = most[i][cw] > top ? most[i][cw] : top;
+        if (top) atomicMax(f.most + c, top);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The pass on pairs with both operands cut before: P = F^T X for slices of 32 T factors.  Workgroup = 256 columns, wave = 64 of
+// them (two tiles of 32), and all four waves walk the same 16-row steps; the planes of F are staged in LDS for the four, a block
+// of 8 steps at a time, double buffered, and brought to their columns' scales on the way; X' is loaded straight into operand
+// registers, D steps ahead.  No vector work but that and the joins: after a block (128 terms, one scale per column of X) the
+// accumulators join the totals.
+//
+// Microseconds per product, bf16 pieces cut in the pass -> halves cut in the pass -> this: rank 256 on 16384 x 8192 380 -> 270 ->
+// 200 (T = 4: 162 would be the matrix work at the rate of a library product); 64 factors 110 -> 113 -> 98; on 20011 x 10000
+// 183 -> 160 -> 133; on 32768 x 16384 400 -> 365 -> 331 (a bare read: 313 to 338).  One workgroup per compute unit: two, with
+// twice the splits, 111 at 64 factors on 16384 x 8192.  T = 4 at one wave per SIMD (its accumulators and totals fill half
+// of the registers) loads X' once for 128 factors: 200 against 210 to 240 as two slices of 64 each.
+// ---------------------------------------------------------------------------
+template <int T, int D, int OCC, int POLICY, bool DEEP>
+__global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const PairPass a)
+{
+    constexpr int KP = 32 * T, kSteps = kPairBlock / 16;
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    constexpr int kUnits = kSteps * 4 * KP;            // 16-byte units of planes in a block
+    constexpr int kEach = kUnits / 256 / kSteps;       // a thread stages so many per step
+    extern __shared__ u32x4 pst[];                     // two blocks
+    __shared__ int fexp[KP];
+    const int64_t rows = a.rows, n = a.n, ldx = a.X.ld;
+    const int gx = (int)((n + 255) / 256), ldf = a.ldf;
+    const int L = blockIdx.x, within = L >> 3;
+    const int z = within % a.nslices;
+    const int t8 = (within / a.nslices) * 8 + (L & 7);
+    if (t8 >= gx * a.splits) return;
+    const int bx = t8 % gx, by = t8 / gx;
+    const int k = a.k[z];
+    const u32x4 *F = static_cast<const u32x4 *>(a.F.units) + z * a.slice_units;
+    const unsigned char *exps = a.F.exps + z * a.slice_exps;
+    const unsigned *most = a.F.most + z * a.slice_most;
+    float *ppart = a.ppart + z * a.slice_ppart;
+    const u32x4 *X = static_cast<const u32x4 *>(a.X.units);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int jj = lane & 31, half = lane >> 5;
+    if (a.gtiles) sum_tile_sets(a.gtiles + z * a.slice_gtiles, a.nsets, k, a.gsum + z * a.slice_gsum, t8, gx * a.splits);
+    if (L == 0)
+        for (int i = tid; i < a.nclear; i += 256) a.clear[i] = 0u;
+    const int64_t jw = (int64_t)bx * 256 + 64 * w;
+    const int64_t r0 = (int64_t)by * a.rps;
+    const int64_t r1 = (r0 + a.rps < rows) ? r0 + a.rps : rows;
+    if (tid < KP) fexp[tid] = tid < k ? half_exponent(most[tid]) - 14 : 0;     // read after the first barrier
+    // columns past the edge of X' read its last ones, whose sums are not stored
+    unsigned xoff[2];
+    int64_t xcol[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        xcol[q] = jw + 32 * q + jj < ldx ? jw + 32 * q + jj : ldx - 1;
+        xoff[q] = (unsigned)((half * 2 * ldx + xcol[q]) * 16);
+    }
+    const unsigned xpiece = (unsigned)(ldx * 16);
+
+    f32x16 acc[T][2], tot[T][2], sum[T][2];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) tot[t][q] = sum[t][q] = f32x16{0};
+    struct Stage { u32x4 x[2][2]; };
+    Stage xs[D];
+    auto load_x = [&](Stage &s, int64_t ib) {
+        const int64_t i = ib < r1 ? ib : r0;           // past the end: anything that is there
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u32x4 *>(X + (i >> 3) * 2 * ldx), 0, (int)(4 * xpiece), kRsrcFlags);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) s.x[q][p] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff[q] + p * xpiece, 0, POLICY);
+    };
+    // planes of the block of rows from ib on; groups past the last row read as zero
+    const int64_t groups = (rows + 7) >> 3;
+    const int fc = tid & (KP - 1), fg = tid / KP;      // unit e of a thread: row group and piece fg + e * 256 / KP, column fc
+    const int fce = fc < k ? half_exponent(most[fc]) : -112;
+    struct Rsrc { __amdgpu_buffer_rsrc_t u, e; };
+    auto rsrc_f = [&](int64_t ib) {
+        int64_t ng = ib < r1 ? groups - (ib >> 3) : 0;
+        ng = ng < 0 ? 0 : (ng > 2 * kSteps ? 2 * kSteps : ng);
+        const int64_t g = ng ? ib >> 3 : 0;
+        return Rsrc{__builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(F + g * 2 * ldf), 0, ng ? (int)(((ng * 2 - 1) * ldf + KP) * 16) : 0,
+                                                      kRsrcFlags),
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(exps + g * ldf), 0, ng ? (int)((ng - 1) * ldf + KP) : 0,
+                                                      kRsrcFlags)};
+    };
+    struct Units { u32x4 u[kEach]; unsigned e[kEach]; };
+    Units th[3];
+    auto load_f = [&](Units &t, const Rsrc &r, int s) {
+#pragma unroll
+        for (int e = 0; e < kEach; ++e) {
+            const int gp = fg + (s * kEach + e) * (256 / KP);
+            t.u[e] = __builtin_amdgcn_raw_buffer_load_b128(r.u, (unsigned)(gp * ldf + fc) * 16, 0, 0);
+            t.e[e] = __builtin_amdgcn_raw_buffer_load_b8(r.e, (unsigned)((gp >> 1) * ldf + fc), 0, 0);
+        }
+    };
+    auto store_f = [&](const Units &t, u32x4 *dst, int s) {
+#pragma unroll
+        for (int e = 0; e < kEach; ++e) dst[(s * kEach + e) * 256 + tid] = to_column_scale(t.u[e], t.e[e], fce);
+    };
+
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+        load_x(xs[s], r0 + 16 * s);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    {
+        const Rsrc rf = rsrc_f(r0);
+#pragma unroll
+        for (int s = 0; s < kSteps; s += 2) {
+            load_f(th[0], rf, s);
+            load_f(th[1], rf, s + 1);
+            store_f(th[0], pst, s);
+            store_f(th[1], pst, s + 1);
+        }
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int64_t i = r0; i < r1; i += kPairBlock) {
+        const Rsrc rf = rsrc_f(i + kPairBlock);
+        u32x4 *mine = pst + buf * kUnits, *next = pst + (buf ^ 1) * kUnits;
+        float inv[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) inv[q] = a.X.inv[i / kPairBlock * ldx + xcol[q]];
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+            load_f(th[s % 3], rf, s);      // the next block's planes, stored two steps later
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                u32x4 wt[2];
+#pragma unroll
+                for (int pl = 0; pl < 2; ++pl) wt[pl] = mine[((2 * s + half) * 2 + pl) * KP + 32 * t + jj];
+                constexpr int PW[3] = {1, 0, 0}, PA[3] = {0, 1, 0};   // smallest first
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        acc[t][q] = mfma_f16(wt[PW[e]], xs[s % D].x[q][PA[e]], s == 0 && e == 0 ? f32x16{0} : acc[t][q]);
+            }
+            load_x(xs[s % D], i + 16 * (s + D));
+            if (s >= 2) store_f(th[(s - 2) % 3], next, s - 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int s = kSteps - 2; s < kSteps; ++s) store_f(th[s % 3], next, s);
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) tot[t][q][v] = __builtin_fmaf(acc[t][q][v], inv[q], tot[t][q][v]);
+        if (DEEP && ((i - r0) / kPairBlock & 7) == 7) {
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) sum[t][q] += tot[t][q], tot[t][q] = f32x16{0};
+        }
+        __syncthreads();    // the next block's planes are written, this block's are read
+        buf ^= 1;
+    }
+    if (DEEP) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) tot[t][q] += sum[t][q];
+    }
+
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int64_t c = jw + 32 * q + jj;
+        if (c >= n) continue;
+        float *dst = ppart + (int64_t)by * k * n + c;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int f = 32 * t + acc_row(v, half);
+                if (f < k) dst[(int64_t)f * n] = ldexpf(tot[t][q][v], fexp[f]);
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The pass for slices of 64 factors on pairs of halves (aligned A, n % 4 == 0, 64 n < 2^31; pair planes), for X that
+// is not cut before.  Workgroup = 256 columns, wave = 64 of them (lane = 2 consecutive columns), the planes of a
+// group of steps staged in LDS for the four waves, three register stages of A.  12 matrix instructions per 16 rows x 64
+// columns x 64 factors instead of 24.  The accumulators join the totals every second group, after 192 terms.
+// Ranks above 64 were bound by the matrix cores (power) on bf16 pieces; rank 256 on 16384 x 8192: 380 -> 270 us per product
+// (of which loads without the matrix work 210, the matrix work without the loads 220), whole iterations 937 -> 718,
+// error against 64 bits after five iterations 2.4 -> 2.3e-7.
+//
+// Scale of a column of A: a column of the accumulators belongs to a lane pair (l, l + 32), so the scale may change from group to
+// group as long as the accumulators are unscaled when they join the totals (one fused multiply-add each).  The running maximum
+// of a column's magnitudes costs half an instruction per element; if an element would leave the halves' range
+// (2^15), the wave joins what it has to the totals and scales anew: the largest entry seen goes to 2^11, so that entries up to
+// 8 times as large come without another change, and after every join the scale follows the maximum since the last one.
+// ---------------------------------------------------------------------------
+// Several 64-factor slices of a wider factor in one launch: workgroup L of a one-dimensional grid stands for (tile, slice) with
+// the slices of one tile of A (slab x row split) 8 workgroups apart, i.e. on the same XCD at about the same time, so that A
+// comes from HBM once and from that XCD's L2 for the other slices (default cache policy).  Slice z reads columns 64 z .. of
+// the planes and writes ppart + z * slice_ppart; it holds min(64, ktotal - 64 z) factors.
+__global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
+    const float *__restrict__ A, PairFactor F, int ldf, float *__restrict__ ppart, int64_t rows, int64_t n, int k, int64_t rps, int gx,
+    int gy, int nslices, int64_t slice_ppart)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr int KP = 64;
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    constexpr int kSteps = 6;                          // 16-row steps per group of staged planes
+    constexpr int kUnits = kSteps * 2 * 2 * KP;        // 16-byte units of planes in a group
+    constexpr float kMost = 32768.f;
+    __shared__ u32x4 pst[2][kUnits];
+    __shared__ int fexp[KP];
+    const int L = blockIdx.x, within = L >> 3;
+    const int z = within % nslices;
+    const int t8 = (within / nslices) * 8 + (L & 7);
+    if (t8 >= gx * gy) return;
+    const int bx = t8 % gx, by = t8 / gx;
+    const u32x4 *units = static_cast<const u32x4 *>(F.units) + KP * z;
+    const unsigned char *exps = F.exps + KP * z;
+    const unsigned *fmost = F.most + KP * z;
+    ppart += (int64_t)z * slice_ppart;
+    k = (k - 64 * z < 64) ? k - 64 * z : 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int jj = lane & 31, half = lane >> 5;
+    const int64_t jw = (int64_t)bx * 256 + 64 * w;
+    const bool live = jw < n;   // a wave wholly past the edge only helps to stage the planes
+    const int64_t colr = jw + 2 * jj;
+    const int64_t col = colr < n ? colr : 0;   // lanes past the edge read valid data that is never stored
+    const int64_t r0 = (int64_t)by * rps;
+    const int64_t r1 = (r0 + rps < rows) ? r0 + rps : rows;
+    const unsigned rowb = (unsigned)(n * 4);
+    const unsigned loff = (unsigned)(half * 8) * rowb + (unsigned)col * 4;
+    const int64_t ngroups = (rows + 7) >> 3;
+    if (tid < KP) fexp[tid] = tid < k ? half_exponent(fmost[tid]) - 14 : 0;     // read after the first barrier
+    const int fc = tid & 63, fg = tid >> 6;      // unit e of a thread: row group and piece fg + 4 e, column fc
+    const int fce = fc < k ? half_exponent(fmost[fc]) : -112;
+
+    f32x16 acc[2][2], tot[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) acc[t][q] = f32x16{0}, tot[t][q] = f32x16{0};
+    // per column: scale, its inverse, largest magnitude since the last join
+    float sc[2], inv[2], most[2] = {0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) sc[q] = power_of_two(126), inv[q] = power_of_two(-126);
+
+    struct Stage { u32x2 a[8]; };
+    auto load_stage = [&](Stage &s, int64_t ib) {
+        int64_t av = live ? r1 - ib : 0;            // rows of this step inside the split
+        av = av < 0 ? 0 : (av > 16 ? 16 : av);
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(A + (av ? ib : 0) * n), 0, (int)(av * rowb), kRsrcFlags);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b64(ra, loff + r * rowb, 0, 0);
+    };
+    // a third of the planes of the group of rows from ib on: 2 units per thread
+    struct Third { u32x4 u[2]; unsigned e[2]; };
+    auto load_third = [&](Third &p, int64_t ib, int part) {
+        const int64_t g = ib >> 3;
+        int64_t ng = ib < r1 ? ngroups - g : 0;     // 8-row groups of planes that exist
+        ng = ng < 0 ? 0 : (ng > 2 * kSteps ? 2 * kSteps : ng);
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u32x4 *>(units + (ng ? g * 2 * ldf : 0)), 0, ng ? (int)(((ng * 2 - 1) * ldf + KP) * 16) : 0, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t re = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char *>(exps + (ng ? g * ldf : 0)), 0, ng ? (int)((ng - 1) * ldf + KP) : 0, kRsrcFlags);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int gp = fg + 4 * (2 * part + e);
+            p.u[e] = __builtin_amdgcn_raw_buffer_load_b128(rp, (unsigned)(gp * ldf + fc) * 16, 0, 0);
+            p.e[e] = __builtin_amdgcn_raw_buffer_load_b8(re, (unsigned)((gp >> 1) * ldf + fc), 0, 0);
+        }
+    };
+    auto store_third = [&](const Third &p, int buf, int part) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) pst[buf][(2 * part + e) * 256 + tid] = to_column_scale(p.u[e], p.e[e], fce);
+    };
+    // the accumulators join the totals; the scales follow the maxima
+    auto join = [&]() {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    tot[t][q][v] = __builtin_fmaf(acc[t][q][v], inv[q], tot[t][q][v]);
+                    acc[t][q][v] = 0.f;
+                }
+            const float both = fmaxf(most[q], __shfl_xor(most[q], 32));
+            if (both > 0.f) {
+                const int e = half_exponent(__float_as_uint(both));
+                sc[q] = power_of_two(11 - e > 126 ? 126 : 11 - e);
+                inv[q] = power_of_two(11 - e > 126 ? -126 : e - 11);
+            }
+            most[q] = 0.f;
+        }
+    };
+    auto compute = [&](const Stage &c, int buf, int st) {
+        u32x4 wt[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl) wt[t][pl] = pst[buf][((2 * st + half) * 2 + pl) * KP + 32 * t + jj];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) most[q] = fmaxf(most[q], __builtin_fabsf(__uint_as_float(c.a[r][q])));
+        if (__any(most[0] * sc[0] >= kMost || most[1] * sc[1] >= kMost)) join();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            u32x4 at[2];
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr)
+                cut2h(__uint_as_float(c.a[2 * pr][q]), __uint_as_float(c.a[2 * pr + 1][q]), sc[q], at, pr);
+            constexpr int PW[3] = {1, 0, 0}, PA[3] = {0, 1, 0};   // smallest first
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) acc[t][q] = mfma_f16(wt[t][PW[e]], at[PA[e]], acc[t][q]);
+        }
+    };
+    Stage s0, s1, s2;
+    Third th;
+    load_stage(s0, r0);
+    __builtin_amdgcn_sched_barrier(0);   // issue order = age order, also here: the waits in the loop count loads in flight
+    load_stage(s1, r0 + 16);
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+        load_third(th, r0, part);
+        store_third(th, 0, part);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int64_t i = r0; i < r1; i += 16 * kSteps) {
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+            const int64_t ib = i + 32 * part;
+            Stage &x = part == 0 ? s0 : (part == 1 ? s2 : s1);
+            Stage &y = part == 0 ? s1 : (part == 1 ? s0 : s2);
+            Stage &z2 = part == 0 ? s2 : (part == 1 ? s1 : s0);
+            load_third(th, i + 16 * kSteps, part);
+            load_stage(z2, ib + 32);
+            __builtin_amdgcn_sched_barrier(0);
+            if (live && ib < r1) compute(x, buf, 2 * part);
+            __builtin_amdgcn_sched_barrier(0);
+            load_stage(x, ib + 48);
+            __builtin_amdgcn_sched_barrier(0);
+            if (live && ib + 16 < r1) compute(y, buf, 2 * part + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            store_third(th, buf ^ 1, part);
+        }
+        if (buf) join();
+        __syncthreads();    // the next group's planes are written, this group's are read
+        buf ^= 1;
+    }
+    join();
+
+    if (colr < n) {
+        float *dst = ppart + (int64_t)by * k * n + colr;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int c = 32 * t + acc_row(v, half);
+                if (c < k) {
+                    const int e = fexp[c];
+                    *reinterpret_cast<f32x2 *>(dst + (int64_t)c * n) = f32x2{ldexpf(tot[t][0][v], e), ldexpf(tot[t][1][v], e)};
+                }
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Host side launchers
+// ---------------------------------------------------------------------------
+
+hipError_t launch_cut_pairs(const float *A, int64_t m, int64_t n, const PairMatrix &a, const PairMatrix &at, unsigned *clear, int nclear,
+                            hipStream_t st)
+{
+    const int64_t tiles = ((m + kCutTile - 1) / kCutTile) * ((n + kCutTile - 1) / kCutTile);
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    if ((reinterpret_cast<uintptr_t>(A) & 15u) == 0 && (n & 3) == 0)
+        hipLaunchKernelGGL(cut_pairs_kernel<true>, dim3((unsigned)tiles), dim3(512), 0, st, A, m, n, a, at, clear, nclear);
+    else
+        hipLaunchKernelGGL(cut_pairs_kernel<false>, dim3((unsigned)tiles), dim3(512), 0, st, A, m, n, a, at, clear, nclear);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const PairFactor &f, int ld, hipStream_t st, unsigned *clear1,
+                              unsigned *clear2)
+{
+    const int64_t groups = (rows + 7) / 8;
+    hipLaunchKernelGGL(split_pairs_kernel, dim3((unsigned)((groups + 31) / 32), (unsigned)(ld / 64)), dim3(256), 0, st, X, rows, k, f, ld,
+                       clear1, clear2);
+    return hipGetLastError();
+}
+
+hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const PairFactor &f, int ld, float *ppart,
+                              int splits, int64_t rps, hipStream_t st)
+{
+    if (wta_planes_only_width(X, n) != 64 || rps % 16) return hipErrorInvalidValue;
+    const int nslices = (k + 63) / 64;
+    const int gx = (int)((n + 255) / 256), gy = splits;
+    const int64_t tiles8 = ((int64_t)gx * gy + 7) / 8 * 8;
+    hipLaunchKernelGGL(wta_pass_pair_kernel, dim3((unsigned)(tiles8 * nslices)), dim3(64 * kWtaWaves), 0, st, X, f, ld, ppart, rows, n,
+                       k, rps, gx, gy, nslices, (int64_t)splits * 64 * n);
+    return hipGetLastError();
+}
+
+template <int T, int D, int OCC, int POLICY, bool DEEP>
+static hipError_t pair_pass_launch(dim3 grid, hipStream_t st, const PairPass &p)
+{
+    constexpr int kLdsBytes = 2 * (kPairBlock / 16) * 4 * 32 * T * 16;
+    static bool raised = false;      // more dynamic LDS than the default limit: asked for once per process
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&pair_pass_kernel<T, D, OCC, POLICY, DEEP>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    hipLaunchKernelGGL((pair_pass_kernel<T, D, OCC, POLICY, DEEP>), grid, dim3(64 * kWtaWaves), kLdsBytes, st, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream_t st)
+{
+    if (p.rps % kPairBlock || p.nslices < 1 || p.nslices > kPairSlices || (int64_t)(p.splits - 1) * p.rps >= p.rows ||
+        p.X.ld >= ((int64_t)1 << 25) || p.X.ld < p.n)
+        return hipErrorInvalidValue;
+    const int64_t tiles8 = ((p.n + 255) / 256 * p.splits + 7) / 8 * 8;
+    const dim3 grid((unsigned)(tiles8 * p.nslices));
+    if (tiles == 4) return stream ? pair_pass_launch<4, 4, 1, 2, false>(grid, st, p) : pair_pass_launch<4, 4, 1, 0, false>(grid, st, p);
+    if (p.nslices > 1) return stream ? pair_pass_launch<2, 4, 2, 2, false>(grid, st, p) : pair_pass_launch<2, 4, 2, 0, false>(grid, st, p);
+    return stream ? pair_pass_launch<2, 4, 1, 2, true>(grid, st, p) : pair_pass_launch<2, 4, 1, 0, true>(grid, st, p);
+}
+
+// Workgroups side by side: one per compute unit; slices of 64 that share X' two.  The fewest splits that leave the last round nearly full
+// (every split is a partial result written and read again), whole blocks of rows to each.
+int pair_splits(int64_t rows, int64_t cols, int tiles, int nslices)
+{
+    const int64_t blocks = (rows + kPairBlock - 1) / kPairBlock, slabs = (cols + 255) / 256, per = slabs * nslices;
+    const double places = tiles == 4 || nslices == 1 ? 256.0 : 512.0;
+    const int64_t cap = slabs >= 16 ? 32 : 128, most = blocks < cap ? blocks : cap;
+    int64_t best = 1;
+    double full = 0.0;
+    for (int64_t s = 1; s <= most; ++s) {
+        const double rounds = (double)(per * s) / places, use = rounds / (double)(int64_t)(rounds + 0.999999);
+        if (use > full + 1e-9) {
+            full = use;
+            best = s;
+        }
+        if (use >= 0.9) break;
+    }
+    const int64_t each = (blocks + best - 1) / best;
+    return (int)((blocks + each - 1) / each);
+}
+
+}  // namespace nmfmu
