@@ -914,7 +914,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_split64_wide_kerne
 // 25 us at k = 50 on 9998 columns and 12 splits, now 19; 10.5 at k = 20 on 4096, now 6.7; 27 at
 // k = 16 on 512 columns and 128 splits, now 10; 13 at k = 32 on 16384, now 9.6.
 // ---------------------------------------------------------------------------
-template <int KP, int CW, bool BIG, bool PAIRS>
+template <int KP, int CW, bool BIG, int PAIRS>
 __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                                                             const float *__restrict__ part,
                                                             int splits,
@@ -923,8 +923,23 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                                                             float *__restrict__ gout,
                                                             u32x4 *__restrict__ planes,
                                                             double *__restrict__ dpart, int k,
-                                                            int64_t len, float eps, BlockMap bm, PairFactor pf)
+                                                            int64_t len, float eps, BlockMap bm_, FinisherSlices sl)
 {
+    // PAIRS: 1 one factor, 2 blockIdx.y = slice
+    const int z = PAIRS == 2 ? blockIdx.y : 0;
+    PairFactor pf{};
+    if (PAIRS) {
+        X = sl.X[z];
+        Xt = sl.Xt[z];
+        k = sl.k[z];
+        if (part) part += z * sl.part;
+        if (gin) gin += z * sl.gin;
+        gout += z * sl.gout;
+        pf.units = static_cast<u32x4 *>(sl.pairs.units) + z * sl.units;
+        pf.exps = sl.pairs.exps + z * sl.exps;
+        pf.most = sl.pairs.most + (z * kPairCopies + blockIdx.x % kPairCopies) * 64;
+    }
+    const BlockMap &bm = PAIRS ? sl.bm[z] : bm_;
     constexpr int NW = 8, KT = KP / 32 > 0 ? KP / 32 : 1, LD = KP + 4;
     constexpr int NG = 512 / CW, FG = NG < KP ? NG : KP, SPL = NG / FG, NC = KP / FG;
     constexpr int SB = 32 / NC < 16 ? 32 / NC : 16;   // splits per batch
@@ -1045,6 +1060,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
     double dacc = 0.0;   // sum over this thread's entries of numerator x new value (objective monitor)
     __shared__ unsigned most[64];    // of each factor, over this block's chunks (pair planes)
     if (PAIRS && tid < 64) most[tid] = 0u;    // the barriers of the first chunk come before its use
+    unsigned top = 0;
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
         const int64_t j = ch * CW + jl;
         const bool okj = j < len;
@@ -1155,8 +1171,8 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
                 float x[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] = c < k ? Ts[(8 * gl + e) * LDT + c] : 0.f;
-                const unsigned top = put_pairs(x, static_cast<u32x4 *>(pf.units) + grow * 2 * PKP + c, PKP, pf.exps + grow * PKP + c);
-                if (top) atomicMax(&most[c], top);
+                const unsigned t = put_pairs(x, static_cast<u32x4 *>(pf.units) + grow * 2 * PKP + c, PKP, pf.exps + grow * PKP + c);
+                top = t > top ? t : top;
             }
         }
         if (gout && G2) {
@@ -1190,6 +1206,7 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
         }
     }
     if (!gout) return;
+    if (PAIRS && top) atomicMax(&most[tid % 64], top);
     __syncthreads();   // the last chunk's readers of Ts are done: Sm changes hands
     if (PAIRS && tid < k && most[tid]) atomicMax(pf.most + tid, most[tid]);
     // Rows and columns of a tile at factor indices >= k hold whatever LDS held;
@@ -3671,40 +3688,55 @@ int factor_update_blocks(int64_t len)
 template <int CW, bool BIG>
 static void factor_update_dispatch(dim3 grid, hipStream_t st, float *X, float *Xt, const float *part, int splits,
                                    const float *Gfull, const float *gin, int nbin, float *gout, u32x4 *pl,
-                                   double *dpart, int k, int64_t len, float eps, const BlockMap &bm, const PairFactor &pf)
+                                   double *dpart, int k, int64_t len, float eps, const BlockMap &bm, const FinisherSlices &sl)
 {
     const dim3 block(512);
 #define NMFMU_FINISHER(KP, PAIRS) \
-    hipLaunchKernelGGL((factor_update_kernel<KP, CW, BIG, PAIRS>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf)
-    if (k <= 8) NMFMU_FINISHER(8, false);
-    else if (k <= 16) NMFMU_FINISHER(16, false);
-    else if (k <= 32) NMFMU_FINISHER(32, false);
-    else if (pf.units) NMFMU_FINISHER(64, true);
-    else NMFMU_FINISHER(64, false);
+    hipLaunchKernelGGL((factor_update_kernel<KP, CW, BIG, PAIRS>), grid, block, 0, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, sl)
+    if (sl.pairs.units && grid.y > 1) NMFMU_FINISHER(64, 2);
+    else if (sl.pairs.units) NMFMU_FINISHER(64, 1);
+    else if (k <= 8) NMFMU_FINISHER(8, 0);
+    else if (k <= 16) NMFMU_FINISHER(16, 0);
+    else if (k <= 32) NMFMU_FINISHER(32, 0);
+    else NMFMU_FINISHER(64, 0);
 #undef NMFMU_FINISHER
+}
+
+static hipError_t factor_update(float *X, float *Xt, const float *part, int splits, const float *Gfull, const float *gin, int nbin,
+                                float *gout, u32x4 *pl, double *dpart, int k, int64_t len, float eps, hipStream_t st,
+                                const BlockMap &bm, int slices, const FinisherSlices &sl)
+{
+    // Without Gram output there is no reason to cap the grid: one block per chunk.
+    const int cw = factor_update_width(len);
+    int64_t blocks = gout ? factor_update_blocks(len) : (len + cw - 1) / cw;
+    if (blocks > 65535) blocks = 65535;
+    const dim3 grid((unsigned)blocks, (unsigned)slices);
+    if (cw == 16) factor_update_dispatch<16, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, sl);
+    else if (cw == 32) factor_update_dispatch<32, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, sl);
+    else if (k * len < ((int64_t)1 << 29)) factor_update_dispatch<64, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, sl);
+    else factor_update_dispatch<64, true>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, sl);
+    return hipGetLastError();
 }
 
 hipError_t launch_factor_update(float *X, float *Xt, const float *part, int splits,
                                 const float *Gfull, const float *gin, int nbin, float *gout, int k,
                                 int64_t len, float eps, hipStream_t st, const BlockMap *map,
-                                void *planes, double *dpart, const PairFactor *pairs)
+                                void *planes, double *dpart)
 {
-    const PairFactor pf = pairs ? *pairs : PairFactor{};
-    if (pairs && (k <= 32 || !gout)) return hipErrorInvalidValue;
     u32x4 *pl = wta_uses_planes(k) ? static_cast<u32x4 *>(planes) : nullptr;
     BlockMap bm;
     if (map) bm = *map;
     else bm.on = 0;
-    // Without Gram output there is no reason to cap the grid: one block per chunk.
-    const int cw = factor_update_width(len);
-    int64_t blocks = gout ? factor_update_blocks(len) : (len + cw - 1) / cw;
-    if (blocks > 65535) blocks = 65535;
-    const dim3 grid((unsigned)blocks);
-    if (cw == 16) factor_update_dispatch<16, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
-    else if (cw == 32) factor_update_dispatch<32, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
-    else if (k * len < ((int64_t)1 << 29)) factor_update_dispatch<64, false>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
-    else factor_update_dispatch<64, true>(grid, st, X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, bm, pf);
-    return hipGetLastError();
+    return factor_update(X, Xt, part, splits, Gfull, gin, nbin, gout, pl, dpart, k, len, eps, st, bm, 1, FinisherSlices{});
+}
+
+hipError_t launch_pair_update(const FinisherSlices &sl, int slices, const float *part, int splits, const float *gin, float *gout,
+                              int64_t len, float eps, hipStream_t st, double *dpart)
+{
+    int kmax = 0;
+    for (int z = 0; z < slices; ++z) kmax = sl.k[z] > kmax ? sl.k[z] : kmax;
+    if (slices < 1 || slices > kPairGroup || kmax > 64 || !gout || (dpart && slices > 1)) return hipErrorInvalidValue;
+    return factor_update(nullptr, nullptr, part, splits, nullptr, gin, gin ? 1 : 0, gout, nullptr, dpart, kmax, len, eps, st, sl.bm[0], slices, sl);
 }
 
 hipError_t launch_sum_partials(const float *ppart, int splits, int64_t count, float *P,

@@ -94,7 +94,7 @@ __device__ __forceinline__ void cut2h(float x0, float x1, float s, u32x4 (&at)[2
 
 // Pair planes of a factor F (rows x k, contracted over its rows): unit (rows 8 g .. 8 g + 7, piece p, column c) = 16 bytes at
 // (g * 2 + p) * ld + c, cut under a scale of the unit's own, its largest magnitude at 2^14; exps[g * ld + c] = that one's
-// half_exponent + 112.  most[c] = the largest magnitude of the column, as bits, which scales it in the pass: what writes the
+// half_exponent + 112.  most[copy * ld + c] = the largest magnitudes of the column in parts of it, as bits, which scales it in the pass: what writes the
 // planes need not know the other rows.  One unit; the largest magnitude is returned.
 __device__ __forceinline__ unsigned put_pairs(const float (&x)[8], u32x4 *unit, int64_t ld, unsigned char *exps)
 {
@@ -115,10 +115,21 @@ __device__ __forceinline__ unsigned put_pairs(const float (&x)[8], u32x4 *unit, 
     return top;
 }
 
-// A unit brought from its own scale to its column's.
-__device__ __forceinline__ u32x4 to_column_scale(u32x4 unit, unsigned exps, int column_exponent)
+// The exponent of a column's scale.
+__device__ __forceinline__ int column_exponent(const unsigned *__restrict__ most, int ld, int c)
 {
-    const int d = column_exponent + 112 - (int)exps;
+    unsigned m[kPairCopies], top = 0;
+#pragma unroll
+    for (int i = 0; i < kPairCopies; ++i) m[i] = most[i * ld + c];
+#pragma unroll
+    for (int i = 0; i < kPairCopies; ++i) top = m[i] > top ? m[i] : top;
+    return half_exponent(top);
+}
+
+// A unit brought from its own scale to its column's.
+__device__ __forceinline__ u32x4 to_column_scale(u32x4 unit, unsigned exps, int exponent)
+{
+    const int d = exponent + 112 - (int)exps;
     const _Float16 r = (_Float16)power_of_two(-(d > 40 ? 40 : d));
     u32x4 o;
 #pragma unroll

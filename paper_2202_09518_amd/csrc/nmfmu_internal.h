@@ -33,6 +33,16 @@ int wta_splits(int64_t rows, int64_t n, int k);
 int wta_splits_bound(int64_t rows, int64_t n, int k);
 int64_t wta_rows_per_split(int64_t rows, int splits);
 
+// The largest magnitudes of the columns meet in atomics; a block takes one of several copies, the reader the largest: 256
+// blocks on the same 64 words cost 2 us.
+constexpr int kPairCopies = 8;
+// Planes of a factor (rows x k) in units of 8 rows x 1 column, ld columns per row group (see put_pairs).
+struct PairFactor {
+    void *units;              // pair_units_bytes(rows, ld)
+    unsigned char *exps;      // pair_exps_bytes(rows, ld)
+    unsigned *most;           // kPairCopies x ld words; zero before the planes are written
+};
+
 // ---- kernel launchers (all asynchronous on `st`; return hipGetLastError) ----
 
 // G (k x k, ld k) = X^T X for X rows x k (row-major, ld k).
@@ -71,12 +81,7 @@ hipError_t launch_wta_pass(const float *A, int64_t rows, int64_t n, int k, const
 // Whether a pass marks A (rows x n) for early eviction; two: A^T is read in turn with it.
 bool stream_a(int64_t rows, int64_t n, bool two = false);
 // ---- pairs of halves ----
-// Planes of a factor (rows x k) in units of 8 rows x 1 column, ld columns per row group (see put_pairs).
-struct PairFactor {
-    void *units;              // pair_units_bytes(rows, ld)
-    unsigned char *exps;      // pair_exps_bytes(rows, ld)
-    unsigned *most;           // ld words; zero before the planes are written
-};
+// Sizes of a factor's planes:
 inline size_t pair_units_bytes(int64_t rows, int64_t ld) { return (size_t)((rows + 7) / 8) * 2 * ld * 16; }
 inline size_t pair_exps_bytes(int64_t rows, int64_t ld) { return (size_t)((rows + 7) / 8) * ld; }
 // X' of a matrix X (rows x cols, contracted over its rows): the same units, cut under one scale per column and kPairBlock
@@ -93,10 +98,10 @@ inline size_t pair_matrix_scales(int64_t rows, int64_t ld) { return (size_t)((ro
 // A' and (A^T)' of A (m x n, any alignment) in one reading; clear (optional): words to set to zero on the way.
 hipError_t launch_cut_pairs(const float *A, int64_t m, int64_t n, const PairMatrix &a, const PairMatrix &at, unsigned *clear, int nclear,
                             hipStream_t st);
-// Planes of X (rows x k, row-major) with ld columns per row group, ld >= k a multiple of 64; clear1, clear2 (optional): k words
-// each to set to zero on the way.
+// Planes of X (rows x k, row-major) with ld columns per row group, ld >= k a multiple of 64; clear (optional): a like array of maxima to
+// set to zero on the way.
 hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const PairFactor &f, int ld, hipStream_t st,
-                              unsigned *clear1 = nullptr, unsigned *clear2 = nullptr);
+                              unsigned *clear = nullptr);
 // One pass: F^T X for slices of `tiles` * 32 factors side by side, slice z with k[z] factors, its operands the z-th along the
 // strides, its partials (splits x k[z] x n) at ppart + z * slice_ppart.
 constexpr int kPairSlices = 16;
@@ -146,8 +151,26 @@ hipError_t launch_factor_update(float *X, float *Xt, const float *part, int spli
                                 const float *Gfull, const float *gin, int nbin, float *gout, int k,
                                 int64_t len, float eps, hipStream_t st,
                                 const BlockMap *map = nullptr, void *planes = nullptr,
-                                double *dpart = nullptr, const PairFactor *pairs = nullptr);
-// pairs (optional, 33 <= k <= 64, with gout): the pair planes of the new X^T instead, 64 columns per row group.
+                                double *dpart = nullptr);
+// The same for runs on pairs: up to kPairGroup factors side by side, slice z's arrays the z-th along the strides; the pair planes
+// of the new X^T (64 columns per row group) are written, the tile set gin is complete.  part null: only planes and gout of X.
+constexpr int kPairGroup = 4;
+struct FinisherSlices {
+    float *X[kPairGroup], *Xt[kPairGroup];      // Xt: optional
+    int k[kPairGroup];
+    BlockMap bm[kPairGroup];
+    int64_t part, gin, gout, units, exps;       // from slice to slice: floats, floats, floats, units, bytes
+    PairFactor pairs;                           // most: kPairCopies x 64 words a slice
+};
+hipError_t launch_pair_update(const FinisherSlices &sl, int slices, const float *part, int splits, const float *gin, float *gout,
+                              int64_t len, float eps, hipStream_t st, double *dpart = nullptr);
+// Factors of up to 64 runs to (in) or from one slice: run r's W (m x k[r]) and rows `at` .. of Wt (ks x m), its H and the
+// same rows of H of the slice (ks x n).
+struct StackedRuns {
+    float *W[64], *H[64];
+    short k[64], at[64];
+};
+hipError_t launch_stack(const StackedRuns &runs, int count, bool in, float *Wt, float *H, int64_t m, int64_t n, hipStream_t st);
 // dpart (with an updating launch): per block, the sum of numerator x new value over its entries
 // (factor_update_blocks(len) doubles when gout is given, else one per chunk of 16, 32 or 64 columns).
 // out[0] = sum of squares of X[0 .. count) in double; partial: 4096 doubles of scratch.

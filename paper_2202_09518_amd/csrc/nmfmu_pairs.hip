@@ -98,17 +98,15 @@ __global__ __launch_bounds__(512) void cut_pairs_kernel(const float *__restrict_
 // ---------------------------------------------------------------------------
 // Pair planes of X (rows x k, row-major), see put_pairs; rows beyond `rows` and columns beyond k are zero.  blockIdx.y = 64 columns;
 // a thread takes eight of a block's 32 row groups, so that a column's maximum costs one atomic per block.
-// clear1, clear2 (optional): k words each to set to zero on the way.
+// clear (optional): maxima to set to zero on the way.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void split_pairs_kernel(const float *__restrict__ X, int64_t rows, int k, PairFactor f, int ld,
-                                                          unsigned *__restrict__ clear1, unsigned *__restrict__ clear2)
+                                                          unsigned *__restrict__ clear)
 {
     __shared__ unsigned most[4][64];
     const int cw = threadIdx.x & 63, w = threadIdx.x >> 6, c = 64 * (int)blockIdx.y + cw;
-    if (blockIdx.x == 0 && w == 0 && c < k) {
-        if (clear1) clear1[c] = 0u;
-        if (clear2) clear2[c] = 0u;
-    }
+    if (blockIdx.x == 0 && clear)
+        for (int i = w; i < kPairCopies; i += 4) clear[i * ld + c] = 0u;
     unsigned top = 0;
     for (int i = 0; i < 8; ++i) {
         const int64_t g = (int64_t)blockIdx.x * 32 + 4 * i + w;
@@ -124,7 +122,7 @@ __global__ __launch_bounds__(256) void split_pairs_kernel(const float *__restric
     if (w == 0 && c < k) {
 #pragma unroll
         for (int i = 1; i < 4; ++i) top = most[i][cw] > top ? most[i][cw] : top;
-        if (top) atomicMax(f.most + c, top);
+        if (top) atomicMax(f.most + (int)(blockIdx.x % kPairCopies) * ld + c, top);
     }
 }
 
@@ -133,11 +131,12 @@ __global__ __launch_bounds__(256) void split_pairs_kernel(const float *__restric
 // them (two tiles of 32), and all four waves walk the same 16-row steps; the planes of F are staged in LDS for the four, a block
 // of 8 steps at a time, double buffered, and brought to their columns' scales on the way; X' is loaded straight into operand
 // registers, D steps ahead.  No vector work but that and the joins: after a block (128 terms, one scale per column of X) the
-// accumulators join the totals.
+// accumulators join the totals (DEEP: and those a sum after every eighth block: with six splits of 20011 rows in one
+// chain the factors were 3.4e-7 off after 20 iterations, 3.1e-7 on bf16 pieces and twelve splits, 3.0e-7 so).
 //
 // Microseconds per product, bf16 pieces cut in the pass -> halves cut in the pass -> this: rank 256 on 16384 x 8192 380 -> 270 ->
 // 200 (T = 4: 162 would be the matrix work at the rate of a library product); 64 factors 110 -> 113 -> 98; on 20011 x 10000
-// 183 -> 160 -> 133; on 32768 x 16384 400 -> 365 -> 331 (a bare read: 313 to 338).  One workgroup per compute unit: two, with
+// 183 -> 160 -> 133 (148 in a long run, as the clock goes); on 32768 x 16384 400 -> 365 -> 331 (a bare read: 313 to 338).  One workgroup per compute unit: two, with
 // twice the splits, 111 at 64 factors on 16384 x 8192.  T = 4 at one wave per SIMD (its accumulators and totals fill half
 // of the registers) loads X' once for 128 factors: 200 against 210 to 240 as two slices of 64 each.
 // ---------------------------------------------------------------------------
@@ -155,9 +154,12 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     const int L = blockIdx.x, within = L >> 3;
     const int z = within % a.nslices;
     const int t8 = (within / a.nslices) * 8 + (L & 7);
-    if (t8 >= gx * a.splits) return;
-    const int bx = t8 % gx, by = t8 / gx;
     const int k = a.k[z];
+    if (a.gtiles)
+        sum_tile_sets(a.gtiles + z * a.slice_gtiles, a.nsets, k, a.gsum + z * a.slice_gsum, (int)gridDim.x / a.nslices - 1 - t8,
+                      (int)gridDim.x / a.nslices);
+    if (t8 >= gx * a.splits) return;      // on small matrices there are workgroups for the tiles alone
+    const int bx = t8 % gx, by = t8 / gx;
     const u32x4 *F = static_cast<const u32x4 *>(a.F.units) + z * a.slice_units;
     const unsigned char *exps = a.F.exps + z * a.slice_exps;
     const unsigned *most = a.F.most + z * a.slice_most;
@@ -166,13 +168,11 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int jj = lane & 31, half = lane >> 5;
-    if (a.gtiles) sum_tile_sets(a.gtiles + z * a.slice_gtiles, a.nsets, k, a.gsum + z * a.slice_gsum, t8, gx * a.splits);
     if (L == 0)
         for (int i = tid; i < a.nclear; i += 256) a.clear[i] = 0u;
     const int64_t jw = (int64_t)bx * 256 + 64 * w;
     const int64_t r0 = (int64_t)by * a.rps;
     const int64_t r1 = (r0 + a.rps < rows) ? r0 + a.rps : rows;
-    if (tid < KP) fexp[tid] = tid < k ? half_exponent(most[tid]) - 14 : 0;     // read after the first barrier
     // columns past the edge of X' read its last ones, whose sums are not stored
     unsigned xoff[2];
     int64_t xcol[2];
@@ -202,7 +202,8 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     // planes of the block of rows from ib on; groups past the last row read as zero
     const int64_t groups = (rows + 7) >> 3;
     const int fc = tid & (KP - 1), fg = tid / KP;      // unit e of a thread: row group and piece fg + e * 256 / KP, column fc
-    const int fce = fc < k ? half_exponent(most[fc]) : -112;
+    const int fce = fc < k ? column_exponent(most, ldf, fc) : -112;
+    if (tid < KP) fexp[tid] = fce - 14;                // read after the first barrier
     struct Rsrc { __amdgpu_buffer_rsrc_t u, e; };
     auto rsrc_f = [&](int64_t ib) {
         int64_t ng = ib < r1 ? groups - (ib >> 3) : 0;
@@ -235,13 +236,11 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     }
     {
         const Rsrc rf = rsrc_f(r0);
+        Units first[kSteps];               // one trip to memory
 #pragma unroll
-        for (int s = 0; s < kSteps; s += 2) {
-            load_f(th[0], rf, s);
-            load_f(th[1], rf, s + 1);
-            store_f(th[0], pst, s);
-            store_f(th[1], pst, s + 1);
-        }
+        for (int s = 0; s < kSteps; ++s) load_f(first[s], rf, s);
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) store_f(first[s], pst, s);
     }
     __syncthreads();
     int buf = 0;
@@ -363,9 +362,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
     const unsigned rowb = (unsigned)(n * 4);
     const unsigned loff = (unsigned)(half * 8) * rowb + (unsigned)col * 4;
     const int64_t ngroups = (rows + 7) >> 3;
-    if (tid < KP) fexp[tid] = tid < k ? half_exponent(fmost[tid]) - 14 : 0;     // read after the first barrier
     const int fc = tid & 63, fg = tid >> 6;      // unit e of a thread: row group and piece fg + 4 e, column fc
-    const int fce = fc < k ? half_exponent(fmost[fc]) : -112;
+    const int fce = fc < k ? column_exponent(fmost, ldf, fc) : -112;
+    if (tid < KP) fexp[tid] = fce - 14;          // read after the first barrier
 
     f32x16 acc[2][2], tot[2][2];
 #pragma unroll
@@ -503,6 +502,41 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// Factors of stacked runs: blockIdx.y = run; the first wblocks blocks turn 64 rows of its W each through LDS, the others
+// copy its H.  One launch a slice instead of two or three copies a run.
+// ---------------------------------------------------------------------------
+template <bool IN>
+__global__ __launch_bounds__(256) void stack_kernel(const StackedRuns runs, float *__restrict__ Wt, float *__restrict__ Hs, int64_t m,
+                                                    int64_t n, int64_t wblocks)
+{
+    __shared__ float tile[64][65];
+    const int run = blockIdx.y, k = runs.k[run], at = runs.at[run], tid = threadIdx.x;
+    if ((int64_t)blockIdx.x >= wblocks) {
+        float *one = runs.H[run], *all = Hs + at * n;
+        const int64_t count = k * n, step = (int64_t)(gridDim.x - wblocks) * 256;
+        for (int64_t e = ((int64_t)blockIdx.x - wblocks) * 256 + tid; e < count; e += step) {
+            if (IN) all[e] = one[e];
+            else one[e] = all[e];
+        }
+        return;
+    }
+    float *W = runs.W[run];
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    const int rows = m - r0 < 64 ? (int)(m - r0) : 64;
+    if (IN) {
+        for (int e = tid; e < rows * k; e += 256) tile[e % k][e / k] = W[r0 * k + e];
+        __syncthreads();
+        for (int e = tid; e < 64 * k; e += 256)
+            if ((e & 63) < rows) Wt[(at + (e >> 6)) * m + r0 + (e & 63)] = tile[e >> 6][e & 63];
+    } else {
+        for (int e = tid; e < 64 * k; e += 256)
+            if ((e & 63) < rows) tile[e >> 6][e & 63] = Wt[(at + (e >> 6)) * m + r0 + (e & 63)];
+        __syncthreads();
+        for (int e = tid; e < rows * k; e += 256) W[r0 * k + e] = tile[e % k][e / k];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Host side launchers
 // ---------------------------------------------------------------------------
 
@@ -518,12 +552,21 @@ hipError_t launch_cut_pairs(const float *A, int64_t m, int64_t n, const PairMatr
     return hipGetLastError();
 }
 
-hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const PairFactor &f, int ld, hipStream_t st, unsigned *clear1,
-                              unsigned *clear2)
+hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const PairFactor &f, int ld, hipStream_t st, unsigned *clear)
 {
     const int64_t groups = (rows + 7) / 8;
     hipLaunchKernelGGL(split_pairs_kernel, dim3((unsigned)((groups + 31) / 32), (unsigned)(ld / 64)), dim3(256), 0, st, X, rows, k, f, ld,
-                       clear1, clear2);
+                       clear);
+    return hipGetLastError();
+}
+
+hipError_t launch_stack(const StackedRuns &runs, int count, bool in, float *Wt, float *H, int64_t m, int64_t n, hipStream_t st)
+{
+    const int64_t wblocks = (m + 63) / 64, hblocks = (n + 63) / 64;
+    if (wblocks + hblocks > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(wblocks + hblocks), (unsigned)count);
+    if (in) hipLaunchKernelGGL(stack_kernel<true>, grid, dim3(256), 0, st, runs, Wt, H, m, n, wblocks);
+    else hipLaunchKernelGGL(stack_kernel<false>, grid, dim3(256), 0, st, runs, Wt, H, m, n, wblocks);
     return hipGetLastError();
 }
 
@@ -559,10 +602,12 @@ hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream
     if (p.rps % kPairBlock || p.nslices < 1 || p.nslices > kPairSlices || (int64_t)(p.splits - 1) * p.rps >= p.rows ||
         p.X.ld >= ((int64_t)1 << 25) || p.X.ld < p.n)
         return hipErrorInvalidValue;
-    const int64_t tiles8 = ((p.n + 255) / 256 * p.splits + 7) / 8 * 8;
+    int64_t tiles8 = ((p.n + 255) / 256 * p.splits + 7) / 8 * 8;
+    if (p.gtiles && tiles8 < 192) tiles8 += 64;      // a workgroup per 64 entries of the Gram matrix
     const dim3 grid((unsigned)(tiles8 * p.nslices));
     if (tiles == 4) return stream ? pair_pass_launch<4, 4, 1, 2, false>(grid, st, p) : pair_pass_launch<4, 4, 1, 0, false>(grid, st, p);
-    if (p.nslices > 1) return stream ? pair_pass_launch<2, 4, 2, 2, false>(grid, st, p) : pair_pass_launch<2, 4, 2, 0, false>(grid, st, p);
+    // slices that share X' keep it in the L2 for each other: three on 16384 x 8192 160 us per product, 230 marked for early eviction
+    if (p.nslices > 1) return pair_pass_launch<2, 2, 2, 0, false>(grid, st, p);
     return stream ? pair_pass_launch<2, 4, 1, 2, true>(grid, st, p) : pair_pass_launch<2, 4, 1, 0, true>(grid, st, p);
 }
 

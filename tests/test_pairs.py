@@ -52,7 +52,8 @@ def columns_off(got, want):
 # odd sizes, ranks that fill one slice and part of the next; sizes at which the other paths of a product run
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["plain", "columns", "rows", "growing", "late", "spikes"])
-@pytest.mark.parametrize("m,n,k", [(1300, 516, 68), (517, 1028, 132), (700, 333, 96)])
+@pytest.mark.parametrize("m,n,k", [(1300, 516, 68), (517, 1028, 132), (700, 333, 96), (900, 1030, 200),      # above 64
+                                   (1300, 2516, 33), (517, 1029, 64), (128, 257, 40), (1, 300, 50)])          # up to 64
 def test_scales_follow_the_data(m, n, k, kind):
     import torch
 
@@ -102,3 +103,95 @@ def test_infinities_and_nan_reach_their_columns_only(bad):
     Hd = Hd.cpu().numpy()
     assert not np.isfinite(Hd[:, 17]).any()
     assert np.isfinite(np.delete(Hd, 17, axis=1)).all()
+
+
+def iterate(A, W, H, iters):
+    for _ in range(iters):
+        W, H = reference(A, W, H)
+    return W, H
+
+
+def off(got, want):
+    return np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want)
+
+
+# Ranks above 64 without room for A' and (A^T)': A is cut as it is loaded.
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(1300, 516, 68), (517, 1028, 132), (400, 700, 193)])
+def test_without_room_for_a_second_layout(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(11)
+    A, W, H = (r.random(s, dtype=np.float32) for s in ((m, n), (m, k), (k, n)))
+    size = nmf.nmf_mu_workspace_bytes(5, m, n, 0, k, 0)
+    runs = []
+    for short in (0, 2 * m * n):        # half a matrix less than the second layout takes
+        ws = torch.empty(size - short, dtype=torch.uint8, device="cuda")
+        Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda()
+        nmf.nmf_mu_set_workspace(ws)
+        try:
+            nmf.nmf_mu_dense(torch.from_numpy(A).cuda(), m, n, k, Wd, Hd, 2, EPS)
+            torch.cuda.synchronize()
+        finally:
+            nmf.nmf_mu_set_workspace(None)
+        runs.append((Wd.cpu().numpy(), Hd.cpu().numpy()))
+    Wr, Hr = iterate(A, W, H, 2)
+    for w, h in runs:
+        assert off(w, Wr) < 2e-6 and off(h, Hr) < 2e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(1500, 700, 40), (4001, 1003, 64), (300, 129, 33), (9000, 260, 50)])
+def test_a_run_cut_in_two_has_the_same_bits(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    A, W, H = (torch.rand(s, generator=g, device="cuda") for s in ((m, n), (m, k), (k, n)))
+    runs = []
+    for parts in ((5,), (2, 3)):
+        w, h = W.clone(), H.clone()
+        for it in parts:
+            nmf.nmf_mu_dense(A, m, n, k, w, h, it, EPS)
+        runs.append((w, h))
+    assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
+
+
+# Ensembles: stacks side by side (up to four in a launch, then the rest on the same A), single runs among them, two matrices.
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,ranks", [(700, 515, [[2, 3, 4, 30], [40, 50, 20]]), (1025, 300, [[64, 64, 33, 60, 50, 7], [1, 63, 5]]),
+                                       (130, 2049, [[33], [12, 11, 30]])])
+def test_stacks_side_by_side(m, n, ranks):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(5)
+    As, ks, Ws, Hs, want = [], [], [], [], []
+    for group in ranks:
+        A = (r.random((m, 6)) @ r.random((6, n))).astype(np.float32)
+        Ad = torch.from_numpy(A).cuda()
+        for k in group:
+            W, H = r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+            As.append(Ad), ks.append(k), Ws.append(torch.from_numpy(W).cuda()), Hs.append(torch.from_numpy(H).cuda())
+            want.append(iterate(A, W, H, 2))
+    nmf.nmf_mu_dense_batched(len(ks), As, m, n, ks, Ws, Hs, 2, EPS)
+    for W, H, (Wr, Hr) in zip(Ws, Hs, want):
+        # two updates of each factor, sums of one sign: a few roundings of 2^-24 per sum
+        assert off(W.cpu().numpy(), Wr) < 2e-6 and off(H.cpu().numpy(), Hr) < 2e-6
+
+
+# The arrival counters at the head of the workspace are other kernels': a run above 64 factors leaves them at zero.
+@pytest.mark.gpu
+def test_counters_are_left_alone():
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    A = torch.rand((600, 260), device="cuda")
+    W, H = torch.rand((600, 68), device="cuda"), torch.rand((68, 260), device="cuda")
+    nmf.nmf_mu_dense(A, 600, 260, 68, W, H, 1, EPS)
+    X, G = torch.rand((4099, 40), device="cuda"), torch.empty((40, 40), device="cuda")
+    nmf.nmf_gram_w(X, 4099, 40, G)
+    want = X.double().t().contiguous() @ X.double()
+    assert ((G.double() - want).norm() / want.norm()).item() < 1e-6
