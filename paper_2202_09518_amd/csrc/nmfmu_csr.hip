@@ -19,11 +19,13 @@
 // handled by a group of LPR lanes, LPR = smallest power of two >= k (at least
 // 4): lane c of the group owns factor index c.  A wave holds 64 / LPR rows, so
 // short rows are packed several to a wave.  The group reads its row's entries
-// LPR at a time with coalesced loads and hands them round with lane shuffles.
+// LPR at a time with coalesced loads and hands them round (from_lane for 5 to 16 factors, else lane shuffles).
 // From 64 entries per row on average a whole wave takes one row at a time.
 // Rows are dealt to wavefronts in contiguous ranges of equal work (stored
 // entries plus a per-row cost), and rows too long for one wave are split
 // over a whole workgroup.
+#include <utility>
+
 #include <hipcub/hipcub.hpp>
 
 #include "nmfmu_internal.h"
@@ -39,6 +41,45 @@ template <int LPR>
 __device__ __forceinline__ int group_bcast(int v, int src)
 {
     return __shfl(v, src, LPR);
+}
+
+// f(0), f(1), ... f(N - 1) with constant arguments.
+template <int... I, class F>
+__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F f) { for_each_index(std::make_integer_sequence<int, N>{}, f); }
+
+// The value of lane SRC of a group of 8 or 16 lanes, in all of its lanes, by data-parallel primitives of the vector unit:
+// a shuffle goes through the LDS unit, and with two for every entry and one for every factor of the update that unit was what the
+// launches on small tables waited for.  All lanes of the wave have to be active.  (Groups of 4: the registers spill, 0.94x.)
+constexpr bool by_lane(int lpr) { return lpr == 8 || lpr == 16; }
+template <int LPR, int SRC>
+__device__ __forceinline__ int from_lane(int v)
+{
+    constexpr int kRowLane = 0x150;      // row_newbcast: a lane of every row of 16
+    if constexpr (LPR == 16) return __builtin_amdgcn_mov_dpp(v, kRowLane + SRC, 0xf, 0xf, true);
+    else {
+        static_assert(LPR == 8, "groups within a row of 16 lanes");
+        const int low = __builtin_amdgcn_mov_dpp(v, kRowLane + SRC, 0xf, 0xf, true);
+        return __builtin_amdgcn_update_dpp(low, v, kRowLane + 8 + SRC, 0xf, 0xc, false);
+    }
+}
+template <int LPR, int SRC>
+__device__ __forceinline__ float from_lane(float v) { return __int_as_float(from_lane<LPR, SRC>(__float_as_int(v))); }
+
+// den[c] as below, from column c of G in registers (zero beyond k, as x is).
+template <int LPR>
+__device__ __forceinline__ float row_times_column(float x, const float (&g)[LPR])
+{
+    float d0 = 0.f, d1 = 0.f;
+    unrolled<LPR / 2>([&](auto i) {
+        d0 += from_lane<LPR, 2 * i>(x) * g[2 * i];
+        d1 += from_lane<LPR, 2 * i + 1>(x) * g[2 * i + 1];
+    });
+    return d0 + d1;
 }
 
 // den[c] = sum_d x[d] * G[d][c] for the row whose element c this lane holds.
@@ -130,6 +171,23 @@ __device__ __forceinline__ float gather_entries(const float *__restrict__ T, int
                                                 int cnt, float acc)
 {
     constexpr int UNR = (LPR < 8) ? LPR : 8;
+    if constexpr (by_lane(LPR)) {
+        auto some = [&](auto t0) {
+            float a[UNR], h[UNR];
+            unrolled<UNR>([&](auto u) {
+                const int o = from_lane<LPR, t0 + u>(off);
+                a[u] = from_lane<LPR, t0 + u>(val);
+                if (NARROW) h[u] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(T) + (unsigned)(o + cc) * 4u);
+                else h[u] = T[(int64_t)o * ldt + cc];
+            });
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) acc += a[u] * h[u];
+        };
+        if (__any(cnt > 0)) some(std::integral_constant<int, 0>{});
+        if constexpr (LPR > UNR)
+            if (__any(cnt > UNR)) some(std::integral_constant<int, UNR>{});
+        return acc;
+    }
     for (int t0 = 0; __any(t0 < cnt); t0 += UNR) {
         float a[UNR], h[UNR];
 #pragma unroll
@@ -177,7 +235,9 @@ __device__ __forceinline__ float gather_chunk(const int32_t *__restrict__ colidx
 // L2 or memory each; so G (one entry or a few per thread) and the row of X are requested before
 // the entries and waited for after them, and the next step's entries are requested before the
 // current ones are gathered.  65536 x 16384, 1.07 million entries, k = 12: 23 and 35 us for the two updates
-// with a launch of 4.5 for the long rows each, now 21 and 18.6 with the long rows in the same launch.
+// with a launch of 4.5 for the long rows each, 21 and 18.6 with the long rows in the same launch, and 16.5 and 14.6
+// since from 5 to 16 factors nothing goes through the LDS unit (from_lane; G by columns in registers).  Tried there: half or a quarter
+// as many waves with the next rows' pointers and entries on their way (no faster), 16 gathered rows in flight (slower).
 // ldx, ldt: row lengths of W and of the table (at least k, see csr_row_length).
 // accumulate != 0: no update; the gathered sums are added to W instead (the
 // numerator of an update collected over several row batches of the matrix; GH unused).
@@ -201,17 +261,23 @@ __global__ __launch_bounds__(256, LPR == 64 ? 6 : 8) void aht_csr_kernel(const i
                                                       int ldx, int ldt)
 {
     constexpr int LDG = LPR + 1, RPW = 64 / LPR, NG = 256 / LPR, EPG = (LPR * LPR + 255) / 256;
-    __shared__ float Gs[LPR * LDG];
+    constexpr bool REG = by_lane(LPR);      // G: a column of it in each lane's registers, else all of it in LDS
+    __shared__ float Gs[REG ? 1 : LPR * LDG];
     __shared__ float part_acc[NG][LPR];
     __shared__ double dsum[4];
     const int lane = threadIdx.x & 63;
     const int c = lane % LPR, cc = (c < k) ? c : 0;
     double dacc = 0.0;
     // G: requested first, put into LDS (one barrier) when the first row's sums are there
-    float gq[EPG];
+    float gq[EPG], gc[REG ? LPR : 1];
+    if constexpr (REG) {
 #pragma unroll
-    for (int i = 0; i < EPG; ++i) gq[i] = !accumulate && (int)threadIdx.x + 256 * i < k * k ? GH[threadIdx.x + 256 * i] : 0.f;
-    bool staged = accumulate != 0;      // uniform over a wave; every wave passes the barrier once
+        for (int d = 0; d < LPR; ++d)
+            gc[d] = !accumulate && d < k && c < k ? GH[d * k + c] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < EPG; ++i) gq[i] = !REG && !accumulate && (int)threadIdx.x + 256 * i < k * k ? GH[threadIdx.x + 256 * i] : 0.f;
+    bool staged = REG || accumulate != 0;      // uniform over a wave; every wave passes the barrier once
     auto stage = [&]() {
         if (staged) return;
         staged = true;
@@ -231,7 +297,9 @@ __global__ __launch_bounds__(256, LPR == 64 ? 6 : 8) void aht_csr_kernel(const i
             if (mine) W[row * ldx + c] = w + acc;
         } else {
             stage();
-            const float den = row_times_gram<LPR>(w, Gs, LDG, k, c) + eps;
+            float den;
+            if constexpr (REG) den = row_times_column<LPR>(w, gc) + eps;
+            else den = row_times_gram<LPR>(w, Gs, LDG, k, c) + eps;
             if (mine) {
                 const float wn = w * acc / den;
                 W[row * ldx + c] = wn;
@@ -264,13 +332,16 @@ __global__ __launch_bounds__(256, LPR == 64 ? 6 : 8) void aht_csr_kernel(const i
             const int64_t row = SPLIT ? base : base + lane / LPR;
             bool valid = row < r_hi;
             // row pointers outside [0, nnz] (malformed input) are pulled into the arrays
-            const int64_t p0 = valid ? rowptr[row] : 0, p1 = valid ? rowptr[row + 1] : 0;
+            // rows past the range read its last one's and drop it: loads without branches
+            const int64_t at = valid ? row : r_hi - 1;
+            const int64_t p0 = rowptr[at], p1 = rowptr[at + 1];
+            const float wv = W[at * ldx + cc];
             int64_t e = min(max(p0, (int64_t)0), nnz), e1 = min(max(p1, (int64_t)0), nnz);
-            if (valid && p1 - p0 > kLongRow) {       // left to the long-row workgroups
+            if (!valid || p1 - p0 > kLongRow) {       // long rows are left to the long-row workgroups
                 valid = false;
                 e1 = e;
             }
-            const float w = (valid && c < k) ? W[row * ldx + c] : 0.f;
+            const float w = (valid && c < k) ? wv : 0.f;
             float acc = 0.f;
             constexpr int CHUNK = SPLIT ? 64 : LPR;      // entries of a row per step
             if (SPLIT) e += lane - c;                    // this group's share of the first step
