@@ -1087,7 +1087,37 @@ __global__ __launch_bounds__(512) void factor_update_kernel(float *X, float *Xt,
             for (int ci = 0; ci < NC; ++ci) Ps[((sp - 1) * KP + fc + FG * ci) * CW + jl] = p[ci];
         }
         __syncthreads();   // Gs and the chunk's old values are complete, Ts is free
-        if (sp == 0) {
+        if (PAIRS) {
+            // denominators on 16 x 16 x 4 instructions, G being symmetric: 16 x 16 tiles of G X dealt to the waves, four chains of
+            // 16 terms each, left in Ts where the thread of an entry finds it
+            if (part) {
+                const int l16 = lane & 15, quad = lane >> 4;
+                for (int t = w; t < KP / 16 * (CW / 16); t += NW) {
+                    const int f0 = t % (KP / 16) * 16, j0 = t / (KP / 16) * 16;
+                    f32x4 d[4];
+#pragma unroll
+                    for (int i = 0; i < KP / 4; ++i)
+                        d[i % 4] = __builtin_amdgcn_mfma_f32_16x16x4f32(Gs[(4 * i + quad) * LD + f0 + l16], Xs[(4 * i + quad) * CW + j0 + l16],
+                                                                        i < 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : d[i % 4], 0, 0, 0);
+                    const f32x4 den = (d[0] + d[1]) + (d[2] + d[3]);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Ts[(j0 + l16) * LDT + f0 + 4 * quad + v] = den[v];
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int ci = 0; ci < NC; ++ci) {
+                const int c = fc + FG * ci;
+                if (c >= k) continue;
+                float nv = okj ? xo[ci] : 0.f;      // Gram-only: as it is
+                if (part && okj) {
+                    nv = xo[ci] * p[ci] / (Ts[jl * LDT + c] + eps);
+                    X[(int64_t)c * len + j] = nv;
+                    dacc += (double)p[ci] * (double)nv;
+                }
+                Ts[jl * LDT + c] = nv;   // columns past the end contribute zeros
+            }
+        } else if (sp == 0) {
             // denominators: 16 old values of the column at a time against all of the thread's rows of G
             float den[NC][4];
 #pragma unroll
