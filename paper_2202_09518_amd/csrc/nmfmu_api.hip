@@ -884,6 +884,12 @@ struct Sliced {
     unsigned *most;   // the largest magnitudes of the columns of F
 };
 
+// Partials of a product that are not added up: slices of 64 factors, `splits` each.
+struct Partials {
+    const float *at;
+    int splits;
+};
+
 // The pair planes of F in e.planes.
 PairFactor sliced_factor(const Sliced &e, int64_t rows, int ld)
 {
@@ -924,9 +930,9 @@ hipError_t sliced_split(const Sliced &e, const float *F, int64_t rows, int k, hi
     return rc != hipSuccess ? rc : launch_split_pairs(F, rows, k, sliced_factor(e, rows, ld), ld, st);
 }
 
-// split: the planes do not hold F yet.
+// split: the planes do not hold F yet.  keep: the partials are left as they are (where they are complete they are in out).
 int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float *X, int64_t cols,
-               float *out, bool accumulate, hipStream_t st, bool split = true)
+               float *out, bool accumulate, hipStream_t st, bool split = true, Partials *keep = nullptr)
 {
     // factor columns per pass: the widest the pass kernels take from planes alone for this X
     // (the slices of F are not contiguous, so the kernel that reads the factor itself is out)
@@ -939,9 +945,11 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
         if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems) return fail(NMF_EHIP, "internal: sliced scratch too small%s");
         if (split) NMF_HIP(sliced_split(e, F, rows, k, st));
         NMF_HIP(launch_pair_slices(X, rows, cols, k, sliced_factor(e, rows, sliced_ld(k)), sliced_ld(k), e.ppart, splits, rps, st));
-        NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate));
+        if (keep) *keep = Partials{e.ppart, splits};
+        else NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate));
         return NMF_OK;
     }
+    if (keep) *keep = Partials{out, 1};
     if ((size_t)splits * kSlice * (size_t)cols > e.ppart_elems || planes_bytes(rows) > e.planes_cap)
         return fail(NMF_EHIP, "internal: sliced scratch too small%s");
     for (int c0 = 0; c0 < k; c0 += kSlice) {
@@ -953,18 +961,27 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
     return NMF_OK;
 }
 
+// Factors of a slice of a pass over A'.  128 (one wave per SIMD) where such slices have more than 64 factors each and every compute
+// unit gets some four blocks of 128 rows x 256 columns of the work: 16384 x 8192, k = 128 346 us per iteration in one slice, 377 in
+// two of 64, k = 256 543 and 556, k = 384 825 and 823; below that the latency of a block decides (2000 x 1000, k = 68: 17.7 us
+// per product in one slice of 128, 13 in two of 64).  A last slice of 64 behind those of 128 is a launch of its own
+// that reads A' again: k = 130 on 32768 x 4096 733 us per iteration, 639 in slices of 64, k = 320 774 and 702.
+int sliced_width(int64_t rows, int64_t cols, int k)
+{
+    const int64_t blocks = (rows + kPairBlock - 1) / kPairBlock * ((cols + 255) / 256) * ((k + 127) / 128);
+    return blocks >= 1024 && (k - 1) % 128 >= 64 ? 128 : 64;
+}
+
+size_t sliced_pass_elems(int64_t rows, int64_t cols, int k)
+{
+    const int width = sliced_width(rows, cols, k), slices = (k + width - 1) / width;
+    return (size_t)pair_splits(rows, cols, width / 32, slices) * slices * width * (size_t)cols;
+}
+
 // Upper bound on splits x 64 x cols over every X with at most `cols` rows and columns (64-factor slices;
 // 32-factor slices have 128-column slabs and half the factors).  wta_splits keeps splits x slabs <= 512 with
 // cols <= 256 slabs, or two splits on fewer than 384 slabs, or one: splits x cols <= 131072 + cols.  And more than
 // 32 splits need fewer than 16 slabs and 256 rows each: at most cols / 256 splits of 15 x 256 columns.
-// Partials of the passes over A': slices of 128 and one of 64.
-size_t sliced_pass_elems(int64_t rows, int64_t cols, int k)
-{
-    const int wide = (k + 63) / 128;
-    const size_t a = wide ? (size_t)pair_splits(rows, cols, 4, wide) * wide * 128 : 0, b = (size_t)pair_splits(rows, cols, 2, 1) * 64;
-    return (a > b ? a : b) * (size_t)cols;
-}
-
 size_t sliced_ppart_elems(int64_t cols)
 {
     const int64_t a = 32 * cols, b = 131072 + cols;
@@ -975,8 +992,10 @@ size_t sliced_ppart_elems(int64_t cols)
 struct SlicedDense {
     Sliced e;
     float *At, *Wt, *Ht, *num, *den, *g;
-    bool pairs;             // A' and (A^T)' instead of At
+    bool pairs;             // A' and (A^T)' instead of At; no num, but
     PairMatrix pa, pt;
+    float *pass;            // partials of a pass over A' or (A^T)'
+    unsigned *most_g;       // maxima of the planes of a Gram matrix
 };
 
 
@@ -999,12 +1018,11 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, bool pairs
     p.e.planes = cv.take<char>(p.e.planes_cap);
     // X is one of A (m x n), W (m x k), H (k x n) or a transpose of those
     p.e.ppart_elems = sliced_ppart_elems(all) * nslices;
+    p.e.ppart = cv.take<float>(p.e.ppart_elems);
     if ((p.pairs = pairs)) {
         const size_t p1 = sliced_pass_elems(m, n, k), p2 = sliced_pass_elems(n, m, k);
-        p.e.ppart_elems = max3(p.e.ppart_elems, p1, p2);
-    }
-    p.e.ppart = cv.take<float>(p.e.ppart_elems);
-    if (pairs) {
+        p.pass = cv.take<float>(p1 > p2 ? p1 : p2);
+        p.most_g = cv.take<unsigned>((size_t)sliced_ld(k) * kPairCopies);
         p.pa = carve_pair_matrix(cv, m, n);
         p.pt = carve_pair_matrix(cv, n, m);
     } else {
@@ -1012,7 +1030,7 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, bool pairs
     }
     p.Wt = cv.take<float>((size_t)k * m);
     p.Ht = cv.take<float>((size_t)n * k);
-    p.num = cv.take<float>((size_t)k * big);
+    p.num = cv.take<float>(pairs ? 0 : (size_t)k * big);
     p.den = cv.take<float>((size_t)k * big);
     p.g = cv.take<float>((size_t)k * k);
     if (bytes) *bytes = cv.off;
@@ -1028,47 +1046,72 @@ size_t sliced_dense_bytes(int64_t m, int64_t n, int k, bool pairs)
     return b;
 }
 
-// P (k x cols) = F^T X over X' = x, the planes of F in e.planes: slices of 128 factors, and one of 64 for up to 64 that are left.
-int sliced_pass(const Sliced &e, int64_t rows, int k, const PairMatrix &x, int64_t cols, bool stream, float *out, hipStream_t st)
+// F^T X over X' = x, the planes of F in e.planes.  The partials are left where `u` says.
+int sliced_pass(const SlicedDense &p, int64_t rows, int k, const PairMatrix &x, int64_t cols, bool stream, SlicedUpdate *u,
+                hipStream_t st)
 {
-    const int ld = sliced_ld(k);
-    for (int c0 = 0; c0 < k;) {
-        const bool wide = k - c0 > 64;
-        const int width = wide ? 128 : 64, tiles = wide ? 4 : 2, kc = wide ? (k - c0 > 64 + (k - c0) / 128 * 128 ? k - c0 : (k - c0) / 128 * 128) : k - c0;
-        PairPass a{};
-        a.F = sliced_factor(e, rows, ld);
-        a.F.units = static_cast<char *>(a.F.units) + (size_t)c0 * 16;
-        a.F.exps += c0;
-        a.F.most += c0;
-        a.ldf = ld;
-        a.slice_units = a.slice_exps = a.slice_most = width;
-        a.X = x;
-        a.ppart = e.ppart;
-        a.rows = rows;
-        a.n = cols;
-        a.nslices = (kc + width - 1) / width;
-        for (int z = 0; z < a.nslices; ++z) a.k[z] = (short)(kc - width * z < width ? kc - width * z : width);
-        a.splits = pair_splits(rows, cols, tiles, a.nslices);
-        a.rps = pair_rows_per_split(rows, a.splits);
-        a.slice_ppart = (int64_t)a.splits * width * cols;
-        NMF_HIP(launch_pair_pass(a, tiles, stream, st));
-        NMF_HIP(launch_sum_partials_slices(e.ppart, a.splits, kc, cols, out + (int64_t)c0 * cols, st, false, width));
-        c0 += kc;
-    }
+    static_assert(kPairSlices * 64 >= NMF_MU_MAX_K_SLICED, "one launch for all slices");
+    const int width = sliced_width(rows, cols, k);
+    PairPass a{};
+    a.ldf = sliced_ld(k);
+    a.F = sliced_factor(p.e, rows, a.ldf);
+    a.slice_units = a.slice_exps = a.slice_most = width;
+    a.X = x;
+    a.rows = rows;
+    a.n = cols;
+    a.nslices = (k + width - 1) / width;
+    for (int z = 0; z < a.nslices; ++z) a.k[z] = (short)(k - width * z < width ? k - width * z : width);
+    a.splits = pair_splits(rows, cols, width / 32, a.nslices);
+    a.rps = pair_rows_per_split(rows, a.splits);
+    a.ppart = p.pass;
+    a.slice_ppart = (int64_t)a.splits * width * cols;
+    NMF_HIP(launch_pair_pass(a, width / 32, stream, st));
+    u->k = k;
+    u->num = p.pass;
+    u->width = width;
+    u->snum = a.splits;
     return NMF_OK;
 }
 
-// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps), F rows x k, X rows x cols (x: X').
-int sliced_update(const SlicedDense &p, const float *F, int64_t rows, int k, const float *X, const PairMatrix &x, int64_t cols, float *Y,
-                  float eps, bool stream, hipStream_t st)
+// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps) and Yt its transpose, F rows x k with its planes in e.planes, X' = x; the planes of Yt
+// take their place.
+int sliced_pairs_update(const SlicedDense &p, const float *F, int64_t rows, int k, const PairMatrix &x, int64_t cols, float *Y, float *Yt,
+                        float eps, bool stream, hipStream_t st)
 {
-    if (p.pairs) {
-        NMF_HIP(sliced_split(p.e, F, rows, k, st));
-        if (int rc = sliced_pass(p.e, rows, k, x, cols, stream, p.num, st)) return rc;
-    } else if (int rc = sliced_ftx(p.e, F, rows, k, X, cols, p.num, false, st)) {
-        return rc;
+    const int ld = sliced_ld(k);
+    SlicedUpdate u{};
+    if (int rc = sliced_pass(p, rows, k, x, cols, stream, &u, st)) return rc;
+    if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, false)) return rc;
+    Partials den{};
+    if (sliced_pairs(Y, cols, k)) {
+        Sliced g = p.e;
+        g.most = p.most_g;
+        NMF_HIP(launch_split_pairs(p.g, k, k, sliced_factor(g, k, ld), ld, st, p.e.most));      // and the maxima of Yt to zero
+        if (int rc = sliced_ftx(g, p.g, k, k, Y, cols, p.den, false, st, false, &den)) return rc;
+    } else {
+        if (int rc = sliced_ftx(p.e, p.g, k, k, Y, cols, p.den, false, st, true, &den)) return rc;
+        NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.e.most), ld * kPairCopies, 0.f, st));
     }
-    if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, !p.pairs && !sliced_pairs(X, cols, k))) return rc;
+    u.X = Y;
+    u.Xt = Yt;
+    u.den = den.at;
+    u.sden = den.splits;
+    u.len = cols;
+    u.eps = eps;
+    u.F = sliced_factor(p.e, cols, ld);
+    u.ld = ld;
+    u.clear = p.most_g;
+    u.nclear = ld * kPairCopies;
+    NMF_HIP(launch_sliced_update(u, st));
+    return NMF_OK;
+}
+
+// The same without a second layout: Y <- Y * (F^T X) / ((F^T F) Y + eps), X rows x cols.
+int sliced_update(const SlicedDense &p, const float *F, int64_t rows, int k, const float *X, int64_t cols, float *Y, float eps,
+                  hipStream_t st)
+{
+    if (int rc = sliced_ftx(p.e, F, rows, k, X, cols, p.num, false, st)) return rc;
+    if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, !sliced_pairs(X, cols, k))) return rc;
     if (int rc = sliced_ftx(p.e, p.g, k, k, Y, cols, p.den, false, st)) return rc;
     NMF_HIP(launch_mu_apply(Y, p.num, p.den, eps, (int64_t)k * cols, st));
     return NMF_OK;
@@ -1077,16 +1120,27 @@ int sliced_update(const SlicedDense &p, const float *F, int64_t rows, int k, con
 int sliced_dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, int iters,
                       float eps, const SlicedDense &p, hipStream_t st)
 {
-    const bool stream = stream_a(m, n, true);
-    if (p.pairs) NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, nullptr, 0, st));
-    else NMF_HIP(launch_transpose(A, m, n, p.At, st));
+    // H update (Algorithm 3 order): numerator W^T A, denominator (W^T W) H; W update with the new H, on the
+    // transposes: (A H^T)^T = H A^T, (W H H^T)^T = (H H^T) W^T
+    if (p.pairs) {
+        const bool stream = stream_a(m, n, true);
+        const int maxima = sliced_ld(k) * kPairCopies;
+        NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, p.e.most, maxima, st));
+        NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.most_g), maxima, 0.f, st));
+        NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
+        NMF_HIP(launch_split_pairs(W, m, k, sliced_factor(p.e, m, sliced_ld(k)), sliced_ld(k), st));
+        for (int it = 0; it < iters; ++it) {
+            if (int rc = sliced_pairs_update(p, W, m, k, p.pa, n, H, p.Ht, eps, stream, st)) return rc;
+            if (int rc = sliced_pairs_update(p, p.Ht, n, k, p.pt, m, p.Wt, W, eps, stream, st)) return rc;
+        }
+        return NMF_OK;
+    }
+    NMF_HIP(launch_transpose(A, m, n, p.At, st));
     NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
     for (int it = 0; it < iters; ++it) {
-        // H update (Algorithm 3 order): numerator W^T A, denominator (W^T W) H
-        if (int rc = sliced_update(p, W, m, k, A, p.pa, n, H, eps, stream, st)) return rc;
+        if (int rc = sliced_update(p, W, m, k, A, n, H, eps, st)) return rc;
         NMF_HIP(launch_transpose(H, k, n, p.Ht, st));
-        // W update with the new H, on the transposes: (A H^T)^T = H A^T, (W H H^T)^T = (H H^T) W^T
-        if (int rc = sliced_update(p, p.Ht, n, k, p.At, p.pt, m, p.Wt, eps, stream, st)) return rc;
+        if (int rc = sliced_update(p, p.Ht, n, k, p.At, m, p.Wt, eps, st)) return rc;
         NMF_HIP(launch_transpose(p.Wt, k, m, W, st));
     }
     return NMF_OK;

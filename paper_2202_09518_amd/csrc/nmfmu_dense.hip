@@ -3427,7 +3427,7 @@ __global__ __launch_bounds__(256) void objective_kernel(const double *__restrict
 // P = sum over the row splits of the partial W^T A results (test entry point only).
 // blockIdx.y = slice of 64 or 128 factors (ranks above 64): partials at ppart + slice * slice_ppart, `count`
 // floats of P per full slice, count_last for the last one.
-// Eight splits are requested together and added in split order: one load at a time, a 256 x 256
+// Eight splits are requested together and added in a tree: one load at a time, a 256 x 256
 // Gram matrix over 32 splits took 35 us on 64 workgroups per slice, a chain of trips to memory
 // (rank 256 on 16384 x 8192: 1041 -> 977 us per iteration).
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float *__restrict__ ppart,
@@ -3445,8 +3445,7 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float *__restri
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = ppart[(int64_t)(t + u) * count + e];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+            s += tree_sum(v);
         }
         for (; t < splits; ++t) s += ppart[(int64_t)t * count + e];
         P[e] = accumulate ? P[e] + s : s;

@@ -134,6 +134,20 @@ inline int64_t pair_rows_per_split(int64_t rows, int splits)
 // planes have ld columns per row group; partials of slice z at ppart + z * splits * 64 * n.  rps: a multiple of 16.
 hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const PairFactor &f, int ld, float *ppart,
                               int splits, int64_t rps, hipStream_t st);
+// Update of ranks above 64 from the partials of its products (see sliced_update_kernel).
+struct SlicedUpdate {
+    float *X, *Xt;                // k x len, len x k
+    const float *num;             // numerator: slices of `width` factors, snum splits each
+    const float *den;             // denominator: slices of 64, sden splits each
+    int k, width, snum, sden;
+    int64_t len;
+    float eps;
+    PairFactor F;                 // planes of Xt, ld columns per row group; maxima zero before
+    int ld;
+    unsigned *clear;              // other maxima to set to zero on the way
+    int nclear;
+};
+hipError_t launch_sliced_update(const SlicedUpdate &a, hipStream_t st);
 // P (k x cols) (+)= the sums over the splits.  width: factors of a slice.
 hipError_t launch_sum_partials_slices(const float *ppart, int splits, int k, int64_t cols, float *P, hipStream_t st,
                                       bool accumulate = false, int width = 64);

@@ -312,7 +312,8 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
 // The pass for slices of 64 factors on pairs of halves (aligned A, n % 4 == 0, 64 n < 2^31; pair planes), for X that
 // is not cut before.  Workgroup = 256 columns, wave = 64 of them (lane = 2 consecutive columns), the planes of a
 // group of steps staged in LDS for the four waves, three register stages of A.  12 matrix instructions per 16 rows x 64
-// columns x 64 factors instead of 24.  The accumulators join the totals every second group, after 192 terms.
+// columns x 64 factors instead of 24.  The accumulators join the totals after every group, 96 terms (192: a
+// contraction over 384 factors 8e-8 off, so 4e-8).
 // Ranks above 64 were bound by the matrix cores (power) on bf16 pieces; rank 256 on 16384 x 8192: 380 -> 270 us per product
 // (of which loads without the matrix work 210, the matrix work without the loads 220), whole iterations 937 -> 718,
 // error against 64 bits after five iterations 2.4 -> 2.3e-7.
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
             __builtin_amdgcn_sched_barrier(0);
             store_third(th, buf ^ 1, part);
         }
-        if (buf) join();
+        join();
         __syncthreads();    // the next group's planes are written, this group's are read
         buf ^= 1;
     }
@@ -499,6 +500,96 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
                 }
             }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Update behind the products of ranks above 64: X[c][j] <- X[c][j] * (sum of the numerator's partials) / (sum of the denominator's +
+// eps) for a tile of 64 factors (blockIdx.y) x CW columns, and from it X^T and its pair planes for the next half of
+// the iteration.  As sums of either product, an element-wise update, a transpose and a split with
+// its cleared maxima (seven launches) 56 us and more per half of an iteration at rank 256 on 16384 x 8192, now 21 to 29 (with
+// tiles of 64 columns 33 to 42: what counts is loads in flight).
+// clear: maxima to set to zero on the way.
+// ---------------------------------------------------------------------------
+template <int CW>
+__global__ __launch_bounds__(256) void sliced_update_kernel(const SlicedUpdate a)
+{
+    constexpr int FG = 256 / CW, NE = 64 / FG;             // factors side by side, entries of a thread
+    __shared__ float tile[64][CW + 1];
+    __shared__ unsigned most[64];
+    const int tid = threadIdx.x, jl = tid % CW, fl = tid / CW, f0 = 64 * (int)blockIdx.y;
+    const int kb = a.k - f0 < 64 ? a.k - f0 : 64;          // factors of this block
+    const int64_t j0 = (int64_t)blockIdx.x * CW, j = j0 + jl, len = a.len;
+    const bool okj = j < len;
+    if (tid < 64) most[tid] = 0u;
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = tid; i < a.nclear; i += 256) a.clear[i] = 0u;
+    // the partials of the numerator: slices of `width` factors; of the denominator: of 64
+    const int zn = f0 / a.width, kn = a.k - a.width * zn < a.width ? a.k - a.width * zn : a.width;
+    const float *num = a.num + ((int64_t)zn * a.snum * a.width + f0 - a.width * zn) * len;
+    const float *den = a.den + (int64_t)blockIdx.y * a.sden * 64 * len;
+    float old[NE], p[NE], d[NE];
+    int64_t at[NE];
+    bool ok[NE];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int c = fl + FG * i;
+        ok[i] = okj && c < kb;
+        at[i] = ok[i] ? (int64_t)c * len + j : 0;
+        old[i] = ok[i] ? a.X[(int64_t)f0 * len + at[i]] : 0.f;
+        p[i] = d[i] = 0.f;
+    }
+    auto add = [&](float (&sum)[NE], const float *from, int splits, int64_t stride) {
+        int t = 0;
+        for (; t + 4 <= splits; t += 4) {
+            float v[NE][4];
+#pragma unroll
+            for (int i = 0; i < NE; ++i)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[i][u] = ok[i] ? from[at[i] + (t + u) * stride] : 0.f;
+#pragma unroll
+            for (int i = 0; i < NE; ++i)
+                sum[i] += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+        }
+        for (; t < splits; ++t) {
+            float v[NE];
+#pragma unroll
+            for (int i = 0; i < NE; ++i) v[i] = ok[i] ? from[at[i] + t * stride] : 0.f;
+#pragma unroll
+            for (int i = 0; i < NE; ++i) sum[i] += v[i];
+        }
+    };
+    if (kb > 0) {
+        add(p, num, a.snum, (int64_t)kn * len);
+        add(d, den, a.sden, (int64_t)kb * len);
+    }
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        float x = 0.f;
+        if (ok[i]) {
+            x = old[i] * p[i] / (d[i] + a.eps);
+            a.X[(int64_t)f0 * len + at[i]] = x;
+        }
+        tile[fl + FG * i][jl] = x;
+    }
+    __syncthreads();
+    // X^T: rows of the tile's columns
+    const int cl = tid & 63, w = tid >> 6;
+#pragma unroll
+    for (int row = w; row < CW; row += 4)
+        if (j0 + row < len && cl < kb) a.Xt[(j0 + row) * a.k + f0 + cl] = tile[cl][row];
+    // its planes; columns beyond k are zero
+    for (int u = w; u < CW / 8; u += 4) {
+        const int64_t g = j0 / 8 + u;
+        if (g * 8 < len) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = tile[cl][8 * u + e];
+            const unsigned t = put_pairs(x, static_cast<u32x4 *>(a.F.units) + g * 2 * a.ld + f0 + cl, a.ld, a.F.exps + g * a.ld + f0 + cl);
+            if (t) atomicMax(&most[cl], t);
+        }
+    }
+    __syncthreads();
+    if (tid < kb && most[tid]) atomicMax(a.F.most + (int)(blockIdx.x % kPairCopies) * a.ld + f0 + tid, most[tid]);
 }
 
 // ---------------------------------------------------------------------------
@@ -557,6 +648,18 @@ hipError_t launch_split_pairs(const float *X, int64_t rows, int k, const PairFac
     const int64_t groups = (rows + 7) / 8;
     hipLaunchKernelGGL(split_pairs_kernel, dim3((unsigned)((groups + 31) / 32), (unsigned)(ld / 64)), dim3(256), 0, st, X, rows, k, f, ld,
                        clear);
+    return hipGetLastError();
+}
+
+hipError_t launch_sliced_update(const SlicedUpdate &a, hipStream_t st)
+{
+    // every 64 columns of the planes: those beyond k are read by slices of 128
+    const int cw = a.len * (a.ld / 64) >= 32 * 1024 ? 32 : 16;      // 1024 workgroups, or as many as there are
+    const int64_t blocks = (a.len + cw - 1) / cw;
+    if (blocks > 0x7fffffff || a.k > a.ld) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks, (unsigned)(a.ld / 64));
+    if (cw == 32) hipLaunchKernelGGL(sliced_update_kernel<32>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(sliced_update_kernel<16>, grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
