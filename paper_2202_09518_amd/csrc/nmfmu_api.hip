@@ -210,6 +210,15 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
 // 33 to 64 factors: the mirrored plan on pairs of halves.
 bool pairs_ok(int64_t m, int64_t n, int k) { return k > 32 && k <= NMF_MU_MAX_K && m < (int64_t)1 << 25 && n < (int64_t)1 << 25; }
 
+// The iterations a call has to have for the cut (A read, two copies written; 300 us on 16384 x 8192, a transposed copy 200) to pay, start ->
+// on pairs: 2000 x 1000, k = 40, one 67 -> 63 us; 16384 x 8192, k = 40, one 456 -> 524, two 685 -> 734, three 917 -> 943, k = 64, three 970 -> 968;
+// 6000 x 4000, k = 64, two 226 -> 210; 100000 x 512, k = 40, two 491 -> 497.  A that would be copied first: 20011 x 9998, k = 50, two 1471 -> 1145.
+int pairs_least(int64_t m, int64_t n, bool copy_a, bool rows_on_a_copy)
+{
+    if (m * n <= 1 << 22) return rows_on_a_copy ? 2 : 1;
+    return !copy_a && m * n > 1 << 25 ? 4 : 2;
+}
+
 PairMatrix carve_pair_matrix(Carve &cv, int64_t rows, int64_t cols)
 {
     PairMatrix x;
@@ -380,7 +389,7 @@ bool have_workspace(size_t need, hipStream_t st)
 
 // The plan of a dense run with `extra` bytes behind it (*tail): the resident plan where it applies, then the
 // one-pass plan, else the row or the mirrored plan, else the small one; whatever the workspace can hold.
-int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStream_t st, DensePlan *p, char **tail)
+int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStream_t st, DensePlan *p, char **tail, bool pairs)
 {
     void *ws = nullptr;
     const int tiles = resident_tiles(m, n, k);
@@ -394,7 +403,7 @@ int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStr
     bytes = one_pass_bytes(m, n, k);
     if (one_pass_ok(A, n, k) && have_workspace(bytes + extra, st)) {
         *p = carve_one_pass(g.ws, m, n, k);
-    } else if (pairs_ok(m, n, k) && have_workspace(pairs_bytes(m, n, k) + extra, st)) {
+    } else if (pairs && have_workspace(pairs_bytes(m, n, k) + extra, st)) {
         bytes = pairs_bytes(m, n, k);
         Carve cv(g.ws);
         *p = carve_pairs(cv, m, n, k);
@@ -453,17 +462,17 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
     bool padded = false, pad_w = false;
     size_t base = 0;
     if (resident_tiles(m, n, k) && have_workspace(resident_bytes(m, n, k) + extra, st))      // takes any A
-        return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
-    // large matrices of more than 32 factors: one iteration alone does not earn a second layout of A
+        return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail, false);
     const bool can_rows = aht_rows_ok(nullptr, m, n4, k), copies_can = eps >= 1.17549435e-38f && iters > 0;
-    if (pairs_ok(m, n, k) && !(iters == 1 && copy_a && can_rows && copies_can)) {
+    const bool pairs = pairs_ok(m, n, k) && iters >= pairs_least(m, n, copy_a, copy_a && can_rows && copies_can);
+    if (pairs) {
         if (aligned && copy_a && copies_can && have_workspace(pairs_bytes(m, n4, k) + copies + extra, st)) {
             base = pairs_bytes(m, n4, k);
             Carve cv(g.ws);
             r->p = carve_pairs(cv, m, n4, k);
             padded = true;
         } else if (have_workspace(pairs_bytes(m, n, k) + extra, st)) {
-            return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
+            return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail, true);
         }
     }
     if (!padded && copies_can && (copy_a || m != m4)) {
@@ -495,7 +504,7 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
             }
         }
     }
-    if (!padded) return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail);
+    if (!padded) return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail, pairs);
     Carve cv(static_cast<char *>(g.ws) + base);
     if (copy_a) {
         float *Ap = cv.take<float>((size_t)m * n4);
@@ -1535,7 +1544,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
     DensePlan p;
-    if (int rc = dense_plan(A, m, n, k, 0, st, &p, nullptr)) return rc;
+    if (int rc = dense_plan(A, m, n, k, 0, st, &p, nullptr, pairs_ok(m, n, k))) return rc;
     const bool mirrored = p.mirrored, one_pass = p.one_pass, resident = p.resident != 0;
     constexpr int NK = kDenseKernels;
     std::vector<hipEvent_t> ev((size_t)iters * NK + 1, nullptr);
