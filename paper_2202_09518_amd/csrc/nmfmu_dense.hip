@@ -19,7 +19,7 @@
 //   aht_pass_kernel : the older direct A H^T kernel (lanes down the rows), for
 //       shapes the others do not serve (unaligned A, short wide matrices)
 //   gram_kernel, gram_sum_kernel, residual_*_kernel, objective_kernel : the small rest.
-// For k <= 64 and aligned A the products are formed from pieces: fp32 operands cut into
+// For k <= 32 and aligned A (and up to 64 where A is not cut into pairs of halves, see nmfmu_pairs.hip) the products are formed from pieces: fp32 operands cut into
 // three bf16 pieces each, exactly, and the six leading of the nine piece products per term
 // (the rest is below 2^-22 of the term, of either sign) on v_mfma_f32_32x32x16_bf16 with
 // fp32 accumulation (see split3 and cut2 below).  wta_pass_kernel and aht_pass_kernel use
@@ -3211,7 +3211,7 @@ __global__ __launch_bounds__(256, 2) void residual_stream_kernel(const float *__
 }
 
 // ---------------------------------------------------------------------------
-// The objective as a streaming pass for any k <= 2 KS <= 64, 16-byte aligned A and H and
+// The objective as a streaming pass for any k <= 2 KS <= 48, 16-byte aligned A and H and
 // n % 4 == 0, with the fp32 matrix instruction, which takes two factors per step instead of 16 and
 // the floats as they are: no rank is rounded up to 16, and the sums are those of residual_kernel.  The
 // geometry of residual_stream_kernel: a wave owns 64 columns and walks down the rows of a split, a
@@ -3337,6 +3337,221 @@ __global__ __launch_bounds__(256, 2) void residual_stream_f32_kernel(const float
         buf ^= 1;
     }
     if (!colok) total = 0.0;   // such lanes subtracted a zero product from columns of other lanes
+    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
+    if (lane == 0) wsum[w] = total;
+    __syncthreads();
+    if (tid == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+}
+
+// ---------------------------------------------------------------------------
+// The objective as a streaming pass on pairs of halves, any k <= 16 S <= 64 and any alignment, in the
+// geometry of residual_stream_kernel; VEC (16-byte aligned A, n % 4 == 0): a lane's two columns are consecutive, else 32 apart.
+// The reduction runs over columns of W and rows of H that may be in units of their own, so each row of H is first brought to
+// its largest entry in the workgroup's columns, the power of two going to that column of W.  H is then cut under a scale per column and
+// the rows of W under one per row.  Three instructions per 16 factors do the work of eight of the fp32 kernel; the
+// large products and the cross products have accumulators of their own and
+// are taken from A one after the other, so that near a good fit the second meets a small difference and
+// few instructions round at the size of W H (a fit to 1e-4: objective 3e-8 to 2.4e-7 off, residual_stream_f32_kernel
+// 5e-9 to 9e-7).  Rows from m on read as zero, of A and of W (outside the tile's buffer extent), and
+// add nothing.
+// ---------------------------------------------------------------------------
+template <int S, bool VEC>
+__global__ __launch_bounds__(256, 2) void residual_pair_kernel(const float *__restrict__ A,
+                                                                 const float *__restrict__ W,
+                                                                 const float *__restrict__ H, int64_t m,
+                                                                 int64_t n, int k, int64_t rps,
+                                                                 double *__restrict__ partial)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    __shared__ double wsum[4];
+    __shared__ u32x4 wlds[2][4][S * 2][64];  // [tile][step * 2 + piece][lane]
+    __shared__ f32x4 wunit[2][4][8];         // 2^(exponent - 14) of the tile's rows
+    __shared__ unsigned fmost[4][16 * S];
+    __shared__ float funit[2][16 * S];       // the factors' units, and one over them
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int jj = lane & 31, half = lane >> 5;
+    const int64_t jw = (int64_t)blockIdx.x * 256 + 64 * w;   // this wave's 64 columns
+    const int64_t j0 = jw < n ? jw : 0;               // a wave wholly past column n fetches the first slab
+    const int64_t r0 = (int64_t)blockIdx.y * rps;     // rps % 32 == 0
+    const int64_t r1 = (r0 + rps < m) ? r0 + rps : m;
+    const unsigned rowb = (unsigned)(n * 4);
+    bool ok[2];                                       // VEC: n is even, both columns or none
+    unsigned off[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int c = VEC ? 2 * jj + q : 32 * q + jj;
+        ok[q] = jw + c < n;
+        off[q] = ok[q] ? (unsigned)(4 * half) * rowb + 4u * c : 0u;
+    }
+
+    float hv[2][S * 8];
+#pragma unroll
+    for (int s = 0; s < S * 8; ++s) {
+        const int c = 16 * (s >> 3) + 8 * half + (s & 7);
+        unsigned top = 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool in = ok[q] && c < k;
+            const float t = H[in ? (int64_t)c * n + jw + (VEC ? 2 * jj + q : 32 * q + jj) : 0];
+            hv[q][s] = in ? t : 0.f;
+            const unsigned x = __float_as_uint(hv[q][s]) & 0x7fffffffu;
+            top = x > top ? x : top;
+        }
+        for (int o = 16; o > 0; o >>= 1) {
+            const unsigned x = __shfl_xor(top, o);
+            top = x > top ? x : top;
+        }
+        if (jj == 0) fmost[w][c] = top;
+    }
+    __syncthreads();
+    if (tid < 16 * S) {
+        unsigned top = 0;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) top = fmost[x][tid] > top ? fmost[x][tid] : top;
+        const int e = half_exponent(top);
+        funit[0][tid] = power_of_two(e < 126 ? e : 126);
+        funit[1][tid] = power_of_two(e < 126 ? -e : -126);
+    }
+    __syncthreads();
+    u32x4 hp[S][2][2];
+    float unit[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        unsigned top = 0;
+#pragma unroll
+        for (int s = 0; s < S * 8; ++s) {
+            hv[q][s] *= funit[1][16 * (s >> 3) + 8 * half + (s & 7)];
+            const unsigned x = __float_as_uint(hv[q][s]) & 0x7fffffffu;
+            top = x > top ? x : top;
+        }
+        const unsigned other = __shfl_xor(top, 32);
+        const int e = half_exponent(other > top ? other : top);
+        const float sc = power_of_two(14 - e);
+        unit[q] = power_of_two(e - 14);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) cut2h(hv[q][8 * s + 2 * pr], hv[q][8 * s + 2 * pr + 1], sc, hp[s][q], pr);
+    }
+
+    // Requests only: nothing below reads a loaded value before the products of the previous
+    // tile are issued, so the loads stay in flight.
+    float wv[S * 8];
+    const unsigned woff = (unsigned)(jj * k + 8 * half) * 4u;
+    auto load_w = [&](int64_t i0) {
+        const int64_t base = i0 < r1 ? i0 : 0;
+        const int64_t av = m - base < 32 ? m - base : 32;
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(W + base * k), 0, (int)(av * k * 4), kRsrcFlags);
+#pragma unroll
+        for (int s = 0; s < S * 8; ++s)      // factors from k on are the next row's
+            wv[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, woff + 64u * (s >> 3) + 4u * (s & 7), 0, 0));
+    };
+    auto store_w = [&](int buf) {
+        unsigned top = 0;
+#pragma unroll
+        for (int s = 0; s < S * 8; ++s) {
+            const int c = 16 * (s >> 3) + 8 * half + (s & 7);
+            wv[s] = c < k ? wv[s] * funit[0][c] : 0.f;
+            const unsigned b = __float_as_uint(wv[s]) & 0x7fffffffu;
+            top = b > top ? b : top;
+        }
+        const unsigned other = __shfl_xor(top, 32);
+        const int e = half_exponent(other > top ? other : top);
+        const float sc = power_of_two(14 - e);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            u32x4 wp[2];
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) cut2h(wv[8 * s + 2 * pr], wv[8 * s + 2 * pr + 1], sc, wp, pr);
+            wlds[buf][w][2 * s][lane] = wp[0];
+            wlds[buf][w][2 * s + 1][lane] = wp[1];
+        }
+        if (half == 0) reinterpret_cast<float *>(wunit[buf][w])[jj] = power_of_two(e - 14);
+    };
+    typedef f32x2 ATile[16];
+    auto load_a = [&](ATile &a, int64_t i0) {
+        const int64_t base = i0 < r1 ? i0 : 0;
+        const int64_t av = m - base < 32 ? m - base : 32;
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(A + base * n + j0), 0, (int)(av * rowb - j0 * 4), kRsrcFlags);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            unsigned row = (unsigned)acc_row(v, 0) * rowb;
+            asm volatile("" : "+s"(row));            // sixteen sums kept in registers otherwise
+            if (VEC) {
+                const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(ra, off[0] + row, 0, kStreamLoad);
+                a[v] = __builtin_bit_cast(f32x2, t);
+            } else {
+                a[v].x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, off[0] + row, 0, kStreamLoad));
+                a[v].y = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, off[1] + row, 0, kStreamLoad));
+            }
+        }
+    };
+    double total = 0.0;
+    // one tile, its A already requested: pairs of W from LDS, products, squares
+    auto tile = [&](const ATile &a, int buf, int t, bool valid) {
+        f32x4 u[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) u[g] = wunit[buf][t][2 * g + half];
+        f32x16 big[2], rest[2];
+        auto products = [&](int q) {
+            big[q] = f32x16{0}, rest[q] = f32x16{0};
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const u32x4 w0 = wlds[buf][t][2 * s][lane], w1 = wlds[buf][t][2 * s + 1][lane];
+                rest[q] = mfma_f16(w1, hp[s][q][0], rest[q]);
+                big[q] = mfma_f16(w0, hp[s][q][0], big[q]);
+                rest[q] = mfma_f16(w0, hp[s][q][1], rest[q]);
+            }
+        };
+        auto squares = [&](int q) {
+            float local = 0.f;      // 16 terms per lane in fp32, double across
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float p = u[v >> 2][v & 3] * unit[q];
+                const float d = __builtin_fmaf(-rest[q][v], p, __builtin_fmaf(-big[q][v], p, a[v][q]));
+                local = __builtin_fmaf(d, d, local);
+            }
+            // not a branch: with one the compiler mixes the tiles' work and spills
+            asm volatile("" : "+v"(local));
+            total += valid && ok[q] ? (double)local : 0.0;
+        };
+        products(0);
+        if (S > 2) __builtin_amdgcn_sched_barrier(0);
+        if (S <= 2) products(1);
+        squares(0);
+        if (S > 2) {
+            __builtin_amdgcn_sched_barrier(0);
+            products(1);
+        }
+        squares(1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // four tiles per trip (every wave of the workgroup makes the same trips: r0 and r1 are the
+    // workgroup's); a tile past the split is tile 0 again, and its sum is dropped
+    ATile at[2];
+    int64_t i = r0;
+    load_w(i + 32 * w);
+    store_w(0);
+    load_w(i + 128 + 32 * w);
+    load_a(at[0], i);
+    __syncthreads();
+    int buf = 0;
+    for (; i < r1; i += 128) {
+        store_w(buf ^ 1);
+        load_w(i + 256 + 32 * w);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            load_a(at[(t + 1) & 1], i + 32 * (t + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            tile(at[t & 1], buf, t, i + 32 * t < r1);
+        }
+        __syncthreads();    // the group's buffer is free, the next group's is written
+        buf ^= 1;
+    }
     for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
     if (lane == 0) wsum[w] = total;
     __syncthreads();
@@ -3843,27 +4058,35 @@ hipError_t launch_residual(const float *A, int64_t m, int64_t n, int k, const fl
         hipLaunchKernelGGL(residual_finish_kernel, dim3(1), dim3(256), 0, st, (const double *)partial, count, out);
         return hipGetLastError();
     }
-    // The fp32 streaming kernel (32 rows of A with 32-bit byte offsets: 128 n < 2^31) from four row
-    // tiles per workgroup on, about 2^24 elements; below that its pipeline does not fill.  Whole call,
-    // residual_kernel against it: 16384 x 8192, k = 10 / 29 / 64: 145 / 226 / 379 -> 111 / 139 / 245 us;
-    // 2000 x 8192, k = 10: 85 -> 40; 8192 x 2048, k = 20: 61 -> 45; but 4099 x 1000, k = 20: 37 -> 41.
-    // Above 48 factors its registers spill, and on few columns (residual_kernel's serial loop over
-    // slabs is short there) it loses: 16384 x 1000, k = 64: 74 -> 80; 8192 x 2048: 99 -> 80.
-    if (n < ((int64_t)1 << 24) && vec_ok(A, n) && vec_ok(H, n) && residual_rows_per_split(m, n) >= 128 &&
-        (k <= 48 || n >= 2048)) {
+    // The other streaming kernels (32 rows of A with 32-bit byte offsets: 128 n < 2^31) from four row
+    // tiles per workgroup on, about 2^24 elements; below that their pipelines do not fill.  On aligned operands the fp32 instruction up to 24
+    // factors and, where a workgroup has fewer than eight tiles for the longer start of the other, up to 48; else pairs of halves.
+    // Whole call in us: 16384 x 8192, k = 10 / 17 / 29 / 64: fp32 101 / 109 / 128 / 237, pairs 103 / 114 / 118 / 180; 8192 x 2048,
+    // k = 20 / 40 / 64: 37 / 50 / 72 and 44 / 54 / 65; 65536 x 1024, k = 40: 102 and 98.  k = 32 on the kernel above 104, pairs 126.
+    // Misaligned: residual_kernel 16384 x 8190, k = 10 192, pairs 118; 9001 x 7003, k = 50 319 and 142; 2050 x 8191, k = 20 162 and 50.
+    if (n < ((int64_t)1 << 24) && residual_rows_per_split(m, n) >= 128) {
         const int splits = residual_splits(m, n);
         const int64_t rps = residual_rows_per_split(m, n);
         const dim3 grid((unsigned)((n + 255) / 256), (unsigned)splits);
         const int64_t count = (int64_t)grid.x * grid.y;
-#define NMFMU_RESIDUAL_F32(KS) \
-    hipLaunchKernelGGL(residual_stream_f32_kernel<KS>, grid, dim3(256), 0, st, A, W, H, m, n, k, rps, partial)
-        if (k <= 8) NMFMU_RESIDUAL_F32(4);
-        else if (k <= 16) NMFMU_RESIDUAL_F32(8);
-        else if (k <= 24) NMFMU_RESIDUAL_F32(12);
-        else if (k <= 32) NMFMU_RESIDUAL_F32(16);
-        else if (k <= 48) NMFMU_RESIDUAL_F32(24);
-        else NMFMU_RESIDUAL_F32(32);
-#undef NMFMU_RESIDUAL_F32
+#define NMFMU_RESIDUAL(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, A, W, H, m, n, k, rps, partial)
+        if (vec_ok(A, n) && vec_ok(H, n) && (k <= 24 || (k <= 48 && rps < 256))) {
+            if (k <= 8) NMFMU_RESIDUAL(residual_stream_f32_kernel<4>);
+            else if (k <= 16) NMFMU_RESIDUAL(residual_stream_f32_kernel<8>);
+            else if (k <= 24) NMFMU_RESIDUAL(residual_stream_f32_kernel<12>);
+            else if (k <= 32) NMFMU_RESIDUAL(residual_stream_f32_kernel<16>);
+            else NMFMU_RESIDUAL(residual_stream_f32_kernel<24>);
+        } else if (k <= 16) NMFMU_RESIDUAL(residual_pair_kernel<1, false>);
+        else if (vec_ok(A, n)) {
+            if (k <= 32) NMFMU_RESIDUAL(residual_pair_kernel<2, true>);
+            else if (k <= 48) NMFMU_RESIDUAL(residual_pair_kernel<3, true>);
+            else NMFMU_RESIDUAL(residual_pair_kernel<4, true>);
+        } else {
+            if (k <= 32) NMFMU_RESIDUAL(residual_pair_kernel<2, false>);
+            else if (k <= 48) NMFMU_RESIDUAL(residual_pair_kernel<3, false>);
+            else NMFMU_RESIDUAL(residual_pair_kernel<4, false>);
+        }
+#undef NMFMU_RESIDUAL
         hipLaunchKernelGGL(residual_finish_kernel, dim3(1), dim3(256), 0, st, (const double *)partial, count, out);
         return hipGetLastError();
     }

@@ -195,3 +195,28 @@ def test_counters_are_left_alone():
     nmf.nmf_gram_w(X, 4099, 40, G)
     want = X.double().t().contiguous() @ X.double()
     assert ((G.double() - want).norm() / want.norm()).item() < 1e-6
+
+
+# the streaming objective: ragged rows and columns, each number of factor steps, aligned and not, one slab and several
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["plain", "units", "fit"])
+@pytest.mark.parametrize("m,n,k", [(2591, 8201, 3), (2600, 8204, 17), (4133, 4099, 33), (4100, 4100, 64), (66001, 61, 48), (66000, 260, 16),
+                                   (66000, 260, 30), (66100, 256, 40)])
+def test_objective(m, n, k, kind):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    r = np.random.default_rng(11)
+    W, H = r.random((m, k), dtype=np.float32), r.random((k, n), dtype=np.float32)
+    A = r.random((m, n), dtype=np.float32)
+    if kind != "plain":
+        A = ((W.astype(np.float64) @ H) * (1 + 1e-3 * (A - 0.5))).astype(np.float32)
+    if kind == "units":     # of the factors, up to 2^60 apart, of the rows and of the columns
+        u = np.ldexp(np.float32(1), r.integers(-30, 31, k)).astype(np.float32)
+        W, H = W * u, H / u[:, None]
+        rows, cols = (np.ldexp(np.float32(1), r.integers(-6, 7, x)).astype(np.float32) for x in (m, n))
+        A, W, H = A * rows[:, None] * cols, W * rows[:, None], H * cols
+    want = np.linalg.norm(A - W.astype(np.float64) @ H)
+    got = nmf.nmf_residual_dense(torch.from_numpy(A).cuda(), m, n, k, torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda())
+    # an error of 2^-22 per entry of W H adds to the difference in the squares: (2^-22 / 3e-4)^2 / 2 of a fit to 3e-4 of A
+    assert abs(got - want) <= 1e-6 * want
