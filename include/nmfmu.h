@@ -9,7 +9,7 @@
  *     W <- W * (A H^T) / (W (H H^T) + eps)          W update, uses the NEW H
  *
  * eps is added once, to the finished denominator.  Operands and results are
- * IEEE single precision.  For k <= NMF_MU_MAX_K and 16-byte aligned A the two
+ * IEEE single precision.  For k <= 32 and 16-byte aligned A the two
  * products over A are formed on the bf16 matrix cores from exact pieces: every
  * float is cut into three bf16 values that add up to it bit for bit, and the six
  * leading piece products of a term are accumulated in fp32.  The three left out
@@ -19,9 +19,19 @@
  * mean square over the result: 5e-8 to 1.6e-7 of sums over 1000 to 500000
  * terms, 2e-7 where A repeats one value down a column or along a row; where A and
  * a factor hold one value each throughout, all terms lose the same bits and a sum
- * can be 2e-6 off.  The Gram matrices, the small plan's A H^T, and W^T A
- * for k > 32 on a misaligned A that is used as it is take the fp32 matrix
- * instruction (fp32 operands, fp32 accumulation).
+ * can be 2e-6 off.  For k > 32, and for stacked runs of an ensemble, the products
+ * are formed on the fp16 matrix cores from pairs of halves: a float times a power of
+ * two of its column (128 rows at a time for A, at most 30 binary orders below the
+ * column's largest value there for a factor) is cut into its nearest half and the
+ * half of what is left, 22 to 24 bits together, and three of the four products of
+ * two pairs are accumulated in fp32, over at most 384 terms before a running total
+ * takes them.  The instructions' rounding of their sums is what remains: the errors of
+ * whole runs against float64 are those of the bf16 pieces or a little lower (2.2e-7
+ * and 2.4e-7 after five iterations of rank 256 on 16384 x 8192).  An entry more than
+ * 2^14 below the largest of its 128 rows of the column loses low bits, in proportion
+ * to that largest entry; infinities and NaN reach the results they belong to.  The Gram matrices up to 64 factors, the small plan's
+ * A H^T, and W^T A for k > 32 on a misaligned A that is used as it is take the fp32
+ * matrix instruction (fp32 operands, fp32 accumulation).
  *
  * Conventions shared by every entry point
  *   - All matrices are row-major and contiguous: A is m x n (leading dimension
@@ -87,7 +97,7 @@ const char *nmf_last_error(void);
  *   A      device, m x n, read-only
  *   W, H   device, in/out
  *   iters  >= 0;  eps >= 0 and finite
- * Asynchronous on `stream`.  Five plans, chosen per call; they give the same
+ * Asynchronous on `stream`.  Six plans, chosen per call; they give the same
  * iteration and differ in low-order bits.  Resident plan (k <= 16, any alignment,
  * ceil(m / 64) ceil(n / 256) <= 256 and n <= 4096): 256 to 4096 iterations in one launch, A on the
  * compute units, at most one workgroup on each, which other work on the device does
@@ -102,14 +112,17 @@ const char *nmf_last_error(void);
  * workspace kind 4 plus 1024 k n bytes at most.  Row plan (16-byte aligned A,
  * n % 4 == 0, n < 2^24, and m >= 12288 with n >= 512, or m n <= 2^22): both products stream
  * the row-major A, the W update is fused into the A H^T pass; workspace kind 4.
- * It comes next for k <= 32.  Mirrored plan (33 <= k <= 64, and shapes the
- * row plan does not serve, if the workspace can hold a second copy of A): A is
+ * It comes next for k <= 32.  Pair plan (33 <= k <= 64, m and n < 2^25, any
+ * alignment, if the workspace can hold two copies of A): A and A^T are cut into pairs
+ * of halves once per call, and both products stream those; workspace kind 0.
+ * Mirrored plan (33 <= k <= 64 with room for one copy only, and shapes the
+ * row plan does not serve): A is
  * transposed once per call and A^T is streamed for the A H^T product;
  * workspace kind 0.  Without room for that copy: the row plan for
  * 33 <= k <= 64 where it applies (its A H^T pass is about a fifth slower than
  * the mirrored one), else the small plan, a direct A H^T kernel on A (lanes
  * down the rows: slower); workspace kind 4.
- * An A whose base is not 16-byte aligned or whose n is not a multiple of 4 is
+ * On the other plans an A whose base is not 16-byte aligned or whose n is not a multiple of 4 is
  * copied once per call, with H, into aligned arrays of n4 = n rounded up to 4
  * columns, and the plan for m x n4 runs on the copies; the mirrored plan, whose A^T
  * has the rows of A as columns, also takes m4 = m rounded up to 4 rows and a copy
@@ -120,11 +133,14 @@ const char *nmf_last_error(void);
  * as it is and takes the slower kernels.
  * Ranks NMF_MU_MAX_K < k <= NMF_MU_MAX_K_SLICED run the same iteration with every
  * product written as F^T X (a reduction over the rows of two row-major
- * matrices) and computed 64 factor columns of F at a time by the k <= 64 pass
- * kernel: W^T A, W^T W, (W^T W) H, and the same three on the transposes A^T,
- * H^T, W^T for the W update, followed by the element-wise update.  A is read
- * ceil(k / 64) times per product; the workspace holds A^T, W^T, H^T and two
- * k x max(m, n) arrays (nmf_mu_workspace_bytes kind 5), else NMF_ENOMEM.
+ * matrices) and computed in slices of 64 or 128 factor columns of F, side by side
+ * in one launch: W^T A, W^T W, (W^T W) H, and the same three on the transposes A^T,
+ * H^T, W^T for the W update, followed by one launch that updates.  A and A^T are cut into
+ * pairs of halves once per call and read ceil(k / 64) or ceil(k / 128) times per
+ * product (mostly from the caches); the workspace holds both, W^T, H^T, partial sums and a
+ * k x max(m, n) array (nmf_mu_workspace_bytes kind 5).  With less, or for m or n >= 2^25, A is cut as it is
+ * read and A^T is kept as it is; with less than A^T, W^T, H^T and two
+ * k x max(m, n) arrays NMF_ENOMEM.
  */
 int nmf_mu_dense(const float *A, int64_t m, int64_t n, int32_t k,
                  float *W, float *H, int32_t iters, float eps, void *stream);
@@ -349,8 +365,9 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
  * not overlap.  The pointer arrays and k live in HOST memory and are read
  * before the call returns; what they point to is device memory.
  * Consecutive runs that name the same A are stacked while their ranks sum to at
- * most NMF_MU_MAX_K: the two passes over A then serve the whole stack at once
- * (order the runs by A to benefit).  Results per run equal a single run's up
+ * most NMF_MU_MAX_K, and up to four such stacks run side by side on one pair of cut
+ * copies of A (the pair plan of nmf_mu_dense): the passes over A then serve all of
+ * them at once (order the runs by A to benefit).  Results per run equal a single run's up
  * to rounding order.
  */
 int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64_t n,
@@ -360,7 +377,7 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
 /*
  * Workspace the given problem needs, in bytes.  kind: 0 dense (mirrored plan:
  * the library keeps a transposed copy of A, so this is about m*n*4 bytes plus
- * the partial sums), 4 dense (row plan and small plan: partial sums and operand
+ * the partial sums; 33 <= k <= 64: pair plan, 8 bytes for each entry of A), 4 dense (row plan and small plan: partial sums and operand
  * planes only), 1 csr (includes the scratch of the one-time sort, about 24 bytes
  * per stored entry), 2 ooc (excluding the
  * staging slots), 3 batched (enough for any mix of ranks; k is only checked; no

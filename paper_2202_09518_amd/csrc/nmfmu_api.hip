@@ -210,8 +210,8 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
 // 33 to 64 factors: the mirrored plan on pairs of halves.
 bool pairs_ok(int64_t m, int64_t n, int k) { return k > 32 && k <= NMF_MU_MAX_K && m < (int64_t)1 << 25 && n < (int64_t)1 << 25; }
 
-// The iterations a call has to have for the cut (A read, two copies written; 300 us on 16384 x 8192, a transposed copy 200) to pay, start ->
-// on pairs: 2000 x 1000, k = 40, one 67 -> 63 us; 16384 x 8192, k = 40, one 456 -> 524, two 685 -> 734, three 917 -> 943, k = 64, three 970 -> 968;
+// The iterations a call has to have for the cut (A read, two copies written; 300 us on 16384 x 8192, a transposed copy 200) to pay, without ->
+// with it: 2000 x 1000, k = 40, one 67 -> 63 us; 16384 x 8192, k = 40, one 456 -> 524, two 685 -> 734, three 917 -> 943, k = 64, three 970 -> 968;
 // 6000 x 4000, k = 64, two 226 -> 210; 100000 x 512, k = 40, two 491 -> 497.  A that would be copied first: 20011 x 9998, k = 50, two 1471 -> 1145.
 int pairs_least(int64_t m, int64_t n, bool copy_a, bool rows_on_a_copy)
 {
