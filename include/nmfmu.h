@@ -113,9 +113,10 @@ const char *nmf_last_error(void);
  * n % 4 == 0, n < 2^24, and m >= 12288 with n >= 512, or m n <= 2^22): both products stream
  * the row-major A, the W update is fused into the A H^T pass; workspace kind 4.
  * It comes next for k <= 32.  Pair plan (33 <= k <= 64, m and n < 2^25, any
- * alignment, if the workspace can hold two copies of A): A and A^T are cut into pairs
+ * alignment, if the workspace can hold two copies of A and the call has at least four
+ * iterations, two up to 2^25 entries or on a misaligned A, one up to 2^22): A and A^T are cut into pairs
  * of halves once per call, and both products stream those; workspace kind 0.
- * Mirrored plan (33 <= k <= 64 with room for one copy only, and shapes the
+ * Mirrored plan (33 <= k <= 64 otherwise, and shapes the
  * row plan does not serve): A is
  * transposed once per call and A^T is streamed for the A H^T product;
  * workspace kind 0.  Without room for that copy: the row plan for
