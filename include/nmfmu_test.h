@@ -40,7 +40,8 @@ int nmfmu_resident_polls(const float *A, int64_t m, int64_t n, int32_t k, float 
 
 /*
  * The plan that nmf_mu_dense would run with these arguments and the workspace as it is, in *plan: 0 the small plan, 1 the
- * mirrored, 2 the row, 3 the one-pass, 4 the resident plan; 8 more if it runs on padded copies (which are made).
+ * mirrored, 2 the row, 3 the one-pass, 4 the resident plan; 8 more if it runs on padded copies (which are made),
+ * 16 more if the mirrored plan runs on pairs of halves.
  * k <= NMF_MU_MAX_K; W and H are read.
  */
 int nmfmu_dense_plan(const float *A, int64_t m, int64_t n, int32_t k, float *W, float *H, int32_t iters, float eps,
@@ -62,7 +63,8 @@ int nmfmu_dense_plan(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
  * [1] except for the run's last W update, whose launch is [4]; on the resident plan
  * [1] is W^T A and the H update, [4] A H^T and the W update, each as a launch of its
  * own), 1 the
- * mirrored plan (see nmf_mu_workspace_bytes), 0 the small plan.  kernel_ms[7] and
+ * mirrored plan (see nmf_mu_workspace_bytes), on pairs of halves where nmf_mu_dense
+ * takes those for as many iterations, 0 the small plan.  kernel_ms[7] and
  * [8]: milliseconds per launch of the W^T A pass and (plans 1 and 2, else 0) of
  * the A H^T pass, from 20 launches back to back between two events after the
  * run, i.e. without the event commands that surround every kernel in [0..5].

@@ -266,7 +266,8 @@ DensePlan carve_pairs(Carve &cv, int64_t m, int64_t n, int k, int groups = 0)
     p.fw.most = cv.take<unsigned>(2 * kPairMost);
     p.fh.most = p.fw.most + kPairMost;
     if (!groups) {
-        p.Wt = cv.take<float>((size_t)k * m);
+        p.Wt = p.Wts[0] = cv.take<float>((size_t)k * m);
+        p.sl.k[0] = k;
         return p;
     }
     p.slice_gw = p.slice_gh = (int64_t)kFinMaxBlocks * 4 * 1024;
@@ -387,6 +388,15 @@ bool have_workspace(size_t need, hipStream_t st)
     return can;
 }
 
+// Whether a run comes first to the pair plan, among those that the workspace decides.
+bool takes_pairs(const float *A, int64_t m, int64_t n, int k, int iters, float eps)
+{
+    const int64_t n4 = (n + 3) & ~(int64_t)3;
+    const bool copy_a = (reinterpret_cast<uintptr_t>(A) & 15u) != 0 || n != n4;
+    const bool rows_on_a_copy = copy_a && aht_rows_ok(nullptr, m, n4, k) && eps >= 1.17549435e-38f;
+    return pairs_ok(m, n, k) && iters > 0 && iters >= pairs_least(m, n, copy_a, rows_on_a_copy);
+}
+
 // The plan of a dense run with `extra` bytes behind it (*tail): the resident plan where it applies, then the
 // one-pass plan, else the row or the mirrored plan, else the small one; whatever the workspace can hold.
 int dense_plan(const float *A, int64_t m, int64_t n, int k, size_t extra, hipStream_t st, DensePlan *p, char **tail, bool pairs)
@@ -464,7 +474,7 @@ int open_run(const float *A, int64_t m, int64_t n, int k, float *W, float *H, in
     if (resident_tiles(m, n, k) && have_workspace(resident_bytes(m, n, k) + extra, st))      // takes any A
         return dense_plan(A, m, n, k, extra, st, &r->p, &r->tail, false);
     const bool can_rows = aht_rows_ok(nullptr, m, n4, k), copies_can = eps >= 1.17549435e-38f && iters > 0;
-    const bool pairs = pairs_ok(m, n, k) && iters >= pairs_least(m, n, copy_a, copy_a && can_rows && copies_can);
+    const bool pairs = takes_pairs(A, m, n, k, iters, eps);
     if (pairs) {
         if (aligned && copy_a && copies_can && have_workspace(pairs_bytes(m, n4, k) + copies + extra, st)) {
             base = pairs_bytes(m, n4, k);
@@ -736,9 +746,7 @@ int dense_body(const float *A, int64_t m, int64_t n, int k, float *W, float *H, 
         const PairPlanes cut = a_is_mirrored ? PairPlanes::there : PairPlanes::none;
         NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
         DensePlan q = p;
-        q.Wts[0] = p.Wt;
         q.Hs[0] = H;
-        q.sl.k[0] = k;
         if (map) q.sl.bm[0] = *map;
         else q.sl.bm[0].on = 0;
         return pairs_body(A, m, n, W, iters, eps, q, st, cut, ev, mon);
@@ -1544,7 +1552,8 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lock(g.mu);
     DensePlan p;
-    if (int rc = dense_plan(A, m, n, k, 0, st, &p, nullptr, pairs_ok(m, n, k))) return rc;
+    if (int rc = dense_plan(A, m, n, k, 0, st, &p, nullptr, takes_pairs(A, m, n, k, iters, eps))) return rc;
+    p.Hs[0] = H;
     const bool mirrored = p.mirrored, one_pass = p.one_pass, resident = p.resident != 0;
     constexpr int NK = kDenseKernels;
     std::vector<hipEvent_t> ev((size_t)iters * NK + 1, nullptr);
@@ -2421,6 +2430,7 @@ int nmfmu_dense_plan(const float *A, int64_t m, int64_t n, int32_t k, float *W, 
     if (int rc = open_run(A, m, n, k, W, H, iters, eps, 0, static_cast<hipStream_t>(stream), &r)) return rc;
     *plan = r.p.resident ? 4 : r.p.one_pass ? 3 : takes_row_plan(r.p, r.A, r.m, r.n, k) ? 2 : r.p.mirrored ? 1 : 0;
     if (r.A != A || r.W != W || r.H != H) *plan += 8;
+    if (r.p.pairs) *plan += 16;
     return NMF_OK;
 }
 

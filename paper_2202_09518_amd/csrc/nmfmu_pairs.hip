@@ -705,6 +705,8 @@ hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream
     if (p.rps % kPairBlock || p.nslices < 1 || p.nslices > kPairSlices || (int64_t)(p.splits - 1) * p.rps >= p.rows ||
         p.X.ld >= ((int64_t)1 << 25) || p.X.ld < p.n)
         return hipErrorInvalidValue;
+    for (int z = 0; z < p.nslices; ++z)
+        if (p.k[z] < 1 || p.k[z] > 32 * tiles) return hipErrorInvalidValue;      // a pass that stores nothing, or not all
     int64_t tiles8 = ((p.n + 255) / 256 * p.splits + 7) / 8 * 8;
     if (p.gtiles && tiles8 < 192) tiles8 += 64;      // a workgroup per 64 entries of the Gram matrix
     const dim3 grid((unsigned)(tiles8 * p.nslices));

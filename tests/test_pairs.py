@@ -220,3 +220,22 @@ def test_objective(m, n, k, kind):
     got = nmf.nmf_residual_dense(torch.from_numpy(A).cuda(), m, n, k, torch.from_numpy(W).cuda(), torch.from_numpy(H).cuda())
     # an error of 2^-22 per entry of W H adds to the difference in the squares: (2^-22 / 3e-4)^2 / 2 of a fit to 3e-4 of A
     assert abs(got - want) <= 1e-6 * want
+
+
+# The profile is of the plan that nmf_mu_dense runs for as many iterations: pairs of halves or, for few on a large aligned matrix,
+# the plan that needs no second copy.  (The launcher refuses a timed pass of no factors.)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k,iters", [(8200, 4100, 40, 1), (8200, 4100, 40, 4), (700, 516, 64, 1), (2100, 2001, 33, 1), (2100, 2001, 33, 2)])
+def test_profile_is_of_the_plan_that_runs(m, n, k, iters):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    A, W, H = (torch.rand(s, generator=g, device="cuda") for s in ((m, n), (m, k), (k, n)))
+    w, h = W.clone(), H.clone()
+    nmf.nmf_mu_dense(A, m, n, k, w, h, iters, EPS)
+    ms = nmf.nmf_mu_dense_profile(A, m, n, k, W, H, iters, EPS)
+    assert ms[7] > 0 and ms[8] > 0
+    if n % 4 == 0 or iters > 1:     # the profile makes no aligned copy of A
+        assert torch.equal(W, w) and torch.equal(H, h)
