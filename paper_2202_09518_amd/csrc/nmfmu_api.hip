@@ -157,6 +157,8 @@ struct DensePlan {
     PairMatrix pa, pt;         // A' and (A^T)'
     PairFactor fw, fh;         // planes of W and of H^T
     float *Wts[kPairGroup], *Hs[kPairGroup];      // slices of stacked runs: W^T and H
+    unsigned *redo;                               // tiles of either pass that are formed from the floats
+    int64_t nredo[2];
     int64_t slice_gw, slice_gh, slice_gs;         // from slice to slice: tile sets of either factor, summed sets
     PairSlices sl;
     int resident = 0;          // the run in one launch, this many row tiles per workgroup: `res` and dry only
@@ -224,7 +226,7 @@ PairMatrix carve_pair_matrix(Carve &cv, int64_t rows, int64_t cols)
     PairMatrix x;
     x.ld = pair_matrix_ld(cols);
     x.units = cv.take<char>(pair_matrix_units(rows, x.ld));
-    x.inv = cv.take<float>(pair_matrix_scales(rows, x.ld) / sizeof(float));
+    x.scale = cv.take<float2>(pair_matrix_scales(rows, x.ld) / sizeof(float2));
     return x;
 }
 
@@ -253,8 +255,12 @@ DensePlan carve_pairs(Carve &cv, int64_t m, int64_t n, int k, int groups = 0)
     p.mirrored = p.pairs = true;
     p.c = carve_common(cv, k);
     size_t part = 0;
+    p.nredo[0] = p.nredo[1] = 0;
     for (int c = 1; c <= (groups ? groups : 1); ++c) {
         set_slices(&p, m, n, c);
+        const int64_t t1 = pair_pass_tiles(n, p.s1, c), t2 = pair_pass_tiles(m, p.s2, c);
+        p.nredo[0] = t1 > p.nredo[0] ? t1 : p.nredo[0];
+        p.nredo[1] = t2 > p.nredo[1] ? t2 : p.nredo[1];
         const size_t p1 = (size_t)p.s1 * c * (groups ? 64 : k) * n, p2 = (size_t)p.s2 * c * (groups ? 64 : k) * m;
         part = max3(part, p1, p2);
     }
@@ -263,8 +269,9 @@ DensePlan carve_pairs(Carve &cv, int64_t m, int64_t n, int k, int groups = 0)
     p.pt = carve_pair_matrix(cv, n, m);
     p.fw = carve_pair_factor(cv, m, 64, groups ? groups : 1);
     p.fh = carve_pair_factor(cv, n, 64, groups ? groups : 1);
-    p.fw.most = cv.take<unsigned>(2 * kPairMost);
+    p.fw.most = cv.take<unsigned>(2 * kPairMost + p.nredo[0] + p.nredo[1]);
     p.fh.most = p.fw.most + kPairMost;
+    p.redo = p.fh.most + kPairMost;
     if (!groups) {
         p.Wt = p.Wts[0] = cv.take<float>((size_t)k * m);
         p.sl.k[0] = k;
@@ -572,10 +579,18 @@ size_t monitored_bytes(int batch, int k)
 
 // A pass of a run on pairs: over A' with the planes of W, or (transposed) over (A^T)' with those of H^T.  The maxima of the planes
 // that come next are set to zero on the way: those planes were read by the pass before.
-hipError_t pass_over(const DensePlan &p, int64_t m, int64_t n, bool transposed, int nsets, hipStream_t st)
+hipError_t pass_over(const DensePlan &p, const float *A, int64_t m, int64_t n, bool transposed, int nsets, hipStream_t st)
 {
     const Common &c = p.c;
     PairPass a{};
+    a.f = transposed ? p.Hs[0] : p.Wts[0];
+    a.f_row = 1;
+    a.f_col = transposed ? n : m;
+    a.slice_f = p.sl.count > 1 ? (transposed ? p.Hs[1] : p.Wts[1]) - a.f : 0;
+    a.x = A;
+    a.x_row = transposed ? 1 : n;
+    a.x_col = transposed ? n : 1;
+    a.redo = p.redo + (transposed ? p.nredo[0] : 0);
     a.F = transposed ? p.fh : p.fw;
     a.ldf = 64;
     a.slice_units = (int64_t)(pair_units_bytes(transposed ? n : m, 64) / 16);
@@ -632,19 +647,20 @@ int pairs_body(const float *A, int64_t m, int64_t n, float *W, int iters, float 
                PairPlanes cut, hipEvent_t *ev = nullptr, const Monitor *mon = nullptr)
 {
     const Common &c = p.c;
-    if (cut == PairPlanes::none) NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, p.fw.most, 2 * kPairMost, st));
-    else NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.fw.most), 2 * kPairMost, 0.f, st));
+    const int64_t words = 2 * kPairMost + p.nredo[0] + p.nredo[1];      // maxima, and all tiles are formed from pairs at first
+    if (cut == PairPlanes::none) NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, p.fw.most, (int)words, st));
+    else NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.fw.most), words, 0.f, st));
     NMF_HIP(update_behind(p, m, n, true, true, nullptr, eps, st));
     const int nbw = factor_update_blocks(m), nbh = factor_update_blocks(n), k = p.sl.k[0];
     if (ev) NMF_HIP(hipEventRecord(*ev++, st));
     for (int it = 0; it < iters; ++it) {
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-        NMF_HIP(pass_over(p, m, n, false, nbw, st));
+        NMF_HIP(pass_over(p, A, m, n, false, nbw, st));
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
         NMF_HIP(update_behind(p, m, n, false, false, nullptr, eps, st));
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
-        NMF_HIP(pass_over(p, m, n, true, nbh, st));
+        NMF_HIP(pass_over(p, A, m, n, true, nbh, st));
         if (ev) NMF_HIP(hipEventRecord(*ev++, st));
         const bool report = mon && (!mon->last_only || it == iters - 1);
         NMF_HIP(update_behind(p, m, n, true, false, it == iters - 1 ? W : nullptr, eps, st, report ? mon->dpart : nullptr));
@@ -961,7 +977,7 @@ int sliced_ftx(const Sliced &e, const float *F, int64_t rows, int k, const float
         // all slices in one launch each: the slices of a tile of X run side by side and share its bytes
         if ((size_t)splits * 64 * (size_t)cols * nslices > e.ppart_elems) return fail(NMF_EHIP, "internal: sliced scratch too small%s");
         if (split) NMF_HIP(sliced_split(e, F, rows, k, st));
-        NMF_HIP(launch_pair_slices(X, rows, cols, k, sliced_factor(e, rows, sliced_ld(k)), sliced_ld(k), e.ppart, splits, rps, st));
+        NMF_HIP(launch_pair_slices(X, rows, cols, k, F, sliced_factor(e, rows, sliced_ld(k)), sliced_ld(k), e.ppart, splits, rps, st));
         if (keep) *keep = Partials{e.ppart, splits};
         else NMF_HIP(launch_sum_partials_slices(e.ppart, splits, k, cols, out, st, accumulate));
         return NMF_OK;
@@ -989,6 +1005,12 @@ int sliced_width(int64_t rows, int64_t cols, int k)
     return blocks >= 1024 && (k - 1) % 128 >= 64 ? 128 : 64;
 }
 
+int64_t sliced_pass_tiles(int64_t rows, int64_t cols, int k)
+{
+    const int width = sliced_width(rows, cols, k), slices = (k + width - 1) / width;
+    return pair_pass_tiles(cols, pair_splits(rows, cols, width / 32, slices), slices);
+}
+
 size_t sliced_pass_elems(int64_t rows, int64_t cols, int k)
 {
     const int width = sliced_width(rows, cols, k), slices = (k + width - 1) / width;
@@ -1013,6 +1035,8 @@ struct SlicedDense {
     PairMatrix pa, pt;
     float *pass;            // partials of a pass over A' or (A^T)'
     unsigned *most_g;       // maxima of the planes of a Gram matrix
+    unsigned *redo;         // tiles of either pass that are formed from the floats
+    int64_t nredo[2];
 };
 
 
@@ -1039,7 +1063,10 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, bool pairs
     if ((p.pairs = pairs)) {
         const size_t p1 = sliced_pass_elems(m, n, k), p2 = sliced_pass_elems(n, m, k);
         p.pass = cv.take<float>(p1 > p2 ? p1 : p2);
-        p.most_g = cv.take<unsigned>((size_t)sliced_ld(k) * kPairCopies);
+        p.nredo[0] = sliced_pass_tiles(m, n, k);
+        p.nredo[1] = sliced_pass_tiles(n, m, k);
+        p.most_g = cv.take<unsigned>((size_t)sliced_ld(k) * kPairCopies + p.nredo[0] + p.nredo[1]);
+        p.redo = p.most_g + sliced_ld(k) * kPairCopies;
         p.pa = carve_pair_matrix(cv, m, n);
         p.pt = carve_pair_matrix(cv, n, m);
     } else {
@@ -1063,9 +1090,9 @@ size_t sliced_dense_bytes(int64_t m, int64_t n, int k, bool pairs)
     return b;
 }
 
-// F^T X over X' = x, the planes of F in e.planes.  The partials are left where `u` says.
-int sliced_pass(const SlicedDense &p, int64_t rows, int k, const PairMatrix &x, int64_t cols, bool stream, SlicedUpdate *u,
-                hipStream_t st)
+// F^T X over X' = x, the planes of F in e.planes; X is A or (transposed) A^T.  The partials are left where `u` says.
+int sliced_pass(const SlicedDense &p, const float *F, int64_t rows, int k, const float *A, bool transposed, int64_t cols, bool stream,
+                SlicedUpdate *u, hipStream_t st)
 {
     static_assert(kPairSlices * 64 >= NMF_MU_MAX_K_SLICED, "one launch for all slices");
     const int width = sliced_width(rows, cols, k);
@@ -1073,7 +1100,15 @@ int sliced_pass(const SlicedDense &p, int64_t rows, int k, const PairMatrix &x, 
     a.ldf = sliced_ld(k);
     a.F = sliced_factor(p.e, rows, a.ldf);
     a.slice_units = a.slice_exps = a.slice_most = width;
-    a.X = x;
+    a.X = transposed ? p.pt : p.pa;
+    a.f = F;
+    a.f_row = k;
+    a.f_col = 1;
+    a.slice_f = width;
+    a.x = A;
+    a.x_row = transposed ? 1 : cols;
+    a.x_col = transposed ? rows : 1;
+    a.redo = p.redo + (transposed ? p.nredo[0] : 0);
     a.rows = rows;
     a.n = cols;
     a.nslices = (k + width - 1) / width;
@@ -1090,14 +1125,14 @@ int sliced_pass(const SlicedDense &p, int64_t rows, int k, const PairMatrix &x, 
     return NMF_OK;
 }
 
-// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps) and Yt its transpose, F rows x k with its planes in e.planes, X' = x; the planes of Yt
-// take their place.
-int sliced_pairs_update(const SlicedDense &p, const float *F, int64_t rows, int k, const PairMatrix &x, int64_t cols, float *Y, float *Yt,
-                        float eps, bool stream, hipStream_t st)
+// Y (k x cols) <- Y * (F^T X) / ((F^T F) Y + eps) and Yt its transpose, F rows x k with its planes in e.planes, X = A or (transposed)
+// A^T; the planes of Yt take their place.
+int sliced_pairs_update(const SlicedDense &p, const float *F, int64_t rows, int k, const float *A, bool transposed, int64_t cols, float *Y,
+                        float *Yt, float eps, bool stream, hipStream_t st)
 {
     const int ld = sliced_ld(k);
     SlicedUpdate u{};
-    if (int rc = sliced_pass(p, rows, k, x, cols, stream, &u, st)) return rc;
+    if (int rc = sliced_pass(p, F, rows, k, A, transposed, cols, stream, &u, st)) return rc;
     if (int rc = sliced_ftx(p.e, F, rows, k, F, k, p.g, false, st, false)) return rc;
     Partials den{};
     if (sliced_pairs(Y, cols, k)) {
@@ -1143,12 +1178,12 @@ int sliced_dense_body(const float *A, int64_t m, int64_t n, int k, float *W, flo
         const bool stream = stream_a(m, n, true);
         const int maxima = sliced_ld(k) * kPairCopies;
         NMF_HIP(launch_cut_pairs(A, m, n, p.pa, p.pt, p.e.most, maxima, st));
-        NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.most_g), maxima, 0.f, st));
+        NMF_HIP(launch_fill_f32(reinterpret_cast<float *>(p.most_g), maxima + p.nredo[0] + p.nredo[1], 0.f, st));
         NMF_HIP(launch_transpose(W, m, k, p.Wt, st));
         NMF_HIP(launch_split_pairs(W, m, k, sliced_factor(p.e, m, sliced_ld(k)), sliced_ld(k), st));
         for (int it = 0; it < iters; ++it) {
-            if (int rc = sliced_pairs_update(p, W, m, k, p.pa, n, H, p.Ht, eps, stream, st)) return rc;
-            if (int rc = sliced_pairs_update(p, p.Ht, n, k, p.pt, m, p.Wt, W, eps, stream, st)) return rc;
+            if (int rc = sliced_pairs_update(p, W, m, k, A, false, n, H, p.Ht, eps, stream, st)) return rc;
+            if (int rc = sliced_pairs_update(p, p.Ht, n, k, A, true, m, p.Wt, W, eps, stream, st)) return rc;
         }
         return NMF_OK;
     }
@@ -1600,7 +1635,7 @@ int nmf_mu_dense_profile(const float *A, int64_t m, int64_t n, int32_t k, float 
                 e = resident ? launch_resident(dry, p.resident, st)
                     : one_pass ? launch_one_pass(A, m, n, k, p.planes2, nullptr, c.ghp, factor_update_blocks(n), W, nullptr, p.ppart,
                                                c.gwp, eps, st, which == 1, which == 0)
-                    : p.pairs ? pass_over(p, m, n, which == 1, 0, st)
+                    : p.pairs ? pass_over(p, A, m, n, which == 1, 0, st)
                     : which == 0 ? launch_wta_pass(A, m, n, k, W, p.planes, true, p.ppart, s1, rps1, false, st, nullptr, 0, nullptr, mirrored)
                     : rows_plan  // the fused pass without its stores to W
                         ? launch_aht_rows(A, m, n, k, p.planes2, c.gh, W, p.planes, c.gwp, eps, st, false, nullptr,

@@ -35,90 +35,10 @@
 
 namespace nmfmu {
 
-
-__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
-// ---- exact fp32 products on the bf16 matrix cores ---------------------------------
-// A float x is cut into three pieces h + m + l = x, each with at most 8
-// significant bits (a bf16 holds 8): h = x truncated to its top 8 bits,
-// m = (x - h) truncated likewise, l = the rest.  Both subtractions are exact,
-// so the sum of the pieces is x bit for bit (for |x| >= 2^-110; below that the
-// last piece can fall under the bf16 range and is dropped by the hardware).  A
-// product of two pieces has at most 16 significant bits and is exact in the
-// fp32 accumulator, so the nine piece products of x y add up to the exact x y:
-// v_mfma_f32_32x32x16_bf16 on pieces computes the same sums of products as
-// v_mfma_f32_32x32x2_f32 on the floats, with the roundings of the running sums
-// only, at a quarter of the matrix-core time per product.
-//
-// Lane layout of v_mfma_f32_32x32x16_bf16: A_op (32 x 16): lane l holds
-// A_op[l % 32][8 (l / 32) .. 8 (l / 32) + 7]; B_op (16 x 32): lane l holds
-// B_op[8 (l / 32) .. + 7][l % 32]; D as for the fp32 instruction.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
 __device__ __forceinline__ f32x4 mfma_bf16_16(u32x4 a, u32x4 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-// Bit patterns of the three pieces as floats (their low 16 bits are zero, or
-// dropped by pack2: the top 16 bits are the bf16).
-__device__ __forceinline__ void split3(float x, unsigned &h, unsigned &m, unsigned &l)
-{
-    h = __float_as_uint(x) & 0xffff0000u;
-    const float r = x - __uint_as_float(h);
-    m = __float_as_uint(r) & 0xffff0000u;
-    l = __float_as_uint(r - __uint_as_float(m));
-}
-
-// Two bf16 in one register: `even` in the low half, `odd` in the high half.
-__device__ __forceinline__ unsigned pack2(unsigned even, unsigned odd)
-{
-    return __builtin_amdgcn_perm(odd, even, 0x07060302u);
-}
-
-// The streamed operand is cut with rounding instead of truncation, two floats at a time (packed
-// conversions, round to nearest even): h = x rounded to 8 significant bits, m = (x - h) rounded
-// likewise, l = the rest; again exact, |m| <= 2^-8 |x|, |l| <= 2^-16 |x| and m, l have either
-// sign.  Against a truncated operand (W or H from the planes: pieces of one sign, m < 2^-7,
-// l < 2^-15 of the float) the passes issue SIX products, h h, h m, m h, m m, h l, l h: the three
-// left out are below 2^-23 (twice) and 2^-31 of the term and signed like A's lower pieces.
-// With the first two of them added back the errors against 64 bits were the same to the second
-// digit on planted, uniform and repeated-value data (2003 x 4004 to 65536 x 1024, k = 20 to 64), and
-// where A and W hold one value each the results agreed to every digit printed: the matrix adder
-// drops bits of that size of every term that joins a grown accumulator (see the running totals
-// below).  They would cost 4 (32768 x 16384, k = 32) to 15 % (rank 256, one pass) of an iteration.
-// Against eight products of truncated pieces, which lose their low bits always downwards, the error
-// is smaller at the same lengths of accumulation: 6.0e-8 against 6.7e-8 at 4096 rows, mean signed
-// error -2e-9 against -28e-9.
-// A value above the largest bf16 (3.39e38) would round to infinity and is held at that bf16.
-__device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
-}
-
-// Pieces of two consecutive elements of an operand into register pr of its three planes.
-__device__ __forceinline__ void cut2(float x0, float x1, u32x4 (&at)[3], int pr)
-{
-    typedef short i16x2 __attribute__((ext_vector_type(2)));
-    const unsigned h = __builtin_bit_cast(unsigned, __builtin_elementwise_min(
-        __builtin_bit_cast(i16x2, cvt_pk_bf16(x0, x1)), i16x2{0x7f7f, 0x7f7f}));
-    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
-    const unsigned m = cvt_pk_bf16(r0, r1);
-    at[0][pr] = h;
-    at[1][pr] = m;
-    at[2][pr] = cvt_pk_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
 
 // Running totals of the piece passes.  The bf16 matrix instruction aligns its 16 products

@@ -21,6 +21,11 @@ __device__ __forceinline__ float tree_sum(float (&t)[N])
     return t[0];
 }
 
+__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
 // Row of the 32 x 32 accumulator held in register v of a lane in half `half`.
 __device__ __forceinline__ int acc_row(int v, int half) { return (v & 3) + 4 * half + 8 * (v >> 2); }
 
@@ -54,6 +59,80 @@ __device__ __forceinline__ void sum_tile_sets(const float *__restrict__ gtiles, 
     }
 }
 
+// ---- exact fp32 products on the bf16 matrix cores ---------------------------------
+// A float x is cut into three pieces h + m + l = x, each with at most 8
+// significant bits (a bf16 holds 8): h = x truncated to its top 8 bits,
+// m = (x - h) truncated likewise, l = the rest.  Both subtractions are exact,
+// so the sum of the pieces is x bit for bit (for |x| >= 2^-110; below that the
+// last piece can fall under the bf16 range and is dropped by the hardware).  A
+// product of two pieces has at most 16 significant bits and is exact in the
+// fp32 accumulator, so the nine piece products of x y add up to the exact x y:
+// v_mfma_f32_32x32x16_bf16 on pieces computes the same sums of products as
+// v_mfma_f32_32x32x2_f32 on the floats, with the roundings of the running sums
+// only, at a quarter of the matrix-core time per product.
+//
+// Lane layout of v_mfma_f32_32x32x16_bf16: A_op (32 x 16): lane l holds
+// A_op[l % 32][8 (l / 32) .. 8 (l / 32) + 7]; B_op (16 x 32): lane l holds
+// B_op[8 (l / 32) .. + 7][l % 32]; D as for the fp32 instruction.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Bit patterns of the three pieces as floats (their low 16 bits are zero, or
+// dropped by pack2: the top 16 bits are the bf16).
+__device__ __forceinline__ void split3(float x, unsigned &h, unsigned &m, unsigned &l)
+{
+    h = __float_as_uint(x) & 0xffff0000u;
+    const float r = x - __uint_as_float(h);
+    m = __float_as_uint(r) & 0xffff0000u;
+    l = __float_as_uint(r - __uint_as_float(m));
+}
+
+// Two bf16 in one register: `even` in the low half, `odd` in the high half.
+__device__ __forceinline__ unsigned pack2(unsigned even, unsigned odd)
+{
+    return __builtin_amdgcn_perm(odd, even, 0x07060302u);
+}
+
+// The streamed operand is cut with rounding instead of truncation, two floats at a time (packed
+// conversions, round to nearest even): h = x rounded to 8 significant bits, m = (x - h) rounded
+// likewise, l = the rest; again exact, |m| <= 2^-8 |x|, |l| <= 2^-16 |x| and m, l have either
+// sign.  Against a truncated operand (W or H from the planes: pieces of one sign, m < 2^-7,
+// l < 2^-15 of the float) the passes issue SIX products, h h, h m, m h, m m, h l, l h: the three
+// left out are below 2^-23 (twice) and 2^-31 of the term and signed like A's lower pieces.
+// With the first two of them added back the errors against 64 bits were the same to the second
+// digit on planted, uniform and repeated-value data (2003 x 4004 to 65536 x 1024, k = 20 to 64), and
+// where A and W hold one value each the results agreed to every digit printed: the matrix adder
+// drops bits of that size of every term that joins a grown accumulator (see the running totals
+// below).  They would cost 4 (32768 x 16384, k = 32) to 15 % (rank 256, one pass) of an iteration.
+// Against eight products of truncated pieces, which lose their low bits always downwards, the error
+// is smaller at the same lengths of accumulation: 6.0e-8 against 6.7e-8 at 4096 rows, mean signed
+// error -2e-9 against -28e-9.
+// A value above the largest bf16 (3.39e38) would round to infinity and is held at that bf16.
+__device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+
+// Pieces of two consecutive elements of an operand into register pr of its three planes.
+__device__ __forceinline__ void cut2(float x0, float x1, u32x4 (&at)[3], int pr)
+{
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
+    const unsigned h = __builtin_bit_cast(unsigned, __builtin_elementwise_min(
+        __builtin_bit_cast(i16x2, cvt_pk_bf16(x0, x1)), i16x2{0x7f7f, 0x7f7f}));
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    const unsigned m = cvt_pk_bf16(r0, r1);
+    at[0][pr] = h;
+    at[1][pr] = m;
+    at[2][pr] = cvt_pk_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+
 // ---- the same from pairs of halves --------------------------------------------------
 // A float scaled by a power of two into the range of a half (11 significant bits) is cut into h = x rounded to nearest
 // even and l = (x - h) rounded likewise: 22 bits and the two signs, so h + l is x or, for a quarter of all floats, its
@@ -65,6 +144,16 @@ __device__ __forceinline__ void sum_tile_sets(const float *__restrict__ gtiles, 
 //
 // Scales: a factor's column c has one for all of a pass, 2^(14 - exponent of its largest entry) (half_exponent of most[c]).
 // The streamed operand's columns belong to lanes, and their scales change along the rows (see the passes).
+//
+// What the scales leave out: an entry below 2^-2 of the scaled range (2^-17 of the largest) is off by up to 2^-25 there, and
+// a factor's, cut under a scale of its eight rows and brought to the column's, by up to 2^-23.  No scale holds every sum against that: a
+// small entry of a factor is all there is to a sum whose other terms meet zeros of the streamed matrix, and the
+// updates drive factors that far by themselves.  So every sum is looked at when it is done, against what is left out of it at most: 2^-23
+// of the sum of the streamed column's magnitudes, and 2^15 (a factor's largest) times 2^-25 for each of its entries that is small and not
+// zero, or simply 128 * 2^15 * (2^-23 + 2^-25) < 1 in its scaled range for up to 128 rows.  If any sum of a workgroup's tile is below kSure
+// times that, or not finite, the whole tile is formed again from the floats as they are (floats_tile); what is left out of the others
+// is 2^-22 of them at most.  Sums of uniform entries are 2^15 times as large as that asks.
+constexpr float kSure = 4194304.f;
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
@@ -115,27 +204,33 @@ __device__ __forceinline__ unsigned put_pairs(const float (&x)[8], u32x4 *unit, 
     return top;
 }
 
-// The exponent of a column's scale.
-__device__ __forceinline__ int column_exponent(const unsigned *__restrict__ most, int ld, int c)
+// The largest magnitude of a column, as bits; its half_exponent is that of the column's scale.
+__device__ __forceinline__ unsigned column_most(const unsigned *__restrict__ most, int ld, int c)
 {
     unsigned m[kPairCopies], top = 0;
 #pragma unroll
     for (int i = 0; i < kPairCopies; ++i) m[i] = most[i * ld + c];
 #pragma unroll
     for (int i = 0; i < kPairCopies; ++i) top = m[i] > top ? m[i] : top;
-    return half_exponent(top);
+    return top;
 }
 
-// A unit brought from its own scale to its column's.
-__device__ __forceinline__ u32x4 to_column_scale(u32x4 unit, unsigned exps, int exponent)
+// A unit brought from its own scale to its column's, in two steps: 2^-24 is the smallest half, and the largest of a unit reaches below
+// the last place of the scaled range 2^-40 further down.  fill: what a column of zeros gets in place of its entries, else zero; added
+// (FMA: 128 factors 2 % faster) or put in (64 factors 1 % faster).
+template <bool FMA>
+__device__ __forceinline__ u32x4 to_column_scale(u32x4 unit, unsigned exps, int exponent, _Float16 fill)
 {
-    const int d = exponent + 112 - (int)exps;
-    const _Float16 r = (_Float16)power_of_two(-(d > 40 ? 40 : d));
+    const int by = exponent + 112 - (int)exps, d = by > 40 ? 40 : by;
+    const _Float16 r = (_Float16)power_of_two(-(d >> 1)), s = (_Float16)power_of_two((d >> 1) - d);
+    const f16x2 ff = {fill, fill};
     u32x4 o;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const unsigned u = unit[i];
-        o[i] = __builtin_bit_cast(unsigned, __builtin_bit_cast(f16x2, u) * f16x2{r, r});
+        const f16x2 part = __builtin_bit_cast(f16x2, u) * f16x2{r, r};
+        if (FMA) o[i] = __builtin_bit_cast(unsigned, __builtin_elementwise_fma(part, f16x2{s, s}, ff));
+        else o[i] = __builtin_bit_cast(unsigned, part * f16x2{s, s}) | __builtin_bit_cast(unsigned, ff);
     }
     return o;
 }

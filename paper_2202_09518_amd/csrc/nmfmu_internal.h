@@ -85,16 +85,17 @@ bool stream_a(int64_t rows, int64_t n, bool two = false);
 inline size_t pair_units_bytes(int64_t rows, int64_t ld) { return (size_t)((rows + 7) / 8) * 2 * ld * 16; }
 inline size_t pair_exps_bytes(int64_t rows, int64_t ld) { return (size_t)((rows + 7) / 8) * ld; }
 // X' of a matrix X (rows x cols, contracted over its rows): the same units, cut under one scale per column and kPairBlock
-// rows, whose inverse is inv[(row / kPairBlock) * ld + column]; rows are filled up to whole blocks with zeros.
+// rows; scale[(row / kPairBlock) * ld + column] = {its inverse, what the halves leave out of these rows' sum with a factor in its scaled range
+// at most (see kSure)}; rows are filled up to whole blocks with zeros.
 constexpr int kPairBlock = 128;
 struct PairMatrix {
     void *units;              // pair_matrix_units(rows, ld) bytes
-    float *inv;               // pair_matrix_scales(rows, ld) bytes
+    float2 *scale;            // pair_matrix_scales(rows, ld) bytes
     int64_t ld;               // pair_matrix_ld(cols)
 };
 inline int64_t pair_matrix_ld(int64_t cols) { return (cols + 63) / 64 * 64; }
 inline size_t pair_matrix_units(int64_t rows, int64_t ld) { return (size_t)((rows + kPairBlock - 1) / kPairBlock) * kPairBlock * ld * 4; }
-inline size_t pair_matrix_scales(int64_t rows, int64_t ld) { return (size_t)((rows + kPairBlock - 1) / kPairBlock) * ld * 4; }
+inline size_t pair_matrix_scales(int64_t rows, int64_t ld) { return (size_t)((rows + kPairBlock - 1) / kPairBlock) * ld * sizeof(float2); }
 // A' and (A^T)' of A (m x n, any alignment) in one reading; clear (optional): words to set to zero on the way.
 hipError_t launch_cut_pairs(const float *A, int64_t m, int64_t n, const PairMatrix &a, const PairMatrix &at, unsigned *clear, int nclear,
                             hipStream_t st);
@@ -110,6 +111,10 @@ struct PairPass {
     int ldf;
     int64_t slice_units, slice_exps, slice_most;      // from slice to slice: in units of 16 bytes, bytes and words
     PairMatrix X;
+    // F and X themselves, for tiles whose sums the halves cannot hold: entries (i, c) of the first slice of F and (i, j) of X
+    const float *f, *x;
+    int64_t f_row, f_col, slice_f, x_row, x_col;
+    unsigned *redo;                                   // pair_pass_tiles words, zero before a run's first pass: which tiles they are
     float *ppart;
     int64_t slice_ppart;
     int64_t rows, n, rps;                             // rps: rows of a split, a multiple of kPairBlock
@@ -125,15 +130,16 @@ struct PairPass {
 // tiles: 2 or 4.  stream: X' is marked for early eviction.
 hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream_t st);
 int pair_splits(int64_t rows, int64_t cols, int tiles, int nslices);
+inline int64_t pair_pass_tiles(int64_t cols, int splits, int nslices) { return (cols + 255) / 256 * splits * nslices; }
 inline int64_t pair_rows_per_split(int64_t rows, int splits)
 {
     const int64_t blocks = (rows + kPairBlock - 1) / kPairBlock;
     return (blocks + splits - 1) / splits * kPairBlock;
 }
 // The same product with X itself, cut as it is loaded (16-byte aligned, n % 4 == 0), for all slices of 64 of k factors whose
-// planes have ld columns per row group; partials of slice z at ppart + z * splits * 64 * n.  rps: a multiple of 16.
-hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const PairFactor &f, int ld, float *ppart,
-                              int splits, int64_t rps, hipStream_t st);
+// planes f (of F, rows x k) have ld columns per row group; partials of slice z at ppart + z * splits * 64 * n.  rps: a multiple of 16.
+hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const float *F, const PairFactor &f, int ld,
+                              float *ppart, int splits, int64_t rps, hipStream_t st);
 // Update of ranks above 64 from the partials of its products (see sliced_update_kernel).
 struct SlicedUpdate {
     float *X, *Xt;                // k x len, len x k

@@ -22,6 +22,7 @@ __global__ __launch_bounds__(512) void cut_pairs_kernel(const float *__restrict_
 {
     __shared__ float tile[kCutTile][kCutTile + 1];
     __shared__ unsigned part[4][kCutTile];
+    __shared__ float left[4][kCutTile];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0)
         for (int i = tid; i < nclear; i += 512) clear[i] = 0u;
@@ -77,6 +78,16 @@ __global__ __launch_bounds__(512) void cut_pairs_kernel(const float *__restrict_
         for (int i = 0; i < 4; ++i) top = part[i][at] > top ? part[i][at] : top;
         const int e = half_exponent(top);
         const float sc = power_of_two(14 - e);
+        // what the halves leave out (see kSure), a little more for the rounding of this sum
+        float sum = 0.f, small = 0.f;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            const float b = __builtin_fabsf(v[i]);
+            sum += b * sc;
+            small += b * sc < 0.25f && b > 0.f ? 1.f : 0.f;
+        }
+        left[quarter][at] = sum * (1.0001f * 0x1p-23f) + small * 0x1p-10f;
+        __syncthreads();
         const PairMatrix &x = side ? at_ : a;
         const int64_t col = (side ? r0 : c0) + at, ld = x.ld, block = side ? bc : br;
         if (col < ld) {
@@ -89,7 +100,10 @@ __global__ __launch_bounds__(512) void cut_pairs_kernel(const float *__restrict_
                 dst[(2 * g) * ld] = o[0];
                 dst[(2 * g + 1) * ld] = o[1];
             }
-            if (quarter == 0) x.inv[block * ld + col] = power_of_two(e - 14);
+            if (quarter == 0) {
+                const float inv = top ? power_of_two(e - 14) : 0.f;
+                x.scale[block * ld + col] = float2{inv, inv * ((left[0][at] + left[1][at]) + (left[2][at] + left[3][at]))};
+            }
         }
         __syncthreads();
     }
@@ -127,6 +141,244 @@ __global__ __launch_bounds__(256) void split_pairs_kernel(const float *__restric
 }
 
 // ---------------------------------------------------------------------------
+// A workgroup's tile of F^T X from the floats as they are, cut into bf16 pieces (which have their exponents), for tiles whose sums the halves
+// cannot hold (kSure): rows r0 .. r1, k of 32 T factors, a lane's two columns col, the totals as the passes have them.  F (entry
+// (i, c) at f + i * fr + c * fc) goes through LDS, 64 rows at a time, double buffered, cut on the way; X (entry (i, j) at
+// x + i * xr + j * xc) straight into registers, D steps of 16 rows ahead, along its rows or along its columns, four entries
+// in one load or one.  What bounds it is the one wave per SIMD of the pass that it is part of: cutting and matrix instructions do not overlap.
+// A of two blocks on the diagonal, all tiles so, 16384 x 8192, 64 factors: 150 us along the rows, 180 along the columns, where
+// pairs take 98 and the mirrored plan, on pieces cut before and a transposed copy, 110 to 128; whole runs there 0.7 to 0.85 of the
+// mirrored plan's speed.  On the fp32 instruction 190 and 200.  As a launch of its own it would cost every pass 3 us.
+// ---------------------------------------------------------------------------
+typedef const __attribute__((address_space(1))) float *GlobalFloats;      // read by global loads, wherever the pointer comes from
+struct Floats {
+    GlobalFloats f, x;
+    int64_t fr, fc, xr, xc;
+};
+
+__device__ __forceinline__ uintptr_t uniform(uintptr_t p)
+{
+    return (uintptr_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)p) |
+           (uintptr_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(p >> 32)) << 32;
+}
+
+enum class Along { rows, columns, columns4 };
+
+template <int T, int D, Along ALONG>
+__device__ __forceinline__ void floats_tile(u32x4 *stage, const Floats &o, int k, int64_t r0, int64_t r1, const int64_t (&col)[2],
+                                            f32x16 (&tot)[T][2])
+{
+    constexpr int KP = 32 * T, kRows = 64, kSteps = kRows / 16, kUnits = kRows / 8 * 3 * KP;
+    constexpr int kEach = KP / 32;           // row groups of F a thread cuts in a block
+    constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
+    const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, half = lane >> 5;
+    const int fc = tid & (KP - 1), fg = tid / KP;                // group e of a thread: fg + e * 256 / KP, column fc
+    const GlobalFloats f = o.f + (fc < k ? fc : 0) * o.fc;
+    const GlobalFloats x[2] = {o.x + col[0] * o.xc + 16 * half, o.x + col[1] * o.xc + 16 * half};
+    const unsigned rowb = (unsigned)o.xr * 4u;
+    unsigned xoff[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) xoff[q] = (unsigned)(16 * half) * rowb + (unsigned)col[q] * 4u;
+    struct Group { float v[8]; };
+    auto load_f = [&](Group &u, int64_t ib, int e) {
+        const int64_t i = ib + 8 * (fg + e * (256 / KP));
+        if (ib + kRows <= r1) {
+            const GlobalFloats p = f + i * o.fr;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) u.v[v] = p[v * o.fr];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                const float t = f[(i + v < r1 ? i + v : r1 - 1) * o.fr];
+                u.v[v] = i + v < r1 ? t : 0.f;
+            }
+        }
+    };
+    auto store_f = [&](const Group &u, u32x4 *dst, int e) {
+        u32x4 p[3];
+#pragma unroll
+        for (int pr = 0; pr < 4; ++pr) {
+            unsigned h[2], m[2], l[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) split3(fc < k ? u.v[2 * pr + b] : 0.f, h[b], m[b], l[b]);
+            p[0][pr] = pack2(h[0], h[1]);
+            p[1][pr] = pack2(m[0], m[1]);
+            p[2][pr] = pack2(l[0], l[1]);
+        }
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) dst[((fg + e * (256 / KP)) * 3 + pl) * KP + fc] = p[pl];
+    };
+    // A step contracts 16 rows: the s-th 8 rows (s = 0, 1) of either half of 32, so that a lane's two steps along a column are
+    // 64 consecutive bytes, requested together.
+    struct Step { float v[2][8]; };
+    auto load_x = [&](Step &t, int64_t ib, int s) {      // ib: of the 32 rows
+        if (ALONG == Along::rows) {
+            const int64_t i = ib + 8 * s;
+            int64_t av = r1 - i;
+            av = av < 0 ? 0 : (av > 24 ? 24 : av);
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)uniform((uintptr_t)(o.x + (av ? i : 0) * o.xr)), 0,
+                                                                               __builtin_amdgcn_readfirstlane((int)((unsigned)av * rowb)), kRsrcFlags);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < 8; ++v)
+                    t.v[q][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, xoff[q] + v * rowb, 0, 0));
+        } else if (ib + 32 <= r1) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const GlobalFloats p = x[q] + ib + 8 * s;
+                if (ALONG == Along::columns4) {
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const f32x4 u = *(const __attribute__((address_space(1))) f32x4 *)(p + 4 * b);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) t.v[q][4 * b + v] = u[v];
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) t.v[q][v] = p[v];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    const int64_t i = ib + 16 * half + 8 * s + v;
+                    const float u = x[q][(i < r1 ? i : r1 - 1) - 16 * half];
+                    t.v[q][v] = i < r1 ? u : 0.f;
+                }
+        }
+    };
+    f32x16 acc[T][2];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) tot[t][q] = f32x16{0};
+    Step xs[D];
+    Group fu[kEach];
+#pragma unroll
+    for (int s = 0; s < D; ++s) load_x(xs[s], r0 + 16 * (s & ~1), s & 1);
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) load_f(fu[e], r0, e);
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) store_f(fu[e], stage, e);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t i = r0; i < r1; i += kRows) {
+        const u32x4 *mine = stage + buf * kUnits;
+        u32x4 *next = stage + (buf ^ 1) * kUnits;
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+            if (s == 0) {      // F of the next block, cut and stored after the last steps
+#pragma unroll
+                for (int e = 0; e < kEach; ++e) load_f(fu[e], i + kRows, e);
+            }
+            u32x4 wt[T][3];
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) wt[t][pl] = mine[((2 * (s & ~1) + 2 * half + (s & 1)) * 3 + pl) * KP + 32 * t + jj];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                u32x4 at[3];
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) cut2(xs[s % D].v[q][2 * pr], xs[s % D].v[q][2 * pr + 1], at, pr);
+                constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PA[6] = {0, 1, 2, 0, 1, 0};   // smallest first
+#pragma unroll
+                for (int e = 0; e < 6; ++e)
+#pragma unroll
+                    for (int t = 0; t < T; ++t)
+                        acc[t][q] = mfma_bf16(wt[t][PW[e]], at[PA[e]], s == 0 && e == 0 ? f32x16{0} : acc[t][q]);
+            }
+            if (s & 1) {
+                load_x(xs[(s - 1) % D], i + 16 * (s - 1 + D), 0);
+                load_x(xs[s % D], i + 16 * (s - 1 + D), 1);
+            }
+#pragma unroll
+            for (int e = 0; e < kEach; ++e)
+                if (s == kSteps - 1 - (kEach - 1 - e) * 2 / kEach) store_f(fu[e], next, e);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) tot[t][q] += acc[t][q];
+        __syncthreads();    // the next block is written, this one is read
+        buf ^= 1;
+    }
+}
+
+template <int T, int D>
+__device__ __forceinline__ void exact_tile(u32x4 *stage, const Floats &o, int k, int64_t r0, int64_t r1, const int64_t (&col)[2],
+                                           f32x16 (&tot)[T][2])
+{
+    // four along a column of X: r0 is a multiple of 16, and so is r1 or it is the end of that column
+    if (o.xc == 1) floats_tile<T, D, Along::rows>(stage, o, k, r0, r1, col, tot);
+    else if ((o.xc & 3) == 0 && ((uintptr_t)o.x & 15u) == 0) floats_tile<T, D, Along::columns4>(stage, o, k, r0, r1, col, tot);
+    else floats_tile<T, D, Along::columns>(stage, o, k, r0, r1, col, tot);
+}
+
+// A kernel's arguments once more, for the few workgroups that need all of them: kept in scalar registers through the passes they
+// cost the others 2 to 5 percent.
+template <class A>
+__device__ __forceinline__ const __attribute__((address_space(4))) A *arguments_again()
+{
+    uintptr_t p = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return (const __attribute__((address_space(4))) A *)p;
+}
+
+// Whether the sums of a lane in one column are at least kSure times what may be left out of them, and finite.
+struct Sums {
+    float least = __builtin_inff(), most = 0.f;
+    __device__ __forceinline__ void add(float x, float y)
+    {
+        least = __builtin_elementwise_minimum(__builtin_elementwise_minimum(least, __builtin_fabsf(x)), __builtin_fabsf(y));
+        most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(most, __builtin_fabsf(x)), __builtin_fabsf(y));
+    }
+    __device__ __forceinline__ bool sure(float left) const { return least >= kSure * left && most < __builtin_inff(); }
+};
+// A factor of a slice that is zero (or is not there) is sure of itself: it is staged as the largest power of two, and its exponent makes its
+// sums zero.
+constexpr int kNoFactor = -4096;
+constexpr _Float16 kLargeHalf = (_Float16)32768.f;
+
+// Passes for which a tile whose sums were not sure is formed from the floats without another try of the pairs.
+constexpr int kRedoPasses = 16;
+
+// 32 T factors from f0 on of the workgroup's tile of pair_pass_kernel.
+template <int T, int D>
+__device__ __forceinline__ void from_floats(u32x4 *stage, int f0)
+{
+    const auto *a = arguments_again<PairPass>();
+    const int gx = (int)((a->n + 255) / 256), within = blockIdx.x >> 3, z = within % a->nslices;
+    const int t8 = (within / a->nslices) * 8 + (blockIdx.x & 7), bx = t8 % gx, by = t8 / gx, k = a->k[z];
+    if (f0 >= k) return;
+    const int lane = threadIdx.x & 63, jj = lane & 31, half = lane >> 5;
+    const int64_t n = a->n, jw = (int64_t)bx * 256 + (threadIdx.x & ~63u);
+    const int64_t r0 = (int64_t)by * a->rps, r1 = (r0 + a->rps < a->rows) ? r0 + a->rps : a->rows;
+    const Floats o{(GlobalFloats)(a->f + z * a->slice_f + f0 * a->f_col), (GlobalFloats)a->x, a->f_row, a->f_col, a->x_row, a->x_col};
+    int64_t col[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) col[q] = jw + 32 * q + jj < n ? jw + 32 * q + jj : n - 1;
+    f32x16 tot[T][2];
+    exact_tile<T, D>(stage, o, k - f0, r0, r1, col, tot);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (jw + 32 * q + jj >= n) continue;
+        float *dst = a->ppart + z * a->slice_ppart + ((int64_t)by * k + f0) * n + col[q];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int f = 32 * t + acc_row(v, half);
+                if (f0 + f < k) dst[(int64_t)f * n] = tot[t][q][v];
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // The pass on pairs with both operands cut before: P = F^T X for slices of 32 T factors.  Workgroup = 256 columns, wave = 64 of
 // them (two tiles of 32), and all four waves walk the same 16-row steps; the planes of F are staged in LDS for the four, a block
 // of 8 steps at a time, double buffered, and brought to their columns' scales on the way; X' is loaded straight into operand
@@ -149,6 +401,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     constexpr int kEach = kUnits / 256 / kSteps;       // a thread stages so many per step
     extern __shared__ u32x4 pst[];                     // two blocks
     __shared__ int fexp[KP];
+    __shared__ int redone;                             // the tile's sums are not sure
     const int64_t rows = a.rows, n = a.n, ldx = a.X.ld;
     const int gx = (int)((n + 255) / 256), ldf = a.ldf;
     const int L = blockIdx.x, within = L >> 3;
@@ -184,10 +437,13 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     const unsigned xpiece = (unsigned)(ldx * 16);
 
     f32x16 acc[T][2], tot[T][2], sum[T][2];
+    float unit[2] = {0.f, 0.f};            // what is left out of the sums of a column at most
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int q = 0; q < 2; ++q) tot[t][q] = sum[t][q] = f32x16{0};
+    const int64_t redo = (int64_t)t8 * a.nslices + z;
+    const int asked = a.redo[redo];        // formed from the floats from a pass before on?  (Looked at when the first operands are there.)
     struct Stage { u32x4 x[2][2]; };
     Stage xs[D];
     auto load_x = [&](Stage &s, int64_t ib) {
@@ -202,8 +458,11 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     // planes of the block of rows from ib on; groups past the last row read as zero
     const int64_t groups = (rows + 7) >> 3;
     const int fc = tid & (KP - 1), fg = tid / KP;      // unit e of a thread: row group and piece fg + e * 256 / KP, column fc
-    const int fce = fc < k ? column_exponent(most, ldf, fc) : -112;
-    if (tid < KP) fexp[tid] = fce - 14;                // read after the first barrier
+    const unsigned ftop = fc < k ? column_most(most, ldf, fc) : 0u;
+    const int fce = half_exponent(ftop);
+    const _Float16 fill = ftop ? (_Float16)0.f : kLargeHalf;
+    if (tid < KP) fexp[tid] = ftop ? fce - 14 : kNoFactor;      // read after the first barrier
+    if (tid == 0) redone = 0;
     struct Rsrc { __amdgpu_buffer_rsrc_t u, e; };
     auto rsrc_f = [&](int64_t ib) {
         int64_t ng = ib < r1 ? groups - (ib >> 3) : 0;
@@ -226,7 +485,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     };
     auto store_f = [&](const Units &t, u32x4 *dst, int s) {
 #pragma unroll
-        for (int e = 0; e < kEach; ++e) dst[(s * kEach + e) * 256 + tid] = to_column_scale(t.u[e], t.e[e], fce);
+        for (int e = 0; e < kEach; ++e) dst[(s * kEach + e) * 256 + tid] = to_column_scale<T == 4>(t.u[e], t.e[e], fce, fill);
     };
 
 #pragma unroll
@@ -243,69 +502,86 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
         for (int s = 0; s < kSteps; ++s) store_f(first[s], pst, s);
     }
     __syncthreads();
-    int buf = 0;
-    for (int64_t i = r0; i < r1; i += kPairBlock) {
-        const Rsrc rf = rsrc_f(i + kPairBlock);
-        u32x4 *mine = pst + buf * kUnits, *next = pst + (buf ^ 1) * kUnits;
-        float inv[2];
+    const int again = __builtin_amdgcn_readfirstlane(asked);
+    if (!again) {
+        int buf = 0;
+        for (int64_t i = r0; i < r1; i += kPairBlock) {
+            const Rsrc rf = rsrc_f(i + kPairBlock);
+            u32x4 *mine = pst + buf * kUnits, *next = pst + (buf ^ 1) * kUnits;
+            float inv[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) inv[q] = a.X.inv[i / kPairBlock * ldx + xcol[q]];
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s) {
-            load_f(th[s % 3], rf, s);      // the next block's planes, stored two steps later
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                u32x4 wt[2];
-#pragma unroll
-                for (int pl = 0; pl < 2; ++pl) wt[pl] = mine[((2 * s + half) * 2 + pl) * KP + 32 * t + jj];
-                constexpr int PW[3] = {1, 0, 0}, PA[3] = {0, 1, 0};   // smallest first
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        acc[t][q] = mfma_f16(wt[PW[e]], xs[s % D].x[q][PA[e]], s == 0 && e == 0 ? f32x16{0} : acc[t][q]);
+            for (int q = 0; q < 2; ++q) {
+                const float2 s = a.X.scale[i / kPairBlock * ldx + xcol[q]];
+                inv[q] = s.x;
+                unit[q] += s.y;
             }
-            load_x(xs[s % D], i + 16 * (s + D));
-            if (s >= 2) store_f(th[(s - 2) % 3], next, s - 2);
-            __builtin_amdgcn_sched_barrier(0);
-        }
 #pragma unroll
-        for (int s = kSteps - 2; s < kSteps; ++s) store_f(th[s % 3], next, s);
+            for (int s = 0; s < kSteps; ++s) {
+                load_f(th[s % 3], rf, s);      // the next block's planes, stored two steps later
 #pragma unroll
-        for (int t = 0; t < T; ++t)
+                for (int t = 0; t < T; ++t) {
+                    u32x4 wt[2];
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+                    for (int pl = 0; pl < 2; ++pl) wt[pl] = mine[((2 * s + half) * 2 + pl) * KP + 32 * t + jj];
+                    constexpr int PW[3] = {1, 0, 0}, PA[3] = {0, 1, 0};   // smallest first
 #pragma unroll
-                for (int v = 0; v < 16; ++v) tot[t][q][v] = __builtin_fmaf(acc[t][q][v], inv[q], tot[t][q][v]);
-        if (DEEP && ((i - r0) / kPairBlock & 7) == 7) {
+                    for (int e = 0; e < 3; ++e)
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+                            acc[t][q] = mfma_f16(wt[PW[e]], xs[s % D].x[q][PA[e]], s == 0 && e == 0 ? f32x16{0} : acc[t][q]);
+                }
+                load_x(xs[s % D], i + 16 * (s + D));
+                if (s >= 2) store_f(th[(s - 2) % 3], next, s - 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int s = kSteps - 2; s < kSteps; ++s) store_f(th[s % 3], next, s);
 #pragma unroll
             for (int t = 0; t < T; ++t)
 #pragma unroll
-                for (int q = 0; q < 2; ++q) sum[t][q] += tot[t][q], tot[t][q] = f32x16{0};
-        }
-        __syncthreads();    // the next block's planes are written, this block's are read
-        buf ^= 1;
-    }
-    if (DEEP) {
+                for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int t = 0; t < T; ++t)
+                    for (int v = 0; v < 16; ++v) tot[t][q][v] = __builtin_fmaf(acc[t][q][v], inv[q], tot[t][q][v]);
+            if (DEEP && ((i - r0) / kPairBlock & 7) == 7) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) tot[t][q] += sum[t][q];
-    }
-
+                for (int t = 0; t < T; ++t)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int64_t c = jw + 32 * q + jj;
-        if (c >= n) continue;
-        float *dst = ppart + (int64_t)by * k * n + c;
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int f = 32 * t + acc_row(v, half);
-                if (f < k) dst[(int64_t)f * n] = ldexpf(tot[t][q][v], fexp[f]);
+                    for (int q = 0; q < 2; ++q) sum[t][q] += tot[t][q], tot[t][q] = f32x16{0};
             }
+            __syncthreads();    // the next block's planes are written, this block's are read
+            buf ^= 1;
+        }
+        if (DEEP) {
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) tot[t][q] += sum[t][q];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int64_t c = jw + 32 * q + jj;
+            if (c >= n) continue;
+            Sums sums;
+            float *dst = ppart + (int64_t)by * k * n + c;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int f = 32 * t + acc_row(v, half);
+                    if (v % 2 == 0) sums.add(tot[t][q][v], tot[t][q][v + 1]);
+                    if (f < k) dst[(int64_t)f * n] = ldexpf(tot[t][q][v], fexp[f]);
+                }
+            if (!sums.sure(unit[q])) redone = 1;
+        }
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(redone)) return;
     }
+    // so are the next passes' tiles: such data stays so for a while
+    if (tid == 0) a.redo[redo] = again ? again - 1 : kRedoPasses;
+    // as many factors at once as the registers hold
+    constexpr int kAtOnce = OCC == 1 ? 2 : 1, kAhead = OCC == 1 ? 4 : 2;
+    from_floats<kAtOnce, kAhead>(pst, 0);
+    if (T > kAtOnce) from_floats<kAtOnce, kAhead>(pst, 32 * kAtOnce);
 }
 
 // ---------------------------------------------------------------------------
@@ -328,10 +604,20 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
 // the slices of one tile of A (slab x row split) 8 workgroups apart, i.e. on the same XCD at about the same time, so that A
 // comes from HBM once and from that XCD's L2 for the other slices (default cache policy).  Slice z reads columns 64 z .. of
 // the planes and writes ppart + z * slice_ppart; it holds min(64, ktotal - 64 z) factors.
-__global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
-    const float *__restrict__ A, PairFactor F, int ldf, float *__restrict__ ppart, int64_t rows, int64_t n, int k, int64_t rps, int gx,
-    int gy, int nslices, int64_t slice_ppart)
+struct PairSlices {
+    const float *X, *f;                // X; F itself, rows x k
+    PairFactor F;
+    float *ppart;
+    int64_t rows, n, rps, slice_ppart;
+    int ldf, k, gx, gy, nslices;
+};
+__global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(const PairSlices args)
 {
+    const float *A = args.X;
+    const PairFactor &F = args.F;
+    const int ldf = args.ldf, gx = args.gx, gy = args.gy, nslices = args.nslices;
+    const int64_t rows = args.rows, n = args.n, rps = args.rps;
+    int k = args.k;
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     constexpr int KP = 64;
@@ -339,8 +625,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
     constexpr int kSteps = 6;                          // 16-row steps per group of staged planes
     constexpr int kUnits = kSteps * 2 * 2 * KP;        // 16-byte units of planes in a group
     constexpr float kMost = 32768.f;
-    __shared__ u32x4 pst[2][kUnits];
+    __shared__ u32x4 lds[2 * kUnits];                  // two groups; as much as floats_tile needs
     __shared__ int fexp[KP];
+    __shared__ int redone;                             // the tile's sums are not sure
     const int L = blockIdx.x, within = L >> 3;
     const int z = within % nslices;
     const int t8 = (within / nslices) * 8 + (L & 7);
@@ -349,7 +636,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
     const u32x4 *units = static_cast<const u32x4 *>(F.units) + KP * z;
     const unsigned char *exps = F.exps + KP * z;
     const unsigned *fmost = F.most + KP * z;
-    ppart += (int64_t)z * slice_ppart;
+    float *ppart = args.ppart + (int64_t)z * args.slice_ppart;
     k = (k - 64 * z < 64) ? k - 64 * z : 64;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -364,8 +651,11 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
     const unsigned loff = (unsigned)(half * 8) * rowb + (unsigned)col * 4;
     const int64_t ngroups = (rows + 7) >> 3;
     const int fc = tid & 63, fg = tid >> 6;      // unit e of a thread: row group and piece fg + 4 e, column fc
-    const int fce = fc < k ? column_exponent(fmost, ldf, fc) : -112;
-    if (tid < KP) fexp[tid] = fce - 14;          // read after the first barrier
+    const unsigned ftop = fc < k ? column_most(fmost, ldf, fc) : 0u;
+    const int fce = half_exponent(ftop);
+    const _Float16 fill = ftop ? (_Float16)0.f : kLargeHalf;
+    if (tid < KP) fexp[tid] = ftop ? fce - 14 : kNoFactor;      // read after the first barrier
+    if (tid == 0) redone = 0;
 
     f32x16 acc[2][2], tot[2][2];
 #pragma unroll
@@ -373,7 +663,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
 #pragma unroll
         for (int q = 0; q < 2; ++q) acc[t][q] = f32x16{0}, tot[t][q] = f32x16{0};
     // per column: scale, its inverse, largest magnitude since the last join
-    float sc[2], inv[2], most[2] = {0.f, 0.f};
+    float sc[2], inv[2], most[2] = {0.f, 0.f}, unit[2] = {0.f, 0.f};      // unit: what is left out at most, one in the scaled range of each join
 #pragma unroll
     for (int q = 0; q < 2; ++q) sc[q] = power_of_two(126), inv[q] = power_of_two(-126);
 
@@ -405,7 +695,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
     };
     auto store_third = [&](const Third &p, int buf, int part) {
 #pragma unroll
-        for (int e = 0; e < 2; ++e) pst[buf][(2 * part + e) * 256 + tid] = to_column_scale(p.u[e], p.e[e], fce);
+        for (int e = 0; e < 2; ++e) lds[buf * kUnits + (2 * part + e) * 256 + tid] = to_column_scale<true>(p.u[e], p.e[e], fce, fill);
     };
     // the accumulators join the totals; the scales follow the maxima
     auto join = [&]() {
@@ -419,6 +709,8 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
                     acc[t][q][v] = 0.f;
                 }
             const float both = fmaxf(most[q], __shfl_xor(most[q], 32));
+            // under the first scale `most` knows all that was added up; a column of zeros has no unit
+            unit[q] += both > 0.f || sc[q] < power_of_two(126) ? inv[q] : 0.f;
             if (both > 0.f) {
                 const int e = half_exponent(__float_as_uint(both));
                 sc[q] = power_of_two(11 - e > 126 ? 126 : 11 - e);
@@ -432,7 +724,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) wt[t][pl] = pst[buf][((2 * st + half) * 2 + pl) * KP + 32 * t + jj];
+            for (int pl = 0; pl < 2; ++pl) wt[t][pl] = lds[buf * kUnits + ((2 * st + half) * 2 + pl) * KP + 32 * t + jj];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -486,20 +778,39 @@ __global__ __launch_bounds__(64 * kWtaWaves, 2) void wta_pass_pair_kernel(
         buf ^= 1;
     }
     join();
-
-    if (colr < n) {
-        float *dst = ppart + (int64_t)by * k * n + colr;
+    float *dst = ppart + (int64_t)by * k * n + colr;
+    auto store = [&](int t, const f32x16 (&sums)[2], bool scaled) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int c = 32 * t + acc_row(v, half);
+            const int e = scaled ? fexp[c] : 0;
+            if (c < k && colr < n) *reinterpret_cast<f32x2 *>(dst + (int64_t)c * n) = f32x2{ldexpf(sums[0][v], e), ldexpf(sums[1][v], e)};
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        Sums sums;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int c = 32 * t + acc_row(v, half);
-                if (c < k) {
-                    const int e = fexp[c];
-                    *reinterpret_cast<f32x2 *>(dst + (int64_t)c * n) = f32x2{ldexpf(tot[t][0][v], e), ldexpf(tot[t][1][v], e)};
-                }
-            }
+            for (int v = 0; v < 16; v += 2) sums.add(tot[t][q][v], tot[t][q][v + 1]);
+        if (colr < n && !sums.sure(unit[q])) redone = 1;
     }
+    store(0, tot[0], true);
+    store(1, tot[1], true);
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(redone)) return;
+    // 32 factors at a time, as many as the registers hold
+    auto again = [&](int t) {
+        const auto *b = arguments_again<PairSlices>();
+        const Floats floats{(GlobalFloats)(b->f + KP * z + 32 * t), (GlobalFloats)b->X, b->k, 1, b->n, 1};
+        const int64_t cols[2] = {col, col + 1};
+        f32x16 some[1][2];
+        floats_tile<1, 2, Along::rows>(lds, floats, k - 32 * t, r0, r1, cols, some);
+        store(t, some[0], false);
+    };
+    again(0);
+    if (k > 32) again(1);
 }
 
 // ---------------------------------------------------------------------------
@@ -673,15 +984,15 @@ hipError_t launch_stack(const StackedRuns &runs, int count, bool in, float *Wt, 
     return hipGetLastError();
 }
 
-hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const PairFactor &f, int ld, float *ppart,
-                              int splits, int64_t rps, hipStream_t st)
+hipError_t launch_pair_slices(const float *X, int64_t rows, int64_t n, int k, const float *F, const PairFactor &f, int ld,
+                              float *ppart, int splits, int64_t rps, hipStream_t st)
 {
     if (wta_planes_only_width(X, n) != 64 || rps % 16) return hipErrorInvalidValue;
     const int nslices = (k + 63) / 64;
     const int gx = (int)((n + 255) / 256), gy = splits;
     const int64_t tiles8 = ((int64_t)gx * gy + 7) / 8 * 8;
-    hipLaunchKernelGGL(wta_pass_pair_kernel, dim3((unsigned)(tiles8 * nslices)), dim3(64 * kWtaWaves), 0, st, X, f, ld, ppart, rows, n,
-                       k, rps, gx, gy, nslices, (int64_t)splits * 64 * n);
+    const PairSlices args{X, F, f, ppart, rows, n, rps, (int64_t)splits * 64 * n, ld, k, gx, gy, nslices};
+    hipLaunchKernelGGL(wta_pass_pair_kernel, dim3((unsigned)(tiles8 * nslices)), dim3(64 * kWtaWaves), 0, st, args);
     return hipGetLastError();
 }
 
@@ -703,7 +1014,7 @@ static hipError_t pair_pass_launch(dim3 grid, hipStream_t st, const PairPass &p)
 hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream_t st)
 {
     if (p.rps % kPairBlock || p.nslices < 1 || p.nslices > kPairSlices || (int64_t)(p.splits - 1) * p.rps >= p.rows ||
-        p.X.ld >= ((int64_t)1 << 25) || p.X.ld < p.n)
+        p.X.ld >= ((int64_t)1 << 25) || p.X.ld < p.n || !p.f || !p.x || !p.redo)
         return hipErrorInvalidValue;
     for (int z = 0; z < p.nslices; ++z)
         if (p.k[z] < 1 || p.k[z] > 32 * tiles) return hipErrorInvalidValue;      // a pass that stores nothing, or not all
