@@ -112,7 +112,7 @@ const char *nmf_last_error(void);
  * workspace kind 4 plus 1024 k n bytes at most.  Row plan (16-byte aligned A,
  * n % 4 == 0, n < 2^24, and m >= 12288 with n >= 512, or m n <= 2^22): both products stream
  * the row-major A, the W update is fused into the A H^T pass; workspace kind 4.
- * It comes next for k <= 32.  Pair plan (33 <= k <= 64, m and n < 2^25, any
+ * It comes next for k <= 32.  Pair plan (33 <= k <= 64, m and n <= 2^25 - 64, any
  * alignment, if the workspace can hold two copies of A and the call has at least four
  * iterations, two up to 2^25 entries or on a misaligned A, one up to 2^22): A and A^T are cut into pairs
  * of halves once per call, and both products stream those; workspace kind 0.
@@ -139,7 +139,7 @@ const char *nmf_last_error(void);
  * H^T, W^T for the W update, followed by one launch that updates.  A and A^T are cut into
  * pairs of halves once per call and read ceil(k / 64) or ceil(k / 128) times per
  * product (mostly from the caches); the workspace holds both, W^T, H^T, partial sums and a
- * k x max(m, n) array (nmf_mu_workspace_bytes kind 5).  With less, or for m or n >= 2^25, A is cut as it is
+ * k x max(m, n) array (nmf_mu_workspace_bytes kind 5).  With less, or for m or n > 2^25 - 64, A is cut as it is
  * read and A^T is kept as it is; with less than A^T, W^T, H^T and two
  * k x max(m, n) arrays NMF_ENOMEM.
  */

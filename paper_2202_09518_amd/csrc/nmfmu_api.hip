@@ -209,8 +209,11 @@ DensePlan carve_dense(void *ws, int64_t m, int64_t n, int k, bool mirrored)
     return p;
 }
 
+// What launch_pair_pass takes: the rows of A' and (A^T)' are as long as A's rounded up.
+bool pair_lengths_ok(int64_t m, int64_t n) { return pair_matrix_ld(m) < (int64_t)1 << 25 && pair_matrix_ld(n) < (int64_t)1 << 25; }
+
 // 33 to 64 factors: the mirrored plan on pairs of halves.
-bool pairs_ok(int64_t m, int64_t n, int k) { return k > 32 && k <= NMF_MU_MAX_K && m < (int64_t)1 << 25 && n < (int64_t)1 << 25; }
+bool pairs_ok(int64_t m, int64_t n, int k) { return k > 32 && k <= NMF_MU_MAX_K && pair_lengths_ok(m, n); }
 
 // The iterations a call has to have for the cut (A read, two copies written; 300 us on 16384 x 8192, a transposed copy 200) to pay, without ->
 // with it: 2000 x 1000, k = 40, one 67 -> 63 us; 16384 x 8192, k = 40, one 456 -> 524, two 685 -> 734, three 917 -> 943, k = 64, three 970 -> 968;
@@ -1081,7 +1084,7 @@ SlicedDense carve_sliced_dense(void *ws, int64_t m, int64_t n, int k, bool pairs
     return p;
 }
 
-bool sliced_cut_ok(int64_t m, int64_t n, int k) { return k > NMF_MU_MAX_K && m < (int64_t)1 << 25 && n < (int64_t)1 << 25; }
+bool sliced_cut_ok(int64_t m, int64_t n, int k) { return k > NMF_MU_MAX_K && pair_lengths_ok(m, n); }
 
 size_t sliced_dense_bytes(int64_t m, int64_t n, int k, bool pairs)
 {

@@ -59,3 +59,17 @@ def test_sparse():
     size = nmf.nmf_mu_workspace_bytes(1, m, n, m * per, k, 0) + 4 * 16 * (m + n) + 512
     nmf.nmf_mu_release()
     assert same_bits(lambda W, H: nmf.nmf_mu_csr(rowptr, col, vals, m, n, m * per, k, W, H, 2, EPS), size, [(m, k), (k, n)])
+
+
+# Cut copies (8 bytes an entry) are planned up to the length that their launches take, which is rounded up to 64: 2^25 - 64.
+@pytest.mark.parametrize("kind,k", [(0, 40), (3, 64), (5, 96)])
+@pytest.mark.parametrize("turned", [False, True])
+def test_cut_copies_end_where_their_launches_do(kind, k, turned):
+    import paper_2202_09518_amd as nmf
+
+    def size(m, n):
+        return nmf.nmf_mu_workspace_bytes(kind, *((n, m) if turned else (m, n)), 0, k, 0) / (m * n)
+    last = (1 << 25) - 64
+    assert size(last, 8192) >= 8
+    for m in (last + 1, last + 32, (1 << 25) - 1, 1 << 25):
+        assert size(m, 8192) < 6
