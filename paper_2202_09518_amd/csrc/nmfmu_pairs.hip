@@ -1027,22 +1027,27 @@ hipError_t launch_pair_pass(const PairPass &p, int tiles, bool stream, hipStream
     return stream ? pair_pass_launch<2, 4, 1, 2, true>(grid, st, p) : pair_pass_launch<2, 4, 1, 0, true>(grid, st, p);
 }
 
-// Workgroups side by side: one per compute unit; slices of 64 that share X' two.  The fewest splits that leave the last round nearly full
-// (every split is a partial result written and read again), whole blocks of rows to each.
+// Workgroups side by side: one per compute unit; slices of 64 that share X' two.  The cost of `s` splits in blocks of 128 rows, as the
+// workgroups walk them: rounds of workgroups times the blocks of each, half a block for its start and end, and the partial results, which are
+// written and read again, against the bytes of a block in all places, with what the update's chain of reads waits for each.  Whole blocks of
+// rows to each.  (Before, the fewest that leave the last round of workgroups nearly full, whatever they cost: 111913 x 448, k = 36 went
+// over A^T in four splits of one block, 205 us an iteration, 177 on the mirrored plan, 167 now in one; 178 shapes as for pairs_least 1.03 times as
+// fast, slower than the plan before 15, now 2, by 2 percent.)
 int pair_splits(int64_t rows, int64_t cols, int tiles, int nslices)
 {
     const int64_t blocks = (rows + kPairBlock - 1) / kPairBlock, slabs = (cols + 255) / 256, per = slabs * nslices;
-    const double places = tiles == 4 || nslices == 1 ? 256.0 : 512.0;
+    const int64_t places = tiles == 4 || nslices == 1 ? 256 : 512;
     const int64_t cap = slabs >= 16 ? 32 : 128, most = blocks < cap ? blocks : cap;
+    const double block = (double)places / nslices * kPairBlock * 256 * 4, partial = 2.0 * 32 * tiles * nslices * (double)cols * 4;
     int64_t best = 1;
-    double full = 0.0;
+    double least = 0.0;
     for (int64_t s = 1; s <= most; ++s) {
-        const double rounds = (double)(per * s) / places, use = rounds / (double)(int64_t)(rounds + 0.999999);
-        if (use > full + 1e-9) {
-            full = use;
+        const int64_t each = (blocks + s - 1) / s, rounds = (per * s + places - 1) / places;
+        const double cost = (double)rounds * ((double)each + 0.5) + (double)s * (partial / block + 0.015);
+        if (s == 1 || cost < least) {
+            least = cost;
             best = s;
         }
-        if (use >= 0.9) break;
     }
     const int64_t each = (blocks + best - 1) / best;
     return (int)((blocks + each - 1) / each);

@@ -1,6 +1,7 @@
 """Row splits of the W^T A pass (host function): enough workgroups for wide matrices, no more than are resident at once
 where several splits fit, and never more partial results than the rounded-up count, which workspaces are sized for."""
 import ctypes
+import random
 
 import pytest
 
@@ -22,6 +23,30 @@ def test_splits_of_wide_matrices(k, width):
                 assert s == 2
             if slabs >= 128:
                 assert splits(256, n, k) == 1       # at least 256 rows per split
+
+
+def pair_splits(rows, cols, tiles, slices):
+    import paper_2202_09518_amd as nmf
+    return getattr(nmf.lib(), "_ZN5nmfmu11pair_splitsEllii")(ctypes.c_int64(rows), ctypes.c_int64(cols), ctypes.c_int(tiles), ctypes.c_int(slices))
+
+
+@pytest.mark.parametrize("rows,cols,want", [(448, 111913, 1), (165, 224000, 1), (300, 400000, 1),      # few rows: every split is a partial
+                                            (16384, 8192, 8), (9998, 20011, 3), (20011, 9998, 6)])     # result; large: a full last round
+def test_pair_splits(rows, cols, want):
+    assert pair_splits(rows, cols, 2, 1) == want
+
+
+def test_pair_splits_beyond_one_round_stay_cheap():
+    r = random.Random(1)
+    for _ in range(4000):
+        rows, cols = int(2 ** r.uniform(0, 20)), int(2 ** r.uniform(0, 20))
+        tiles, slices = r.choice([(2, 1), (2, 2), (2, 4), (4, 1), (4, 3)])
+        s = pair_splits(rows, cols, tiles, slices)
+        each = -(-(-(-rows // 128)) // s)
+        assert s >= 1 and (s - 1) * each * 128 < rows <= s * each * 128      # no empty split
+        if -(-cols // 256) * slices * (s - 1) > 512:
+            # partial results written and read, against the blocks of the streamed operand
+            assert 2 * 32 * tiles * slices * s <= 128 * s * each
 
 
 # 258 slabs and two splits at both widths; A and A^T just above and below what the cache is taken to hold of two
