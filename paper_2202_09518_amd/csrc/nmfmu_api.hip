@@ -1400,17 +1400,26 @@ int stacks_side_by_side(const std::vector<Stack> &stacks, const float *const *A)
     return most;
 }
 
-// More than 32 factors on every A: below that the row plan has no second layout to make.
-bool ensemble_on_pairs(int64_t m, int64_t n, const std::vector<Stack> &stacks, const float *const *A)
+// More than 32 factors on every A: below that the row plan has no second layout to make.  Several stacks on an A earn the cut by
+// sharing it, a single one by its iterations, as a single run does, or by its runs, whose factors are two or three copies each for the plan
+// before.  Against that plan, 10 shapes of 0.1 to 270 million entries: two or three stacks, one iteration 1.05 to 1.5 times as fast, ten 1.4 to
+// 2.3; one stack of two runs, one, two and four iterations 1.19, 1.14 and 1.07 on 3000 x 2000, 0.94, 0.99 and 1.03 on 8192 x 4000, 0.89, 0.94
+// and 0.99 on 16384 x 8192; of five 1.53, 1.36 and 1.23, then 1.13, 1.10 and 1.10, then 0.95, 0.97 and 1.01.  One rule for the call: what more of its
+// matrices ask for.
+bool ensemble_on_pairs(int64_t m, int64_t n, const std::vector<Stack> &stacks, const float *const *A, int iters)
 {
     if (!pairs_ok(m, n, NMF_MU_MAX_K)) return false;
+    int for_it = 0, against = 0;
     for (size_t si = 0; si < stacks.size();) {
         const float *a = A[stacks[si].first];
-        int K = 0;
-        for (; si < stacks.size() && A[stacks[si].first] == a; ++si) K += stacks[si].K;
+        const bool aligned = (reinterpret_cast<uintptr_t>(a) & 15u) == 0 && n % 4 == 0;
+        int K = 0, count = 0, runs = 0;
+        for (; si < stacks.size() && A[stacks[si].first] == a; ++si, ++count) K += stacks[si].K, runs += stacks[si].count;
         if (K <= 32) return false;
+        const int least = runs == 1 ? pairs_least(m, n, false, false) : m * n > 1 << 26 ? 4 : runs == 2 && m * n > 1 << 24 ? 2 : 1;
+        ++(count > 1 || !aligned || iters >= least ? for_it : against);
     }
-    return true;
+    return for_it >= against;
 }
 
 int pairs_ensemble(const float *const *A, int64_t m, int64_t n, const int32_t *k, float *const *W, float *const *H, int iters,
@@ -1423,6 +1432,18 @@ int pairs_ensemble(const float *const *A, int64_t m, int64_t n, const int32_t *k
         const int count = stacks_from(stacks, si, A);
         const float *a = A[stacks[si].first];
         set_slices(&p, m, n, count);
+        const PairPlanes planes = cut == a ? PairPlanes::there : PairPlanes::none;
+        cut = a;
+        if (count == 1 && stacks[si].count == 1) {      // a run by itself stays where it is
+            const int r = stacks[si++].first;
+            DensePlan q = p;
+            q.Hs[0] = H[r];
+            q.sl.k[0] = k[r];
+            q.sl.bm[0].on = 0;
+            NMF_HIP(launch_transpose(W[r], m, k[r], q.Wts[0], st));
+            if (int rc = pairs_body(a, m, n, W[r], iters, eps, q, st, planes)) return rc;
+            continue;
+        }
         StackedRuns runs[kPairGroup];
         for (int z = 0; z < count; ++z) {
             const Stack &sk = stacks[si + z];
@@ -1442,8 +1463,7 @@ int pairs_ensemble(const float *const *A, int64_t m, int64_t n, const int32_t *k
             p.sl.k[z] = sk.K;
             NMF_HIP(launch_stack(runs[z], sk.count, true, p.Wts[z], p.Hs[z], m, n, st));
         }
-        if (int rc = pairs_body(a, m, n, nullptr, iters, eps, p, st, cut == a ? PairPlanes::there : PairPlanes::none)) return rc;
-        cut = a;
+        if (int rc = pairs_body(a, m, n, nullptr, iters, eps, p, st, planes)) return rc;
         for (int z = 0; z < count; ++z)
             NMF_HIP(launch_stack(runs[z], stacks[si + z].count, false, p.Wts[z], p.Hs[z], m, n, st));
         si += count;
@@ -1699,7 +1719,7 @@ int nmf_mu_dense_batched(int32_t n_runs, const float *const *A, int64_t m, int64
     // one launch per product, which reads A' once for all of them, and of one per update.  16384 x 8192, ranks 2 to 16 (stacks
     // of 54, 50 and 31 factors): 10 iterations of the 30 runs on two copies
     // of A 14.5 -> 9.4 ms.
-    if (ensemble_on_pairs(m, n, stacks, A)) {
+    if (ensemble_on_pairs(m, n, stacks, A, iters)) {
         const int groups = stacks_side_by_side(stacks, A);
         if (have_workspace(pairs_bytes(m, n, NMF_MU_MAX_K, groups), st))
             return pairs_ensemble(A, m, n, k, W, H, iters, eps, stacks, groups, st);

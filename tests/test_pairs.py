@@ -182,6 +182,29 @@ def test_stacks_side_by_side(m, n, ranks):
         assert off(W.cpu().numpy(), Wr) < 2e-6 and off(H.cpu().numpy(), Hr) < 2e-6
 
 
+# One stack on a large matrix earns the cut by its iterations, as a single run does: below that the runs go one by one, and a single run is
+# that of nmf_mu_dense in either case.  An A that is not aligned, and several stacks, are cut for one iteration.
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,ranks,iters", [(8200, 4100, [40], 3), (8200, 4100, [40], 4), (8200, 8200, [20, 20], 3), (8200, 8200, [20, 20], 4),
+                                             (2100, 2001, [33], 1), (700, 516, [50], 1), (8200, 4100, [64, 33], 1)])
+def test_ensembles_by_iterations(m, n, ranks, iters):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    A = torch.rand((m, n), generator=g, device="cuda")
+    Ws, Hs = [torch.rand((m, k), generator=g, device="cuda") for k in ranks], [torch.rand((k, n), generator=g, device="cuda") for k in ranks]
+    W, H = [w.clone() for w in Ws], [h.clone() for h in Hs]
+    nmf.nmf_mu_dense_batched(len(ranks), [A] * len(ranks), m, n, ranks, W, H, iters, EPS)
+    for k, w0, h0, w, h in zip(ranks, Ws, Hs, W, H):
+        nmf.nmf_mu_dense(A, m, n, k, w0, h0, iters, EPS)
+        if len(ranks) == 1 and n % 4 == 0:      # the same plan
+            assert torch.equal(w0, w) and torch.equal(h0, h)
+        else:      # `iters` updates of each factor, a few roundings of 2^-24 per sum
+            assert ((w - w0).norm() / w0.norm()).item() < 4e-6 and ((h - h0).norm() / h0.norm()).item() < 4e-6
+
+
 # The arrival counters at the head of the workspace are other kernels': a run above 64 factors leaves them at zero.
 @pytest.mark.gpu
 def test_counters_are_left_alone():
