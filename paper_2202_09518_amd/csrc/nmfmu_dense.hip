@@ -3560,7 +3560,7 @@ __global__ __launch_bounds__(256) void objective_kernel(const double *__restrict
 }
 
 // P = sum over the row splits of the partial W^T A results (test entry point only).
-// blockIdx.y = slice of 64 or 128 factors (ranks above 64): partials at ppart + slice * slice_ppart, `count`
+// blockIdx.y = slice of 64 factors (ranks above 64): partials at ppart + slice * slice_ppart, `count`
 // floats of P per full slice, count_last for the last one.
 // Eight splits are requested together and added in a tree: one load at a time, a 256 x 256
 // Gram matrix over 32 splits took 35 us on 64 workgroups per slice, a chain of trips to memory
@@ -3750,15 +3750,15 @@ hipError_t launch_split_planes_slice(const float *X, int64_t rows, int64_t ld, i
 }
 
 hipError_t launch_sum_partials_slices(const float *ppart, int splits, int k, int64_t cols, float *P, hipStream_t st,
-                                      bool accumulate, int width)
+                                      bool accumulate)
 {
-    const int nslices = (k + width - 1) / width;
-    const int64_t count = width * cols, count_last = (int64_t)(k - width * (nslices - 1)) * cols;
+    const int nslices = (k + 63) / 64;
+    const int64_t count = 64 * cols, count_last = (int64_t)(k - 64 * (nslices - 1)) * cols;
     int64_t b = (count + 255) / 256;
     if (b > 4096) b = 4096;
     // the partials of slice z hold splits x (factors of z) x cols floats, packed for that slice's width
     hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)b, (unsigned)nslices), dim3(256), 0, st, ppart, splits, count, P,
-                       accumulate ? 1 : 0, (int64_t)splits * width * cols, count_last);
+                       accumulate ? 1 : 0, (int64_t)splits * 64 * cols, count_last);
     return hipGetLastError();
 }
 

@@ -154,9 +154,9 @@ struct SlicedUpdate {
     int nclear;
 };
 hipError_t launch_sliced_update(const SlicedUpdate &a, hipStream_t st);
-// P (k x cols) (+)= the sums over the splits.  width: factors of a slice.
+// P (k x cols) (+)= the sums over the splits, slices of 64 factors.
 hipError_t launch_sum_partials_slices(const float *ppart, int splits, int k, int64_t cols, float *P, hipStream_t st,
-                                      bool accumulate = false, int width = 64);
+                                      bool accumulate = false);
 // P[e] (+)= sum_s ppart[s][e], e < count.
 hipError_t launch_sum_partials(const float *ppart, int splits, int64_t count, float *P,
                                hipStream_t st, bool accumulate = false);
