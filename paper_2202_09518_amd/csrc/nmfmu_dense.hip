@@ -3472,10 +3472,30 @@ __global__ __launch_bounds__(256, 2) void residual_pair_kernel(const float *__re
         __syncthreads();    // the group's buffer is free, the next group's is written
         buf ^= 1;
     }
-    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
-    if (lane == 0) wsum[w] = total;
-    __syncthreads();
-    if (tid == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    auto sum = [&]() {
+        for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
+        if (lane == 0) wsum[w] = total;
+        __syncthreads();
+        total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    };
+    sum();
+    if (!(total < __builtin_inf())) {
+        // An infinity has no two halves, their differences are no number.  What the floats give, a column a thread.
+        total = 0.0;
+        const int64_t j = (int64_t)blockIdx.x * 256 + tid;
+        if (j < n)
+#pragma unroll 1
+            for (int64_t i = r0; i < r1; ++i) {
+                float p = 0.f;
+#pragma unroll 4
+                for (int c = 0; c < k; ++c) p = __builtin_fmaf(W[i * k + c], H[c * n + j], p);
+                const float d = A[i * n + j] - p;
+                total += (double)(d * d);
+            }
+        __syncthreads();      // wsum is read
+        sum();
+    }
+    if (tid == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = total;
 }
 
 // Sum of `count` doubles by one block of 256 threads in a fixed order: thread t adds entries

@@ -262,3 +262,28 @@ def test_profile_is_of_the_plan_that_runs(m, n, k, iters):
     assert ms[7] > 0 and ms[8] > 0
     if n % 4 == 0 or iters > 1:     # the profile makes no aligned copy of A
         assert torch.equal(W, w) and torch.equal(H, h)
+
+
+# An infinite entry of a factor makes the objective infinite, as in single precision; NaN where the floats give NaN.
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,k", [(2591, 8201, 10), (4100, 4100, 64), (66001, 61, 48)])
+def test_objective_of_infinite_factors(m, n, k):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    A, W, H = (torch.rand(s, generator=g, device="cuda") + 0.1 for s in ((m, n), (m, k), (k, n)))
+
+    def objective():
+        return nmf.nmf_residual_dense(A, m, n, k, W, H)
+    assert np.isfinite(objective())
+    for x, at in ((W, (m - 1, k // 2)), (H, (k - 1, n - 1)), (A, (m // 2, 0))):
+        old = x[at].clone()
+        x[at] = np.inf
+        assert objective() == np.inf
+        x[at] = np.nan
+        assert np.isnan(objective())
+        x[at] = old
+    W[5, 0], H[0, 7] = np.inf, 0
+    assert np.isnan(objective())
