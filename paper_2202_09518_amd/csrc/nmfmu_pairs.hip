@@ -402,6 +402,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     extern __shared__ u32x4 pst[];                     // two blocks
     __shared__ int fexp[KP];
     __shared__ int redone;                             // the tile's sums are not sure
+    __shared__ int before;                             // passes for which it is formed from the floats as it is
     const int64_t rows = a.rows, n = a.n, ldx = a.X.ld;
     const int gx = (int)((n + 255) / 256), ldf = a.ldf;
     const int L = blockIdx.x, within = L >> 3;
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
 #pragma unroll
         for (int q = 0; q < 2; ++q) tot[t][q] = sum[t][q] = f32x16{0};
     const int64_t redo = (int64_t)t8 * a.nslices + z;
-    const int asked = a.redo[redo];        // formed from the floats from a pass before on?  (Looked at when the first operands are there.)
+    const int asked = tid == 0 ? (int)a.redo[redo] : 0;
     struct Stage { u32x4 x[2][2]; };
     Stage xs[D];
     auto load_x = [&](Stage &s, int64_t ib) {
@@ -501,8 +502,9 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) store_f(first[s], pst, s);
     }
+    if (tid == 0) before = asked;          // one look for all four waves: the word changes below
     __syncthreads();
-    const int again = __builtin_amdgcn_readfirstlane(asked);
+    const int again = __builtin_amdgcn_readfirstlane(before);
     if (!again) {
         int buf = 0;
         for (int64_t i = r0; i < r1; i += kPairBlock) {

@@ -198,3 +198,37 @@ def test_factors_that_are_zero(k):
     Wr, Hr = reference(A, W, H, 3)
     assert off(Hg, Hr) < 5e-6 and off(Wg, Wr) < 5e-6
     assert (Hg[:, 7] == 0).all() and (Wg[128:256] == 0).all() and (Wg[:, 5] == 0).all() and (Hg[9] == 0).all()
+
+
+# The same over many workgroups: several splits, ragged edges, A along its rows, along its columns four entries at a time and one at
+# a time, slices of 128 factors and of 64 side by side.
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,ks", [(5001, 3003, [50]), (4100, 4100, [64]), (3001, 4096, [33]), (8200, 4100, [128]), (8197, 4101, [200]),
+                                    (4100, 3000, [20, 30, 14, 40, 24]), (2049, 5003, [64, 64, 33])])
+def test_blocks_over_many_workgroups(m, n, ks):
+    import torch
+
+    import paper_2202_09518_amd as nmf
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + n)
+    rows, cols = torch.rand(m, generator=g, device="cuda") < 0.5, torch.rand(n, generator=g, device="cuda") < 0.5
+    A = torch.rand((m, n), generator=g, device="cuda")
+    A *= (rows[:, None] == cols).float() * torch.where(rows, 0.07, 1.0)[:, None]
+    Ws, Hs = [torch.rand((m, k), generator=g, device="cuda") for k in ks], [torch.rand((k, n), generator=g, device="cuda") for k in ks]
+    Wg, Hg = [w.clone() for w in Ws], [h.clone() for h in Hs]
+    if len(ks) == 1:
+        nmf.nmf_mu_dense(A, m, n, ks[0], Wg[0], Hg[0], 6, EPS)
+    else:
+        nmf.nmf_mu_dense_batched(len(ks), [A] * len(ks), m, n, ks, Wg, Hg, 6, EPS)
+    A = A.double()
+    At = A.t().contiguous()
+    eps = float(np.float32(EPS))
+    for W, H, Wd, Hd in zip(Ws, Hs, Wg, Hg):
+        W, Ht = W.double(), H.double().t().contiguous()
+        for _ in range(6):
+            Ht = Ht * (At @ W) / (Ht @ (W.t().contiguous() @ W) + eps)
+            W = W * (A @ Ht) / (W @ (Ht.t().contiguous() @ Ht) + eps)
+        for part in (False, True):
+            r, c = rows == part, cols == part
+            assert ((Wd.double() - W)[r].norm() / W[r].norm()).item() < TOL
+            assert ((Hd.double().t() - Ht)[c].norm() / Ht[c].norm()).item() < TOL
