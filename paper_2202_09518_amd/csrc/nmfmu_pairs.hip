@@ -16,6 +16,7 @@ namespace nmfmu {
 // clear: words to set to zero on the way.
 // ---------------------------------------------------------------------------
 constexpr int kCutTile = kPairBlock;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 template <bool VEC>
 __global__ __launch_bounds__(512) void cut_pairs_kernel(const float *__restrict__ A, int64_t m, int64_t n, PairMatrix a, PairMatrix at_,
                                                         unsigned *__restrict__ clear, int nclear)
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
     constexpr int kUnits = kSteps * 4 * KP;            // 16-byte units of planes in a block
     constexpr int kEach = kUnits / 256 / kSteps;       // a thread stages so many per step
     extern __shared__ u32x4 pst[];                     // two blocks
-    __shared__ int fexp[KP];
+    __shared__ __align__(16) int fexp[KP];
     __shared__ int redone;                             // the tile's sums are not sure
     __shared__ int before;                             // passes for which it is formed from the floats as it is
     const int64_t rows = a.rows, n = a.n, ldx = a.X.ld;
@@ -559,22 +560,34 @@ __global__ __launch_bounds__(64 * kWtaWaves, OCC) void pair_pass_kernel(const Pa
 #pragma unroll
                 for (int q = 0; q < 2; ++q) tot[t][q] += sum[t][q];
         }
+        unsigned off[2];                   // of a lane's columns in four rows of factors on; past the edge out of reach
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int64_t c = jw + 32 * q + jj;
-            if (c >= n) continue;
             Sums sums;
-            float *dst = ppart + (int64_t)by * k * n + c;
 #pragma unroll
             for (int t = 0; t < T; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int f = 32 * t + acc_row(v, half);
-                    if (v % 2 == 0) sums.add(tot[t][q][v], tot[t][q][v + 1]);
-                    if (f < k) dst[(int64_t)f * n] = ldexpf(tot[t][q][v], fexp[f]);
-                }
-            if (!sums.sure(unit[q])) redone = 1;
+                for (int v = 0; v < 16; v += 2) sums.add(tot[t][q][v], tot[t][q][v + 1]);
+            const bool in = jw + 32 * q + jj < n;
+            off[q] = in ? ((unsigned)(4 * half) * (unsigned)n + (unsigned)(jw + 32 * q + jj)) * 4u : 0xffffffffu;
+            if (in && !sums.sure(unit[q])) redone = 1;
         }
+        // register v is factor 32 t + v % 4 + 8 (v / 4), or four on: a descriptor holds both rows, or the first if the second is past k
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const i32x4 e = *reinterpret_cast<const i32x4 *>(&fexp[32 * t + 8 * g + 4 * half]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int f = 32 * t + 8 * g + u;
+                    const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
+                        ppart + ((int64_t)by * k + (f < k ? f : 0)) * n, 0, (int)(f + 4 < k ? 5 * n * 4 : f < k ? n * 4 : 0), kRsrcFlags);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ldexpf(tot[t][q][4 * g + u], e[u])), row, off[q], 0, 0);
+                }
+            }
         __syncthreads();
         if (!__builtin_amdgcn_readfirstlane(redone)) return;
     }
