@@ -21,15 +21,21 @@
  * a factor hold one value each throughout, all terms lose the same bits and a sum
  * can be 2e-6 off.  For k > 32, and for stacked runs of an ensemble, the products
  * are formed on the fp16 matrix cores from pairs of halves: a float times a power of
- * two of its column (128 rows at a time for A, at most 30 binary orders below the
- * column's largest value there for a factor) is cut into its nearest half and the
+ * two of its column (of 128 rows of it for A, of the whole column for a factor) is
+ * cut into its nearest half and the
  * half of what is left, 22 to 24 bits together, and three of the four products of
- * two pairs are accumulated in fp32, over at most 384 terms before a running total
+ * two pairs are accumulated in fp32, over at most 384 products before a running total
  * takes them.  The instructions' rounding of their sums is what remains: the errors of
  * whole runs against float64 are those of the bf16 pieces or a little lower (2.2e-7
  * and 2.4e-7 after five iterations of rank 256 on 16384 x 8192).  An entry more than
- * 2^14 below the largest of its 128 rows of the column loses low bits, in proportion
- * to that largest entry; infinities and NaN reach the results they belong to.  The Gram matrices up to 64 factors, the small plan's
+ * 2^17 below the largest that it shares a scale with loses low bits, in proportion
+ * to that largest entry.  A sum that could miss them is not used: each is compared
+ * with what may have been left out of it, and where one of 64 or 128 factors x 256
+ * columns is less than 2^22 times that, or not finite, all of those are formed from bf16
+ * pieces of the floats as above, so that factors and parts of A in units of their own, blocks on
+ * a diagonal and factors that the updates drive towards zero keep their relative
+ * accuracy (and such data part of the plan's speed: 0.7 to 0.85 of what the mirrored
+ * plan reaches on two blocks).  Infinities and NaN reach the results they belong to.  The Gram matrices up to 64 factors, the small plan's
  * A H^T, and W^T A for k > 32 on a misaligned A that is used as it is take the fp32
  * matrix instruction (fp32 operands, fp32 accumulation).
  *
@@ -113,8 +119,8 @@ const char *nmf_last_error(void);
  * n % 4 == 0, n < 2^24, and m >= 12288 with n >= 512, or m n <= 2^22): both products stream
  * the row-major A, the W update is fused into the A H^T pass; workspace kind 4.
  * It comes next for k <= 32.  Pair plan (33 <= k <= 64, m and n <= 2^25 - 64, any
- * alignment, if the workspace can hold two copies of A and the call has at least four
- * iterations, two up to 2^25 entries or on a misaligned A, one up to 2^22): A and A^T are cut into pairs
+ * alignment, if the workspace can hold two copies of A and the call has at least six
+ * iterations, four up to 2^27 entries, two up to 2^25 or on a misaligned A, one up to 2^22): A and A^T are cut into pairs
  * of halves once per call, and both products stream those; workspace kind 0.
  * Mirrored plan (33 <= k <= 64 otherwise, and shapes the
  * row plan does not serve): A is
@@ -367,7 +373,8 @@ int nmf_mu_csr_ooc(const int64_t *rowptr_host, const int32_t *colidx_host, const
  * before the call returns; what they point to is device memory.
  * Consecutive runs that name the same A are stacked while their ranks sum to at
  * most NMF_MU_MAX_K, and up to four such stacks run side by side on one pair of cut
- * copies of A (the pair plan of nmf_mu_dense): the passes over A then serve all of
+ * copies of A (the pair plan of nmf_mu_dense, which an A with one stack only takes from
+ * as many iterations on as earn it): the passes over A then serve all of
  * them at once (order the runs by A to benefit).  Results per run equal a single run's up
  * to rounding order.
  */
