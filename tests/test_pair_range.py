@@ -232,3 +232,38 @@ def test_blocks_over_many_workgroups(m, n, ks):
             r, c = rows == part, cols == part
             assert ((Wd.double() - W)[r].norm() / W[r].norm()).item() < TOL
             assert ((Hd.double().t() - Ht)[c].norm() / Ht[c].norm()).item() < TOL
+
+
+# Sums of one sign are as exact as their terms, entry by entry, whatever lies beside them.
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["A", "W", "H", "all", "rows", "columns", "sparse", "decayed"])
+@pytest.mark.parametrize("way,m,n,k", [(dense, 700, 516, 40), (dense, 1301, 333, 64), (dense, 640, 1028, 96), (dense, 333, 700, 130),
+                                       (streamed, 640, 260, 70), ("stack", 516, 700, 30)])
+def test_every_entry_of_wide_data(way, m, n, k, kind):
+    r = np.random.default_rng(9)
+
+    def wide(orders, *shape):
+        return np.ldexp(r.random(shape) + 0.5, r.integers(-orders, orders + 1, shape)).astype(np.float32)
+    A, W, H = (r.random(s, dtype=np.float32) for s in ((m, n), (m, k), (k, n)))
+    if kind in ("A", "all"):
+        A = wide(15, m, n)
+    if kind in ("W", "all"):
+        W = wide(15, m, k)
+    if kind in ("H", "all"):
+        H = wide(12, k, n)
+    if kind == "rows":
+        A *= wide(25, m, 1)
+    elif kind == "columns":
+        A *= wide(25, 1, n)
+    elif kind == "sparse":
+        A, W = wide(20, m, n) * (r.random((m, n)) < 0.05), wide(20, m, k) * (r.random((m, k)) < 0.05) + np.float32(1e-12) * W
+    elif kind == "decayed":
+        A, W, H = A * (r.random((m, n)) < 0.3), np.exp2(-60 * W), np.exp2(-30 * H)
+    A, W, H = (np.ascontiguousarray(x, dtype=np.float32) for x in (A, W, H))
+    if way == "stack":
+        got = [x[0] for x in stacked(A, [W, W[:, :20].copy()], [H, H[:20].copy()], 1)]
+    else:
+        got = way(A, W, H, 1)
+    for x, want in zip(got, reference(A, W, H, 1)):
+        live = (want > 1e-25) & (want < 1e30)
+        assert live.any() and (np.abs(x - want)[live] <= 6e-6 * want[live]).all()      # 2e-6 at most on exact pieces
