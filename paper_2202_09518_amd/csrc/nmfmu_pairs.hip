@@ -4,6 +4,7 @@
 //   split_pairs_kernel : the planes of a factor (factor_update_kernel writes them itself)
 //   pair_pass_kernel : the pass over A' or (A^T)' for slices of 64 or 128 factors
 //   wta_pass_pair_kernel : the same over a matrix that is cut as it is loaded
+//   floats_tile : a tile of either pass again from the floats, where a sum could have lost more to the halves than it may
 #include "nmfmu_device.h"
 
 namespace nmfmu {
